@@ -38,10 +38,13 @@ pf_status pf_debug_schedule_check(const pf_case_desc* desc, const pf_schedule* s
  * 2x2-block pattern, Ybus-to-block map, ILU(0) update lists, the forward and
  * backward level schedules, block-Jacobi groups), then factor a random
  * diagonally dominant matrix on that pattern with block ILU(0) through the
- * update lists in level order and apply it through both schedules.
+ * update lists in level order and apply it through both level schedules
+ * and through the merged-level sweep plans (every index and dependency of
+ * those checked).
  * *ilu_deviation receives max |(L U - A)_ij| / max |A_ij| over the pattern
- * (ILU(0) reproduces A there), *rel_residual the relative residual of
- * L U z = v, *checks the number of checks.  PF_E_INVALID on a failed check
+ * (ILU(0) reproduces A there), *rel_residual the larger of the relative
+ * residual of L U z = v and the difference of the sweep plans' z from it
+ * over max |z|, *checks the number of checks.  PF_E_INVALID on a failed check
  * (reason in pf_last_error()).  Outputs are host pointers. */
 pf_status pf_debug_krylov_check(const pf_case_desc* desc, uint64_t seed, double* ilu_deviation,
                                 double* rel_residual, int64_t* checks);

@@ -34,6 +34,7 @@ SOURCES = [
     "serve.cpp",
     "hostcheck.cpp",
     "krylov_analysis.cpp",
+    "krylov_sweep.cpp",
     "nk.cpp",
     "krylov_check.cpp",
     "tune.cpp",

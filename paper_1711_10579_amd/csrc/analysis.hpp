@@ -113,6 +113,32 @@ struct KAnalysis {
   int nblocks() const { return (int)bj_ptr.size() - 1; }
 };
 
+// The ILU(0) sweeps z = U^{-1} L^{-1} w with runs of levels merged into
+// parts (a partitioned inverse): inside a part every row is written out in
+// terms of the part's input and of rows of earlier parts, so the rows of a
+// part need nothing from each other and one launch runs them all.
+//   lower part: y_r = w_r + sum_e V(e) x(e)   (x = w inside the part, y before it)
+//   upper part: z_r = sum_e V(e) x(e)         (x = y inside the part, z before it;
+//                                              the row's own entry first)
+// The entry values follow from the factor by levels inside each part, parts
+// side by side ("steps"):
+//   lower: V(e) = -sum over ops (q, s) of L(q) V(s)
+//   upper: V(e) = -D_r^{-1} sum over ops (q, s) of U(q) V(s); no ops: D_r^{-1}
+// with V(-1) the identity, q a block of the factor pattern and s an entry of
+// a row of the same part.
+struct KSweep {
+  int nlp = 0, nup = 0;             // lower and upper parts
+  std::vector<int> part_ptr;        // [nlp + nup + 1] positions
+  std::vector<int> step;            // [2 nu] level of a position inside its part
+  int nsteps = 0;
+  std::vector<int> rows;            // [4 x 2 nu] per position {row, first entry, end, 0}; lower rows first
+  std::vector<int> col;             // [ne] ~c: input at row c; c: row c of an earlier part
+  std::vector<int> op_ptr;          // [ne + 1]
+  std::vector<int> ops;             // [2 x nops] pairs (q, s)
+  int64_t ne() const { return (int64_t)col.size(); }
+  int64_t nops() const { return (int64_t)ops.size() / 2; }
+};
+
 // The reverse Cuthill-McKee order of an undirected graph (adjacency lists,
 // no self loops): breadth-first from a pseudo-peripheral start in every
 // connected component, neighbours taken by increasing degree, the whole
@@ -120,6 +146,15 @@ struct KAnalysis {
 std::vector<int> rcm_order(const std::vector<std::vector<int>>& adj);
 
 KAnalysis analyze_krylov(const Analysis& an, int n, const int* row_ptr, const int* col, int bj_cap);
+
+// Merge the sweep levels into parts whose rows have at most `cap` entries
+// each (the rows of a level on its own may have more); false, and the plan
+// unusable, past max_entries.
+bool build_sweep(const KAnalysis& ka, int cap, int64_t max_entries, KSweep* out);
+// The plan the solver uses, chosen from the case alone; `wide`: without a
+// plan the sweeps take one launch per level.  False when no plan of at most
+// max_entries entries beats the level sweeps.
+bool plan_sweep(const KAnalysis& ka, bool wide, int64_t max_entries, KSweep* out);
 
 // Ybus entry -> block position in the Krylov pattern, -1 when the row or the
 // column node has no unknowns.

@@ -863,6 +863,7 @@ pf_status pf_destroy(pf_case* c) {
   delete c->single;
   c->single = nullptr;
   free_krylov(c);
+  if (c->swbase) c->ctx->dfree(c->swbase);
   if (c->wown) c->ctx->dfree(c->wbase);
   c->ctx->dfree(c->base);
   c->ctx->ncases--;

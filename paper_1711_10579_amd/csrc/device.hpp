@@ -99,6 +99,14 @@ struct Inst {
   // entries
   const int *kl_ptr, *ku_ptr;
   const int4 *kl_info, *ku_info;
+  // the ILU(0) sweeps in parts (null: by levels): per position {row, first
+  // entry, end, 0}, the forward rows first; per entry its column (~c: the
+  // part's input at row c, else row c of an earlier part) and its list of
+  // (factor block, entry) pairs; the entry values, in the block-Jacobi
+  // inverses' storage (a solve uses one preconditioner)
+  const int4* sw_rows;
+  const int *sw_col, *sw_op_ptr;
+  const int2* sw_ops;
   const int *bj_ptr, *bj_rows, *bj_loc;
   const int64_t* bj_off;
   int* bjbad;  // per group: 1 when its inverse needs partial pivoting

@@ -139,6 +139,11 @@ struct Case {
   bool kown = false;  // false: lent by the serving loop for one request
   int km = 0;         // restart length the storage holds
   std::vector<int4> k_linfo, k_uinfo;  // per level position {row, first, end, 0}
+  // ILU(0) sweeps in parts: made by the case's first ILU(0) solve; its index
+  // lists are launch-plan memory of the case's own (freed with the case)
+  enum { SW_NEW = 0, SW_NONE, SW_PLAN } sw_state = SW_NEW;
+  pfh::KSweep sw;
+  char* swbase = nullptr;
 
   int64_t lu_count() const { return 4LL * (an.ns + 2 * an.nnzl); }
   int64_t tail_count() const { return (int64_t)an.ldt * (M + 1); }
@@ -213,6 +218,14 @@ struct Batch {
   int k_min_nu = 0, k_max_nu = 0;
   bool k_wide = false;    // some instance has an ILU(0) level wider than one work-group pass
   bool k_narrow = false;  // some instance runs its ILU(0) in one work-group
+  // ILU(0) sweeps (built on the first ILU(0) step of the batch): row ranges
+  // of the parts, forward then backward, and of the value set-up's steps in
+  // d_swork, rows padded to whole work-groups of one instance each
+  bool sbuilt = false;
+  char* smem = nullptr;
+  int2* d_swork = nullptr;
+  std::vector<std::pair<int64_t, int>> s_low, s_up, s_step;
+  bool s_narrow = false, s_wide = false;  // some instance sweeps by levels: in one work-group, a launch per level
 
   ~Batch();
   // launch plan and device table in memory the batch allocates (and pinned
@@ -225,6 +238,7 @@ struct Batch {
   size_t plan_bytes(size_t nwork) const;
   bool place(char* mem, const std::vector<int2>& work);
   bool build_krylov();
+  bool build_sweeps();
 };
 
 // Kernel-class timing of the launches issued while it lives.
@@ -248,6 +262,10 @@ void free_krylov(Case* c);
 // detach_krylov), launched on stream s (no synchronisation).
 size_t krylov_bytes(const Case* c, int m);
 bool krylov_wide(const pfh::KAnalysis& ka);
+// The sweep plan of a case's ILU(0) preconditioner: made (host work, one
+// device allocation) on first use; SW_NONE where the sweeps go by levels.
+// False on a device failure.
+bool ensure_sweep(Case* c);
 bool attach_krylov(Case* c, int m, char* base, bool own, hipStream_t s);
 void detach_krylov(Case* c);
 // Working storage of a solve: its size, its set-up in the given memory on

@@ -76,6 +76,14 @@ template <typename T>
 void launch_ilu_apply_wg(hipStream_t, const Inst* const* insts, int nslots, int mode, int min_nu, int max_nu);
 template <typename T>
 void launch_bj_apply(hipStream_t, const Inst* const* insts, const int2* work, int nbig, int nwork, int mode);
+// ILU(0) sweeps in parts: rows of one launch are positions p0.. of the only
+// instance (work null), or a list of (slot, position) padded with position -1
+// to whole work-groups (sweep_rows_per_group rows) of one instance each
+int sweep_rows_per_group();
+template <typename T>
+void launch_sweep_values(hipStream_t, const Inst* const* insts, const int2* work, int nrows);
+template <typename T>
+void launch_sweep_part(hipStream_t, const Inst* const* insts, const int2* work, int p0, int nrows, int upper, int mode);
 template <typename T>
 void launch_karnoldi(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, KOpts o);
 template <typename T>

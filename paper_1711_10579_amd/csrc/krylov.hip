@@ -531,7 +531,7 @@ __global__ __launch_bounds__(256) void k_ilu_fwd(const Inst* const* insts, const
   if (idx >= nwork) return;
   const int2 wk = ld_item(work, idx);
   const auto& I = *gp(gp(insts)[wk.x]);
-  if (!kstate_is(I, apply_state(mode))) return;
+  if (!kstate_is(I, apply_state(mode)) || I.sw_rows) return;
   const int r = wk.y;
   const auto w = gp((const T*)I.kw);
   const auto z = gp((T*)I.kz);
@@ -560,7 +560,7 @@ __global__ __launch_bounds__(256) void k_ilu_bwd(const Inst* const* insts, const
   if (idx >= nwork) return;
   const int2 wk = ld_item(work, idx);
   const auto& I = *gp(gp(insts)[wk.x]);
-  if (!kstate_is(I, apply_state(mode))) return;
+  if (!kstate_is(I, apply_state(mode)) || I.sw_rows) return;
   const int r = wk.y;
   const auto z = gp((T*)I.kz);
   const auto P = gp((const T*)I.pval);
@@ -569,6 +569,153 @@ __global__ __launch_bounds__(256) void k_ilu_bwd(const Inst* const* insts, const
   const Blk<T> D = ld_blk((const T*)I.pdinv, r);
   z[2 * r] = (T)((double)D.a * s0 + (double)D.b * s1);
   z[2 * r + 1] = (T)((double)D.c * s0 + (double)D.d * s1);
+}
+
+// ILU(0) sweeps in parts.  The level sweeps are bound by their chain: 48
+// levels (10,000-bus grid) to 108 (48,000 buses) that each cost a barrier
+// and a few dependent loads of one CU, or a launch.  The factor's triangles
+// are nearly trees, so their inverses stay sparse over runs of levels: a
+// part (KSweep) writes every row of such a run out in terms of the part's
+// input and earlier parts, and one launch does a part across the device.
+// The entry values are formed once per Newton step and used by every
+// application of it.  kSweepLanes lanes per row (rows hold up to 64
+// entries, in the mean 4-25), four entries of a lane in flight.
+
+constexpr int kSweepLanes = 8;
+
+// Row `idx` of a launch: the work-group's instance and the row's position
+// (-1: none).  Without a list the rows are positions p0, p0 + 1, ... of the
+// batch's only instance, and no load stands before the descriptor's; a list
+// holds whole work-groups of one instance each.
+struct SweepRow {
+  int slot, pos;
+};
+template <int G>
+__device__ inline SweepRow sweep_row(const int2* work, int p0, int nrows) {
+  constexpr int R = 256 / G;
+  const int idx = (int)blockIdx.x * R + (int)threadIdx.x / G;
+  if (!work) return {0, idx < nrows ? p0 + idx : -1};
+  const auto wp = (const PF_AS1 int*)work;
+  return {__builtin_amdgcn_readfirstlane(wp[2 * R * (int)blockIdx.x]), wp[2 * idx + 1]};
+}
+
+// Entry values of the rows of one step: the rows of a part's first level
+// come from the factor alone, those of its next levels from the entries of
+// rows of earlier steps.  Twice the lanes of an application: an entry is a
+// chain of three loads, so the longest rows set a step's time.
+constexpr int kValueLanes = 16;
+template <typename T>
+__global__ __launch_bounds__(256) void k_sweep_values(const Inst* const* insts, const int2* __restrict__ work) {
+  const SweepRow sr = sweep_row<kValueLanes>(work, 0, 0);
+  const auto& I = *gp(gp(insts)[sr.slot]);
+  if (sr.pos < 0 || !gp(I.red)->active) return;
+  const i4v inf = ((const PF_AS1 i4v*)I.sw_rows)[sr.pos];
+  const bool upper = sr.pos >= I.nu;
+  const auto P = gp((const T*)I.pval);
+  const auto V = gp((T*)I.bjinv);
+  const auto optr = gp(I.sw_op_ptr);
+  Blk<T> D = {T(0), T(0), T(0), T(0)};
+  if (upper) D = ld_blk(gp((const T*)I.pdinv), inf.x);
+  for (int e = inf.y + (int)threadIdx.x % kValueLanes; e < inf.z; e += kValueLanes) {
+    const int o0 = optr[e], o1 = optr[e + 1];
+    Blk<T> acc = {T(0), T(0), T(0), T(0)};
+    // two terms' loads at once, added in order
+    for (int o = o0; o < o1; o += 2) {
+      int2 op[2];
+      Blk<T> F[2], S[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) op[u] = ld_item(I.sw_ops, o + u < o1 ? o + u : o);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        F[u] = ld_blk<T>(P, op[u].x);
+        if (op[u].y >= 0)
+          S[u] = ld_blk<T>(V, op[u].y);
+        else
+          S[u] = {T(1), T(0), T(0), T(1)};
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (o + u < o1) blk_msub(acc, F[u], S[u]);
+    }
+    if (upper) acc = o0 == o1 ? D : blk_mul(D, acc);
+    st_blk(V, e, acc);
+  }
+}
+
+// One part of the forward (Upper false) or backward sweep.  The forward
+// sweep's result y goes to the basis storage's last vector (an Arnoldi cycle
+// of m <= km steps stores v_0 .. v_{m-1}, BiCGStab seven vectors of at least
+// 31), since a backward part reads y at rows whose z it writes.  In an Arnoldi
+// step (mode 0) the scaled input is also stored as basis vector v_j.
+template <typename T, bool Upper>
+__global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, const int2* __restrict__ work, int p0,
+                                                    int nrows, int mode) {
+  constexpr int G = kSweepLanes;
+  const SweepRow sr = sweep_row<G>(work, p0, nrows);
+  if (sr.pos < 0) return;  // whole lane groups leave together
+  const auto& I = *gp(gp(insts)[sr.slot]);
+  // tested only before the stores: the row's loads need not wait for it
+  const bool on = kstate_is(I, apply_state(mode));
+  const int lane = threadIdx.x % G;
+  const i4v inf = ((const PF_AS1 i4v*)I.sw_rows)[sr.pos];
+  const int r = inf.x;
+  const auto V = gp((const T*)I.bjinv);
+  const auto col = gp(I.sw_col);
+  const auto yv = gp((T*)I.kv) + (int64_t)I.km * 2 * I.nu;
+  const auto z = gp((T*)I.kz);
+  const auto w = gp((const T*)I.kw);
+  const PF_AS1 T* in = Upper ? (const PF_AS1 T*)yv : w;
+  const PF_AS1 T* out = Upper ? (const PF_AS1 T*)z : (const PF_AS1 T*)yv;
+  const double sc = !Upper && mode == 0 ? gp(I.ks)->scale : 1.0;
+  T v0 = T(0), v1 = T(0);
+  if (!Upper) {
+    v0 = (T)((double)w[2 * r] * sc);
+    v1 = (T)((double)w[2 * r + 1] * sc);
+  }
+  double a0 = 0.0, a1 = 0.0;
+  for (int e = inf.y + lane; e < inf.z; e += 4 * G) {
+    int c[4];
+    Blk<T> B[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int q = e + u * G < inf.z ? e + u * G : e;
+      c[u] = col[q];
+      B[u] = ld_blk<T>(V, q);
+    }
+    double x0[4], x1[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool own = c[u] < 0;
+      const PF_AS1 T* s = own ? in - 2 * (int64_t)(c[u] + 1) : out + 2 * (int64_t)c[u];
+      const T s0 = s[0], s1 = s[1];
+      x0[u] = !Upper && own ? (double)(T)((double)s0 * sc) : (double)s0;
+      x1[u] = !Upper && own ? (double)(T)((double)s1 * sc) : (double)s1;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e + u * G < inf.z) {
+        a0 += (double)B[u].a * x0[u] + (double)B[u].b * x1[u];
+        a1 += (double)B[u].c * x0[u] + (double)B[u].d * x1[u];
+      }
+  }
+#pragma unroll
+  for (int off = G / 2; off > 0; off >>= 1) {
+    a0 += __shfl_xor(a0, off, 64);
+    a1 += __shfl_xor(a1, off, 64);
+  }
+  if (!on || lane != 0) return;
+  if (Upper) {
+    z[2 * r] = (T)a0;
+    z[2 * r + 1] = (T)a1;
+  } else {
+    yv[2 * r] = (T)((double)v0 + a0);
+    yv[2 * r + 1] = (T)((double)v1 + a1);
+    if (mode == 0) {
+      const auto vj = gp((T*)I.kv) + (int64_t)gp(I.ks)->j * 2 * I.nu;
+      vj[2 * r] = v0;
+      vj[2 * r + 1] = v1;
+    }
+  }
 }
 
 // The whole ILU(0) factor of an instance in one work-group: the rows of
@@ -677,7 +824,7 @@ __global__ __launch_bounds__(1024) void k_ilu_apply_wg(const Inst* const* insts,
   __shared__ int lpf[LPM + 1], lpb[LPM + 1];
   const auto& I = *gp(insts[blockIdx.x]);
   const auto ks = gp(I.ks);
-  if (!gp(I.red)->active || I.kwide || ks->state != (apply_state(mode))) return;
+  if (!gp(I.red)->active || I.kwide || I.sw_rows || ks->state != (apply_state(mode))) return;
   const int nu = I.nu;
   if (2 * nu <= zmin || (ZV > 0 && 2 * nu > ZV)) return;
   T* z = ZV > 0 ? zl : (T*)I.kz;
@@ -1639,6 +1786,23 @@ void launch_ilu_apply_wg(hipStream_t st, const Inst* const* insts, int nslots, i
   if (2 * max_nu > small && 2 * min_nu <= big) k_ilu_apply_wg<T, big><<<g, 1024, 0, st>>>(insts, mode, small);
   if (2 * max_nu > big) k_ilu_apply_wg<T, 0><<<g, 1024, 0, st>>>(insts, mode, big);
 }
+int sweep_rows_per_group() { return 256 / kSweepLanes; }
+template <typename T>
+void launch_sweep_values(hipStream_t st, const Inst* const* insts, const int2* work, int nrows) {
+  constexpr int R = 256 / kValueLanes;  // lists are padded for the application's rows per group, a multiple
+  if (nrows > 0) k_sweep_values<T><<<dim3((unsigned)(nrows / R)), 256, 0, st>>>(insts, work);
+}
+template <typename T>
+void launch_sweep_part(hipStream_t st, const Inst* const* insts, const int2* work, int p0, int nrows, int upper,
+                       int mode) {
+  constexpr int R = 256 / kSweepLanes;
+  if (nrows <= 0) return;
+  const dim3 g((unsigned)((nrows + R - 1) / R));
+  if (upper)
+    k_sweep_part<T, true><<<g, 256, 0, st>>>(insts, work, p0, nrows, mode);
+  else
+    k_sweep_part<T, false><<<g, 256, 0, st>>>(insts, work, p0, nrows, mode);
+}
 template <typename T>
 void launch_bj_apply(hipStream_t st, const Inst* const* insts, const int2* work, int nbig, int nwork, int mode) {
   if (nwork > 0) k_bj_apply<T><<<dim3((unsigned)(nbig + (nwork - nbig) / 4)), 64, 0, st>>>(insts, work, nbig, mode);
@@ -1707,6 +1871,8 @@ int krylov_max_restart() { return KMAX; }
   template void launch_ilu_bwd<T>(hipStream_t, const Inst* const*, const int2*, int, int);  \
   template void launch_bj_apply<T>(hipStream_t, const Inst* const*, const int2*, int, int, int);\
   template void launch_ilu_factor_wg<T>(hipStream_t, const Inst* const*, int);              \
+  template void launch_sweep_values<T>(hipStream_t, const Inst* const*, const int2*, int);  \
+  template void launch_sweep_part<T>(hipStream_t, const Inst* const*, const int2*, int, int, int, int); \
   template void launch_ilu_apply_wg<T>(hipStream_t, const Inst* const*, int, int, int, int);\
   template void launch_karnoldi<T>(hipStream_t, const Inst* const*, int, int, KOpts);       \
   template void launch_kbegin<T>(hipStream_t, const Inst* const*, int, int, KOpts);         \

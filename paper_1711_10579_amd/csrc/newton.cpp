@@ -29,6 +29,7 @@ Batch::~Batch() {
     ctx->prof_flush();
     if (dmem) ctx->dfree(dmem);
     if (kmem) ctx->dfree(kmem);
+    if (smem) ctx->dfree(smem);
   }
   if (h_reds) (void)hipHostFree(h_reds);
   for (auto& g : graphs) g.reset();
@@ -356,6 +357,10 @@ pf_status start_batch(Batch* b, const pf_options* opt) {
       if (!ensure_krylov(c, opt->gmres_m)) return PF_E_NOMEM;
     if (!b->kbuilt && !b->build_krylov()) {
       set_error("pf_solve: Krylov batch set-up failed");
+      return PF_E_NOMEM;
+    }
+    if (opt->precond == PF_PRECOND_ILU0 && !b->sbuilt && !b->build_sweeps()) {
+      set_error("pf_solve: set-up of the ILU(0) sweeps failed");
       return PF_E_NOMEM;
     }
   }

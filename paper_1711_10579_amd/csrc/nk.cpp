@@ -242,7 +242,6 @@ bool Batch::build_krylov() {
   k_ulev.clear();
   max_kchunks = 0;
   size_t max_l = 0, max_u = 0;
-  k_min_nu = k_max_nu = 0;
   k_wide = k_narrow = false;
   // each instance takes its own path (one work-group, or one launch per
   // level when some level is too wide), whatever the batch holds
@@ -258,9 +257,7 @@ bool Batch::build_krylov() {
       max_l = std::max(max_l, ka.lev_ptr.size() - 1);
       max_u = std::max(max_u, ka.ulev_ptr.size() - 1);
     } else {
-      k_min_nu = k_narrow ? std::min(k_min_nu, ka.nu) : ka.nu;
       k_narrow = true;
-      k_max_nu = std::max(k_max_nu, ka.nu);
     }
   }
   auto levels = [&](bool upper, size_t nl, std::vector<std::pair<int64_t, int>>* out) {
@@ -311,6 +308,112 @@ bool Batch::build_krylov() {
   return ok;
 }
 
+bool ensure_sweep(Case* c) {
+  if (c->sw_state != Case::SW_NEW) return true;
+  const pfh::KAnalysis& ka = *c->ka;
+  // the entry values take the place of the block-Jacobi inverses
+  if (!pfh::plan_sweep(ka, krylov_wide(ka), ka.bj_off.back() / 4, &c->sw)) {
+    c->sw_state = Case::SW_NONE;
+    return true;
+  }
+  const int64_t nu = ka.nu, ne = c->sw.ne(), nops = c->sw.nops();
+  const size_t total = carve_bytes<int4>(2 * nu) + carve_bytes<int>(ne) + carve_bytes<int>(ne + 1) +
+                       carve_bytes<int2>(nops);
+  Ctx* ctx = c->ctx;
+  c->swbase = (char*)ctx->dalloc(total);
+  if (!c->swbase) {  // without room for the lists the sweeps go by levels
+    c->sw = pfh::KSweep();
+    c->sw_state = Case::SW_NONE;
+    return true;
+  }
+  // the four lists packed on the host as on the device: one copy
+  std::vector<char> pack(total);
+  char *p = c->swbase, *q = pack.data();
+  auto put = [&](const std::vector<int>& src) {
+    if (!src.empty()) std::memcpy(q + (p - c->swbase), src.data(), sizeof(int) * src.size());
+    return (const int*)carve<int>(p, (int64_t)src.size());
+  };
+  pfd::Inst& h = c->hinst;
+  h.sw_rows = (const int4*)put(c->sw.rows);
+  h.sw_col = put(c->sw.col);
+  h.sw_op_ptr = put(c->sw.op_ptr);
+  h.sw_ops = (const int2*)put(c->sw.ops);
+  hipStream_t s = ctx->stream;
+  bool ok = hipMemcpyAsync(c->swbase, pack.data(), total, hipMemcpyHostToDevice, s) == hipSuccess;
+  pfd::launch_set_inst(s, c->d_inst, h);
+  ok &= hipStreamSynchronize(s) == hipSuccess;
+  // the launch lists need the plan's rows and steps only
+  c->sw.col = c->sw.op_ptr = c->sw.ops = std::vector<int>();
+  c->sw_state = Case::SW_PLAN;
+  return ok;
+}
+
+bool Batch::build_sweeps() {
+  std::vector<int2> work;
+  s_low.clear();
+  s_up.clear();
+  s_step.clear();
+  s_narrow = s_wide = false;
+  k_min_nu = k_max_nu = 0;
+  int nlp = 0, nup = 0, nst = 0;
+  for (Case* c : cases) {
+    if (!c->ka || !ensure_sweep(c)) return false;
+    if (c->sw_state == Case::SW_PLAN) {
+      nlp = std::max(nlp, c->sw.nlp);
+      nup = std::max(nup, c->sw.nup);
+      nst = std::max(nst, c->sw.nsteps);
+    } else if (krylov_wide(*c->ka)) {
+      s_wide = true;
+    } else {
+      const int nu = c->ka->nu;
+      k_min_nu = s_narrow ? std::min(k_min_nu, nu) : nu;
+      k_max_nu = std::max(k_max_nu, nu);
+      s_narrow = true;
+    }
+  }
+  const size_t per = (size_t)pfd::sweep_rows_per_group();
+  auto list = [&](std::vector<std::pair<int64_t, int>>* out, auto&& positions) {
+    const size_t off = work.size();
+    for (int s = 0; s < nslots; ++s) {
+      if (cases[s]->sw_state != Case::SW_PLAN) continue;
+      positions(s, cases[s]->sw);
+      while ((work.size() - off) % per != 0) work.push_back(make_int2(s, -1));
+    }
+    out->emplace_back((int64_t)off, (int)(work.size() - off));
+  };
+  auto parts = [&](int np, bool upper, std::vector<std::pair<int64_t, int>>* out) {
+    for (int p = 0; p < np; ++p) {
+      if (nslots == 1) {  // positions of the only instance, no list
+        const int* pp = &cases[0]->sw.part_ptr[upper ? nlp + p : p];
+        out->emplace_back(pp[0], pp[1] - pp[0]);
+        continue;
+      }
+      list(out, [&](int s, const pfh::KSweep& sw) {
+        if (p >= (upper ? sw.nup : sw.nlp)) return;
+        const int* pp = &sw.part_ptr[upper ? sw.nlp + p : p];
+        for (int k = pp[0]; k < pp[1]; ++k) work.push_back(make_int2(s, k));
+      });
+    }
+  };
+  parts(nlp, false, &s_low);
+  parts(nup, true, &s_up);
+  for (int t = 0; t < nst; ++t)
+    list(&s_step, [&](int s, const pfh::KSweep& sw) {
+      for (int k = 0; k < (int)sw.step.size(); ++k)
+        if (sw.step[k] == t) work.push_back(make_int2(s, k));
+    });
+  if (smem) ctx->dfree(smem);
+  smem = (char*)ctx->dalloc(carve_bytes<int2>(std::max<int64_t>((int64_t)work.size(), 1)));
+  if (!smem) return false;
+  d_swork = (int2*)smem;
+  bool ok = true;
+  if (!work.empty())
+    ok &= hipMemcpyAsync(d_swork, work.data(), sizeof(int2) * work.size(), hipMemcpyHostToDevice, stream) == hipSuccess;
+  ok &= hipStreamSynchronize(stream) == hipSuccess;
+  sbuilt = ok;
+  return ok;
+}
+
 namespace {
 
 template <typename T>
@@ -341,6 +444,7 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
     if (ilu) {
       if (b->k_narrow) pfd::launch_ilu_factor_wg<T>(s, I, ns);
       for (const auto& l : b->k_lev) pfd::launch_ilu_rows<T>(s, I, kw + l.first, l.second);
+      for (const auto& l : b->s_step) pfd::launch_sweep_values<T>(s, I, b->d_swork + l.first, l.second);
     } else {
       pfd::launch_bj_inv<T>(s, I, kw + b->k_blocks.first, b->k_blocks_big, b->k_blocks.second - b->k_blocks_big);
     }
@@ -358,9 +462,20 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
   auto apply = [&](int mode) {
     Prof p(ctx, PF_K_PRECOND_APPLY, 0.0, 0.0);
     if (ilu) {
-      if (b->k_narrow) pfd::launch_ilu_apply_wg<T>(s, I, ns, mode, b->k_min_nu, b->k_max_nu);
-      for (const auto& l : b->k_lev) pfd::launch_ilu_fwd<T>(s, I, kw + l.first, l.second, mode);
-      for (const auto& l : b->k_ulev) pfd::launch_ilu_bwd<T>(s, I, kw + l.first, l.second, mode);
+      auto part = [&](const std::pair<int64_t, int>& l, int upper) {
+        if (ns == 1)
+          pfd::launch_sweep_part<T>(s, I, nullptr, (int)l.first, l.second, upper, mode);
+        else
+          pfd::launch_sweep_part<T>(s, I, b->d_swork + l.first, 0, l.second, upper, mode);
+      };
+      for (const auto& l : b->s_low) part(l, 0);
+      for (const auto& l : b->s_up) part(l, 1);
+      // the instances without a plan, by levels
+      if (b->s_narrow) pfd::launch_ilu_apply_wg<T>(s, I, ns, mode, b->k_min_nu, b->k_max_nu);
+      if (b->s_wide) {
+        for (const auto& l : b->k_lev) pfd::launch_ilu_fwd<T>(s, I, kw + l.first, l.second, mode);
+        for (const auto& l : b->k_ulev) pfd::launch_ilu_bwd<T>(s, I, kw + l.first, l.second, mode);
+      }
     } else {
       pfd::launch_bj_apply<T>(s, I, kw + b->k_blocks.first, b->k_blocks_big, b->k_blocks.second, mode);
     }
