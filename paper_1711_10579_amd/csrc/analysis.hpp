@@ -93,11 +93,11 @@ struct KAnalysis {
   int nu = 0;
   std::vector<int> p_of_r, r_of_p;       // Krylov row <-> factor position of the node
   std::vector<int> row_ptr, col, diag;   // block CSR pattern in Krylov order
-  // ILU(0) in its IKJ form: lower entry q of row r (column k < r) is
-  // followed by the updates A(r, j) -= L(r, k) U(k, j) for the listed pairs
-  // (t = position of (r, j), s = position of (k, j)), j > k
-  std::vector<int> up_ptr;               // [nnz+1], non-empty only for lower entries
-  std::vector<int> up_t, up_s;
+  // ILU(0) by targets: block t = (r, j) receives A(r, j) -= L(r, k) U(k, j)
+  // for the listed pairs (q = position of (r, k), s = position of (k, j)),
+  // k < min(r, j) ascending
+  std::vector<int> up_ptr;               // [nnz+1]
+  std::vector<int> up_q, up_s;
   // rows by level: a row's lower neighbours are in earlier levels (factor
   // and forward solve); its upper neighbours are in earlier levels of the
   // backward order
@@ -109,7 +109,7 @@ struct KAnalysis {
   std::vector<int64_t> bj_off;
   int bj_max = 0;
   int64_t nnz() const { return (int64_t)col.size(); }
-  int64_t nup() const { return (int64_t)up_t.size(); }
+  int64_t nup() const { return (int64_t)up_q.size(); }
   int nblocks() const { return (int)bj_ptr.size() - 1; }
 };
 
@@ -146,6 +146,12 @@ struct KSweep {
 std::vector<int> rcm_order(const std::vector<std::vector<int>>& adj);
 
 KAnalysis analyze_krylov(const Analysis& an, int n, const int* row_ptr, const int* col, int bj_cap);
+
+// The factor's targets by level (a block (r, j) with updates is due in the
+// level of row min(r, j), row r's diagonal block, listed as ~t, in its own):
+// ptr [levels + 1] into tgt.  The blocks left of the diagonal hold A - sum
+// L U, unscaled, until the factor's last pass multiplies them by D^{-1}.
+void factor_targets(const KAnalysis& ka, std::vector<int>* ptr, std::vector<int>* tgt);
 
 // Merge the sweep levels into parts whose rows have at most `cap` entries
 // each (the rows of a level on its own may have more); false, and the plan

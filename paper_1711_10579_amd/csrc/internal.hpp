@@ -192,8 +192,7 @@ struct Batch {
   int64_t max_lu = 0, max_tail = 0;
   int trsv_single = 0;
 
-  // Krylov launch lists (built on the first Krylov step of the batch): rows
-  // by ILU level (factor and forward solve), by backward level, and the
+  // Krylov launch lists (built on the first Krylov step of the batch): the
   // block-Jacobi blocks, as (offset, count) ranges of d_kwork
   // the Newton step of the LU inner solve captured as a HIP graph, per
   // precision, with the convergence-test options baked into it
@@ -211,21 +210,24 @@ struct Batch {
   bool kbuilt = false;
   char* kmem = nullptr;
   int2* d_kwork = nullptr;
-  std::vector<std::pair<int64_t, int>> k_lev, k_ulev;
   std::pair<int64_t, int> k_blocks{0, 0};
   int k_blocks_big = 0;  // the first k_blocks_big groups of k_blocks are above the small size
   int max_kchunks = 0;
-  int k_min_nu = 0, k_max_nu = 0;
-  bool k_wide = false;    // some instance has an ILU(0) level wider than one work-group pass
-  bool k_narrow = false;  // some instance runs its ILU(0) in one work-group
-  // ILU(0) sweeps (built on the first ILU(0) step of the batch): row ranges
-  // of the parts, forward then backward, and of the value set-up's steps in
-  // d_swork, rows padded to whole work-groups of one instance each
+  // ILU(0) lists (built on the first ILU(0) step of the batch).  Factor: per
+  // launch a range of work-group descriptors (an instance's k-th launch is
+  // its k-th run of narrow levels or wide level).  Sweeps: row ranges of the
+  // parts, forward then backward, and of the value set-up's steps in d_swork,
+  // rows padded to whole work-groups of one instance each; rows by forward
+  // and by backward level of the instances that take a launch per level
   bool sbuilt = false;
   char* smem = nullptr;
   int2* d_swork = nullptr;
-  std::vector<std::pair<int64_t, int>> s_low, s_up, s_step;
-  bool s_narrow = false, s_wide = false;  // some instance sweeps by levels: in one work-group, a launch per level
+  std::vector<std::pair<int64_t, int>> f_seg;
+  const int4* d_fdesc = nullptr;
+  const int *d_ftgt = nullptr, *d_flev = nullptr;
+  std::vector<std::pair<int64_t, int>> s_low, s_up, s_step, s_lev, s_ulev;
+  bool s_narrow = false;  // some instance sweeps by levels in one work-group
+  int s_min_nu = 0, s_max_nu = 0;  // least and most rows of those
 
   ~Batch();
   // launch plan and device table in memory the batch allocates (and pinned
@@ -238,7 +240,7 @@ struct Batch {
   size_t plan_bytes(size_t nwork) const;
   bool place(char* mem, const std::vector<int2>& work);
   bool build_krylov();
-  bool build_sweeps();
+  bool build_ilu();
 };
 
 // Kernel-class timing of the launches issued while it lives.

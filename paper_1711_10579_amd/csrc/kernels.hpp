@@ -61,8 +61,15 @@ void launch_bwd_solve(hipStream_t, const Inst* const* insts, const int2* work, i
 // iteration
 template <typename T>
 void launch_kfill(hipStream_t, const Inst* const* insts, int nslots, int max_nnz, int ilu);
+// ILU(0) factor: work-group descriptors {slot, a, b, kind} (kind 0: targets
+// tgt[a, b) of one level, ilu_factor_threads at a time; 1: levels a .. b - 1
+// of the pointers lev into tgt), then the scaling of the lower blocks
+int ilu_factor_threads();
 template <typename T>
-void launch_ilu_rows(hipStream_t, const Inst* const* insts, const int2* work, int nwork);
+void launch_ilu_factor(hipStream_t, const Inst* const* insts, const int4* desc, int ngroups, const int* tgt,
+                       const int* lev);
+template <typename T>
+void launch_ilu_scale(hipStream_t, const Inst* const* insts, int nslots, int max_chunks);
 template <typename T>
 void launch_bj_inv(hipStream_t, const Inst* const* insts, const int2* work, int nbig, int nsmall);
 int bj_small_nodes();  // groups of at most this many nodes are inverted one per wave
@@ -70,8 +77,6 @@ template <typename T>
 void launch_ilu_fwd(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int mode);
 template <typename T>
 void launch_ilu_bwd(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int mode);
-template <typename T>
-void launch_ilu_factor_wg(hipStream_t, const Inst* const* insts, int nslots);
 template <typename T>
 void launch_ilu_apply_wg(hipStream_t, const Inst* const* insts, int nslots, int mode, int min_nu, int max_nu);
 template <typename T>

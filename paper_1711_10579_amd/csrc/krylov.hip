@@ -189,77 +189,131 @@ __device__ inline void spmv_row(const IR& I, int r, XP x, double& acc0, double& 
 // ---------------------------------------------------------------------------
 // preconditioner set-up
 
-// ILU(0) rows of one level (IKJ form): each lower block of row r becomes
-// L(r,k) = A(r,k) U(k,k)^{-1}, followed by its listed updates
-// A(r,j) -= L(r,k) U(k,j); then the row's diagonal block is inverted.  One
-// thread per row; rows of earlier levels are final.
-// The updates of row r from one of its lower entries, L = L(r, k):
-// P(t_u) -= L P(s_u) for u in [u0, u1).  The targets are distinct entries of
-// row r and the sources lie in row k < r, so the loads of four updates are
-// issued together; every target still sees its updates in the order of the
-// row's lower entries.
-template <typename T, typename PP, typename IP>
-__device__ inline void ilu_updates(PP P, IP kup_t, IP kup_s, int u0, int u1, const Blk<T>& L) {
-  for (int u = u0; u < u1; u += 4) {
-    int t[4], sr[4];
+// ILU(0), target by target: block t = (r, j) becomes A(r, j) - sum L(r, k)
+// U(k, j) over its list, k ascending, one thread per target.  Its inputs are
+// due in earlier levels, and the blocks left of the diagonal stay unscaled
+// (L(r, k) = P(r, k) D_k^{-1} is formed where it is read) until the last pass
+// multiplies them, so a target needs nothing of its own row's level and a
+// level is one round of loads.  Bound by that round and the barrier, about 3
+// us a level: 110 -> 78 us a factor at 3,000 buses, 1,456 -> 596 us on the
+// 2,000-bus feeder (row by row before, each lower entry waiting for the one
+// before it).
+//
+// A work-group takes a range of targets of one level, or, where levels hold
+// few, a run of levels with a barrier between them; the indices of a thread's
+// first target of the next level arrive during the level before.
+
+constexpr int kFacThreads = 512;  // eight waves: four terms' blocks of a thread stay in registers
+constexpr int kFacOps = 4;  // terms of a target fetched ahead
+
+struct FacIdx {
+  int code, n;  // target (~t: a diagonal block), its terms
+  int o;        // first term
+  int q[kFacOps], s[kFacOps], m[kFacOps];
+};
+
+template <typename IR>
+__device__ inline void fac_index(const IR& I, const PF_AS1 int* tgt, int i, int i1, FacIdx* f) {
+  f->n = -1;
+  if (i >= i1) return;
+  f->code = tgt[i];
+  const int t = f->code < 0 ? ~f->code : f->code;
+  f->o = gp(I.kup_ptr)[t];
+  f->n = gp(I.kup_ptr)[t + 1] - f->o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (u + e < u1) {
-        t[e] = kup_t[u + e];
-        sr[e] = kup_s[u + e];
-      }
-    Blk<T> a[4], b[4];
+  for (int u = 0; u < kFacOps; ++u)
+    if (u < f->n) {
+      f->q[u] = gp(I.kup_q)[f->o + u];
+      f->s[u] = gp(I.kup_s)[f->o + u];
+    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (u + e < u1) {
-        a[e] = ld_blk<T>(P, t[e]);
-        b[e] = ld_blk<T>(P, sr[e]);
-      }
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (u + e < u1) {
-        blk_msub(a[e], L, b[e]);
-        st_blk(P, t[e], a[e]);
-      }
-  }
+  for (int u = 0; u < kFacOps; ++u)
+    if (u < f->n) f->m[u] = gp(I.kcol)[f->q[u]];
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_ilu_rows(const Inst* const* insts, const int2* __restrict__ work, int nwork) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nwork) return;
-  const int2 wk = ld_item(work, idx);
-  const auto& I = *gp(gp(insts)[wk.x]);
-  if (!gp(I.red)->active) return;
-  const int r = wk.y;
+// the target's block formed and stored; true when a diagonal block has no
+// inverse (its stored inverse is then zero)
+template <typename T, typename IR>
+__device__ inline bool fac_target(const IR& I, const FacIdx& f) {
+  if (f.n < 0) return false;
   const auto P = gp((T*)I.pval);
   const auto D = gp((T*)I.pdinv);
-  const int qd = gp(I.kdiag)[r];
-  const auto kcol = gp(I.kcol), kup_ptr = gp(I.kup_ptr), kup_t = gp(I.kup_t), kup_s = gp(I.kup_s);
-  const int q0 = gp(I.krow_ptr)[r];
-  // as in k_ilu_factor_wg: the next lower entry's column, update range and
-  // diagonal inverse fetched during this entry's updates
-  if (q0 < qd) {
-    int u0 = kup_ptr[q0], u1 = kup_ptr[q0 + 1];
-    Blk<T> Dk = ld_blk<T>(D, kcol[q0]);
-    for (int q = q0; q < qd; ++q) {
-      const int qn = q + 1 < qd ? q + 1 : q;
-      const int cn = kcol[qn], un = kup_ptr[qn + 1];
-      const Blk<T> L = blk_mul(ld_blk<T>(P, q), Dk);
-      st_blk(P, q, L);
-      const Blk<T> Dn = ld_blk<T>(D, cn);
-      ilu_updates<T>(P, kup_t, kup_s, u0, u1, L);
-      u0 = u1;
-      u1 = un;
-      Dk = Dn;
+  const int t = f.code < 0 ? ~f.code : f.code;
+  Blk<T> acc = ld_blk<T>(P, t);
+  Blk<T> L[kFacOps], Dk[kFacOps], U[kFacOps];
+#pragma unroll
+  for (int u = 0; u < kFacOps; ++u)
+    if (u < f.n) {
+      L[u] = ld_blk<T>(P, f.q[u]);
+      Dk[u] = ld_blk<T>(D, f.m[u]);
+      U[u] = ld_blk<T>(P, f.s[u]);
+    }
+#pragma unroll
+  for (int u = 0; u < kFacOps; ++u)
+    if (u < f.n) blk_msub(acc, blk_mul(L[u], Dk[u]), U[u]);
+  for (int u = kFacOps; u < f.n; ++u) {
+    const int q = gp(I.kup_q)[f.o + u], s = gp(I.kup_s)[f.o + u];
+    blk_msub(acc, blk_mul(ld_blk<T>(P, q), ld_blk<T>(D, gp(I.kcol)[q])), ld_blk<T>(P, s));
+  }
+  if (f.n > 0) st_blk(P, t, acc);
+  if (f.code >= 0) return false;
+  Blk<T> inv;
+  const bool bad = !blk_inv(acc, &inv);
+  if (bad) inv.a = inv.b = inv.c = inv.d = T(0);
+  st_blk(D, gp(I.kcol)[t], inv);
+  return bad;
+}
+
+// Work-group descriptor {slot, a, b, kind}: kind 0 targets tgt[a, b) of one
+// level, kind 1 levels a .. b - 1 of the pointers lev (into tgt).
+template <typename T>
+__global__ __launch_bounds__(kFacThreads) void k_ilu_factor(const Inst* const* insts, const int4* __restrict__ desc,
+                                                            const int* __restrict__ tgt_, const int* __restrict__ lev_) {
+  const i4v d = ((const PF_AS1 i4v*)desc)[blockIdx.x];
+  const auto& I = *gp(gp(insts)[d.x]);
+  if (!gp(I.red)->active) return;
+  const auto tgt = gp(tgt_), lev = gp(lev_);
+  const int tid = threadIdx.x;
+  bool bad = false;
+  if (d.w == 0) {
+    for (int i = d.y + tid; i < d.z; i += kFacThreads) {
+      FacIdx f;
+      fac_index(I, tgt, i, d.z, &f);
+      bad |= fac_target<T>(I, f);
+    }
+  } else {
+    FacIdx f, g;
+    int p0 = lev[d.y], p1 = lev[d.y + 1];
+    fac_index(I, tgt, p0 + tid, p1, &f);
+    for (int l = d.y; l < d.z; ++l) {
+      const int n1 = l + 1 < d.z ? lev[l + 2] : p1;
+      fac_index(I, tgt, p1 + tid, n1, &g);
+      bad |= fac_target<T>(I, f);
+      for (int i = p0 + tid + kFacThreads; i < p1; i += kFacThreads) {
+        FacIdx x;
+        fac_index(I, tgt, i, p1, &x);
+        bad |= fac_target<T>(I, x);
+      }
+      __syncthreads();
+      p0 = p1;
+      p1 = n1;
+      f = g;
     }
   }
-  Blk<T> inv;
-  if (!blk_inv(ld_blk(P, qd), &inv)) {
-    gp(I.red)->singular = 1;
-    inv.a = inv.b = inv.c = inv.d = T(0);
-  }
-  st_blk(D, r, inv);
+  if (bad) gp(I.red)->singular = 1;
+}
+
+// The last pass: L(r, k) = P(r, k) D_k^{-1} for the blocks left of the
+// diagonal, one thread per row.
+template <typename T>
+__global__ __launch_bounds__(KCH) void k_ilu_scale(const Inst* const* insts) {
+  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const int r = blockIdx.x * KCH + threadIdx.x;
+  if (!gp(I.red)->active || r >= I.nu) return;
+  const auto P = gp((T*)I.pval);
+  const auto D = gp((const T*)I.pdinv);
+  const int q1 = gp(I.kdiag)[r];
+  for (int q = gp(I.krow_ptr)[r]; q < q1; ++q) st_blk(P, q, blk_mul(ld_blk<T>(P, q), ld_blk<T>(D, gp(I.kcol)[q])));
 }
 
 // Block-Jacobi: inverse of the diagonal block A_bb of one node group (order
@@ -531,7 +585,7 @@ __global__ __launch_bounds__(256) void k_ilu_fwd(const Inst* const* insts, const
   if (idx >= nwork) return;
   const int2 wk = ld_item(work, idx);
   const auto& I = *gp(gp(insts)[wk.x]);
-  if (!kstate_is(I, apply_state(mode)) || I.sw_rows) return;
+  if (!kstate_is(I, apply_state(mode))) return;
   const int r = wk.y;
   const auto w = gp((const T*)I.kw);
   const auto z = gp((T*)I.kz);
@@ -560,7 +614,7 @@ __global__ __launch_bounds__(256) void k_ilu_bwd(const Inst* const* insts, const
   if (idx >= nwork) return;
   const int2 wk = ld_item(work, idx);
   const auto& I = *gp(gp(insts)[wk.x]);
-  if (!kstate_is(I, apply_state(mode)) || I.sw_rows) return;
+  if (!kstate_is(I, apply_state(mode))) return;
   const int r = wk.y;
   const auto z = gp((T*)I.kz);
   const auto P = gp((const T*)I.pval);
@@ -716,55 +770,6 @@ __global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, co
       vj[2 * r + 1] = v1;
     }
   }
-}
-
-// The whole ILU(0) factor of an instance in one work-group: the rows of
-// each level as in k_ilu_rows, a barrier between levels.  Used when the
-// instance's levels are short (one launch instead of one per level).
-template <typename T>
-__global__ __launch_bounds__(1024) void k_ilu_factor_wg(const Inst* const* insts) {
-  const auto& I = *gp(insts[blockIdx.x]);
-  if (!gp(I.red)->active || I.kwide) return;
-  auto P = gp((T*)I.pval);
-  auto D = gp((T*)I.pdinv);
-  const auto kl_ptr = gp(I.kl_ptr), kcol = gp(I.kcol), kup_ptr = gp(I.kup_ptr), kup_t = gp(I.kup_t),
-             kup_s = gp(I.kup_s);
-  const auto kl_info = (const PF_AS1 i4v*)I.kl_info;
-  bool bad = false;
-  for (int l = 0; l < I.knl; ++l) {
-    const int k1 = kl_ptr[l + 1];
-    for (int k = kl_ptr[l] + (int)threadIdx.x; k < k1; k += 1024) {
-      const i4v inf = kl_info[k];
-      const int r = inf.x, qd = inf.z;
-      // the next lower entry's column, update range and diagonal inverse
-      // (read-only, or final from earlier levels) are fetched during this
-      // entry's updates; its own block is read after them, as they may
-      // change it
-      if (inf.y < qd) {
-        int u0 = kup_ptr[inf.y], u1 = kup_ptr[inf.y + 1];
-        Blk<T> Dk = ld_blk<T>(D, kcol[inf.y]);
-        for (int q = inf.y; q < qd; ++q) {
-          const int qn = q + 1 < qd ? q + 1 : q;
-          const int cn = kcol[qn], un = kup_ptr[qn + 1];
-          const Blk<T> L = blk_mul(ld_blk<T>(P, q), Dk);
-          st_blk(P, q, L);
-          const Blk<T> Dn = ld_blk<T>(D, cn);
-          ilu_updates<T>(P, kup_t, kup_s, u0, u1, L);
-          u0 = u1;
-          u1 = un;
-          Dk = Dn;
-        }
-      }
-      Blk<T> inv;
-      if (!blk_inv(ld_blk<T>(P, qd), &inv)) {
-        bad = true;
-        inv.a = inv.b = inv.c = inv.d = T(0);
-      }
-      st_blk(D, r, inv);
-    }
-    __syncthreads();
-  }
-  if (bad) gp(I.red)->singular = 1;
 }
 
 namespace {
@@ -1751,9 +1756,15 @@ static inline dim3 chunk_grid(int max_chunks, int nslots) {
 static inline dim3 slot_grid(int nslots) { return dim3((unsigned)((nslots + 63) / 64)); }
 static inline dim3 item_grid(int nwork) { return dim3((unsigned)((nwork + 255) / 256)); }
 
+int ilu_factor_threads() { return kFacThreads; }
 template <typename T>
-void launch_ilu_rows(hipStream_t st, const Inst* const* insts, const int2* work, int nwork) {
-  if (nwork > 0) k_ilu_rows<T><<<item_grid(nwork), 256, 0, st>>>(insts, work, nwork);
+void launch_ilu_factor(hipStream_t st, const Inst* const* insts, const int4* desc, int ngroups, const int* tgt,
+                       const int* lev) {
+  if (ngroups > 0) k_ilu_factor<T><<<dim3((unsigned)ngroups), kFacThreads, 0, st>>>(insts, desc, tgt, lev);
+}
+template <typename T>
+void launch_ilu_scale(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks) {
+  k_ilu_scale<T><<<chunk_grid(max_chunks, nslots), KCH, 0, st>>>(insts);
 }
 template <typename T>
 void launch_bj_inv(hipStream_t st, const Inst* const* insts, const int2* work, int nbig, int nsmall) {
@@ -1769,10 +1780,6 @@ void launch_ilu_fwd(hipStream_t st, const Inst* const* insts, const int2* work, 
 template <typename T>
 void launch_ilu_bwd(hipStream_t st, const Inst* const* insts, const int2* work, int nwork, int mode) {
   if (nwork > 0) k_ilu_bwd<T><<<item_grid(nwork), 256, 0, st>>>(insts, work, nwork, mode);
-}
-template <typename T>
-void launch_ilu_factor_wg(hipStream_t st, const Inst* const* insts, int nslots) {
-  k_ilu_factor_wg<T><<<dim3((unsigned)nslots), 1024, 0, st>>>(insts);
 }
 // z in LDS up to 160,000 bytes of values per work-group, in two sizes so that
 // small instances keep several work-groups per CU
@@ -1865,12 +1872,12 @@ void launch_kgather(hipStream_t st, const Inst* const* insts, int nslots, int* o
 int krylov_max_restart() { return KMAX; }
 
 #define PF_KINST(T)                                                                    \
-  template void launch_ilu_rows<T>(hipStream_t, const Inst* const*, const int2*, int);      \
+  template void launch_ilu_factor<T>(hipStream_t, const Inst* const*, const int4*, int, const int*, const int*); \
+  template void launch_ilu_scale<T>(hipStream_t, const Inst* const*, int, int);             \
   template void launch_bj_inv<T>(hipStream_t, const Inst* const*, const int2*, int, int);   \
   template void launch_ilu_fwd<T>(hipStream_t, const Inst* const*, const int2*, int, int);  \
   template void launch_ilu_bwd<T>(hipStream_t, const Inst* const*, const int2*, int, int);  \
   template void launch_bj_apply<T>(hipStream_t, const Inst* const*, const int2*, int, int, int);\
-  template void launch_ilu_factor_wg<T>(hipStream_t, const Inst* const*, int);              \
   template void launch_sweep_values<T>(hipStream_t, const Inst* const*, const int2*, int);  \
   template void launch_sweep_part<T>(hipStream_t, const Inst* const*, const int2*, int, int, int, int); \
   template void launch_ilu_apply_wg<T>(hipStream_t, const Inst* const*, int, int, int, int);\

@@ -140,23 +140,39 @@ KAnalysis analyze_krylov(const Analysis& an, int n, const int* row_ptr, const in
   }
   // ILU(0) update lists
   ka.up_ptr.assign(ka.nnz() + 1, 0);
-  std::vector<int> where(nu, -1);
+  std::vector<int> where(nu, -1), rt, rq, rs, fill;
   for (int r = 0; r < nu; ++r) {
-    for (int q = ka.row_ptr[r]; q < ka.row_ptr[r + 1]; ++q) where[ka.col[q]] = q;
-    for (int q = ka.row_ptr[r]; q < ka.row_ptr[r + 1]; ++q) {
-      if (q < ka.diag[r]) {
-        const int k = ka.col[q];
-        for (int s = ka.diag[k] + 1; s < ka.row_ptr[k + 1]; ++s) {
-          const int t = where[ka.col[s]];
-          if (t >= 0) {
-            ka.up_t.push_back(t);
-            ka.up_s.push_back(s);
-          }
+    const int b = ka.row_ptr[r], e = ka.row_ptr[r + 1], o0 = ka.up_ptr[b];
+    for (int q = b; q < e; ++q) where[ka.col[q]] = q;
+    rt.clear();
+    rq.clear();
+    rs.clear();
+    for (int q = b; q < ka.diag[r]; ++q) {
+      const int k = ka.col[q];
+      for (int s = ka.diag[k] + 1; s < ka.row_ptr[k + 1]; ++s) {
+        const int t = where[ka.col[s]];
+        if (t >= 0) {
+          rt.push_back(t);
+          rq.push_back(q);
+          rs.push_back(s);
         }
       }
-      ka.up_ptr[q + 1] = (int)ka.up_t.size();
     }
-    for (int q = ka.row_ptr[r]; q < ka.row_ptr[r + 1]; ++q) where[ka.col[q]] = -1;
+    // the row's pairs by target, each target's in the order found
+    for (int t : rt) ka.up_ptr[t + 1]++;
+    fill.assign(e - b, 0);
+    for (int t = b; t < e; ++t) {
+      fill[t - b] = ka.up_ptr[t];
+      ka.up_ptr[t + 1] += ka.up_ptr[t];
+    }
+    ka.up_q.resize(o0 + rt.size());
+    ka.up_s.resize(o0 + rt.size());
+    for (size_t i = 0; i < rt.size(); ++i) {
+      const int at = fill[rt[i] - b]++;
+      ka.up_q[at] = rq[i];
+      ka.up_s[at] = rs[i];
+    }
+    for (int q = b; q < e; ++q) where[ka.col[q]] = -1;
   }
   // levels
   auto group = [&](const std::vector<int>& lev, std::vector<int>* ptr, std::vector<int>* rows) {

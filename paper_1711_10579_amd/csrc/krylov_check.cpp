@@ -117,19 +117,19 @@ extern "C" pf_status pf_debug_krylov_check(const pf_case_desc* d, uint64_t seed,
         hit[kmap[q]]++;
       }
     for (int64_t q = 0; q < nnz; ++q) req(hit[q] == 1, "block not hit exactly once by the map");
-    // ILU(0) update lists: exactly the pairs (r,j) in row r and (k,j) in row k, j > k
+    // ILU(0) update lists: of block (r, j) exactly the pairs (r, k), (k, j)
+    // of the pattern with k < min(r, j), k ascending
     for (int r = 0; r < nu; ++r)
-      for (int q = ka.row_ptr[r]; q < ka.row_ptr[r + 1]; ++q) {
-        const int k = ka.col[q];
+      for (int t = ka.row_ptr[r]; t < ka.row_ptr[r + 1]; ++t) {
+        const int j = ka.col[t];
         std::vector<std::pair<int, int>> want;
-        if (q < ka.diag[r])
-          for (int s = ka.diag[k] + 1; s < ka.row_ptr[k + 1]; ++s) {
-            const int t = find(r, ka.col[s]);
-            if (t >= 0) want.emplace_back(t, s);
-          }
-        req(ka.up_ptr[q + 1] - ka.up_ptr[q] == (int)want.size(), "update list length");
-        for (int u = ka.up_ptr[q], w = 0; u < ka.up_ptr[q + 1]; ++u, ++w)
-          req(ka.up_t[u] == want[w].first && ka.up_s[u] == want[w].second, "update list entry");
+        for (int q = ka.row_ptr[r]; q < ka.diag[r] && ka.col[q] < j; ++q) {
+          const int s = find(ka.col[q], j);
+          if (s >= 0) want.emplace_back(q, s);
+        }
+        req(ka.up_ptr[t + 1] - ka.up_ptr[t] == (int)want.size(), "update list length");
+        for (int u = ka.up_ptr[t], w = 0; u < ka.up_ptr[t + 1]; ++u, ++w)
+          req(ka.up_q[u] == want[w].first && ka.up_s[u] == want[w].second, "update list entry");
       }
     // level schedules
     auto check_levels = [&](const std::vector<int>& ptr, const std::vector<int>& lr, bool upper) {
@@ -192,23 +192,46 @@ extern "C" pf_status pf_debug_krylov_check(const pf_case_desc* d, uint64_t seed,
     }
     P = A;
     std::vector<B2> Dinv(nu);
-    for (size_t l = 0; l + 1 < ka.lev_ptr.size(); ++l)
-      for (int k = ka.lev_ptr[l]; k < ka.lev_ptr[l + 1]; ++k) {
-        const int r = ka.lev_rows[k];
-        for (int q = ka.row_ptr[r]; q < ka.diag[r]; ++q) {
-          const B2 L = mul(P[q], Dinv[ka.col[q]]);
-          P[q] = L;
-          for (int u = ka.up_ptr[q]; u < ka.up_ptr[q + 1]; ++u) {
-            const B2 t = mul(L, P[ka.up_s[u]]);
-            B2& a = P[ka.up_t[u]];
-            a.a -= t.a;
-            a.b -= t.b;
-            a.c -= t.c;
-            a.d -= t.d;
+    std::vector<int> tptr, tgt;
+    pfh::factor_targets(ka, &tptr, &tgt);
+    {
+      // every block with updates once and every diagonal block, in the level
+      // after those of every block its updates read
+      std::vector<int> lev(nnz, -1), dlev(nu, -1);
+      for (size_t l = 0; l + 1 < tptr.size(); ++l)
+        for (int i = tptr[l]; i < tptr[l + 1]; ++i) {
+          const int t = tgt[i] < 0 ? ~tgt[i] : tgt[i];
+          req(t >= 0 && t < nnz && lev[t] < 0, "factor target out of range or listed twice");
+          lev[t] = (int)l;
+          if (tgt[i] < 0) {
+            req(ka.diag[ka.col[t]] == t, "factor target marked as a diagonal block");
+            dlev[ka.col[t]] = (int)l;
           }
         }
-        Dinv[r] = inv(P[ka.diag[r]]);
+      for (int r = 0; r < nu; ++r) req(dlev[r] >= 0, "diagonal block without a factor target");
+      for (int64_t t = 0; t < nnz; ++t) {
+        req(lev[t] >= 0 || ka.up_ptr[t] == ka.up_ptr[t + 1], "block with updates without a factor target");
+        for (int u = ka.up_ptr[t]; u < ka.up_ptr[t + 1]; ++u)
+          req(lev[ka.up_q[u]] < lev[t] && lev[ka.up_s[u]] < lev[t] && dlev[ka.col[ka.up_q[u]]] < lev[t],
+              "factor target reads a block that is not final");
       }
+    }
+    for (int i : tgt) {
+      const int t = i < 0 ? ~i : i;
+      B2 a = P[t];
+      for (int u = ka.up_ptr[t]; u < ka.up_ptr[t + 1]; ++u) {
+        const B2 L = mul(P[ka.up_q[u]], Dinv[ka.col[ka.up_q[u]]]);
+        const B2 m = mul(L, P[ka.up_s[u]]);
+        a.a -= m.a;
+        a.b -= m.b;
+        a.c -= m.c;
+        a.d -= m.d;
+      }
+      P[t] = a;
+      if (i < 0) Dinv[ka.col[t]] = inv(a);
+    }
+    for (int r = 0; r < nu; ++r)
+      for (int q = ka.row_ptr[r]; q < ka.diag[r]; ++q) P[q] = mul(P[q], Dinv[ka.col[q]]);
     // (L U)(r, c) = sum over k <= min(r, c) of L(r, k) U(k, c), L(r, r) = I
     double dev = 0, amax = 0;
     for (int r = 0; r < nu; ++r)

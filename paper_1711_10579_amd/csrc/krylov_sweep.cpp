@@ -1,7 +1,7 @@
-// Parts of the ILU(0) sweeps (Sec. III-B preconditioner): runs of levels
-// whose rows are written out in terms of the part's input, so that an
-// application is one launch per part instead of one barrier or launch per
-// level.
+// ILU(0) preconditioner (Sec. III-B): the factor's targets by level, and the
+// parts of its sweeps: runs of levels whose rows are written out in terms of
+// the part's input, so that an application is one launch per part instead of
+// one barrier or launch per level.
 
 #include <algorithm>
 #include <cstdint>
@@ -9,6 +9,33 @@
 #include "analysis.hpp"
 
 namespace pfh {
+
+void factor_targets(const KAnalysis& ka, std::vector<int>* ptr, std::vector<int>* tgt) {
+  const int nl = (int)ka.lev_ptr.size() - 1;
+  std::vector<int> lev(ka.nu);
+  for (int l = 0; l < nl; ++l)
+    for (int k = ka.lev_ptr[l]; k < ka.lev_ptr[l + 1]; ++k) lev[ka.lev_rows[k]] = l;
+  ptr->assign(nl + 1, 0);
+  tgt->clear();
+  std::vector<int> fill;
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int r = 0; r < ka.nu; ++r)
+      for (int t = ka.row_ptr[r]; t < ka.row_ptr[r + 1]; ++t) {
+        const bool diag = t == ka.diag[r];
+        if (!diag && ka.up_ptr[t] == ka.up_ptr[t + 1]) continue;
+        const int l = lev[t < ka.diag[r] ? ka.col[t] : r];
+        if (pass == 0)
+          (*ptr)[l + 1]++;
+        else
+          (*tgt)[fill[l]++] = diag ? ~t : t;
+      }
+    if (pass == 0) {
+      for (int l = 0; l < nl; ++l) (*ptr)[l + 1] += (*ptr)[l];
+      tgt->resize(ptr->back());
+      fill.assign(ptr->begin(), ptr->end() - 1);
+    }
+  }
+}
 
 bool build_sweep(const KAnalysis& ka, int cap, int64_t max_entries, KSweep* out) {
   KSweep& s = *out;

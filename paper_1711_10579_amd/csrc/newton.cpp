@@ -359,8 +359,8 @@ pf_status start_batch(Batch* b, const pf_options* opt) {
       set_error("pf_solve: Krylov batch set-up failed");
       return PF_E_NOMEM;
     }
-    if (opt->precond == PF_PRECOND_ILU0 && !b->sbuilt && !b->build_sweeps()) {
-      set_error("pf_solve: set-up of the ILU(0) sweeps failed");
+    if (opt->precond == PF_PRECOND_ILU0 && !b->sbuilt && !b->build_ilu()) {
+      set_error("pf_solve: set-up of the ILU(0) lists failed");
       return PF_E_NOMEM;
     }
   }

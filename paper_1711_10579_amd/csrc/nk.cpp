@@ -108,7 +108,7 @@ bool attach_krylov(Case* c, int m, char* base, bool own, hipStream_t s) {
   int* kdiag = carve<int>(p, nu);
   int* kmap = carve<int>(p, c->nnz);
   int* kup_ptr = carve<int>(p, knnz + 1);
-  int* kup_t = carve<int>(p, nup);
+  int* kup_q = carve<int>(p, nup);
   int* kup_s = carve<int>(p, nup);
   int* bj_ptr = carve<int>(p, nb + 1);
   int* bj_rows = carve<int>(p, nu);
@@ -143,7 +143,7 @@ bool attach_krylov(Case* c, int m, char* base, bool own, hipStream_t s) {
   h.kdiag = kdiag;
   h.kmap = kmap;
   h.kup_ptr = kup_ptr;
-  h.kup_t = kup_t;
+  h.kup_q = kup_q;
   h.kup_s = kup_s;
   h.bj_ptr = bj_ptr;
   h.bj_rows = bj_rows;
@@ -178,7 +178,7 @@ bool attach_krylov(Case* c, int m, char* base, bool own, hipStream_t s) {
   up(kdiag, ka.diag.data(), sizeof(int) * nu);
   up(kmap, c->kmap_host.data(), sizeof(int) * c->nnz);
   up(kup_ptr, ka.up_ptr.data(), sizeof(int) * (knnz + 1));
-  up(kup_t, ka.up_t.data(), sizeof(int) * nup);
+  up(kup_q, ka.up_q.data(), sizeof(int) * nup);
   up(kup_s, ka.up_s.data(), sizeof(int) * nup);
   up(bj_ptr, ka.bj_ptr.data(), sizeof(int) * (nb + 1));
   up(bj_rows, ka.bj_rows.data(), sizeof(int) * nu);
@@ -238,44 +238,12 @@ bool ensure_krylov(Case* c, int m) {
 
 bool Batch::build_krylov() {
   std::vector<int2> work;
-  k_lev.clear();
-  k_ulev.clear();
   max_kchunks = 0;
-  size_t max_l = 0, max_u = 0;
-  k_wide = k_narrow = false;
-  // each instance takes its own path (one work-group, or one launch per
-  // level when some level is too wide), whatever the batch holds
-  std::vector<char> wide(nslots, 0);
-  for (int s = 0; s < nslots; ++s) {
-    Case* c = cases[s];
+  k_blocks_big = 0;
+  for (Case* c : cases) {
     if (!c->ka) return false;
-    const pfh::KAnalysis& ka = *c->ka;
-    max_kchunks = std::max(max_kchunks, (ka.nu + pfd::KCH - 1) / pfd::KCH);
-    wide[s] = krylov_wide(ka);
-    if (wide[s]) {
-      k_wide = true;
-      max_l = std::max(max_l, ka.lev_ptr.size() - 1);
-      max_u = std::max(max_u, ka.ulev_ptr.size() - 1);
-    } else {
-      k_narrow = true;
-    }
+    max_kchunks = std::max(max_kchunks, (c->ka->nu + pfd::KCH - 1) / pfd::KCH);
   }
-  auto levels = [&](bool upper, size_t nl, std::vector<std::pair<int64_t, int>>* out) {
-    for (size_t l = 0; l < nl; ++l) {
-      const int64_t off = (int64_t)work.size();
-      for (int s = 0; s < nslots; ++s) {
-        if (!wide[s]) continue;
-        const pfh::KAnalysis& ka = *cases[s]->ka;
-        const auto& ptr = upper ? ka.ulev_ptr : ka.lev_ptr;
-        const auto& rows = upper ? ka.ulev_rows : ka.lev_rows;
-        if (l + 1 >= ptr.size()) continue;
-        for (int k = ptr[l]; k < ptr[l + 1]; ++k) work.push_back(make_int2(s, rows[k]));
-      }
-      out->emplace_back(off, (int)((int64_t)work.size() - off));
-    }
-  };
-  levels(false, max_l, &k_lev);
-  levels(true, max_u, &k_ulev);
   {
     // the groups above the small size first (a work-group each), then the
     // small ones (a wave each for their inverse, four to a wave when
@@ -348,26 +316,60 @@ bool ensure_sweep(Case* c) {
   return ok;
 }
 
-bool Batch::build_sweeps() {
+namespace {
+
+// Levels of up to this many targets run behind barriers of one work-group (a
+// pass of 512 targets takes about 1.2 us, a launch of its own 4.5 us).
+constexpr int kNarrowTargets = 1536;
+
+}  // namespace
+
+bool Batch::build_ilu() {
   std::vector<int2> work;
-  s_low.clear();
-  s_up.clear();
-  s_step.clear();
-  s_narrow = s_wide = false;
-  k_min_nu = k_max_nu = 0;
+  for (auto* v : {&f_seg, &s_low, &s_up, &s_step, &s_lev, &s_ulev}) v->clear();
+  s_narrow = false;
+  s_min_nu = s_max_nu = 0;
+  // factor targets and levels of every instance, its launches' descriptors
+  std::vector<int> tgt, lev, ptr, one;
+  std::vector<std::vector<int4>> seg;
   int nlp = 0, nup = 0, nst = 0;
-  for (Case* c : cases) {
+  size_t max_l = 0, max_u = 0;
+  // each instance takes its own path, whatever the batch holds
+  std::vector<char> by_level(nslots, 0);
+  for (int s = 0; s < nslots; ++s) {
+    Case* c = cases[s];
     if (!c->ka || !ensure_sweep(c)) return false;
+    const pfh::KAnalysis& ka = *c->ka;
+    pfh::factor_targets(ka, &ptr, &one);
+    const int t0 = (int)tgt.size(), l0 = (int)lev.size(), nl = (int)ptr.size() - 1;
+    tgt.insert(tgt.end(), one.begin(), one.end());
+    for (int p : ptr) lev.push_back(t0 + p);
+    size_t k = 0;
+    for (int l = 0; l < nl; ++k) {
+      if (seg.size() <= k) seg.emplace_back();
+      int e = l;
+      while (e < nl && ptr[e + 1] - ptr[e] <= kNarrowTargets) ++e;
+      if (e > l) {
+        seg[k].push_back(make_int4(s, l0 + l, l0 + e, 1));
+        l = e;
+      } else {
+        const int per = pfd::ilu_factor_threads();
+        for (int i = ptr[l]; i < ptr[l + 1]; i += per)
+          seg[k].push_back(make_int4(s, t0 + i, t0 + std::min(i + per, ptr[l + 1]), 0));
+        ++l;
+      }
+    }
     if (c->sw_state == Case::SW_PLAN) {
       nlp = std::max(nlp, c->sw.nlp);
       nup = std::max(nup, c->sw.nup);
       nst = std::max(nst, c->sw.nsteps);
-    } else if (krylov_wide(*c->ka)) {
-      s_wide = true;
+    } else if (krylov_wide(ka)) {
+      by_level[s] = 1;
+      max_l = std::max(max_l, ka.lev_ptr.size() - 1);
+      max_u = std::max(max_u, ka.ulev_ptr.size() - 1);
     } else {
-      const int nu = c->ka->nu;
-      k_min_nu = s_narrow ? std::min(k_min_nu, nu) : nu;
-      k_max_nu = std::max(k_max_nu, nu);
+      s_min_nu = s_narrow ? std::min(s_min_nu, ka.nu) : ka.nu;
+      s_max_nu = std::max(s_max_nu, ka.nu);
       s_narrow = true;
     }
   }
@@ -402,13 +404,46 @@ bool Batch::build_sweeps() {
       for (int k = 0; k < (int)sw.step.size(); ++k)
         if (sw.step[k] == t) work.push_back(make_int2(s, k));
     });
+  auto levels = [&](bool upper, size_t nl, std::vector<std::pair<int64_t, int>>* out) {
+    for (size_t l = 0; l < nl; ++l) {
+      const int64_t off = (int64_t)work.size();
+      for (int s = 0; s < nslots; ++s) {
+        if (!by_level[s]) continue;
+        const pfh::KAnalysis& ka = *cases[s]->ka;
+        const auto& lp = upper ? ka.ulev_ptr : ka.lev_ptr;
+        const auto& rows = upper ? ka.ulev_rows : ka.lev_rows;
+        if (l + 1 >= lp.size()) continue;
+        for (int k = lp[l]; k < lp[l + 1]; ++k) work.push_back(make_int2(s, rows[k]));
+      }
+      out->emplace_back(off, (int)((int64_t)work.size() - off));
+    }
+  };
+  levels(false, max_l, &s_lev);
+  levels(true, max_u, &s_ulev);
+  std::vector<int4> desc;
+  for (const auto& v : seg) {
+    f_seg.emplace_back((int64_t)desc.size(), (int)v.size());
+    desc.insert(desc.end(), v.begin(), v.end());
+  }
+  // the lists packed on the host as on the device: one copy
+  const size_t total = carve_bytes<int2>((int64_t)work.size()) + carve_bytes<int4>((int64_t)desc.size()) +
+                       carve_bytes<int>((int64_t)tgt.size()) + carve_bytes<int>((int64_t)lev.size());
   if (smem) ctx->dfree(smem);
-  smem = (char*)ctx->dalloc(carve_bytes<int2>(std::max<int64_t>((int64_t)work.size(), 1)));
+  smem = (char*)ctx->dalloc(std::max<size_t>(total, 256));
   if (!smem) return false;
-  d_swork = (int2*)smem;
+  std::vector<char> pack(total);
+  char* p = smem;
+  auto put = [&](const auto& src) {
+    typedef typename std::decay_t<decltype(src)>::value_type V;
+    if (!src.empty()) std::memcpy(pack.data() + (p - smem), src.data(), sizeof(V) * src.size());
+    return carve<V>(p, (int64_t)src.size());
+  };
+  d_swork = put(work);
+  d_fdesc = put(desc);
+  d_ftgt = put(tgt);
+  d_flev = put(lev);
   bool ok = true;
-  if (!work.empty())
-    ok &= hipMemcpyAsync(d_swork, work.data(), sizeof(int2) * work.size(), hipMemcpyHostToDevice, stream) == hipSuccess;
+  if (total) ok &= hipMemcpyAsync(smem, pack.data(), total, hipMemcpyHostToDevice, stream) == hipSuccess;
   ok &= hipStreamSynchronize(stream) == hipSuccess;
   sbuilt = ok;
   return ok;
@@ -442,8 +477,9 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
   {
     Prof p(ctx, PF_K_PRECOND_SETUP, 0.0, 0.0);
     if (ilu) {
-      if (b->k_narrow) pfd::launch_ilu_factor_wg<T>(s, I, ns);
-      for (const auto& l : b->k_lev) pfd::launch_ilu_rows<T>(s, I, kw + l.first, l.second);
+      for (const auto& l : b->f_seg)
+        pfd::launch_ilu_factor<T>(s, I, b->d_fdesc + l.first, l.second, b->d_ftgt, b->d_flev);
+      pfd::launch_ilu_scale<T>(s, I, ns, mc);
       for (const auto& l : b->s_step) pfd::launch_sweep_values<T>(s, I, b->d_swork + l.first, l.second);
     } else {
       pfd::launch_bj_inv<T>(s, I, kw + b->k_blocks.first, b->k_blocks_big, b->k_blocks.second - b->k_blocks_big);
@@ -471,11 +507,9 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
       for (const auto& l : b->s_low) part(l, 0);
       for (const auto& l : b->s_up) part(l, 1);
       // the instances without a plan, by levels
-      if (b->s_narrow) pfd::launch_ilu_apply_wg<T>(s, I, ns, mode, b->k_min_nu, b->k_max_nu);
-      if (b->s_wide) {
-        for (const auto& l : b->k_lev) pfd::launch_ilu_fwd<T>(s, I, kw + l.first, l.second, mode);
-        for (const auto& l : b->k_ulev) pfd::launch_ilu_bwd<T>(s, I, kw + l.first, l.second, mode);
-      }
+      if (b->s_narrow) pfd::launch_ilu_apply_wg<T>(s, I, ns, mode, b->s_min_nu, b->s_max_nu);
+      for (const auto& l : b->s_lev) pfd::launch_ilu_fwd<T>(s, I, b->d_swork + l.first, l.second, mode);
+      for (const auto& l : b->s_ulev) pfd::launch_ilu_bwd<T>(s, I, b->d_swork + l.first, l.second, mode);
     } else {
       pfd::launch_bj_apply<T>(s, I, kw + b->k_blocks.first, b->k_blocks_big, b->k_blocks.second, mode);
     }

@@ -71,11 +71,11 @@ extern "C" pf_status pf_debug_precond_check(pf_case* c, int32_t precond, double*
   hipStream_t s = b.stream;
   const bool ilu = precond == PF_PRECOND_ILU0;
   pfd::launch_kfill<double>(s, b.d_insts, 1, b.max_nnz, ilu ? 1 : 0);
-  if (ilu && b.k_narrow)
-    pfd::launch_ilu_factor_wg<double>(s, b.d_insts, 1);
-  else if (ilu)
-    for (const auto& l : b.k_lev) pfd::launch_ilu_rows<double>(s, b.d_insts, b.d_kwork + l.first, l.second);
-  else
+  if (ilu) {
+    for (const auto& l : b.f_seg)
+      pfd::launch_ilu_factor<double>(s, b.d_insts, b.d_fdesc + l.first, l.second, b.d_ftgt, b.d_flev);
+    pfd::launch_ilu_scale<double>(s, b.d_insts, 1, b.max_kchunks);
+  } else
     pfd::launch_bj_inv<double>(s, b.d_insts, b.d_kwork + b.k_blocks.first, b.k_blocks_big,
                                 b.k_blocks.second - b.k_blocks_big);
   st = launch_status("pf_debug_precond_check");

@@ -553,9 +553,9 @@ pf_status pf_submit(pf_ctx* ctx, pf_case* c, const pf_options* opt, uint64_t* ti
       set_error("pf_submit: Krylov launch-list set-up failed");
       return PF_E_NOMEM;
     }
-    if (o.solver != PF_SOLVER_LU && o.precond == PF_PRECOND_ILU0 && !c->single->sbuilt && !c->single->build_sweeps()) {
+    if (o.solver != PF_SOLVER_LU && o.precond == PF_PRECOND_ILU0 && !c->single->sbuilt && !c->single->build_ilu()) {
       c->busy.store(0);
-      set_error("pf_submit: set-up of the ILU(0) sweeps failed");
+      set_error("pf_submit: set-up of the ILU(0) lists failed");
       return PF_E_NOMEM;
     }
   }
