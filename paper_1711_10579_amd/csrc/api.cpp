@@ -459,6 +459,13 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
       c->fac_flops[l] = 16.0 * upd + 40.0 * blocks;
       c->fac_bytes[l] = 8.0 * upd + 2 * 32.0 * blocks;  // index pairs + read/write of target blocks (FP64)
     }
+    // columns of a level by lane class
+    for (int l = 0; l < c->nlev; ++l)
+      std::stable_sort(an.col_order.begin() + an.col_lev_ptr[l], an.col_order.begin() + an.col_lev_ptr[l + 1],
+                       [&](int a, int b) {
+                         return pfd::fac_class(an.colptr[a + 1] - an.colptr[a], c->fac_g[l]) <
+                                pfd::fac_class(an.colptr[b + 1] - an.colptr[b], c->fac_g[l]);
+                       });
     int64_t mt = 0;
     for (int i = an.ns; i < an.nu; ++i) mt = std::max<int64_t>(mt, an.lrow_ptr[i + 1] - an.lrow_ptr[i]);
     c->tailfwd_g = pick(mt);
@@ -491,6 +498,11 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
     return PF_E_INVALID;
   }
   const int ns = an.ns;
+  std::vector<int4> colinfo(ns);
+  for (int k = 0; k < ns; ++k) {
+    const int j = an.col_order[k];
+    colinfo[k] = make_int4(j, an.colptr[j], an.colptr[j + 1] - an.colptr[j], 0);
+  }
   // rows the mismatch gives a work-group of their own
   std::vector<int> heavy;
   for (int i = 0; i < n; ++i)
@@ -506,7 +518,7 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   total += 2 * carve_size<double>(n) + 2 * carve_size<double>(2LL * n) + carve_size<double>(2LL * nu);
   total += carve_size<double>(2LL * nu);
   total += carve_size<int>(ns + 1) + carve_size<int>(an.nnzl) + carve_size<int64_t>(c->ntg + 1) +
-           2 * carve_size<int>(nupd) + carve_size<int>(ns);
+           2 * carve_size<int>(nupd) + carve_size<int4>(ns);
   total += carve_size<int>(c->ntt) + carve_size<int64_t>(c->ntt + 1) + 2 * carve_size<int>(ntail);
   total += carve_size<int>(nu + 1) + 2 * carve_size<int>(an.nnzl) + carve_size<int>(ns);
   total += carve_size<double>(n) + carve_size<int>(2LL * n) + carve_size<double>(6LL * n);
@@ -549,7 +561,7 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   c->uptr = carve<int64_t>(p, c->ntg + 1);
   c->upd_l = carve<int>(p, nupd);
   c->upd_u = carve<int>(p, nupd);
-  c->col_order = carve<int>(p, ns);
+  c->colinfo = carve<int4>(p, ns);
   c->tail_tgt = carve<int>(p, c->ntt);
   c->tail_uptr = carve<int64_t>(p, c->ntt + 1);
   c->tail_l = carve<int>(p, ntail);
@@ -560,6 +572,7 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   c->bwd_rows = carve<int>(p, ns);
   c->red = carve<pfd::Red>(p, 1);
   c->d_inst = carve<pfd::Inst>(p, 1);
+  static_assert(pfd::kRedOffset == 256, "carve's alignment puts the descriptor right behind the state");
   int* d_heavy = carve<int>(p, c->nheavy);
   double* d_mpart = carve<double>(p, nmpart);
   double* d_upart = carve<double>(p, nupart);
@@ -611,7 +624,7 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   ok &= up(c->uptr, an.uptr.data(), sizeof(int64_t) * (c->ntg + 1));
   ok &= up(c->upd_l, an.upd_l.data(), sizeof(int) * nupd);
   ok &= up(c->upd_u, an.upd_u.data(), sizeof(int) * nupd);
-  ok &= up(c->col_order, an.col_order.data(), sizeof(int) * ns);
+  ok &= up(c->colinfo, colinfo.data(), sizeof(int4) * ns);
   ok &= up(c->tail_tgt, an.tail_tgt.data(), sizeof(int) * c->ntt);
   ok &= up(c->tail_uptr, an.tail_uptr.data(), sizeof(int64_t) * (c->ntt + 1));
   ok &= up(c->tail_l, an.tail_l.data(), sizeof(int) * ntail);
@@ -671,6 +684,7 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
     hi.upd_l = c->upd_l;
     hi.upd_u = c->upd_u;
     hi.uptr = c->uptr;
+    hi.colinfo = c->colinfo;
     hi.tail_tgt = c->tail_tgt;
     hi.tail_l = c->tail_l;
     hi.tail_u = c->tail_u;

@@ -27,6 +27,7 @@
 
 #include "blk.hpp"
 #include "device.hpp"
+#include "inst.hpp"
 #include "kernels.hpp"
 #include "mfma16.hpp"
 
@@ -87,8 +88,8 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
   T* stage = smem;                    // two sets of four staged blocks
   T* xs = smem + 8 * kStage;          // the work-group's rows of A_ik, column-major [NB][kQuarterLd]
   T* ls = xs + NB * kQuarterLd;       // the same rows of L_ik
-  const auto& I = *gp(gp(insts)[w.x]);
-  if (gp(I.red)->active == 0) return;
+  const auto& I = inst_at(insts, w.x);
+  if (red_of(I)->active == 0) return;
   // the launch is uniform per work-group: keep these in scalar registers
   const int g = __builtin_amdgcn_readfirstlane(w.y);
   if (g == 0 && h != 0) return;
@@ -114,7 +115,7 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
   const bool wait = g > 0 && k0 > 0;
   unsigned long long want = 0, f1 = 0, f2 = 0;
   if (wait) {
-    want = panel_flag(gp(I.red)->epoch, k0);
+    want = panel_flag(red_of(I)->epoch, k0);
     f1 = flag_ld(&I.pflags[r0 / NB]);
     f2 = flag_ld(&I.pflags[k0 / NB]);
   }
@@ -225,7 +226,7 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
     for (int ib = 0; ib < 4; ++ib)
 #pragma unroll
       for (int e = 0; e < 4; ++e) bad = bad || !isfinite((double)d[ib][e]);
-    if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) gp(I.red)->singular = 1;
+    if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) red_of(I)->singular = 1;
     T* ui = (T*)I.dinvu + (int64_t)(k0 / NB) * NB * NB;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -244,7 +245,7 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
       if (__builtin_amdgcn_readfirstlane((f1 >= want && f2 >= want) ? 1 : 0)) break;
       if (rt_now() - t_start > kWaitTicks) {
         expired = true;
-        if (lane == 0) gp(I.red)->timeout = 1;
+        if (lane == 0) red_of(I)->timeout = 1;
         break;
       }
       __builtin_amdgcn_s_sleep(1);
@@ -297,8 +298,8 @@ template <typename T>
 __device__ __forceinline__ void gemm_tile(const Inst* const* insts, const int2 wk, int k0, T* smem) {
   T(*sa)[kGemmLd] = (T(*)[kGemmLd])smem;                   // [k][row]
   T(*sb)[kGemmLd] = (T(*)[kGemmLd])(smem + NB * kGemmLd);  // [k][col]
-  const auto& I = *gp(gp(insts)[wk.x]);
-  if (gp(I.red)->active == 0) return;
+  const auto& I = inst_at(insts, wk.x);
+  if (red_of(I)->active == 0) return;
   T* A = (T*)I.tail;
   const int ld = I.ldt, M = I.M;
   const int bi0 = __builtin_amdgcn_readfirstlane((wk.y >> 12) & 0xfff);
@@ -382,7 +383,7 @@ __device__ __forceinline__ void gemm_tile(const Inst* const* insts, const int2 w
     wait_vmem();
     __syncthreads();
     if (tid == 0)
-      __hip_atomic_store((PF_AS1 unsigned long long*)&I.pflags[bi0], panel_flag(gp(I.red)->epoch, k0), __ATOMIC_RELAXED,
+      __hip_atomic_store((PF_AS1 unsigned long long*)&I.pflags[bi0], panel_flag(red_of(I)->epoch, k0), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   }
 }
@@ -705,8 +706,8 @@ __device__ __forceinline__ void bwd_rows(const Inst* const* insts, const int2* _
   const int g = threadIdx.x / G, lane = threadIdx.x % G;
   if (g >= count) return;  // whole groups leave together
   const int2 w = ld_item(rows, g);
-  const auto& I = *gp(gp(insts)[w.x]);
-  if (gp(I.red)->active == 0) return;
+  const auto& I = inst_at(insts, w.x);
+  if (red_of(I)->active == 0) return;
   const auto lu = gp((const T*)I.lu);
   const auto x = gp((T*)I.x);
   T* xs = (T*)I.xs;
@@ -792,8 +793,8 @@ __global__ __launch_bounds__(256, 2) void k_bwd_solve(const Inst* const* insts, 
   const unsigned long long t0 = rt_now();
   const int2 wk = ld_item(work, blockIdx.x);
   if ((int)blockIdx.x < nd) {
-    const auto& I = *gp(gp(insts)[wk.x]);
-    if (gp(I.red)->active == 0 || I.M == 0) return;
+    const auto& I = inst_at(insts, wk.x);
+    if (red_of(I)->active == 0 || I.M == 0) return;
     const int nblk = (I.M + NB - 1) / NB;
     if (threadIdx.x == 0) abort_flag = 0;
     __syncthreads();

@@ -76,6 +76,7 @@ struct Inst {
   // panel of block step k has stored its tile L_ik
   unsigned long long* pflags;
   const int *colptr, *rowidx, *upd_l, *upd_u;
+  const int4* colinfo;  // columns by level: {column, its first block, blocks, 0}
   const int64_t* uptr;
   const int *tail_tgt, *tail_l, *tail_u;
   const int64_t* tail_uptr;
@@ -137,6 +138,25 @@ struct KState {
 // KS_BP, KS_BS: the two halves of a BiCGStab iteration; KS_BH: the first
 // half met the tolerance (its update of x pending)
 enum { KS_DONE = 0, KS_ITER = 1, KS_CYCLE = 2, KS_RESTART = 3, KS_FINISH = 4, KS_BP = 5, KS_BS = 6, KS_BH = 7 };
+
+// A launch of factor columns: classes of 8, 16, 32, 64 and 256 lanes per
+// column (fac_class), class c the work-groups [end[c-1], end[c]) and `count`
+// columns from `first`.
+constexpr int kFacClasses = 5;
+struct FacLaunch {
+  int end[kFacClasses], first[kFacClasses], count[kFacClasses];
+};
+// the class of a column of `len` blocks at G lanes per target: the fewest
+// lanes that hold its 2 len + 2 targets in one pass, else a work-group
+inline int fac_class(int len, int G) {
+  const long long lanes = (2LL * len + 2) * G;
+  return lanes <= 8 ? 0 : lanes <= 16 ? 1 : lanes <= 32 ? 2 : lanes <= 64 ? 3 : 4;
+}
+
+// A case's Newton state lies this many bytes before its descriptor, so a
+// kernel reads both at once.
+constexpr int kRedOffset = 256;
+static_assert(sizeof(Red) <= kRedOffset, "Newton state before the descriptor");
 
 // Options of the Krylov inner solve.
 struct KOpts {

@@ -121,7 +121,8 @@ struct Case {
   void *x = nullptr, *lu = nullptr, *dinv = nullptr, *tail = nullptr, *dinvu = nullptr;
   void* xs = nullptr;     // the backward solve's published copy of the solution (2 nu values)
   unsigned long long* pflags = nullptr;  // per 64-row block: panel-tile flags
-  int *colptr = nullptr, *rowidx = nullptr, *upd_l = nullptr, *upd_u = nullptr, *col_order = nullptr;
+  int *colptr = nullptr, *rowidx = nullptr, *upd_l = nullptr, *upd_u = nullptr;
+  int4* colinfo = nullptr;  // columns in level order (by class inside a level)
   int64_t* uptr = nullptr;
   int *tail_tgt = nullptr, *tail_l = nullptr, *tail_u = nullptr;
   int64_t* tail_uptr = nullptr;
@@ -161,6 +162,7 @@ struct Launch {
   int64_t off;     // first work item
   int count;       // work items
   double flops, bytes;
+  pfd::FacLaunch fac;  // factor columns by class
 };
 enum { L_FACTOR = 0, L_FWD, L_SCHUR, L_PANEL, L_BWD };
 
@@ -173,6 +175,8 @@ struct Batch {
   std::vector<Case*> cases;
   int nslots = 0;
   char* dmem = nullptr;  // instance pointer table, work items
+  // what the kernels take: the table, or for a batch of one its descriptor's
+  // address marked by the low bit
   const pfd::Inst* const* d_insts = nullptr;
   int2* d_work = nullptr;
   // pinned host memory that the state gathers write into directly: the

@@ -18,6 +18,7 @@
 
 #include "blk.hpp"
 #include "device.hpp"
+#include "inst.hpp"
 #include "kernels.hpp"
 
 namespace pfd {
@@ -39,7 +40,7 @@ __device__ inline double wave_max(double local) {
 }
 
 template <typename IR>
-__device__ inline bool inactive(const IR& I) { return gp(I.red)->active == 0; }
+__device__ inline bool inactive(const IR& I) { return red_of(I)->active == 0; }
 
 // max over a work-group of 256 threads (every thread calls it), stored by
 // thread 0 as the work-group's partial maximum (the instance's convergence
@@ -67,7 +68,7 @@ __device__ inline void block_max_store(double local, double* out) {
 // PV node's generator Q at its given starting value) or the stored voltage,
 // and the rectangular voltage v.
 __global__ void k_init(const Inst* const* insts, int flat) {
-  const Inst& I = *insts[blockIdx.y];
+  const auto& I = inst_at(insts, blockIdx.y);
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= I.n) return;
   double m, a;
@@ -99,7 +100,7 @@ __global__ void k_init(const Inst* const* insts, int flat) {
 __global__ void k_start(const Inst* const* insts, int nslots) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= nslots) return;
-  Red& r = *insts[s]->red;
+  PF_AS1 Red& r = *red_of(inst_at(insts, s));
   r.norm_bits = 0ull;
   r.step_bits = 0ull;
   r.norm0 = 0.0;
@@ -139,8 +140,8 @@ __device__ inline double strided_max(const double* a, int n) {
 // Sets status and active; prepares the step counters for the next step.
 __global__ __launch_bounds__(256) void k_decide(const Inst* const* insts, DevOpts o) {
   __shared__ double wm[2][4];
-  const Inst& I = *insts[blockIdx.x];
-  Red& r = *I.red;
+  const auto& I = inst_at(insts, blockIdx.x);
+  PF_AS1 Red& r = *red_of(I);
   if (!r.active) return;
   const int it = r.it;
   double nm = strided_max(I.mpart, I.nmpart);
@@ -201,7 +202,15 @@ __global__ void k_zero_words(unsigned* p, int64_t words) {
 // copy every instance's state into one contiguous array for the host
 __global__ void k_gather_red(const Inst* const* insts, int nslots, Red* out) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < nslots) out[s] = *insts[s]->red;
+  if (s >= nslots) return;
+  const auto src = (const PF_AS1 unsigned*)red_of(inst_at(insts, s));
+  const auto dst = (PF_AS1 unsigned*)(out + s);
+  constexpr int W = sizeof(Red) / 4;
+  unsigned w[W];
+#pragma unroll
+  for (int k = 0; k < W; ++k) w[k] = src[k];
+#pragma unroll
+  for (int k = 0; k < W; ++k) dst[k] = w[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -391,10 +400,10 @@ __device__ inline void mismatch_heavy_row(const InstRef& I, int h) {
 constexpr int kMisLanes = 4;
 template <int S>
 __global__ __launch_bounds__(256) void k_mismatch(const Inst* const* insts, int nh) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   // whether the instance is still iterating is tested only before the
   // first store: the row's loads need not wait for that flag
-  const bool active = gp(I.red)->active != 0;
+  const bool active = red_of(I)->active != 0;
   const int blk = xcd_block((int)blockIdx.x, (int)gridDim.x);
   if (blk < nh) {
     if (blk < I.nheavy && active) mismatch_heavy_row(I, blk);
@@ -466,7 +475,7 @@ constexpr int ZCH = 8192;
 template <typename T>
 __global__ __launch_bounds__(256) void k_zero_chunks(const Inst* const* insts, const int2* __restrict__ work) {
   const int2 w = ld_item(work, blockIdx.x);
-  const auto& I = *gp(gp(insts)[w.x]);
+  const auto& I = inst_at(insts, w.x);
   if (inactive(I)) return;
   const bool tail = w.y < 0;
   const int64_t c = tail ? -1 - (int64_t)w.y : (int64_t)w.y;
@@ -656,12 +665,15 @@ __device__ inline void jblock(const IR& I, int e, double* out) {
 // solve's published copy of the solution marked unsolved.
 template <typename T>
 __global__ void k_jfill(const Inst* const* insts, int nj) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
-  if (inactive(I)) return;
+  const auto& I = inst_at(insts, blockIdx.y);
+  // tested only before the stores: the loads need not wait for it
+  const bool off = inactive(I);
   if ((int)blockIdx.x >= nj) {
     const int i = ((int)blockIdx.x - nj) * blockDim.x + threadIdx.x;
     if (i < 2 * I.nu) {
-      gp((T*)I.x)[i] = (T)gp(I.F)[i];
+      const T f = (T)gp(I.F)[i];
+      if (off) return;
+      gp((T*)I.x)[i] = f;
       gp((T*)I.xs)[i] = unsolved_value<T>();
     }
     return;
@@ -672,6 +684,7 @@ __global__ void k_jfill(const Inst* const* insts, int nj) {
   if (code == -1) return;
   double blk[4];
   jblock(I, e, blk);
+  if (off) return;
   jstore<T>(I, code, blk[0], blk[1], blk[2], blk[3]);
 }
 
@@ -680,7 +693,7 @@ __global__ void k_jfill(const Inst* const* insts, int nj) {
 // the block is also the starting value of the factor.
 template <typename T>
 __global__ void k_kfill(const Inst* const* insts, int ilu) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (inactive(I)) return;
   int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= I.nnz) return;
@@ -703,10 +716,11 @@ __global__ void k_kfill(const Inst* const* insts, int ilu) {
 }
 
 // ---------------------------------------------------------------------------
-// sparse block refactorisation: one work-group per (instance, column) of a
-// level; each target block (D_j, U(j, .), L(., j)) is reduced by a group of G
+// sparse block refactorisation, one launch per level and lane count: each
+// target block (D_j, U(j, .), L(., j)) of a column is reduced by a group of G
 // lanes that split its update list (lane-strided partial sums, fixed-order
-// tree).
+// tree); a column's node runs its forward row beside them, so the forward
+// substitution of the sparse part needs no launches of its own.
 
 // acc -= sum over updates q = q0, q0 + G, ... < q1 of L(q) U(q) (block ids
 // from il / iu), in that order, the loads of four updates issued at once
@@ -735,18 +749,16 @@ __device__ inline void sub_updates(Blk<T>& acc, const T* lu_, const int* il_, co
   }
 }
 
-// Forward row of node i by a group of G lanes: y_i = b_i - sum_k L(i,k) y_k
-// over the row's L blocks (in place in x, which holds b_i before), lane-
-// strided partial sums with the loads of four entries issued at once, then
-// the fixed-order tree.  Every L(i,k) and y_k lies in an earlier level.
-// Rows of the dense block also copy the result into its right-hand side
-// column.
+// Partial sum of the forward row of node i over a group of G lanes: y_i = b_i
+// - sum_k L(i,k) y_k over the row's L blocks (b_i in x), lane-strided, the
+// loads of four entries issued at once; the fixed-order tree follows.  Every
+// L(i,k) and y_k lies in an earlier level.  (a, c) carry the 2-vector.
 template <typename T, int G, typename IR>
-__device__ inline void fwd_row(const IR& I, const T* lu_, T* x_, int i, int lane) {
+__device__ inline Blk<T> fwd_partial(const IR& I, const T* lu_, const T* x_, int i, int lane) {
   const auto lu = gp(lu_);
   const auto x = gp(x_);
   const auto lrow_ptr = gp(I.lrow_ptr), lrow_blk = gp(I.lrow_blk), lrow_col = gp(I.lrow_col);
-  Blk<T> acc = {T(0), T(0), T(0), T(0)};  // (a, c) carry the 2-vector
+  Blk<T> acc = {T(0), T(0), T(0), T(0)};
   if (lane == 0) {
     acc.a = x[2 * i];
     acc.c = x[2 * i + 1];
@@ -776,16 +788,7 @@ __device__ inline void fwd_row(const IR& I, const T* lu_, T* x_, int i, int lane
         acc.c -= L[u].c * x0[u] + L[u].d * x1[u];
       }
   }
-  acc = group_sum<T, G>(acc);
-  if (lane == 0) {
-    x[2 * i] = acc.a;
-    x[2 * i + 1] = acc.c;
-    if (i >= I.ns) {
-      const auto rhs = gp((T*)I.tail) + (int64_t)I.M * I.ldt;
-      rhs[2 * (i - I.ns)] = acc.a;
-      rhs[2 * (i - I.ns) + 1] = acc.c;
-    }
-  }
+  return acc;
 }
 
 template <typename T, int G, typename IR>
@@ -796,117 +799,140 @@ __device__ inline Blk<T> gather_target(const IR& I, const T* lu, int64_t dest, i
   return group_sum<T, G>(acc);
 }
 
-// One column per wave (four per work-group) for levels whose columns have at
-// most 64/G targets: the targets of a column then take one pass of the
-// wave's lane groups, and the diagonal inverse goes to the wave by a
-// shuffle instead of a work-group barrier.  Same arithmetic as k_factor_cols.
-// Both kernels also run the forward row of the column's node (target len + 1
-// of the first pass), so the forward substitution of the sparse part needs
-// no launches of its own.
-template <typename T, int G>
-__global__ __launch_bounds__(256) void k_factor_cols_wave(const Inst* const* insts, const int2* __restrict__ work,
-                                                          int nwork) {
-  const int item = blockIdx.x * 4 + (int)(threadIdx.x / 64);
-  if (item >= nwork) return;
-  const int2 w = ld_item(work, item);
-  const auto& I = *gp(gp(insts)[w.x]);
-  if (inactive(I)) return;
+// One column j (len blocks from c0) by LANES threads in groups of G: targets
+// t = 0 the diagonal block D, 1 .. len the row of U, len + 1 the forward row
+// of the column's node, len + 2 .. 2 len + 1 the column of L.  The sums of
+// the first NP passes stay in registers, so the L targets are summed beside
+// D and only their product with D^{-1} waits for it: a column is one chain
+// list range -> block ids -> blocks -> D^{-1}, not two.  Columns with more
+// targets take the rest one by one after it.  LANES > 64: a whole work-group
+// (every thread calls this), D^{-1} through sd.
+template <typename T, int G, int LANES, int NP, typename IR>
+__device__ __forceinline__ void factor_column(const IR& I, bool on, int j, int c0, int len, int tid, T* sd) {
   T* lu = (T*)I.lu;
-  const int j = w.y;
-  const int c0 = gp(I.colptr)[j];
-  const int len = gp(I.colptr)[j + 1] - c0;
+  const int lane = tid % G, grp = tid / G;
+  constexpr int NG = LANES / G;
+  const int nt = 2 * len + 2;
   const int64_t tb = (int64_t)j + 2LL * c0;
-  const int wl = threadIdx.x % 64;
-  const int lane = wl % G, grp = wl / G;
-  constexpr int ngrp = 64 / G;
-  T d0 = T(0), d1 = T(0), d2 = T(0), d3 = T(0);
-  for (int t = grp; t <= len + 1; t += ngrp) {
+  auto dest = [&](int t) -> int64_t {
+    return t == 0 ? (int64_t)j : t <= len ? (int64_t)I.ns + I.nnzl + c0 + (t - 1) : (int64_t)I.ns + c0 + (t - len - 2);
+  };
+  auto sum = [&](int t) -> Blk<T> {
+    if (t == len + 1) return group_sum<T, G>(fwd_partial<T, G>(I, lu, (const T*)I.x, j, lane));
+    return gather_target<T, G>(I, lu, dest(t), t <= len ? tb + t : tb + t - 1, lane);
+  };
+  auto store = [&](int t, const Blk<T>& v, const Blk<T>& di) {
     if (t == len + 1) {
-      fwd_row<T, G>(I, lu, (T*)I.x, j, lane);
-      continue;
+      const auto x = gp((T*)I.x);
+      x[2 * j] = v.a;
+      x[2 * j + 1] = v.c;
+    } else {
+      st_blk(gp(lu), dest(t), t <= len ? v : blk_mul(v, di));
     }
-    int64_t dest = t == 0 ? (int64_t)j : (int64_t)I.ns + I.nnzl + c0 + (t - 1);
-    Blk<T> acc = gather_target<T, G>(I, lu, dest, tb + t, lane);
-    if (lane == 0) {
-      st_blk(gp(lu), dest, acc);
-      if (t == 0) {
-        T det = acc.a * acc.d - acc.b * acc.c;
-        bool bad = !(det != T(0)) || !isfinite((double)det);
-        if (bad) {
-          gp(I.red)->singular = 1;
-          det = T(1);
-        }
-        T r = T(1) / det;
-        d0 = acc.d * r;
-        d1 = -acc.b * r;
-        d2 = -acc.c * r;
-        d3 = acc.a * r;
-        const auto q = gp((T*)I.dinv) + 4 * (int64_t)j;
-        q[0] = d0;
-        q[1] = d1;
-        q[2] = d2;
-        q[3] = d3;
-      }
+  };
+  Blk<T> acc[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int t = p * NG + grp;
+    acc[p] = {T(0), T(0), T(0), T(0)};
+    if (t < nt) acc[p] = sum(t);
+  }
+  Blk<T> di = {T(0), T(0), T(0), T(0)};
+  if (tid == 0) {
+    T det = acc[0].a * acc[0].d - acc[0].b * acc[0].c;
+    bool bad = !(det != T(0)) || !isfinite((double)det);
+    if (bad) {
+      if (on) red_of(I)->singular = 1;
+      det = T(1);
+    }
+    T r = T(1) / det;
+    di.a = acc[0].d * r;
+    di.b = -acc[0].b * r;
+    di.c = -acc[0].c * r;
+    di.d = acc[0].a * r;
+    if (on) st_blk(gp((T*)I.dinv), j, di);
+    if (LANES > 64) {
+      sd[0] = di.a;
+      sd[1] = di.b;
+      sd[2] = di.c;
+      sd[3] = di.d;
     }
   }
-  // the diagonal target was group 0's first, lane 0 of the wave holds it
-  const Blk<T> di = {__shfl(d0, 0, 64), __shfl(d1, 0, 64), __shfl(d2, 0, 64), __shfl(d3, 0, 64)};
-  for (int t = grp; t < len; t += ngrp) {
-    int64_t dest = (int64_t)I.ns + c0 + t;
-    Blk<T> acc = gather_target<T, G>(I, lu, dest, tb + 1 + len + t, lane);
-    if (lane == 0) st_blk(gp(lu), dest, blk_mul(acc, di));
+  if (LANES > 64) {
+    __syncthreads();
+    di = {sd[0], sd[1], sd[2], sd[3]};
+  } else {
+    const int src = (int)(threadIdx.x & 63) - tid;  // lane of this column's thread 0
+    di = {__shfl(di.a, src, 64), __shfl(di.b, src, 64), __shfl(di.c, src, 64), __shfl(di.d, src, 64)};
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int t = p * NG + grp;
+    if (t < nt && lane == 0 && on) store(t, acc[p], di);
+  }
+  for (int t = NP * NG + grp; t < nt; t += NG) {
+    const Blk<T> v = sum(t);
+    if (lane == 0 && on) store(t, v, di);
   }
 }
 
-template <typename T, int G, int NT>
-__global__ __launch_bounds__(NT) void k_factor_cols(const Inst* const* insts, const int2* __restrict__ work) {
-  __shared__ T sdinv[4];
-  const int2 w = ld_item(work, blockIdx.x);
-  const auto& I = *gp(gp(insts)[w.x]);
-  if (inactive(I)) return;
-  T* lu = (T*)I.lu;
-  const int j = w.y;
-  const int c0 = gp(I.colptr)[j];
-  const int len = gp(I.colptr)[j + 1] - c0;
-  const int64_t tb = (int64_t)j + 2LL * c0;
-  const int lane = threadIdx.x % G, grp = threadIdx.x / G, ngrp = blockDim.x / G;
-  // D_j and U(j, .), and the forward row of node j (t = len + 1)
-  for (int t = grp; t <= len + 1; t += ngrp) {
-    if (t == len + 1) {
-      fwd_row<T, G>(I, lu, (T*)I.x, j, lane);
-      continue;
-    }
-    int64_t dest = t == 0 ? (int64_t)j : (int64_t)I.ns + I.nnzl + c0 + (t - 1);
-    Blk<T> acc = gather_target<T, G>(I, lu, dest, tb + t, lane);
-    if (lane == 0) {
-      st_blk(gp(lu), dest, acc);
-      if (t == 0) {
-        T det = acc.a * acc.d - acc.b * acc.c;
-        bool bad = !(det != T(0)) || !isfinite((double)det);
-        if (bad) {
-          gp(I.red)->singular = 1;
-          det = T(1);
-        }
-        T r = T(1) / det;
-        sdinv[0] = acc.d * r;
-        sdinv[1] = -acc.b * r;
-        sdinv[2] = -acc.c * r;
-        sdinv[3] = acc.a * r;
-        const auto q = gp((T*)I.dinv) + 4 * (int64_t)j;
-        q[0] = sdinv[0];
-        q[1] = sdinv[1];
-        q[2] = sdinv[2];
-        q[3] = sdinv[3];
-      }
-    }
+// The columns of one level and lane count.  Columns of few targets share a
+// wave (8, 16 or 32 lanes each): a leaf column of a radial feeder has up to
+// 14 targets of no updates, and a wave per column left most lanes idle
+// (231K-bus feeder, first levels 243 us a launch).  Classes are consecutive
+// in the list; class c takes work-groups [end[c-1], end[c]) and columns from
+// first[c].  Without a work list, columns are positions of the only
+// instance's level order.
+struct FacCol {
+  int slot;
+  bool any;
+  int pos;
+};
+__device__ inline FacCol fac_col(const int2* work, int idx, bool any) {
+  if (!work) return {0, any, idx};
+  const int2 w = any ? ld_item(work, idx) : make_int2(0, 0);
+  return {w.x, any, w.y};
+}
+template <typename T, int G, int LANES, int NP>
+__device__ __forceinline__ void factor_class(const Inst* const* insts, const int2* work, const FacLaunch& f, int c,
+                                             T* sd) {
+  constexpr int C = 256 / (LANES < 256 ? LANES : 256);
+  const int b = (int)blockIdx.x - (c ? f.end[c - 1] : 0);
+  const int idx = b * C + (int)threadIdx.x / LANES;
+  const FacCol w = fac_col(work, f.first[c] + idx, idx < f.count[c]);
+  if (!w.any) return;  // whole columns leave together
+  const auto& I = inst_at(insts, w.slot);
+  const bool on = !inactive(I);
+  const i4v q = ((const PF_AS1 i4v*)I.colinfo)[w.pos];
+  factor_column<T, G, LANES, NP>(I, on, q.x, q.y, q.z, (int)threadIdx.x % LANES, sd);
+}
+template <typename T, int G>
+__global__ __launch_bounds__(256, 4) void k_factor_cols(const Inst* const* insts, const int2* __restrict__ work,
+                                                     FacLaunch f) {
+  __shared__ T sd[4];
+  const int b = blockIdx.x;
+  if (b < f.end[0]) {
+    if constexpr (G <= 8) factor_class<T, G, 8, 1>(insts, work, f, 0, sd);
+  } else if (b < f.end[1]) {
+    if constexpr (G <= 16) factor_class<T, G, 16, 1>(insts, work, f, 1, sd);
+  } else if (b < f.end[2]) {
+    if constexpr (G <= 32) factor_class<T, G, 32, 1>(insts, work, f, 2, sd);
+  } else if (b < f.end[3]) {
+    factor_class<T, G, 64, 1>(insts, work, f, 3, sd);
+  } else {
+    factor_class<T, G, 256, 2>(insts, work, f, 4, sd);
   }
-  __syncthreads();
-  const Blk<T> di = {sdinv[0], sdinv[1], sdinv[2], sdinv[3]};
-  for (int t = grp; t < len; t += ngrp) {
-    int64_t dest = (int64_t)I.ns + c0 + t;
-    Blk<T> acc = gather_target<T, G>(I, lu, dest, tb + 1 + len + t, lane);
-    if (lane == 0) st_blk(gp(lu), dest, blk_mul(acc, di));
-  }
+}
+// levels of few columns with many targets: 1024 threads a column
+template <typename T, int G>
+__global__ __launch_bounds__(1024) void k_factor_cols_wide(const Inst* const* insts, const int2* __restrict__ work,
+                                                           int first) {
+  __shared__ T sd[4];
+  const FacCol w = fac_col(work, first + (int)blockIdx.x, true);
+  const auto& I = inst_at(insts, w.slot);
+  const bool on = !inactive(I);
+  const i4v q = ((const PF_AS1 i4v*)I.colinfo)[w.pos];
+  factor_column<T, G, 1024, 2>(I, on, q.x, q.y, q.z, (int)threadIdx.x, sd);
 }
 
 // Schur complement of the sparse part into the dense trailing block:
@@ -915,7 +941,7 @@ __global__ __launch_bounds__(NT) void k_factor_cols(const Inst* const* insts, co
 template <typename T, int G>
 __global__ __launch_bounds__(256) void k_tail_schur(const Inst* const* insts, const int2* __restrict__ work) {
   const int2 w = ld_item(work, blockIdx.x);
-  const auto& I = *gp(gp(insts)[w.x]);
+  const auto& I = inst_at(insts, w.x);
   // the activity flag is tested only before the store, so that the loads
   // need not wait for it
   const bool active = !inactive(I);
@@ -945,17 +971,25 @@ __global__ __launch_bounds__(256) void k_tail_schur(const Inst* const* insts, co
 // ---------------------------------------------------------------------------
 // triangular solves over sparse rows
 
-// Forward rows of the dense block's nodes (after every sparse level): one
-// (instance, row) per group of G lanes.
+// Forward rows of the dense block's nodes (after every sparse level), also
+// into its right-hand side column: one (instance, row) per group of G lanes.
 template <typename T, int G>
 __global__ __launch_bounds__(256) void k_fwd_rows(const Inst* const* insts, const int2* __restrict__ work,
                                                   int nwork) {
   const int gid = (blockIdx.x * blockDim.x + threadIdx.x) / G, lane = threadIdx.x % G;
   if (gid >= nwork) return;  // whole groups leave together
   const int2 w = ld_item(work, gid);
-  const auto& I = *gp(gp(insts)[w.x]);
-  if (inactive(I)) return;
-  fwd_row<T, G>(I, (const T*)I.lu, (T*)I.x, w.y, lane);
+  const auto& I = inst_at(insts, w.x);
+  const bool on = !inactive(I);
+  const int i = w.y;
+  const Blk<T> v = group_sum<T, G>(fwd_partial<T, G>(I, (const T*)I.lu, (const T*)I.x, i, lane));
+  if (!on || lane != 0) return;
+  const auto x = gp((T*)I.x);
+  x[2 * i] = v.a;
+  x[2 * i + 1] = v.c;
+  const auto rhs = gp((T*)I.tail) + (int64_t)I.M * I.ldt + 2 * (i - I.ns);
+  rhs[0] = v.a;
+  rhs[1] = v.c;
 }
 
 // ---------------------------------------------------------------------------
@@ -967,8 +1001,10 @@ __global__ __launch_bounds__(256) void k_fwd_rows(const Inst* const* insts, cons
 // lines), on PV nodes angle += dx[2p] and Q_g += dx[2p+1].  Refreshes the rectangular voltage and records max |dx|.
 template <typename T>
 __global__ __launch_bounds__(256) void k_update(const Inst* const* insts) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
-  if (inactive(I) || (int)(blockIdx.x * blockDim.x) >= I.nu) return;
+  const auto& I = inst_at(insts, blockIdx.y);
+  if ((int)(blockIdx.x * blockDim.x) >= I.nu) return;
+  // tested after the loads and before the stores (uniform over the work-group)
+  const bool off = inactive(I);
   double local = 0.0;
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p < I.nu) {
@@ -978,15 +1014,19 @@ __global__ __launch_bounds__(256) void k_update(const Inst* const* insts) {
     const auto va = gp(I.va), vm = gp(I.vm);
     double* v = I.v;  // complex, as pairs
     double d0 = (double)x[2 * p], d1 = (double)x[2 * p + 1];
+    const int ty = type[i];
     if (I.model == 0) {
-      if (type[i] != 1) d1 = 0.0;
+      if (ty != 1) d1 = 0.0;
       double a = va[i] + d0, m = vm[i] + d1;
+      if (off) return;
       va[i] = a;
       vm[i] = m;
       double s, c;
       sincos(a, &s, &c);
       st_c(v, i, m * c, m * s);
-    } else if (type[i] == 2) {
+    } else if (off) {
+      return;
+    } else if (ty == 2) {
       // PV node: rotate by the angle step at the set-point magnitude; the
       // second unknown is the generator Q
       double2 vv = ld_c(v, i);
@@ -1004,6 +1044,7 @@ __global__ __launch_bounds__(256) void k_update(const Inst* const* insts) {
     if (!(m == m)) m = __longlong_as_double(0x7ff8000000000000ll);
     local = m;
   }
+  if (off) return;
   block_max_store(local, I.upart + blockIdx.x);
 }
 
@@ -1068,12 +1109,13 @@ void launch_kfill(hipStream_t st, const Inst* const* insts, int nslots, int max_
   }
 
 template <typename T>
-void launch_factor_cols(hipStream_t st, const Inst* const* insts, const int2* work, int nwork, int G, int wide) {
-  if (nwork <= 0) return;
+void launch_factor_cols(hipStream_t st, const Inst* const* insts, const int2* work, const FacLaunch& f, int G,
+                        int wide) {
   if (wide) {
-    PF_GSWITCH(G, (k_factor_cols<T, GG, 1024><<<dim3((unsigned)nwork), 1024, 0, st>>>(insts, work)));
-  } else {
-    PF_GSWITCH(G, (k_factor_cols<T, GG, 256><<<dim3((unsigned)nwork), 256, 0, st>>>(insts, work)));
+    if (f.count[4] > 0)
+      PF_GSWITCH(G, (k_factor_cols_wide<T, GG><<<dim3((unsigned)f.count[4]), 1024, 0, st>>>(insts, work, f.first[4])));
+  } else if (f.end[4] > 0) {
+    PF_GSWITCH(G, (k_factor_cols<T, GG><<<dim3((unsigned)f.end[4]), 256, 0, st>>>(insts, work, f)));
   }
 }
 
@@ -1081,12 +1123,6 @@ template <typename T>
 void launch_tail_schur(hipStream_t st, const Inst* const* insts, const int2* work, int nwork, int G) {
   if (nwork <= 0) return;
   PF_GSWITCH(G, (k_tail_schur<T, GG><<<dim3((unsigned)nwork), 256, 0, st>>>(insts, work)));
-}
-
-template <typename T>
-void launch_factor_cols_wave(hipStream_t st, const Inst* const* insts, const int2* work, int nwork, int G) {
-  if (nwork <= 0) return;
-  PF_GSWITCH(G, (k_factor_cols_wave<T, GG><<<dim3((unsigned)((nwork + 3) / 4)), 256, 0, st>>>(insts, work, nwork)));
 }
 
 template <typename T>
@@ -1103,9 +1139,8 @@ void launch_update(hipStream_t st, const Inst* const* insts, int nslots, int max
 
 #define PF_INST(T)                                                                                         \
   template void launch_fill<T>(hipStream_t, const Inst* const*, int, int, const int2*, int, int);          \
-  template void launch_factor_cols<T>(hipStream_t, const Inst* const*, const int2*, int, int, int);        \
+  template void launch_factor_cols<T>(hipStream_t, const Inst* const*, const int2*, const FacLaunch&, int, int); \
   template void launch_tail_schur<T>(hipStream_t, const Inst* const*, const int2*, int, int);              \
-  template void launch_factor_cols_wave<T>(hipStream_t, const Inst* const*, const int2*, int, int);        \
   template void launch_fwd_rows<T>(hipStream_t, const Inst* const*, const int2*, int, int);                \
   template void launch_update<T>(hipStream_t, const Inst* const*, int, int);                                \
   template void launch_kfill<T>(hipStream_t, const Inst* const*, int, int, int);

@@ -32,18 +32,16 @@ void launch_fill(hipStream_t, const Inst* const* insts, int nslots, int max_nu2,
                  int max_nnz);
 int zero_chunk_values();
 
-// sparse part (work items (slot, column) or (slot, row); G lanes per list)
-// (wide: 1024 threads per column instead of 256, for levels of few columns
-// with many targets each)
+// sparse part (G lanes per list).  Factor columns: (slot, position in the
+// instance's level order) items, or positions of the only instance (work
+// null), by class of lanes per column; wide: all in class 4, 1024 threads a
+// column
 template <typename T>
-void launch_factor_cols(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int G, int wide);
+void launch_factor_cols(hipStream_t, const Inst* const* insts, const int2* work, const FacLaunch& f, int G, int wide);
 template <typename T>
 void launch_fwd_rows(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int G);
 template <typename T>
 void launch_tail_schur(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int G);
-// one column per wave; for levels whose columns have at most 64/G targets
-template <typename T>
-void launch_factor_cols_wave(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int G);
 
 // dense trailing block
 template <typename T>

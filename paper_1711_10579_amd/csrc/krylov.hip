@@ -28,6 +28,7 @@
 #include "blk.hpp"
 #include "mfma16.hpp"
 #include "device.hpp"
+#include "inst.hpp"
 #include "kernels.hpp"
 
 namespace pfd {
@@ -41,7 +42,7 @@ constexpr int KMAX = 128;  // largest restart length the kernels accept
 // loads of its fields and vector loads counted by one wait counter).
 template <typename IR>
 __device__ inline bool kstate_is(const IR& I, int want) {
-  return gp(I.red)->active && gp(I.ks)->state == want;
+  return red_of(I)->active && gp(I.ks)->state == want;
 }
 
 // the Krylov state a preconditioner application serves: mode 0 an Arnoldi
@@ -70,9 +71,9 @@ __device__ inline PF_AS1 double* kpart(const IR& I, int pass, int chunk) {
 // status linear failure and the step is not taken (not counted).
 template <typename IR>
 __device__ inline void linear_failure(const IR& I) {
-  gp(I.red)->status = 4;
-  gp(I.red)->active = 0;
-  gp(I.red)->it -= 1;
+  red_of(I)->status = 4;
+  red_of(I)->active = 0;
+  red_of(I)->it -= 1;
   gp(I.ks)->state = KS_DONE;
 }
 
@@ -270,8 +271,8 @@ template <typename T>
 __global__ __launch_bounds__(kFacThreads) void k_ilu_factor(const Inst* const* insts, const int4* __restrict__ desc,
                                                             const int* __restrict__ tgt_, const int* __restrict__ lev_) {
   const i4v d = ((const PF_AS1 i4v*)desc)[blockIdx.x];
-  const auto& I = *gp(gp(insts)[d.x]);
-  if (!gp(I.red)->active) return;
+  const auto& I = inst_at(insts, d.x);
+  if (!red_of(I)->active) return;
   const auto tgt = gp(tgt_), lev = gp(lev_);
   const int tid = threadIdx.x;
   bool bad = false;
@@ -300,16 +301,16 @@ __global__ __launch_bounds__(kFacThreads) void k_ilu_factor(const Inst* const* i
       f = g;
     }
   }
-  if (bad) gp(I.red)->singular = 1;
+  if (bad) red_of(I)->singular = 1;
 }
 
 // The last pass: L(r, k) = P(r, k) D_k^{-1} for the blocks left of the
 // diagonal, one thread per row.
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_ilu_scale(const Inst* const* insts) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   const int r = blockIdx.x * KCH + threadIdx.x;
-  if (!gp(I.red)->active || r >= I.nu) return;
+  if (!red_of(I)->active || r >= I.nu) return;
   const auto P = gp((T*)I.pval);
   const auto D = gp((const T*)I.pdinv);
   const int q1 = gp(I.kdiag)[r];
@@ -383,8 +384,8 @@ __global__ __launch_bounds__(256) void k_bj_inv_mfma(const Inst* const* insts, c
   __shared__ double stage[8 * kStage];
   __shared__ int bad_s;
   const int2 wk = work[blockIdx.x];
-  const auto& I = *gp(gp(insts)[wk.x]);
-  if (!gp(I.red)->active) return;
+  const auto& I = inst_at(insts, wk.x);
+  if (!red_of(I)->active) return;
   const int b = wk.y;
   const int r0 = gp(I.bj_ptr)[b];
   const int s = gp(I.bj_ptr)[b + 1] - r0;
@@ -445,8 +446,8 @@ __global__ __launch_bounds__(256) void k_bj_inv_small(const Inst* const* insts, 
   // identity and stores nothing
   int2 wk = make_int2(0, -1);
   if (k < nwork) wk = work[k];
-  const auto ip = wk.y >= 0 ? gp(gp(insts)[wk.x]) : nullptr;
-  const bool ok = ip && gp(ip->red)->active;
+  const PF_AS1 Inst* ip = wk.y >= 0 ? &inst_at(insts, wk.x) : nullptr;
+  const bool ok = ip && red_of(*ip)->active;
   const int b = wk.y;
   const int r0 = ok ? gp(ip->bj_ptr)[b] : 0;
   const int s = ok ? gp(ip->bj_ptr)[b + 1] - r0 : 0;
@@ -494,8 +495,8 @@ __global__ __launch_bounds__(256) void k_bj_inv(const Inst* const* insts, const 
   __shared__ int piv;
   __shared__ int bad;
   const int2 wk = work[blockIdx.x];
-  const auto& I = *gp(gp(insts)[wk.x]);
-  if (!gp(I.red)->active) return;
+  const auto& I = inst_at(insts, wk.x);
+  if (!red_of(I)->active) return;
   const int b = wk.y;
   if (b < 0 || !I.bjbad[b]) return;  // padding, or inverted without pivoting
   const int r0 = gp(I.bj_ptr)[b];
@@ -560,7 +561,7 @@ __global__ __launch_bounds__(256) void k_bj_inv(const Inst* const* insts, const 
     __syncthreads();
   }
   if (bad) {
-    if (tid == 0) gp(I.red)->singular = 1;
+    if (tid == 0) red_of(I)->singular = 1;
     return;
   }
   // stored column-major: entry (i, c) at c N + i, so that a wave applying the
@@ -584,7 +585,7 @@ __global__ __launch_bounds__(256) void k_ilu_fwd(const Inst* const* insts, const
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= nwork) return;
   const int2 wk = ld_item(work, idx);
-  const auto& I = *gp(gp(insts)[wk.x]);
+  const auto& I = inst_at(insts, wk.x);
   if (!kstate_is(I, apply_state(mode))) return;
   const int r = wk.y;
   const auto w = gp((const T*)I.kw);
@@ -613,7 +614,7 @@ __global__ __launch_bounds__(256) void k_ilu_bwd(const Inst* const* insts, const
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= nwork) return;
   const int2 wk = ld_item(work, idx);
-  const auto& I = *gp(gp(insts)[wk.x]);
+  const auto& I = inst_at(insts, wk.x);
   if (!kstate_is(I, apply_state(mode))) return;
   const int r = wk.y;
   const auto z = gp((T*)I.kz);
@@ -661,8 +662,8 @@ constexpr int kValueLanes = 16;
 template <typename T>
 __global__ __launch_bounds__(256) void k_sweep_values(const Inst* const* insts, const int2* __restrict__ work) {
   const SweepRow sr = sweep_row<kValueLanes>(work, 0, 0);
-  const auto& I = *gp(gp(insts)[sr.slot]);
-  if (sr.pos < 0 || !gp(I.red)->active) return;
+  const auto& I = inst_at(insts, sr.slot);
+  if (sr.pos < 0 || !red_of(I)->active) return;
   const i4v inf = ((const PF_AS1 i4v*)I.sw_rows)[sr.pos];
   const bool upper = sr.pos >= I.nu;
   const auto P = gp((const T*)I.pval);
@@ -707,7 +708,7 @@ __global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, co
   constexpr int G = kSweepLanes;
   const SweepRow sr = sweep_row<G>(work, p0, nrows);
   if (sr.pos < 0) return;  // whole lane groups leave together
-  const auto& I = *gp(gp(insts)[sr.slot]);
+  const auto& I = inst_at(insts, sr.slot);
   // tested only before the stores: the row's loads need not wait for it
   const bool on = kstate_is(I, apply_state(mode));
   const int lane = threadIdx.x % G;
@@ -827,9 +828,9 @@ template <typename T, int ZV>
 __global__ __launch_bounds__(1024) void k_ilu_apply_wg(const Inst* const* insts, int mode, int zmin) {
   __shared__ T zl[ZV > 0 ? ZV : 1];
   __shared__ int lpf[LPM + 1], lpb[LPM + 1];
-  const auto& I = *gp(insts[blockIdx.x]);
+  const auto& I = inst_at(insts, blockIdx.x);
   const auto ks = gp(I.ks);
-  if (!gp(I.red)->active || I.kwide || I.sw_rows || ks->state != (apply_state(mode))) return;
+  if (!red_of(I)->active || I.kwide || I.sw_rows || ks->state != (apply_state(mode))) return;
   const int nu = I.nu;
   if (2 * nu <= zmin || (ZV > 0 && 2 * nu > ZV)) return;
   T* z = ZV > 0 ? zl : (T*)I.kz;
@@ -989,7 +990,7 @@ __global__ __launch_bounds__(64) void k_bj_apply(const Inst* const* insts, const
   const auto wp = (const PF_AS1 int*)work;
   const bool big = (int)blockIdx.x < nbig;
   const int k0 = big ? (int)blockIdx.x : nbig + 4 * ((int)blockIdx.x - nbig);
-  const auto& I = *gp(gp(insts)[wp[2 * k0]]);
+  const auto& I = inst_at(insts, wp[2 * k0]);
   if (!kstate_is(I, apply_state(mode))) return;
   const double sc = mode == 0 ? gp(I.ks)->scale : 1.0;
   if (big) {
@@ -1014,7 +1015,7 @@ __global__ __launch_bounds__(64) void k_bj_apply(const Inst* const* insts, const
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_kspmv_dot(const Inst* const* insts) {
   __shared__ double red[KMAX + 1][KCH / 64];
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_ITER) || (int)blockIdx.x >= I.kchunks) return;
   const int j = gp(I.ks)->j;
   const int r = blockIdx.x * KCH + threadIdx.x;
@@ -1049,7 +1050,7 @@ __global__ __launch_bounds__(KCH) void k_korth(const Inst* const* insts, int pas
   __shared__ double red[KMAX + 1][KCH / 64];
   __shared__ double h[KMAX + 1];
   __shared__ double hg[8][KMAX + 1];
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_ITER) || (int)blockIdx.x >= I.kchunks) return;
   const int j = gp(I.ks)->j;
   // h_i = sum over chunks of the pass's partial dots: 8 interleaved groups
@@ -1128,7 +1129,7 @@ __global__ __launch_bounds__(KCH) void k_korth(const Inst* const* insts, int pas
 __global__ __launch_bounds__(64) void k_karnoldi_end(const Inst* const* insts, KOpts o) {
   __shared__ double hc[KMAX + 1], scs[KMAX], ssn[KMAX], y[KMAX];
   __shared__ int fin;
-  const auto& I = *gp(gp(insts)[blockIdx.x]);
+  const auto& I = inst_at(insts, blockIdx.x);
   if (!kstate_is(I, KS_ITER)) return;
   KState& ks = *I.ks;
   const int lane = threadIdx.x;
@@ -1168,7 +1169,7 @@ __global__ __launch_bounds__(64) void k_karnoldi_end(const Inst* const* insts, K
       ks.rel = rel;
       ks.j = j + 1;
       ks.total += 1;
-      gp(I.red)->linear_iters += 1;
+      red_of(I)->linear_iters += 1;
       fin = (rel <= ks.eta || j + 1 >= o.m || !(h > 0.0)) ? 1 : 0;
       if (fin) ks.met = rel <= ks.eta;
       else ks.scale = 1.0 / h;
@@ -1200,8 +1201,8 @@ __global__ __launch_bounds__(64) void k_karnoldi_end(const Inst* const* insts, K
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_kbegin(const Inst* const* insts) {
   __shared__ double red[KMAX + 1][KCH / 64];
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
-  if (!gp(I.red)->active || (int)blockIdx.x >= I.kchunks) return;
+  const auto& I = inst_at(insts, blockIdx.y);
+  if (!red_of(I)->active || (int)blockIdx.x >= I.kchunks) return;
   const int r = blockIdx.x * KCH + threadIdx.x;
   double f0 = 0.0, f1 = 0.0;
   if (r < I.nu) {
@@ -1223,13 +1224,13 @@ __global__ __launch_bounds__(KCH) void k_kbegin(const Inst* const* insts) {
 // ||F||_inf), eta_floor) and the first cycle.  A singular preconditioner
 // ends the instance's Newton iteration with status singular.
 __global__ __launch_bounds__(64) void k_kbegin_fin(const Inst* const* insts, KOpts o) {
-  const auto& I = *gp(gp(insts)[blockIdx.x]);
-  if (!gp(I.red)->active) return;
+  const auto& I = inst_at(insts, blockIdx.x);
+  if (!red_of(I)->active) return;
   KState& ks = *I.ks;
-  if (gp(I.red)->singular) {
+  if (red_of(I)->singular) {
     if (threadIdx.x == 0) {
-      gp(I.red)->status = 3;
-      gp(I.red)->active = 0;
+      red_of(I)->status = 3;
+      red_of(I)->active = 0;
       ks.state = KS_DONE;
     }
     return;
@@ -1237,7 +1238,7 @@ __global__ __launch_bounds__(64) void k_kbegin_fin(const Inst* const* insts, KOp
   const double bn = sqrt(chunk_sum(I, 2, 0));
   if (threadIdx.x != 0) return;
   ks.bnorm = bn;
-  ks.eta = fmax(fmin(o.eta_max, gp(I.red)->last_norm), o.eta_floor);
+  ks.eta = fmax(fmin(o.eta_max, red_of(I)->last_norm), o.eta_floor);
   ks.j = 0;
   ks.cycle = 0;
   ks.met = 0;
@@ -1257,7 +1258,7 @@ __global__ __launch_bounds__(64) void k_kbegin_fin(const Inst* const* insts, KOp
 // u = V y over the basis of the finished cycle (into w).
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_kycomb(const Inst* const* insts) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_CYCLE) || (int)blockIdx.x >= I.kchunks) return;
   const int r = blockIdx.x * KCH + threadIdx.x;
   if (r >= I.nu) return;
@@ -1278,7 +1279,7 @@ __global__ __launch_bounds__(KCH) void k_kycomb(const Inst* const* insts) {
 // x += z (the preconditioned correction of the cycle).
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_kxadd(const Inst* const* insts) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_CYCLE) || (int)blockIdx.x >= I.kchunks) return;
   const int r = blockIdx.x * KCH + threadIdx.x;
   if (r >= I.nu) return;
@@ -1295,7 +1296,7 @@ __global__ __launch_bounds__(KCH) void k_kxadd(const Inst* const* insts) {
 __global__ void k_kcycle_fin(const Inst* const* insts, int nslots, KOpts o) {
   const int sl = blockIdx.x * blockDim.x + threadIdx.x;
   if (sl >= nslots) return;
-  const auto& I = *gp(gp(insts)[sl]);
+  const auto& I = inst_at(insts, sl);
   if (!kstate_is(I, KS_CYCLE)) return;
   KState& ks = *I.ks;
   if (ks.met) {
@@ -1315,7 +1316,7 @@ __global__ void k_kcycle_fin(const Inst* const* insts, int nslots, KOpts o) {
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_kresid(const Inst* const* insts) {
   __shared__ double red[KMAX + 1][KCH / 64];
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_RESTART) || (int)blockIdx.x >= I.kchunks) return;
   const int r = blockIdx.x * KCH + threadIdx.x;
   double w0 = 0.0, w1 = 0.0;
@@ -1338,7 +1339,7 @@ __global__ __launch_bounds__(KCH) void k_kresid(const Inst* const* insts) {
 // Per instance: the true residual starts the next cycle, or ends the solve
 // when it already meets the forcing term.
 __global__ __launch_bounds__(64) void k_krestart_fin(const Inst* const* insts) {
-  const auto& I = *gp(gp(insts)[blockIdx.x]);
+  const auto& I = inst_at(insts, blockIdx.x);
   if (!kstate_is(I, KS_RESTART)) return;
   KState& ks = *I.ks;
   const double beta = sqrt(chunk_sum(I, 2, 0));
@@ -1358,7 +1359,7 @@ __global__ __launch_bounds__(64) void k_krestart_fin(const Inst* const* insts) {
 // The Newton step in the factor layout that the voltage update reads.
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_kfinish(const Inst* const* insts) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_FINISH) || (int)blockIdx.x >= I.kchunks) return;
   const int r = blockIdx.x * KCH + threadIdx.x;
   if (r >= I.nu) return;
@@ -1411,13 +1412,13 @@ __device__ inline void bcg_stop(const IR& I, KOpts o) {
 // Per instance, after k_kbegin (w = F, x = 0, partial ||F||^2): ||F||_2,
 // the forcing term, <r0, r> = ||F||^2 and the first iteration.
 __global__ __launch_bounds__(64) void k_bcg_begin_fin(const Inst* const* insts, KOpts o) {
-  const auto& I = *gp(gp(insts)[blockIdx.x]);
-  if (!gp(I.red)->active) return;
+  const auto& I = inst_at(insts, blockIdx.x);
+  if (!red_of(I)->active) return;
   KState& ks = *I.ks;
-  if (gp(I.red)->singular) {
+  if (red_of(I)->singular) {
     if (threadIdx.x == 0) {
-      gp(I.red)->status = 3;
-      gp(I.red)->active = 0;
+      red_of(I)->status = 3;
+      red_of(I)->active = 0;
       ks.state = KS_DONE;
     }
     return;
@@ -1426,7 +1427,7 @@ __global__ __launch_bounds__(64) void k_bcg_begin_fin(const Inst* const* insts, 
   if (threadIdx.x != 0) return;
   const double bn = sqrt(b2);
   ks.bnorm = bn;
-  ks.eta = fmax(fmin(o.eta_max, gp(I.red)->last_norm), o.eta_floor);
+  ks.eta = fmax(fmin(o.eta_max, red_of(I)->last_norm), o.eta_floor);
   ks.j = 0;
   ks.cycle = 0;
   ks.met = 0;
@@ -1447,7 +1448,7 @@ __global__ __launch_bounds__(64) void k_bcg_begin_fin(const Inst* const* insts, 
 // p = r + beta (p - omega v), or r = r0 = p = F in the first iteration; w = p.
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts) {
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
   const int r = blockIdx.x * KCH + threadIdx.x;
   if (r >= I.nu) return;
@@ -1476,7 +1477,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts) {
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_bcg_v(const Inst* const* insts) {
   __shared__ double red[KMAX + 1][KCH / 64];
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
   const int r = blockIdx.x * KCH + threadIdx.x;
   double d = 0.0;
@@ -1503,7 +1504,7 @@ template <typename T>
 __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, int it) {
   __shared__ double red[KMAX + 1][KCH / 64];
   __shared__ double alpha_s;
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
   if (threadIdx.x < 64) {
     const double a = gp(I.ks)->rho[it & 1] / chunk_sum(I, 0, 0);
@@ -1544,7 +1545,7 @@ template <typename T>
 __global__ __launch_bounds__(KCH) void k_bcg_t(const Inst* const* insts, KOpts o) {
   __shared__ double red[KMAX + 1][KCH / 64];
   __shared__ int decision;  // 0 second half, 1 first half met, 2 breakdown
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   if ((!kstate_is(I, KS_BP) && !kstate_is(I, KS_BS)) || (int)blockIdx.x >= I.kchunks) return;
   auto& ks = *gp(I.ks);
   if (threadIdx.x < 64) {
@@ -1557,7 +1558,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_t(const Inst* const* insts, KOpts o
       decision = dec;
       if (blockIdx.x == 0) {
         ks.total += 1;
-        gp(I.red)->linear_iters += 1;
+        red_of(I)->linear_iters += 1;
         if (dec == 2) {
           bcg_stop(I, o);
         } else if (dec == 1) {
@@ -1602,7 +1603,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts) {
   __shared__ double red[KMAX + 1][KCH / 64];
   __shared__ double omega_s;
   __shared__ bool skip_s;
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   const bool half = kstate_is(I, KS_BH);
   if ((!half && !kstate_is(I, KS_BS)) || (int)blockIdx.x >= I.kchunks) return;
   const auto& ks = *gp(I.ks);
@@ -1662,7 +1663,7 @@ template <typename T>
 __global__ __launch_bounds__(KCH) void k_bcg_next(const Inst* const* insts, KOpts o, int it) {
   __shared__ double beta_s;
   __shared__ int go;
-  const auto& I = *gp(gp(insts)[blockIdx.y]);
+  const auto& I = inst_at(insts, blockIdx.y);
   const bool half = kstate_is(I, KS_BH);
   if ((!half && !kstate_is(I, KS_BS) && !kstate_is(I, KS_BP)) || (int)blockIdx.x >= I.kchunks) return;
   auto& ks = *gp(I.ks);
@@ -1732,7 +1733,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_next(const Inst* const* insts, KOpt
 __global__ void k_kretire(const Inst* const* insts, int nslots) {
   const int sl = blockIdx.x * blockDim.x + threadIdx.x;
   if (sl >= nslots) return;
-  const auto& I = *gp(gp(insts)[sl]);
+  const auto& I = inst_at(insts, sl);
   if (kstate_is(I, KS_FINISH)) gp(I.ks)->state = KS_DONE;
 }
 
@@ -1742,8 +1743,8 @@ __global__ void k_kretire(const Inst* const* insts, int nslots) {
 __global__ void k_kgather(const Inst* const* insts, int nslots, int* out) {
   const int sl = blockIdx.x * blockDim.x + threadIdx.x;
   if (sl >= nslots) return;
-  const auto& I = *gp(gp(insts)[sl]);
-  out[sl] = gp(I.red)->active ? gp(I.ks)->state : KS_DONE;
+  const auto& I = inst_at(insts, sl);
+  out[sl] = red_of(I)->active ? gp(I.ks)->state : KS_DONE;
   out[nslots + sl] = gp(I.ks)->total;
 }
 

@@ -69,12 +69,12 @@ size_t Batch::plan_bytes(size_t nwork) const {
 bool Batch::place(char* mem, const std::vector<int2>& work) {
   auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
   const size_t b_tab = al(sizeof(void*) * std::max(nslots, 1));
-  d_insts = (const pfd::Inst* const*)mem;
+  d_insts = nslots == 1 ? (const pfd::Inst* const*)((uintptr_t)cases[0]->d_inst + 1) : (const pfd::Inst* const*)mem;
   d_work = (int2*)(mem + b_tab);
   std::vector<const pfd::Inst*> tab(nslots);
   for (int s = 0; s < nslots; ++s) tab[s] = cases[s]->d_inst;
   hipStream_t st = stream;
-  bool ok = hipMemcpyAsync((void*)d_insts, tab.data(), sizeof(void*) * nslots, hipMemcpyHostToDevice, st) == hipSuccess;
+  bool ok = hipMemcpyAsync((void*)mem, tab.data(), sizeof(void*) * nslots, hipMemcpyHostToDevice, st) == hipSuccess;
   if (!work.empty())
     ok &= hipMemcpyAsync(d_work, work.data(), sizeof(int2) * work.size(), hipMemcpyHostToDevice, st) == hipSuccess;
   ok &= hipStreamSynchronize(st) == hipSuccess;
@@ -120,35 +120,63 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
   }
   // sparse refactorisation, level by level, one launch per lane-group size;
   // each column's launch also runs the forward row of its node (the rows of
-  // a level depend only on earlier levels' L blocks and solution entries)
-  // (factor launches whose columns all fit one wave's lane groups in one
-  // pass run a column per wave: k0 = 1)
+  // a level depend only on earlier levels' L blocks and solution entries).
+  // A batch of one names its columns by their positions in the level order;
+  // else the items are (slot, position), by lane class.
   for (int l = 0; l < max_lev; ++l) {
-    std::map<int, std::vector<int2>> byG;
-    std::map<int, double> fl, by;
-    std::map<int, int> maxt;  // most targets of a column's first pass
+    struct Group {
+      std::vector<int2> cls[pfd::kFacClasses];
+      double fl = 0, by = 0;
+      int maxt = 0;  // most targets of a column before its L targets
+      size_t count = 0;
+    };
+    std::map<int, Group> byG;
     for (int s = 0; s < nslots; ++s) {
       Case* c = cs[s];
       if (l >= c->nlev) continue;
       const int G = c->fac_g[l];
-      auto& v = byG[G];
-      int& mt = maxt[G];
+      Group& g = byG[G];
       for (int k = c->an.col_lev_ptr[l]; k < c->an.col_lev_ptr[l + 1]; ++k) {
-        const int j = c->an.col_order[k];
-        v.push_back(make_int2(s, j));
-        // first pass: D, the U blocks and the forward row
-        mt = std::max(mt, 2 + c->an.colptr[j + 1] - c->an.colptr[j]);
+        const int j = c->an.col_order[k], len = c->an.colptr[j + 1] - c->an.colptr[j];
+        g.cls[pfd::fac_class(len, G)].push_back(make_int2(s, k));
+        g.maxt = std::max(g.maxt, 2 + len);
+        ++g.count;
       }
-      fl[G] += c->fac_flops[l];
-      by[G] += c->fac_bytes[l];
+      g.fl += c->fac_flops[l];
+      g.by += c->fac_bytes[l];
     }
     for (auto& kv : byG) {
-      // k0 = 1: a column per wave when its targets fit one pass of the
-      // wave's lane groups; 2: 1024 threads per column when the level has
-      // few columns and they need several passes of 256 threads
-      int wave = maxt[kv.first] * kv.first <= 64 ? 1 : 0;
-      if (!wave && kv.second.size() < 128 && maxt[kv.first] * kv.first > 256) wave = 2;
-      emit(L_FACTOR, PF_K_SPARSE_FACTOR, kv.first, wave, kv.second, fl[kv.first], by[kv.first]);
+      const int G = kv.first;
+      Group& g = kv.second;
+      // 1024 threads per column when the level has few columns and they need
+      // several passes of 256 threads
+      const bool wide = g.count < 128 && (int64_t)g.maxt * G > 256;
+      Launch f;
+      f.kind = L_FACTOR;
+      f.cls = PF_K_SPARSE_FACTOR;
+      f.G = G;
+      f.k0 = wide ? 1 : 0;
+      f.nflag = 0;
+      f.off = (int64_t)work.size();
+      f.count = (int)g.count;
+      f.flops = g.fl;
+      f.bytes = g.by;
+      int first = nslots == 1 ? cs[0]->an.col_lev_ptr[l] : 0, end = 0;
+      for (int k = 0; k < pfd::kFacClasses; ++k) {
+        const int n = (int)g.cls[k].size(), per = pfd::kFacClasses - 1 - k;  // 32, 16, 8, 4, 1 columns a work-group
+        const int cols = per == 0 ? 1 : 2 << per;
+        end += (n + cols - 1) / cols;
+        f.fac.end[k] = end;
+        f.fac.first[k] = first;
+        f.fac.count[k] = n;
+        first += n;
+        if (nslots > 1) work.insert(work.end(), g.cls[k].begin(), g.cls[k].end());
+      }
+      if (wide) {
+        f.fac.first[4] = f.fac.first[0];
+        f.fac.count[4] = (int)g.count;
+      }
+      seq.push_back(f);
     }
   }
   // forward rows of the dense block, then the Schur complement into it
@@ -265,10 +293,7 @@ void lu_solve(Batch* b) {
     const int2* w = b->d_work + l.off;
     switch (l.kind) {
       case L_FACTOR:
-        if (l.k0 == 1)
-          pfd::launch_factor_cols_wave<T>(s, I, w, l.count, l.G);
-        else
-          pfd::launch_factor_cols<T>(s, I, w, l.count, l.G, l.k0 == 2);
+        pfd::launch_factor_cols<T>(s, I, b->nslots == 1 ? nullptr : w, l.fac, l.G, l.k0);
         break;
       case L_FWD:
         pfd::launch_fwd_rows<T>(s, I, w, l.count, l.G);
