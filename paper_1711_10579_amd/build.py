@@ -39,6 +39,7 @@ SOURCES = [
     "krylov_check.cpp",
     "tune.cpp",
     "dense_plan.cpp",
+    "tree_plan.cpp",
     "precond_check.cpp",
     "kernels.hip",
     "dense.hip",

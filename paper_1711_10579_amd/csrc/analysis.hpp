@@ -66,6 +66,47 @@ struct Analysis {
   std::string summary() const;
 };
 
+// Lanes (a power of two) for lists of up to m entries.
+inline int pick_lanes(int64_t m, int lane_scale) {
+  int g = 1;
+  while (g < 64 && 4LL * g < m) g *= 2;
+  return g * lane_scale < 64 ? g * lane_scale : 64;
+}
+// Lanes per update list and forward row of each level.
+std::vector<int> factor_lanes(const Analysis& an, int lane_scale);
+
+// The sparse refactorisation of a case solved alone: levels below
+// first_level take a launch each; the others run in one launch or two
+// (stages, cutting the levels).  The subtrees of the elimination tree inside a
+// stage need nothing from each other, so they are dealt out to bins, and a
+// bin is a work-group that walks its levels with a barrier between them, its
+// columns' lists in LDS.  Only who forms a column and when depends on this,
+// not how (the lanes are the level's).
+// A bin's program, in words from its start: number of records, number of
+// slots; kTreeRec words per level with columns {first slot, slots, lanes per
+// list, columns of the whole work-group}; a word per slot of a wave {first
+// column entry, log2 of its lanes per column << 16, columns << 24} and, after
+// a level's slots, per column of the whole work-group; per column {column,
+// first block, blocks, target table}; per table the offsets of its 2 len + 2
+// lists and the end; lists of pairs, (L, U) block ids or, the forward row
+// (target len + 1), (L block, column).
+constexpr int kTreeClasses = 6;     // columns of up to 8, 16, 32, 64, 128, 256 lanes; above: the whole work-group
+constexpr int kTreeRec = 4, kTreeHead = 4;
+constexpr int kTreeWords = 16000;   // a program's most words (of 64 KB of LDS)
+constexpr int kTreeColumns = 20000; // levels of more columns always take a launch
+struct TreePlan {
+  struct Stage {
+    int bin0, nbins, threads;
+  };
+  int first_level = 0;
+  std::vector<Stage> stages;
+  std::vector<int> bin_off;  // [bins + 1] first word of a bin's program (a multiple of 4)
+  std::vector<int> prog;
+};
+// max_bins work-groups of 256 threads, or half as many of 512; first_level
+// -1: where the estimated time is least (possibly no level in trees).
+TreePlan plan_trees(const Analysis& an, const std::vector<int>& lanes, int max_bins, int first_level = -1);
+
 struct GraphInput {
   int n_nodes = 0;
   std::vector<char> unknown;          // [n_nodes]

@@ -433,29 +433,19 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   c->M = 2 * an.nt;
   c->type.assign(d->bus_type, d->bus_type + n);
   {
-    auto pick = [&](int64_t m) {
-      int g = 1;
-      while (g < 64 && 4LL * g < m) g *= 2;
-      return std::min(64, g * sched.lane_scale);
-    };
-    c->fac_g.resize(c->nlev);
+    auto pick = [&](int64_t m) { return pfh::pick_lanes(m, sched.lane_scale); };
+    c->fac_g = pfh::factor_lanes(an, sched.lane_scale);
     c->fac_flops.resize(c->nlev);
     c->fac_bytes.resize(c->nlev);
     for (int l = 0; l < c->nlev; ++l) {
-      int64_t mf = 0, mr = 0;
       double upd = 0, blocks = 0;
       for (int k = an.col_lev_ptr[l]; k < an.col_lev_ptr[l + 1]; ++k) {
         int j = an.col_order[k];
         int len = an.colptr[j + 1] - an.colptr[j];
         int64_t t0 = j + 2LL * an.colptr[j];
-        for (int t = 0; t <= 2 * len; ++t) mf = std::max(mf, an.uptr[t0 + t + 1] - an.uptr[t0 + t]);
-        mr = std::max<int64_t>(mr, an.lrow_ptr[j + 1] - an.lrow_ptr[j]);
         upd += (double)(an.uptr[t0 + 1 + 2 * len] - an.uptr[t0]);
         blocks += 1 + 2 * len;
       }
-      // one lane count for the level's update lists and its forward rows
-      // (run by the same launch)
-      c->fac_g[l] = pick(std::max(mf, mr));
       c->fac_flops[l] = 16.0 * upd + 40.0 * blocks;
       c->fac_bytes[l] = 8.0 * upd + 2 * 32.0 * blocks;  // index pairs + read/write of target blocks (FP64)
     }
@@ -498,6 +488,11 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
     return PF_E_INVALID;
   }
   const int ns = an.ns;
+  // (the trees' kernel addresses blocks by 32-bit byte offsets)
+  const bool small = c->lu_count() * (int64_t)sizeof(double) <= UINT32_MAX;
+  const pfh::TreePlan tp = pfh::plan_trees(an, c->fac_g, kTreeBins, small ? -1 : c->nlev);
+  c->tree_level = tp.first_level;
+  c->tree_stages = tp.stages;
   std::vector<int4> colinfo(ns);
   for (int k = 0; k < ns; ++k) {
     const int j = an.col_order[k];
@@ -518,9 +513,10 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   total += 2 * carve_size<double>(n) + 2 * carve_size<double>(2LL * n) + carve_size<double>(2LL * nu);
   total += carve_size<double>(2LL * nu);
   total += carve_size<int>(ns + 1) + carve_size<int>(an.nnzl) + carve_size<int64_t>(c->ntg + 1) +
-           2 * carve_size<int>(nupd) + carve_size<int4>(ns);
+           2 * carve_size<int>(nupd) + carve_size<int4>(ns) + carve_size<int>((int64_t)tp.bin_off.size()) +
+           carve_size<int>((int64_t)tp.prog.size());
   total += carve_size<int>(c->ntt) + carve_size<int64_t>(c->ntt + 1) + 2 * carve_size<int>(ntail);
-  total += carve_size<int>(nu + 1) + 2 * carve_size<int>(an.nnzl) + carve_size<int>(ns);
+  total += carve_size<int>(nu + 1) + 2 * carve_size<int>(an.nnzl);
   total += carve_size<double>(n) + carve_size<int>(2LL * n) + carve_size<double>(6LL * n);
   const int nmpart = (n + 63) / 64, nupart = (nu + 255) / 256;
   total += carve_size<pfd::Red>(1) + carve_size<pfd::Inst>(1) + carve_size<int>(c->nheavy);
@@ -562,6 +558,8 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   c->upd_l = carve<int>(p, nupd);
   c->upd_u = carve<int>(p, nupd);
   c->colinfo = carve<int4>(p, ns);
+  c->tree_off = carve<int>(p, (int64_t)tp.bin_off.size());
+  c->tree_prog = carve<int>(p, (int64_t)tp.prog.size());
   c->tail_tgt = carve<int>(p, c->ntt);
   c->tail_uptr = carve<int64_t>(p, c->ntt + 1);
   c->tail_l = carve<int>(p, ntail);
@@ -569,7 +567,6 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   c->lrow_ptr = carve<int>(p, nu + 1);
   c->lrow_blk = carve<int>(p, an.nnzl);
   c->lrow_col = carve<int>(p, an.nnzl);
-  c->bwd_rows = carve<int>(p, ns);
   c->red = carve<pfd::Red>(p, 1);
   c->d_inst = carve<pfd::Inst>(p, 1);
   static_assert(pfd::kRedOffset == 256, "carve's alignment puts the descriptor right behind the state");
@@ -625,6 +622,8 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   ok &= up(c->upd_l, an.upd_l.data(), sizeof(int) * nupd);
   ok &= up(c->upd_u, an.upd_u.data(), sizeof(int) * nupd);
   ok &= up(c->colinfo, colinfo.data(), sizeof(int4) * ns);
+  ok &= up(c->tree_off, tp.bin_off.data(), sizeof(int) * tp.bin_off.size());
+  ok &= up(c->tree_prog, tp.prog.data(), sizeof(int) * tp.prog.size());
   ok &= up(c->tail_tgt, an.tail_tgt.data(), sizeof(int) * c->ntt);
   ok &= up(c->tail_uptr, an.tail_uptr.data(), sizeof(int64_t) * (c->ntt + 1));
   ok &= up(c->tail_l, an.tail_l.data(), sizeof(int) * ntail);
@@ -632,7 +631,6 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   ok &= up(c->lrow_ptr, an.lrow_ptr.data(), sizeof(int) * (nu + 1));
   ok &= up(c->lrow_blk, an.lrow_blk.data(), sizeof(int) * an.nnzl);
   ok &= up(c->lrow_col, an.lrow_col.data(), sizeof(int) * an.nnzl);
-  ok &= up(c->bwd_rows, an.bwd_rows.data(), sizeof(int) * ns);
   ok &= up(d_heavy, heavy.data(), sizeof(int) * heavy.size());
   ok &= hipMemsetAsync(c->red, 0, sizeof(pfd::Red), s) == hipSuccess;
   {

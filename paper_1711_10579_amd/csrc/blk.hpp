@@ -115,22 +115,38 @@ __device__ inline void st_blk(T* p, int64_t id, const Blk<T>& v) {
   q[3] = v.d;
 }
 
+// The block operations name their fused multiply-adds: a column is formed by
+// different kernels alone and in a batch, and left to the compiler each could
+// fuse another product of a sum (results must agree to the bit).
+
+// a - (x y + z w)
+template <typename T>
+__device__ inline T sub2(T a, T x, T y, T z, T w) {
+  return fma(-x, y, fma(-z, w, a));
+}
+
 // acc -= X * Y
 template <typename T>
 __device__ inline void blk_msub(Blk<T>& acc, const Blk<T>& X, const Blk<T>& Y) {
-  acc.a -= X.a * Y.a + X.b * Y.c;
-  acc.b -= X.a * Y.b + X.b * Y.d;
-  acc.c -= X.c * Y.a + X.d * Y.c;
-  acc.d -= X.c * Y.b + X.d * Y.d;
+  acc.a = sub2(acc.a, X.a, Y.a, X.b, Y.c);
+  acc.b = sub2(acc.b, X.a, Y.b, X.b, Y.d);
+  acc.c = sub2(acc.c, X.c, Y.a, X.d, Y.c);
+  acc.d = sub2(acc.d, X.c, Y.b, X.d, Y.d);
+}
+
+// the determinant of a 2x2 block
+template <typename T>
+__device__ inline T blk_det(const Blk<T>& m) {
+  return fma(m.a, m.d, -(m.b * m.c));
 }
 
 template <typename T>
 __device__ inline Blk<T> blk_mul(const Blk<T>& X, const Blk<T>& Y) {
   Blk<T> r;
-  r.a = X.a * Y.a + X.b * Y.c;
-  r.b = X.a * Y.b + X.b * Y.d;
-  r.c = X.c * Y.a + X.d * Y.c;
-  r.d = X.c * Y.b + X.d * Y.d;
+  r.a = fma(X.a, Y.a, X.b * Y.c);
+  r.b = fma(X.a, Y.b, X.b * Y.d);
+  r.c = fma(X.c, Y.a, X.d * Y.c);
+  r.d = fma(X.c, Y.b, X.d * Y.d);
   return r;
 }
 

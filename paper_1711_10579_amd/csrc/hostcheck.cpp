@@ -271,6 +271,99 @@ void check_bwd_plan(const pfh::Analysis& an, int M, const std::vector<int>& gs, 
   for (size_t q = nd + nrw; q < items.size(); ++q) req(covered[q] == 1, "backward plan: row item outside every work-group");
 }
 
+// The subtree plan of the sparse refactorisation: every column of its levels
+// in exactly one record, of its level and lane count, in a class that holds
+// its targets, with the lists of the analysis; and every column whose blocks
+// it reads (its descendants) formed before it, by a level launch, in an
+// earlier stage or in an earlier record of the same bin.
+void check_tree_plan(const pfh::Analysis& an, const std::vector<int>& g, int bins, int first, int64_t* nchk) {
+  const pfh::TreePlan tp = pfh::plan_trees(an, g, bins, first);
+  const int ns = an.ns, nl = (int)an.col_lev_ptr.size() - 1;
+  req(tp.first_level >= 0 && tp.first_level <= nl && tp.bin_off[0] == 0, "tree plan: first level");
+  req(!tp.stages.empty() || tp.first_level == nl, "tree plan: levels without a stage");
+  std::vector<int> lev(ns), stage(ns, -1), bin(ns), recno(ns);
+  for (int l = 0; l < nl; ++l)
+    for (int k = an.col_lev_ptr[l]; k < an.col_lev_ptr[l + 1]; ++k) lev[an.col_order[k]] = l;
+  int next_bin = 0;
+  for (size_t s = 0; s < tp.stages.size(); ++s) {
+    const auto& st = tp.stages[s];
+    req(st.bin0 == next_bin && st.nbins >= 1 && st.nbins <= bins && (st.threads == 256 || st.threads == 512),
+        "tree plan: stage");
+    next_bin += st.nbins;
+    req(next_bin + 1 <= (int)tp.bin_off.size(), "tree plan: bins");
+    for (int b = st.bin0; b < next_bin; ++b) {
+      const int w0 = tp.bin_off[b], size = tp.bin_off[b + 1] - w0;
+      req(w0 % 4 == 0 && size >= pfh::kTreeHead && size <= pfh::kTreeWords && w0 + size <= (int)tp.prog.size(),
+          "tree plan: program size");
+      const int* P = &tp.prog[w0];
+      auto in = [&](int a, int n) { return a >= 0 && n >= 0 && a + n <= size; };
+      req(in(pfh::kTreeHead, pfh::kTreeRec * P[0] + P[1]), "tree plan: records out of range");
+      for (int r = 0; r < P[0]; ++r) {
+        const int* q = P + pfh::kTreeHead + pfh::kTreeRec * r;
+        const int G = q[2];
+        req(q[1] >= 0 && q[3] >= 0 && q[0] >= pfh::kTreeHead + pfh::kTreeRec * P[0] &&
+                q[0] + q[1] + q[3] <= pfh::kTreeHead + pfh::kTreeRec * P[0] + P[1],
+            "tree plan: slots out of range");
+        for (int s2 = 0; s2 < q[1] + q[3]; ++s2) {
+          const int e = P[q[0] + s2], ll = (e >> 16) & 0xff, n = e >> 24;
+          const bool whole = s2 >= q[1];
+          int col = e & 0xffff;
+          req(whole ? n == 1 : n >= 1 && ll >= 3 && ll <= 6 && (n << ll) <= 64, "tree plan: slot");
+          for (int i = 0; i < n; ++i, col += 4) {
+            req(in(col, 4), "tree plan: column entry out of range");
+            const int j = P[col], len = P[col + 2], tab = P[col + 3];
+            ++*nchk;
+            req(j >= 0 && j < ns && stage[j] < 0 && lev[j] >= tp.first_level, "tree plan: column listed twice");
+            req(P[col + 1] == an.colptr[j] && len == an.colptr[j + 1] - an.colptr[j], "tree plan: column blocks");
+            stage[j] = (int)s;
+            bin[j] = b;
+            recno[j] = r;
+            req(col % 4 == 0 && G == g[lev[j]], "tree plan: lanes differ from the level's");
+            const int64_t need = (2LL * len + 2) * G;
+            req(whole ? need > 256 : (ll == 6 ? need <= 256 : need <= 1 << ll) && G <= 1 << ll,
+                "tree plan: column in the wrong class");
+            req(in(tab, 2 * len + 3), "tree plan: target table out of range");
+            const int64_t t0 = j + 2LL * an.colptr[j];
+            for (int t = 0; t < 2 * len + 2; ++t) {
+              const bool fwd = t == len + 1;
+              const int64_t a = fwd ? an.lrow_ptr[j] : an.uptr[t <= len ? t0 + t : t0 + t - 1];
+              const int64_t e = fwd ? an.lrow_ptr[j + 1] : an.uptr[(t <= len ? t0 + t : t0 + t - 1) + 1];
+              req(in(P[tab + t], (int)(2 * (e - a))) && P[tab + t + 1] - P[tab + t] == 2 * (e - a),
+                  "tree plan: list length");
+              for (int64_t k = a; k < e; ++k) {
+                const int* p = P + P[tab + t] + 2 * (k - a);
+                req(p[0] == (fwd ? an.lrow_blk[k] : an.upd_l[k]) && p[1] == (fwd ? an.lrow_col[k] : an.upd_u[k]),
+                    "tree plan: list entry");
+              }
+            }
+          }
+        }
+      }
+    }
+  }
+  req(next_bin + 1 == (int)tp.bin_off.size(), "tree plan: bins outside the stages");
+  auto col_of_block = [&](int64_t id) {
+    const int q = (int)(id < ns + an.nnzl ? id - ns : id - ns - an.nnzl);
+    return (int)(std::upper_bound(an.colptr.begin(), an.colptr.end(), q) - an.colptr.begin()) - 1;
+  };
+  for (int j = 0; j < ns; ++j) {
+    req((stage[j] >= 0) == (lev[j] >= tp.first_level), "tree plan: a column is missing");
+    if (stage[j] < 0) continue;
+    auto before = [&](int k) {
+      ++*nchk;
+      req(stage[k] < stage[j] || (stage[k] == stage[j] && bin[k] == bin[j] && recno[k] < recno[j]),
+          "tree plan: a column reads blocks that are not formed before it");
+    };
+    const int64_t t0 = j + 2LL * an.colptr[j];
+    const int len = an.colptr[j + 1] - an.colptr[j];
+    for (int64_t q = an.uptr[t0]; q < an.uptr[t0 + 1 + 2 * len]; ++q) {
+      before(col_of_block(an.upd_l[q]));
+      before(col_of_block(an.upd_u[q]));
+    }
+    for (int q = an.lrow_ptr[j]; q < an.lrow_ptr[j + 1]; ++q) before(an.lrow_col[q]);
+  }
+}
+
 }  // namespace
 
 extern "C" pf_status pf_debug_schedule_check(const pf_case_desc* d, const pf_schedule* sched, uint64_t seed,
@@ -525,6 +618,8 @@ extern "C" pf_status pf_debug_schedule_check(const pf_case_desc* d, const pf_sch
         for (int copies : {1, 3})
           for (bool single : {false, true}) check_bwd_plan(an, M, *gs, copies, single, &nchk);
     }
+    check_tree_plan(an, pfh::factor_lanes(an, sc.lane_scale), kTreeBins, -1, &nchk);
+    check_tree_plan(an, pfh::factor_lanes(an, 4), 6, 0, &nchk);
     // the dense block's launch plan, alone and batched with other orders
     if (M > 0) {
       check_dense_plan({M}, &nchk);

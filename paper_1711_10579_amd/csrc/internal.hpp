@@ -17,6 +17,7 @@
 #include "../../include/pf.h"
 #include "analysis.hpp"
 #include "device.hpp"
+#include "kernels.hpp"
 
 namespace pfi {
 
@@ -123,10 +124,14 @@ struct Case {
   unsigned long long* pflags = nullptr;  // per 64-row block: panel-tile flags
   int *colptr = nullptr, *rowidx = nullptr, *upd_l = nullptr, *upd_u = nullptr;
   int4* colinfo = nullptr;  // columns in level order (by class inside a level)
+  // upper levels of the sparse refactorisation of the case alone (tree_plan.cpp)
+  int tree_level = 0;
+  std::vector<pfh::TreePlan::Stage> tree_stages;
+  int *tree_off = nullptr, *tree_prog = nullptr;
   int64_t* uptr = nullptr;
   int *tail_tgt = nullptr, *tail_l = nullptr, *tail_u = nullptr;
   int64_t* tail_uptr = nullptr;
-  int *lrow_ptr = nullptr, *lrow_blk = nullptr, *lrow_col = nullptr, *bwd_rows = nullptr;
+  int *lrow_ptr = nullptr, *lrow_blk = nullptr, *lrow_col = nullptr;
   pfd::Red* red = nullptr;
   pfd::Inst* d_inst = nullptr;  // device descriptor
   pfd::Inst hinst;              // host copy of the descriptor
@@ -164,7 +169,7 @@ struct Launch {
   double flops, bytes;
   pfd::FacLaunch fac;  // factor columns by class
 };
-enum { L_FACTOR = 0, L_FWD, L_SCHUR, L_PANEL, L_BWD };
+enum { L_FACTOR = 0, L_TREES, L_FWD, L_SCHUR, L_PANEL, L_BWD };
 
 // A batch of cases: device instance table, flattened work lists and the
 // launch sequence of one Newton step's LU solve.  Each item's arithmetic
@@ -304,6 +309,10 @@ pf_status nk_step(Batch* b, const pf_options* opt);
 // k0 - 64's update to tile (i, j) in 64-blocks; a flagged one then sets its
 // row block's flag, which the panel items of rows i and k0 / 64 wait for.
 constexpr int kDenseNB = 64;
+// work-groups the upper levels of a case's sparse refactorisation are dealt
+// to (256 threads, two to a CU; half as many of 512)
+constexpr int kTreeBins = 512;
+static_assert(pfh::kTreeWords <= pfd::kTreeLds, "a bin's program fits the kernel's LDS");
 void dense_grid(int M, int k, int* kb, int* nrt, int* nct);
 void dense_plan_step(const std::vector<int>& Ms, int k0, std::vector<int2>* items, int* nflag, int* npanel);
 // The backward solve's work list (one launch): nd dense items, then nrw

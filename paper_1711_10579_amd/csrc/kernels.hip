@@ -784,8 +784,8 @@ __device__ inline Blk<T> fwd_partial(const IR& I, const T* lu_, const T* x_, int
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (q + u * G < q1) {
-        acc.a -= L[u].a * x0[u] + L[u].b * x1[u];
-        acc.c -= L[u].c * x0[u] + L[u].d * x1[u];
+        acc.a = sub2(acc.a, L[u].a, x0[u], L[u].b, x1[u]);
+        acc.c = sub2(acc.c, L[u].c, x0[u], L[u].d, x1[u]);
       }
   }
   return acc;
@@ -839,7 +839,7 @@ __device__ __forceinline__ void factor_column(const IR& I, bool on, int j, int c
   }
   Blk<T> di = {T(0), T(0), T(0), T(0)};
   if (tid == 0) {
-    T det = acc[0].a * acc[0].d - acc[0].b * acc[0].c;
+    T det = blk_det(acc[0]);
     bool bad = !(det != T(0)) || !isfinite((double)det);
     if (bad) {
       if (on) red_of(I)->singular = 1;
@@ -933,6 +933,206 @@ __global__ __launch_bounds__(1024) void k_factor_cols_wide(const Inst* const* in
   const bool on = !inactive(I);
   const i4v q = ((const PF_AS1 i4v*)I.colinfo)[w.pos];
   factor_column<T, G, 1024, 2>(I, on, q.x, q.y, q.z, (int)threadIdx.x, sd);
+}
+
+// The upper levels of the refactorisation as subtrees (TreePlan), for a case
+// solved alone: a work-group walks the levels of its subtrees, a barrier after
+// each.  A level of few columns is a chain of dependent loads (list range ->
+// block ids -> blocks -> D^{-1} -> store), 3.5-6.9 us as a launch of its own,
+// since every load after a launch's start comes from the last-level cache.
+// Here the lists come into LDS once, in one round, and the blocks from this
+// CU's caches.  Waves take the level's columns by class, several small
+// columns to a wave.
+
+// Block `id` at a 32-bit offset from a uniform base: such a level is as much
+// bound by one wave's instructions as by its loads, and 64-bit addresses cost
+// several per block (the plan is used up to 4 GB of factor values).
+template <typename T>
+__device__ __forceinline__ PF_AS1 T* blk_at(PF_AS1 T* lu, unsigned id) {
+  return (PF_AS1 T*)((PF_AS1 char*)lu + id * (unsigned)(4 * sizeof(T)));
+}
+template <typename T>
+__device__ __forceinline__ Blk<T> ld_blk32(PF_AS1 T* lu, unsigned id) {
+  const PF_AS1 T* q = blk_at(lu, id);
+  return {q[0], q[1], q[2], q[3]};
+}
+
+// acc -= the updates of a list of (L, U) pairs in LDS, as sub_updates
+template <typename T>
+__device__ __forceinline__ void tree_updates(Blk<T>& acc, PF_AS1 T* lu, const int* p, int e, int G) {
+  // p: this lane's first pair; e: words of the list from there
+  for (int q = 0; q < e; q += 8 * G) {
+    Blk<T> L[4], U[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (q + 2 * u * G < e) {
+        L[u] = ld_blk32(lu, (unsigned)p[q + 2 * u * G]);
+        U[u] = ld_blk32(lu, (unsigned)p[q + 2 * u * G + 1]);
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (q + 2 * u * G < e) blk_msub(acc, L[u], U[u]);
+  }
+}
+// the forward row's partial sum over a list of (L block, column) pairs, as
+// fwd_partial
+template <typename T>
+__device__ __forceinline__ void tree_forward(Blk<T>& acc, PF_AS1 T* lu, PF_AS1 T* x, const int* p, int e, int G) {
+  for (int q = 0; q < e; q += 8 * G) {
+    Blk<T> L[4];
+    T x0[4], x1[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (q + 2 * u * G < e) {
+        L[u] = ld_blk32(lu, (unsigned)p[q + 2 * u * G]);
+        const unsigned k = (unsigned)p[q + 2 * u * G + 1];
+        const PF_AS1 T* xk = (const PF_AS1 T*)((const PF_AS1 char*)x + k * (unsigned)(2 * sizeof(T)));
+        x0[u] = xk[0];
+        x1[u] = xk[1];
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (q + 2 * u * G < e) {
+        acc.a = sub2(acc.a, L[u].a, x0[u], L[u].b, x1[u]);
+        acc.c = sub2(acc.c, L[u].c, x0[u], L[u].d, x1[u]);
+      }
+  }
+}
+// group_sum for a group size known only when the kernel runs (the same tree)
+template <typename T>
+__device__ inline Blk<T> group_sum_rt(Blk<T> v, int G) {
+  for (int off = G / 2; off > 0; off >>= 1) {
+    v.a += __shfl_xor(v.a, off, 64);
+    v.b += __shfl_xor(v.b, off, 64);
+    v.c += __shfl_xor(v.c, off, 64);
+    v.d += __shfl_xor(v.d, off, 64);
+  }
+  return v;
+}
+
+// A column (its entry at `col` of the program) by `lanes` threads, as
+// factor_column
+template <typename T, int NP, bool Group, typename IR>
+__device__ __forceinline__ void tree_column(const IR& I, const int* prog, int col, int tid, int G, int lanes, T* sd) {
+  const i4v ci = *(const i4v*)(prog + col);
+  const int j = ci.x, c0 = ci.y, len = ci.z;
+  const int* tab = prog + ci.w;
+  const auto lu = gp((T*)I.lu);
+  const auto x = gp((T*)I.x);
+  const int lane = tid & (G - 1), grp = tid / G, NG = lanes / G;
+  const int nt = 2 * len + 2;
+  const unsigned u0 = (unsigned)(I.ns + I.nnzl) + (unsigned)c0 - 1, l0 = (unsigned)I.ns + (unsigned)c0 - (unsigned)len - 2;
+  auto dest = [&](int t) -> unsigned { return t == 0 ? (unsigned)j : (unsigned)t + (t <= len ? u0 : l0); };
+  auto sum = [&](int t) -> Blk<T> {
+    Blk<T> acc = {T(0), T(0), T(0), T(0)};
+    const int* p = prog + tab[t] + 2 * lane;
+    const int e = tab[t + 1] - tab[t] - 2 * lane;
+    if (t == len + 1) {
+      if (lane == 0) {
+        acc.a = x[2 * j];
+        acc.c = x[2 * j + 1];
+      }
+      tree_forward<T>(acc, lu, x, p, e, G);
+    } else {
+      if (lane == 0) acc = ld_blk32(lu, dest(t));
+      tree_updates<T>(acc, lu, p, e, G);
+    }
+    return group_sum_rt(acc, G);
+  };
+  auto store = [&](int t, const Blk<T>& v, const Blk<T>& di) {
+    if (t == len + 1) {
+      x[2 * j] = v.a;
+      x[2 * j + 1] = v.c;
+    } else {
+      const Blk<T> w = t <= len ? v : blk_mul(v, di);
+      PF_AS1 T* q = blk_at(lu, dest(t));
+      q[0] = w.a;
+      q[1] = w.b;
+      q[2] = w.c;
+      q[3] = w.d;
+    }
+  };
+  Blk<T> acc[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int t = p * NG + grp;
+    acc[p] = {T(0), T(0), T(0), T(0)};
+    if (t < nt) acc[p] = sum(t);
+  }
+  Blk<T> di = {T(0), T(0), T(0), T(0)};
+  if (tid == 0) {
+    T det = blk_det(acc[0]);
+    bool bad = !(det != T(0)) || !isfinite((double)det);
+    if (bad) {
+      red_of(I)->singular = 1;
+      det = T(1);
+    }
+    T r = T(1) / det;
+    di.a = acc[0].d * r;
+    di.b = -acc[0].b * r;
+    di.c = -acc[0].c * r;
+    di.d = acc[0].a * r;
+    st_blk(gp((T*)I.dinv), j, di);
+    if (Group) {
+      sd[0] = di.a;
+      sd[1] = di.b;
+      sd[2] = di.c;
+      sd[3] = di.d;
+    }
+  }
+  if (Group) {
+    __syncthreads();
+    di = {sd[0], sd[1], sd[2], sd[3]};
+  } else {
+    const int src = (int)(threadIdx.x & 63) - tid;  // lane of this column's thread 0
+    di = {__shfl(di.a, src, 64), __shfl(di.b, src, 64), __shfl(di.c, src, 64), __shfl(di.d, src, 64)};
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int t = p * NG + grp;
+    if (t < nt && lane == 0) store(t, acc[p], di);
+  }
+  for (int t = NP * NG + grp; t < nt; t += NG) {
+    const Blk<T> v = sum(t);
+    if (lane == 0) store(t, v, di);
+  }
+}
+
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void k_factor_trees(const Inst* const* insts, const int* __restrict__ bin_off,
+                                                     const int* __restrict__ words) {
+  __shared__ __align__(16) int prog[kTreeLds];
+  __shared__ T sd[4];
+  const auto& I = inst_at(insts, 0);
+  const auto off = gp(bin_off) + (int)blockIdx.x;
+  const int w0 = off[0], w1 = off[1];
+  {
+    // whole quads: a program starts and ends on one
+    const auto src = (const PF_AS1 i4v*)(words + w0);
+    i4v* dst = (i4v*)prog;
+    for (int i = threadIdx.x; i < (w1 - w0) / 4; i += NT) dst[i] = src[i];
+  }
+  if (inactive(I)) return;
+  __syncthreads();
+  const int nrec = __builtin_amdgcn_readfirstlane(prog[0]);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wl = threadIdx.x & 63;
+#pragma unroll 1
+  for (int r = 0; r < nrec; ++r) {
+    const i4v rec = ((const i4v*)prog)[1 + r];  // first slot, slots, lanes, columns of the whole work-group
+    const int G = rec.z;
+#pragma unroll 1
+    for (int s = wave; s < rec.y; s += NT / 64) {
+      const int e = prog[rec.x + s];
+      const int ll = (e >> 16) & 0xff, k = wl >> ll;
+      if (k < (e >> 24)) tree_column<T, 2, false>(I, prog, (e & 0xffff) + 4 * k, wl & ((1 << ll) - 1), G, 1 << ll, sd);
+    }
+#pragma unroll 1
+    for (int k = 0; k < rec.w; ++k) {
+      if (k > 0) __syncthreads();  // sd of the column before has been read
+      tree_column<T, 2, true>(I, prog, prog[rec.x + rec.y + k] & 0xffff, (int)threadIdx.x, G, NT, sd);
+    }
+    __syncthreads();
+  }
 }
 
 // Schur complement of the sparse part into the dense trailing block:
@@ -1120,6 +1320,16 @@ void launch_factor_cols(hipStream_t st, const Inst* const* insts, const int2* wo
 }
 
 template <typename T>
+void launch_factor_trees(hipStream_t st, const Inst* const* insts, const int* bin_off, const int* words, int nbins,
+                         int threads) {
+  if (nbins <= 0) return;
+  if (threads == 256)
+    k_factor_trees<T, 256><<<dim3((unsigned)nbins), 256, 0, st>>>(insts, bin_off, words);
+  else
+    k_factor_trees<T, 512><<<dim3((unsigned)nbins), 512, 0, st>>>(insts, bin_off, words);
+}
+
+template <typename T>
 void launch_tail_schur(hipStream_t st, const Inst* const* insts, const int2* work, int nwork, int G) {
   if (nwork <= 0) return;
   PF_GSWITCH(G, (k_tail_schur<T, GG><<<dim3((unsigned)nwork), 256, 0, st>>>(insts, work)));
@@ -1141,6 +1351,7 @@ void launch_update(hipStream_t st, const Inst* const* insts, int nslots, int max
   template void launch_fill<T>(hipStream_t, const Inst* const*, int, int, const int2*, int, int);          \
   template void launch_factor_cols<T>(hipStream_t, const Inst* const*, const int2*, const FacLaunch&, int, int); \
   template void launch_tail_schur<T>(hipStream_t, const Inst* const*, const int2*, int, int);              \
+  template void launch_factor_trees<T>(hipStream_t, const Inst* const*, const int*, const int*, int, int);   \
   template void launch_fwd_rows<T>(hipStream_t, const Inst* const*, const int2*, int, int);                \
   template void launch_update<T>(hipStream_t, const Inst* const*, int, int);                                \
   template void launch_kfill<T>(hipStream_t, const Inst* const*, int, int, int);

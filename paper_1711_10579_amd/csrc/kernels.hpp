@@ -38,6 +38,13 @@ int zero_chunk_values();
 // column
 template <typename T>
 void launch_factor_cols(hipStream_t, const Inst* const* insts, const int2* work, const FacLaunch& f, int G, int wide);
+// one stage of the upper levels' subtrees: `nbins` programs at
+// words[bin_off[b]], each of at most kTreeLds words, `threads` (256 or 512)
+// threads each
+constexpr int kTreeLds = 16000;
+template <typename T>
+void launch_factor_trees(hipStream_t, const Inst* const* insts, const int* bin_off, const int* words, int nbins,
+                         int threads);
 template <typename T>
 void launch_fwd_rows(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int G);
 template <typename T>

@@ -123,7 +123,9 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
   // a level depend only on earlier levels' L blocks and solution entries).
   // A batch of one names its columns by their positions in the level order;
   // else the items are (slot, position), by lane class.
-  for (int l = 0; l < max_lev; ++l) {
+  // Alone, the upper levels run as subtrees.
+  const int launch_lev = nslots == 1 ? std::min(max_lev, cs[0]->tree_level) : max_lev;
+  for (int l = 0; l < launch_lev; ++l) {
     struct Group {
       std::vector<int2> cls[pfd::kFacClasses];
       double fl = 0, by = 0;
@@ -179,6 +181,24 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
       seq.push_back(f);
     }
   }
+  if (nslots == 1)
+    for (size_t k = 0; k < cs[0]->tree_stages.size(); ++k) {
+      const auto& st = cs[0]->tree_stages[k];
+      Launch f;
+      f.kind = L_TREES;
+      f.cls = PF_K_SPARSE_FACTOR;
+      f.G = st.threads;
+      f.k0 = st.bin0;
+      f.nflag = 0;
+      f.off = 0;
+      f.count = st.nbins;
+      f.flops = f.bytes = 0;
+      for (int l = launch_lev; k == 0 && l < max_lev; ++l) {
+        f.flops += cs[0]->fac_flops[l];
+        f.bytes += cs[0]->fac_bytes[l];
+      }
+      seq.push_back(f);
+    }
   // forward rows of the dense block, then the Schur complement into it
   {
     std::map<int, std::vector<int2>> byG, schur;
@@ -294,6 +314,9 @@ void lu_solve(Batch* b) {
     switch (l.kind) {
       case L_FACTOR:
         pfd::launch_factor_cols<T>(s, I, b->nslots == 1 ? nullptr : w, l.fac, l.G, l.k0);
+        break;
+      case L_TREES:
+        pfd::launch_factor_trees<T>(s, I, b->cases[0]->tree_off + l.k0, b->cases[0]->tree_prog, l.count, l.G);
         break;
       case L_FWD:
         pfd::launch_fwd_rows<T>(s, I, w, l.count, l.G);
