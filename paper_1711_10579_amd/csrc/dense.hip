@@ -10,15 +10,22 @@
 // substitution along.  The backward solve x_k = P_k (z_k - sum_{j>k} A_kj x_j)
 // finishes the block.
 //
-// One launch per 64-wide block step k: the previous step's update of the
-// tiles right of the diagonal block and below its block row (k-1 <- the
-// tiles' last but one step), beside the panel of step k: every panel
+// One launch per 64-wide block step k: updates of the tiles right of the
+// diagonal block by the steps before, beside the panel of step k: every panel
 // work-group inverts the diagonal block on the matrix cores (block
-// Gauss-Jordan over 16x16 blocks), multiplies one 64-row tile below it by
-// the inverse and applies this step's update to that row's tile of the next
-// block column, so that the next launch's panel finds its block column up
-// to date.  The rest of this step's update runs in the next launch, beside
-// the next panel.
+// Gauss-Jordan over 16x16 blocks), multiplies one 64-row tile below it (or a
+// quarter of it) by the inverse and applies this step's update to those rows'
+// tile of the next block column, so that the next launch's panel finds its
+// block column up to date.  The rest of this step's update runs in the next
+// launch, beside the next panel, or with the next step's in the launch after:
+// a tile that is not read in between takes two steps at once.
+//
+// What bounds a launch: alone, the panel's chain (10,000-bus grid, order
+// 1,642: 14.5 us a launch, 15.8 with 8-byte loads of the diagonal block in the
+// N-form's rows and every tile updated by every launch: about 2.2 us to read
+// the block, 4 x 1.9 for its inverse, 1.6 for the row quarter's product and
+// update, 1.3 between launches); batched, the tiles' bytes and the inverses
+// formed side by side (16 such grids: 73 us a launch, before 90).
 
 #include <hip/hip_runtime.h>
 
@@ -39,9 +46,11 @@ constexpr int NB = 64;
 // blocks, a quarter row tile and its L rows) and the update's (two operand
 // tiles)
 constexpr int kQuarterLd = 17;
-constexpr int kGemmLd = NB + 2;
+template <typename T>
+constexpr int kGemmLd = NB + 16 / sizeof(T);
 constexpr int kPanelSmem = 8 * kStage + 2 * NB * kQuarterLd;
-constexpr int kDenseSmem = 2 * NB * kGemmLd > kPanelSmem ? 2 * NB * kGemmLd : kPanelSmem;
+template <typename T>
+constexpr int kDenseSmem = NB * (NB + kGemmLd<T>) > kPanelSmem ? NB * (NB + kGemmLd<T>) : kPanelSmem;
 
 // Value of a row block's flag once the previous step's update of its tile
 // in the next block column of step k0 is stored, in Newton step `epoch`
@@ -64,8 +73,8 @@ __device__ inline unsigned long long flag_ld(const unsigned long long* p) {
 // launch drains whatever else shares the device (the bound only turns a
 // broken invariant into a recorded timeout instead of a hang).
 
-// Panel step k0 of every instance in the work list: item (slot, g), one of
-// four work-groups h of four waves.  Every work-group inverts the diagonal
+// Panel step k0 of every instance in the work list: item (slot, g), one
+// work-group of four waves, or one of four, from quarter h on.  Every work-group inverts the diagonal
 // block D = A_kk (identity-padded to 64x64) by block Gauss-Jordan over 4x4
 // blocks of 16: wave j keeps block column j in N-form; at pivot block p wave
 // p inverts D_pp (P) and stages P and its other blocks D_ip in LDS, then
@@ -73,8 +82,8 @@ __device__ inline unsigned long long flag_ld(const unsigned long long* p) {
 // D_ij -= D_ip D_pj (i != p) and wave p D_ip <- -D_ip P.  Then
 //   g = 0:        (h = 0 only) P is stored, column-major, for the backward
 //                 solve;
-//   g in 1..nrt:  rows 16h..16h+15 of row tile i = g - 1 below the block:
-//                 L_ik = A_ik P, computed transposed (P^T A_ik^T) so that
+//   g in 1..nrt:  row tile i = g - 1 below the block, QUARTERS times 16 rows
+//                 from 16h on: L_ik = A_ik P, computed transposed (P^T A_ik^T) so that
 //                 consecutive lanes store consecutive rows; then the same
 //                 rows of the row's tile C in the next block column take this
 //                 step's update, C -= L_ik A_{k,k+1}, once the previous step's
@@ -83,13 +92,13 @@ __device__ inline unsigned long long flag_ld(const unsigned long long* p) {
 //                 wave reads the flags as it starts and loads its part of C
 //                 and A_{k,k+1} as soon as both are seen, while the inverse
 //                 is still being formed.
-template <typename T>
+template <typename T, int QUARTERS>
 __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 w, int h, int k0, T* smem) {
   T* stage = smem;                    // two sets of four staged blocks
   T* xs = smem + 8 * kStage;          // the work-group's rows of A_ik, column-major [NB][kQuarterLd]
   T* ls = xs + NB * kQuarterLd;       // the same rows of L_ik
   const auto& I = inst_at(insts, w.x);
-  if (red_of(I)->active == 0) return;
+  const int active = red_of(I)->active, epoch = red_of(I)->epoch;
   // the launch is uniform per work-group: keep these in scalar registers
   const int g = __builtin_amdgcn_readfirstlane(w.y);
   if (g == 0 && h != 0) return;
@@ -103,7 +112,7 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
   const int lane = threadIdx.x & 63, c = lane & 15;
   int r0 = 0, nr = 0;  // this work-group's rows, nr <= 16
   if (g > 0) {
-    r0 = k0 + kb + (g - 1) * NB + 16 * h;
+    r0 = k0 + kb + (g - 1) * NB + 16 * h;  // h: the first quarter
     nr = M - r0 < 16 ? M - r0 : 16;
     if (nr <= 0) return;
   }
@@ -115,7 +124,7 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
   const bool wait = g > 0 && k0 > 0;
   unsigned long long want = 0, f1 = 0, f2 = 0;
   if (wait) {
-    want = panel_flag(red_of(I)->epoch, k0);
+    want = panel_flag(epoch, k0);
     f1 = flag_ld(&I.pflags[r0 / NB]);
     f2 = flag_ld(&I.pflags[k0 / NB]);
   }
@@ -123,11 +132,15 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
   V4<T> d[4];
   {
     const int cc = 16 * wv + c;
-    const int64_t cb = (int64_t)(k0 + min(cc, kb - 1)) * ld + k0;
+    // (the leading dimension is a multiple of 64: a block's rows never leave
+    // their column)
+    const auto col = G + (int64_t)(k0 + min(cc, kb - 1)) * ld + k0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) d[i] = blk_rows<T>(col + 16 * i, lane);
+    // tested with the block's loads in flight (reads stay in the instance)
+    if (active == 0) return;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) d[i][e] = G[cb + min(16 * i + Mfma<T>::row(lane, e), kb - 1)];
+    for (int i = 0; i < 4; ++i) d[i] = blk_nform<T>(d[i]);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -137,30 +150,38 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
       }
   }
   // the rows of A_ik (zero outside nr x kb), staged column-major
-  if (g > 0) {
-    const int tr = threadIdx.x & 15, tc = threadIdx.x >> 4;
-    T v[4];
+  const int tr = threadIdx.x & 15, tc = threadIdx.x >> 4;
+  T v[4];
+  auto load_rows = [&]() {
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = G[(int64_t)(k0 + min(tc + 16 * q, kb - 1)) * ld + r0 + min(tr, nr - 1)];
+  };
+  auto stage_rows = [&]() {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int cc = tc + 16 * q;
       xs[cc * kQuarterLd + tr] = (tr < nr && cc < kb) ? v[q] : T(0);
     }
+  };
+  if (g > 0) {
+    load_rows();
+    stage_rows();
   }
   // this wave's part of the update: C^T block (wv) of the rows, N-form, and
   // the blocks (q, wv) of U = A_{k,k+1}, N-form
   V4<T> ct, un[4];
-  auto fetch = [&]() {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  auto fetch_c = [&]() {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       ct[e] = ld_dev(&A[(int64_t)(c1 + min(16 * wv + Mfma<T>::row(lane, e), nc - 1)) * ld + r0 + min(c, nr - 1)]);
+  };
+  auto fetch = [&]() {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    fetch_c();
+    const auto ub = rsrc_of(A + (int64_t)c1 * ld + k0);
+    const unsigned uo = (unsigned)min(16 * wv + c, nc - 1) * (unsigned)ld * sizeof(T);
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        un[q][e] = ld_dev(&A[(int64_t)(c1 + min(16 * wv + c, nc - 1)) * ld + k0 + min(16 * q + Mfma<T>::row(lane, e), kb - 1)]);
+    for (int q = 0; q < 4; ++q) un[q] = blk_rows_dev<T>(ub, uo + 16 * q * sizeof(T), lane);
   };
   bool have = false;
   if (g > 0 && !wait) {
@@ -252,61 +273,92 @@ __device__ __forceinline__ void panel_step(const Inst* const* insts, const int2 
     }
     fetch();
   }
-  // (A_ik P)_{wv}^T = sum_q P_{q,wv}^T (A_ik)_q^T over the rows
-  V4<T> acc = zero;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    V4<T> xn;
+  for (int q = 0; q < 4; ++q) un[q] = -blk_nform<T>(un[q]);
+#pragma unroll 1
+  for (int quarter = 1;; ++quarter) {
+    // the next quarter's rows and tile
+    const int rc = r0, nrc = nr;
+    V4<T> cu = ct;
+    r0 += 16;
+    nr = M - r0 < 16 ? M - r0 : 16;
+    const bool last = quarter == QUARTERS || nr <= 0;
+    if (!last) {
+      load_rows();
+      fetch_c();
+    }
+    // (A_ik P)_{wv}^T = sum_q P_{q,wv}^T (A_ik)_q^T over the rows
+    V4<T> acc = zero;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) xn[e] = xs[(16 * q + Mfma<T>::row(lane, e)) * kQuarterLd + c];
-    acc = mm16<T>(d[q], xn, acc);
-  }
+    for (int q = 0; q < 4; ++q) {
+      V4<T> xn;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int col = 16 * wv + Mfma<T>::row(lane, e);
-    if (c < nr && col < kb) st_dev(&A[(int64_t)(k0 + col) * ld + r0 + c], acc[e]);
-    ls[col * kQuarterLd + c] = acc[e];
-  }
-  __syncthreads();
-  // C -= L_ik U, transposed like the product above
-  V4<T> cu = ct;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    V4<T> yn;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) yn[e] = ls[(16 * q + Mfma<T>::row(lane, e)) * kQuarterLd + c];
-    cu = mm16<T>(-un[q], yn, cu);
-  }
-  if (!expired)
+      for (int e = 0; e < 4; ++e) xn[e] = xs[(16 * q + Mfma<T>::row(lane, e)) * kQuarterLd + c];
+      acc = mm16<T>(d[q], xn, acc);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int col = 16 * wv + Mfma<T>::row(lane, e);
-      if (c < nr && col < nc) st_dev(&A[(int64_t)(c1 + col) * ld + r0 + c], cu[e]);
+      if (c < nrc && col < kb) st_dev(&A[(int64_t)(k0 + col) * ld + rc + c], acc[e]);
+      ls[col * kQuarterLd + c] = acc[e];
     }
+    __syncthreads();
+    if (!last) stage_rows();
+    // C -= L_ik U, transposed like the product above
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      V4<T> yn;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) yn[e] = ls[(16 * q + Mfma<T>::row(lane, e)) * kQuarterLd + c];
+      cu = mm16<T>(un[q], yn, cu);
+    }
+    if (!expired)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int col = 16 * wv + Mfma<T>::row(lane, e);
+        if (c < nrc && col < nc) st_dev(&A[(int64_t)(c1 + col) * ld + rc + c], cu[e]);
+      }
+    if (last) break;
+    __syncthreads();
+  }
 }
 
-// The previous block step's update of one 64x64 tile, A_ij -= L_{i,k-1}
+// The update of one 64x64 tile by the previous block step, A_ij -= L_{i,k-1}
 // A_{k-1,j} (k-1 at column k0 - 64; the tile's columns may include the
-// right-hand side column M), on the matrix cores: four waves, each a 32x32
-// quarter of the tile as 2x2 blocks of 16x16, K = 64 in steps of 4.  Item
-// (slot, j | i << 12 | flag << 24) for block row i and block column j; with
-// the flag the tile is announced in pflags[i] once stored.  The tile is
-// loaded with the operands, straight into the accumulators; operands sit
-// k-major in LDS (L negated) so that each quarter-wave reads 16 consecutive
-// values.
+// right-hand side column M), or by the two steps before k0, on the matrix
+// cores: four waves, each a 32x32 quarter of the tile as 2x2 blocks of 16x16,
+// K = 64 in steps of 4.  Item (slot, j | i << 12 | flag << 24 | two << 25) for
+// block row i and block column j; with the flag the tile is announced in
+// pflags[i] once stored.  The tile is loaded with the operands, straight into
+// the accumulators, and the second step's operands while the first step
+// multiplies: a tile kept over two steps moves half the bytes, and a large
+// trailing block's updates are bound by those (16 bytes read and written per
+// 128 operations of a step).  The sums' order is that of one step after the
+// other.
+// Operands come in by 16-byte loads and sit in LDS as they come (rows of one
+// column side by side): L negated, [k][row], the rows of odd k (FP32: of each
+// k mod 4) in another group of banks, and A_{k-1,j} [column][k], so that the
+// lanes of a half (FP32: whole) wave read from different banks.
 template <typename T>
 __device__ __forceinline__ void gemm_tile(const Inst* const* insts, const int2 wk, int k0, T* smem) {
-  T(*sa)[kGemmLd] = (T(*)[kGemmLd])smem;                   // [k][row]
-  T(*sb)[kGemmLd] = (T(*)[kGemmLd])(smem + NB * kGemmLd);  // [k][col]
+  constexpr int W = 16 / sizeof(T);    // values of a load
+  constexpr int NL = NB * NB / W / 256;  // loads per thread and operand
+  constexpr int CL = NB / W;             // loads of a column
+  typedef T vw __attribute__((ext_vector_type(W)));
+  typedef const PF_AS1 vw gvw;
+  T* sa = smem;                                        // [k][row, swizzled]
+  T(*sb)[kGemmLd<T>] = (T(*)[kGemmLd<T>])(smem + NB * NB);  // [col][k]
+  auto sw = [](int k) { return (k & (sizeof(T) == 8 ? 1 : 3)) << 4; };
   const auto& I = inst_at(insts, wk.x);
-  if (red_of(I)->active == 0) return;
+  const int active = red_of(I)->active, epoch = red_of(I)->epoch;
   T* A = (T*)I.tail;
   const int ld = I.ldt, M = I.M;
   const int bi0 = __builtin_amdgcn_readfirstlane((wk.y >> 12) & 0xfff);
   const int bj0 = __builtin_amdgcn_readfirstlane(wk.y & 0xfff);
-  const bool flag = (wk.y >> 24) != 0;
+  const bool flag = ((wk.y >> 24) & 1) != 0;
+  int more = __builtin_amdgcn_readfirstlane((wk.y >> 25) & 1);
   if (flag) __builtin_amdgcn_s_setprio(2);
-  const int kp = k0 - NB;
+  int kp = k0 - NB - more * NB;
   const int tid = threadIdx.x;
   const int r0 = bi0 * NB, c0 = bj0 * NB;
   const int nr = min(NB, M - r0);
@@ -316,8 +368,18 @@ __device__ __forceinline__ void gemm_tile(const Inst* const* insts, const int2 w
   const int li = lane % 16, lk = lane / 16;
   typedef typename Mfma<T>::v4 v4;
   const auto G = gp((const T*)A);
-  // every load of a thread in flight at once (addresses clamped into the
-  // tiles, values masked afterwards)
+  // every load of a thread in flight at once (columns clamped into the
+  // tiles; rows stay in their column, the leading dimension being a multiple
+  // of 64; values masked afterwards)
+  vw va[NL], vb[NL];
+  const int l0 = tid % CL * W, l1 = tid / CL;  // first row / k of the thread's loads, first column
+  auto operands = [&]() {
+#pragma unroll
+    for (int q = 0; q < NL; ++q) va[q] = *(gvw*)(G + (int64_t)(kp + l1 + 256 / CL * q) * ld + r0 + l0);
+#pragma unroll
+    for (int q = 0; q < NL; ++q) vb[q] = *(gvw*)(G + (int64_t)(c0 + min(l1 + 256 / CL * q, nc - 1)) * ld + kp + l0);
+  };
+  operands();
   v4 acc[2][2];
 #pragma unroll
   for (int bi = 0; bi < 2; ++bi)
@@ -328,44 +390,47 @@ __device__ __forceinline__ void gemm_tile(const Inst* const* insts, const int2 w
         const int r = rb + bi * 16 + li, c = cb + bj * 16 + Mfma<T>::row(lane, e);
         acc[bi][bj][e] = G[(int64_t)(c0 + min(c, nc - 1)) * ld + r0 + min(r, nr - 1)];
       }
-  T va[16], vb[16];
+  // tested with the loads in flight (reads stay in the instance)
+  if (active == 0) return;
+  for (;;) {
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int idx = tid + 256 * q;
-    const int r = idx % NB, k = idx / NB;
-    va[q] = G[(int64_t)(kp + k) * ld + r0 + min(r, nr - 1)];
-  }
+    for (int q = 0; q < NL; ++q) {
+      const int k = l1 + 256 / CL * q;
+      vw x;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int idx = tid + 256 * q;
-    const int k = idx % NB, c = idx / NB;
-    vb[q] = G[(int64_t)(c0 + min(c, nc - 1)) * ld + kp + k];
-  }
+      for (int u = 0; u < W; ++u) x[u] = l0 + u < nr ? -va[q][u] : T(0);
+      *(vw*)&sa[k * NB + (l0 ^ sw(k))] = x;
+    }
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int idx = tid + 256 * q;
-    const int r = idx % NB, k = idx / NB;
-    sa[k][r] = r < nr ? -va[q] : T(0);
-  }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int idx = tid + 256 * q;
-    const int k = idx % NB, c = idx / NB;
-    sb[k][c] = c < nc ? vb[q] : T(0);
-  }
-  __syncthreads();
-  // the transposed product (L U)^T = U^T L^T: the matrix core's first
-  // operand is the column block, so a lane's result row is a tile column and
-  // its lane index within 16 a tile row -- consecutive lanes then update
-  // consecutive rows of the column-major tile
+    for (int q = 0; q < NL; ++q) {
+      const int c = l1 + 256 / CL * q;
+      vw x = vb[q];
+      if (c >= nc) x = vw(T(0));
+      *(vw*)&sb[c][l0] = x;
+    }
+    __syncthreads();
+    if (more) {
+      kp += NB;
+      operands();
+    }
+    // the transposed product (L U)^T = U^T L^T: the matrix core's first
+    // operand is the column block, so a lane's result row is a tile column and
+    // its lane index within 16 a tile row -- consecutive lanes then update
+    // consecutive rows of the column-major tile
 #pragma unroll 4
-  for (int ks = 0; ks < NB; ks += 4) {
-    T a0 = sa[ks + lk][rb + li], a1 = sa[ks + lk][rb + 16 + li];
-    T b0 = sb[ks + lk][cb + li], b1 = sb[ks + lk][cb + 16 + li];
-    acc[0][0] = Mfma<T>::run(b0, a0, acc[0][0]);
-    acc[0][1] = Mfma<T>::run(b1, a0, acc[0][1]);
-    acc[1][0] = Mfma<T>::run(b0, a1, acc[1][0]);
-    acc[1][1] = Mfma<T>::run(b1, a1, acc[1][1]);
+    for (int ks = 0; ks < NB; ks += 4) {
+      const int k = ks + lk;
+      const T* ra = sa + k * NB;
+      const T a0 = ra[(rb + li) ^ sw(k)], a1 = ra[(rb + 16 + li) ^ sw(k)];
+      const T b0 = sb[cb + li][k], b1 = sb[cb + 16 + li][k];
+      acc[0][0] = Mfma<T>::run(b0, a0, acc[0][0]);
+      acc[0][1] = Mfma<T>::run(b1, a0, acc[0][1]);
+      acc[1][0] = Mfma<T>::run(b0, a1, acc[1][0]);
+      acc[1][1] = Mfma<T>::run(b1, a1, acc[1][1]);
+    }
+    if (!more) break;
+    more = 0;
+    __syncthreads();  // before the operands are overwritten
   }
 #pragma unroll
   for (int bi = 0; bi < 2; ++bi)
@@ -383,7 +448,7 @@ __device__ __forceinline__ void gemm_tile(const Inst* const* insts, const int2 w
     wait_vmem();
     __syncthreads();
     if (tid == 0)
-      __hip_atomic_store((PF_AS1 unsigned long long*)&I.pflags[bi0], panel_flag(red_of(I)->epoch, k0), __ATOMIC_RELAXED,
+      __hip_atomic_store((PF_AS1 unsigned long long*)&I.pflags[bi0], panel_flag(epoch, k0), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   }
 }
@@ -391,22 +456,22 @@ __device__ __forceinline__ void gemm_tile(const Inst* const* insts, const int2 w
 // Block step k0 in one launch: items [0, nflag) the previous step's update
 // of the tiles of the next block column (and of the block row's tile
 // there), which announce themselves; then the npanel panel items of step
-// k0, four work-groups each (a quarter of the item's row tile apiece), which
-// wait for those; then the rest of the previous step's update.  Work-groups
+// k0, SPLIT work-groups each (4: a quarter of the item's row tile apiece),
+// which wait for those; then the rest of the updates.  Work-groups
 // start in index order, so every wait is on a work-group that already runs.
 // The items write disjoint tiles except the next block column's, written by
 // its flagged update and then, after the flag, by its panel work-groups.
-template <typename T>
+template <typename T, int SPLIT>
 __global__ __launch_bounds__(256, 2) void k_dense_step(const Inst* const* insts, const int2* __restrict__ work,
                                                     int nflag, int npanel, int k0) {
-  __shared__ T smem[kDenseSmem];
+  __shared__ __attribute__((aligned(16))) T smem[kDenseSmem<T>];
   const int b = blockIdx.x;
   if (b < nflag)
     gemm_tile<T>(insts, ld_item(work, b), k0, smem);
-  else if (b < nflag + 4 * npanel)
-    panel_step<T>(insts, ld_item(work, nflag + (b - nflag) / 4), (b - nflag) % 4, k0, smem);
+  else if (b < nflag + SPLIT * npanel)
+    panel_step<T, 4 / SPLIT>(insts, ld_item(work, nflag + (b - nflag) / SPLIT), (b - nflag) % SPLIT * (4 / SPLIT), k0, smem);
   else
-    gemm_tile<T>(insts, ld_item(work, b - 3 * npanel), k0, smem);
+    gemm_tile<T>(insts, ld_item(work, b - (SPLIT - 1) * npanel), k0, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -820,11 +885,22 @@ __global__ __launch_bounds__(256, 2) void k_bwd_solve(const Inst* const* insts, 
 
 // ---------------------------------------------------------------------------
 
+// A row tile's quarters on four work-groups shorten the panel's chain by three
+// products and updates, 5 us, but each inverts the diagonal block; past one
+// panel work-group per CU these inverses take the matrix cores from the
+// updates.  16 grids of order 1,642: 11.7 ms a solve with quarters
+// throughout, 10.75 with whole tiles from 1,024 quarters on, 10.35 from 512,
+// 10.3 from 256; 512 mixed grids in FP32 24.8 ms with quarters, 23.7 from 256.
+constexpr int kPanelSplitMax = 256;
+
 template <typename T>
 void launch_dense_step(hipStream_t st, const Inst* const* insts, const int2* work, int nwork, int nflag, int npanel,
                        int k0) {
   if (nwork <= 0) return;
-  k_dense_step<T><<<dim3((unsigned)(nwork + 3 * npanel)), 256, 0, st>>>(insts, work, nflag, npanel, k0);
+  if (4 * npanel > kPanelSplitMax)
+    k_dense_step<T, 1><<<dim3((unsigned)nwork), 256, 0, st>>>(insts, work, nflag, npanel, k0);
+  else
+    k_dense_step<T, 4><<<dim3((unsigned)(nwork + 3 * npanel)), 256, 0, st>>>(insts, work, nflag, npanel, k0);
 }
 
 template <typename T>

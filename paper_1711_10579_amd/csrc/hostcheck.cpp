@@ -115,18 +115,23 @@ void check_dense_plan(const std::vector<int>& Ms, int64_t* nchk) {
         upd.push_back(nx);
         continue;
       }
-      // the previous step's update of a tile
-      const int y = items[i].y, cb = y & 0xfff, rb = (y >> 12) & 0xfff, fl = y >> 24;
+      // the update of a tile by the previous step or the two before
+      const int y = items[i].y, cb = y & 0xfff, rb = (y >> 12) & 0xfff, fl = (y >> 24) & 1, two = y >> 25;
       req(fl == ((int)i < nflag ? 1 : 0), "dense plan: flag of an update item");
-      req(k0 >= 64, "dense plan: update of a step before the first");
+      req(k0 >= 64 + 64 * two && (two == 0 || two == 1), "dense plan: update of a step before the first");
       const int r0 = 64 * rb, c0 = 64 * cb;
       req(r0 >= k0 && r0 < Ms[s] && c0 > k0 && c0 <= Ms[s], "dense plan: update tile off the grid");
-      const Key x(s, r0, c0), l(s, r0, k0 - 64), u(s, k0 - 64, c0);
-      req(cnt[x] == p - 1 && !fin.count(x), "dense plan: updated tile not up to date");
-      req(fin.count(l) && fin.count(u), "dense plan: update before its panel");
-      rd[i] = {x, l, u};
+      const Key x(s, r0, c0);
+      req(cnt[x] == p - 1 - two && !fin.count(x), "dense plan: updated tile not up to date");
+      rd[i] = {x};
+      for (int k = k0 - 64 - 64 * two; k < k0; k += 64) {
+        const Key l(s, r0, k), u(s, k, c0);
+        req(fin.count(l) && fin.count(u), "dense plan: update before its panel");
+        rd[i].push_back(l);
+        rd[i].push_back(u);
+        upd.push_back(x);
+      }
       writers[x].push_back(i);
-      upd.push_back(x);
       if (fl) {
         req(c0 == k0 + 64, "dense plan: flagged update away from the next block column");
         req(flagged.emplace(std::make_pair(s, r0), i).second, "dense plan: two flagged items of one row block");

@@ -305,9 +305,10 @@ pf_status nk_step(Batch* b, const pf_options* opt);
 // next block column, then the *npanel panel items (slot, g) of step k0 (g = 0
 // the diagonal block, g = 1..nrt its row tiles, each also applying step k0's
 // update to its row's tile of the next block column), then the other update
-// items.  An update item (slot, j | i << 12 | flag << 24) applies step
-// k0 - 64's update to tile (i, j) in 64-blocks; a flagged one then sets its
-// row block's flag, which the panel items of rows i and k0 / 64 wait for.
+// items.  An update item (slot, j | i << 12 | flag << 24 | two << 25) applies
+// step k0 - 64's update, with two those of k0 - 128 and k0 - 64, to tile
+// (i, j) in 64-blocks; a flagged one then sets its row block's flag, which the
+// panel items of rows i and k0 / 64 wait for.
 constexpr int kDenseNB = 64;
 // work-groups the upper levels of a case's sparse refactorisation are dealt
 // to (256 threads, two to a CU; half as many of 512)

@@ -86,6 +86,75 @@ __device__ inline V4<T> blk_get_t(const T* st, int lane) {
   return z;
 }
 
+// N-form of a block of a column-major matrix, read in two steps.  First
+// blk_rows: each lane its column's four rows 4 (l/16) + j, 16-byte loads (a
+// column of the block is one 128-byte line; by the N-form's own rows every
+// load would touch each line again); col points to row 0 of the lane's column,
+// 16-byte aligned.  Then blk_nform: between the lane groups (for FP64; the
+// FP32 N-form has those rows).
+template <typename T>
+__device__ inline V4<T> blk_rows(const __attribute__((address_space(1))) T* col, int lane) {
+  typedef T v2 __attribute__((ext_vector_type(16 / sizeof(T))));
+  typedef const __attribute__((address_space(1))) v2 gv2;
+  gv2* p = (gv2*)(col + 4 * (lane >> 4));
+  V4<T> z;
+  if constexpr (sizeof(T) == 4) {
+    z = p[0];
+  } else {
+    const v2 a = p[0], b = p[1];
+    z[0] = a[0], z[1] = a[1], z[2] = b[0], z[3] = b[1];
+  }
+  return z;
+}
+// the same through device-coherent loads, off bytes behind base (the wave's)
+template <typename T>
+__device__ inline V4<T> blk_rows_dev(__amdgpu_buffer_rsrc_t base, unsigned off, int lane) {
+  typedef T v2 __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int kSc1 = 16;
+  off += 4 * sizeof(T) * (lane >> 4);
+  const v2 a = __builtin_bit_cast(v2, __builtin_amdgcn_raw_buffer_load_b128(base, off, 0, kSc1));
+  V4<T> z;
+  if constexpr (sizeof(T) == 4) {
+    z = a;
+  } else {
+    const v2 b = __builtin_bit_cast(v2, __builtin_amdgcn_raw_buffer_load_b128(base, off + 16, 0, kSc1));
+    z[0] = a[0], z[1] = a[1], z[2] = b[0], z[3] = b[1];
+  }
+  return z;
+}
+// descriptor of the memory from p on (4 GB; p the same in every lane)
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p) {
+  const uintptr_t u = (uintptr_t)p;
+  const uintptr_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)u), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(u >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(hi << 32 | lo), 0, -1, 0x00020000);
+}
+__device__ inline void swap32(double& x, double& y) {
+  const auto u = __builtin_bit_cast(int2, x), v = __builtin_bit_cast(int2, y);
+  const auto lo = __builtin_amdgcn_permlane32_swap(u.x, v.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(u.y, v.y, false, false);
+  x = __builtin_bit_cast(double, make_int2(lo[0], hi[0]));
+  y = __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
+}
+__device__ inline void swap16(double& x, double& y) {
+  const auto u = __builtin_bit_cast(int2, x), v = __builtin_bit_cast(int2, y);
+  const auto lo = __builtin_amdgcn_permlane16_swap(u.x, v.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(u.y, v.y, false, false);
+  x = __builtin_bit_cast(double, make_int2(lo[0], hi[0]));
+  y = __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
+}
+template <typename T>
+__device__ inline V4<T> blk_nform(V4<T> z) {
+  if constexpr (sizeof(T) == 8) {
+    double a = z[0], b = z[1], c = z[2], d = z[3];
+    swap32(a, c);
+    swap32(b, d);
+    swap16(a, b);
+    swap16(c, d);
+    z[0] = a, z[1] = b, z[2] = c, z[3] = d;
+  }
+  return z;
+}
+
 // value of lane K of each 16-lane row in the whole row (DPP row broadcast;
 // every lane's source is valid, so no old value is kept)
 template <int K>

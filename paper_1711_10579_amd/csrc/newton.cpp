@@ -246,11 +246,14 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
         fl += 2.0 * kb * kb * kb + 2.0 * kb * kb * rr + 2.0 * rr * kb * nc;
         by += 8.0 * (2.0 * kb * kb + 2.0 * kb * rr + 2.0 * rr * nc + nrt * kb * nc);
       }
-      // per update of a tile: 2 NB^3 flops, read L_ik and A_kj, read and
-      // write A_ij (once per item)
-      const double nupd = (double)(items.size() - npanel);
+      // per update of a tile by a step: 2 NB^3 flops, read L_ik and A_kj;
+      // read and write A_ij once per item (of one step or two)
+      const double nitem = (double)(items.size() - npanel);
+      double nupd = nitem;
+      for (size_t i = 0; i < items.size(); ++i)
+        if ((int)i < nflag || (int)i >= nflag + npanel) nupd += items[i].y >> 25;
       fl += nupd * 2.0 * NB * NB * NB;
-      by += nupd * 8.0 * 4.0 * NB * NB;
+      by += 8.0 * 2.0 * NB * NB * (nupd + nitem);
       emit(L_PANEL, PF_K_DENSE_PANEL, npanel, k0, items, fl, by);
       if (!items.empty()) seq.back().nflag = nflag;
     }
