@@ -485,8 +485,12 @@ def pf_serve_stats(ctx):
 def pf_get_voltage(case):
     re = np.empty(case.n)
     im = np.empty(case.n)
-    _check(_lib.pf_get_voltage(case.handle, _dptr(re), _dptr(im)), "pf_get_voltage")
-    return re + 1j * im
+    # (an array of at least one value; data_as costs as much as a device round trip's third)
+    _check(_lib.pf_get_voltage(case.handle, C.byref(C.c_double.from_buffer(re)), C.byref(C.c_double.from_buffer(im))),
+           "pf_get_voltage")
+    V = 1j * im
+    V.real += re  # re + 1j im to the bit, without casting re
+    return V
 
 
 def pf_set_voltage(case, V):

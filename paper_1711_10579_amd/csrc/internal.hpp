@@ -62,6 +62,12 @@ struct Ctx {
   std::mutex launch_mu;  // serialises launches of the serving thread and callers
   std::mutex tune_mu;
   std::map<uint64_t, pf_schedule> tuned;  // topology hash -> autotuned schedule
+  // pf_get_voltage: two pinned halves of kVoltChunk nodes (real | imaginary
+  // parts), the flags of their blocks, and the last launch's flag value
+  std::mutex volt_mu;
+  double* h_volt = nullptr;
+  unsigned long long* h_vflag = nullptr;
+  unsigned long long volt_seq = 0;
   bool use_graphs = true;                 // replay reused batches' Newton steps from HIP graphs
   std::vector<Batch*> bcache;             // batches of recent pf_solve_batch calls, newest first
 

@@ -213,6 +213,32 @@ __global__ void k_gather_red(const Inst* const* insts, int nslots, Red* out) {
   for (int k = 0; k < W; ++k) dst[k] = w[k];
 }
 
+// Voltages of nodes [0, n) into pinned host memory, real parts and imaginary
+// parts apart; block b announces its kVoltBlock nodes in flag[b] (the host
+// copies them out while later blocks are still on their way).
+__global__ __launch_bounds__(256) void k_read_volt(const double2* __restrict__ v, int n, double* re, double* im,
+                                                unsigned long long* flag, unsigned long long seq) {
+  constexpr int P = kVoltBlock / 256;
+  const int i0 = blockIdx.x * kVoltBlock + threadIdx.x;
+  const auto src = gp(v);
+  double2 x[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k)
+    if (i0 + 256 * k < n) x[k] = make_double2(src[i0 + 256 * k].x, src[i0 + 256 * k].y);
+#pragma unroll
+  for (int k = 0; k < P; ++k)
+    if (i0 + 256 * k < n) {
+      __hip_atomic_store(&gp(re)[i0 + 256 * k], x[k].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(&gp(im)[i0 + 256 * k], x[k].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  // every wave's stores have completed (they go through to the host; a
+  // release would write back the whole L2 first) before the flag is set
+  wait_vmem();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store((PF_AS1 unsigned long long*)&flag[blockIdx.x], seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---------------------------------------------------------------------------
 // mismatch (FP64)
 
@@ -1276,6 +1302,10 @@ void launch_decide(hipStream_t st, const Inst* const* insts, int nslots, DevOpts
 }
 void launch_gather_red(hipStream_t st, const Inst* const* insts, int nslots, Red* out) {
   k_gather_red<<<dim3((unsigned)((nslots + 63) / 64)), 64, 0, st>>>(insts, nslots, out);
+}
+void launch_read_volt(hipStream_t st, const double* v, int n, double* re, double* im, unsigned long long* flag,
+                      unsigned long long seq) {
+  k_read_volt<<<dim3((unsigned)((n + kVoltBlock - 1) / kVoltBlock)), 256, 0, st>>>((const double2*)v, n, re, im, flag, seq);
 }
 void launch_mismatch(hipStream_t st, const Inst* const* insts, int nslots, int max_n, int max_heavy) {
   const dim3 g = grid2((int64_t)max_n * kMisLanes, nslots);

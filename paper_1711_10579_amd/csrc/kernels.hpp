@@ -18,6 +18,11 @@ void launch_init(hipStream_t, const Inst* const* insts, int nslots, int max_n, i
 void launch_start(hipStream_t, const Inst* const* insts, int nslots);
 void launch_decide(hipStream_t, const Inst* const* insts, int nslots, DevOpts o);
 void launch_gather_red(hipStream_t, const Inst* const* insts, int nslots, Red* out);
+// voltages of n >= 1 nodes to pinned host memory, by blocks of kVoltBlock
+// nodes that each set their flag to seq once stored
+constexpr int kVoltBlock = 1024;
+void launch_read_volt(hipStream_t, const double* v, int n, double* re, double* im, unsigned long long* flag,
+                      unsigned long long seq);
 // rows of more than kHeavyRow Ybus entries run one work-group each (max_heavy:
 // the most such rows of an instance in the batch)
 constexpr int kHeavyRow = 64;
