@@ -164,17 +164,56 @@ __device__ inline bool blk_inv(const Blk<T>& m, Blk<T>* out) {
   return true;
 }
 
-// sum over the G lanes of a group (G a power of two, groups aligned to G)
-template <typename T, int G>
-__device__ inline Blk<T> group_sum(Blk<T> v) {
-#pragma unroll
-  for (int off = G / 2; off > 0; off >>= 1) {
-    v.a += __shfl_xor(v.a, off, 64);
-    v.b += __shfl_xor(v.b, off, 64);
-    v.c += __shfl_xor(v.c, off, 64);
-    v.d += __shfl_xor(v.d, off, 64);
-  }
+// v of this lane plus that of lane ^ OFF, once all lanes of a group of OFF
+// hold the same value (a butterfly taken from the smallest offset up): within
+// rows of 16 lanes a mirror reaches the other group's lanes as well as an xor
+// does, so these are data-parallel moves (a few cycles) and lane swaps, not
+// LDS permutes (some 130 cycles a step)
+template <int OFF>
+__device__ inline int lane_other(int x) {
+  if constexpr (OFF == 1) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, true);   // quad (1,0,3,2)
+  if constexpr (OFF == 2) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xf, 0xf, true);   // quad (2,3,0,1)
+  if constexpr (OFF == 4) return __builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true);  // half row mirrored
+  return __builtin_amdgcn_mov_dpp(x, 0x140, 0xf, 0xf, true);                          // row mirrored
+}
+template <int OFF>
+__device__ inline float lane_add(float v) {
+  if constexpr (OFF <= 8) return v + __builtin_bit_cast(float, lane_other<OFF>(__builtin_bit_cast(int, v)));
+  const int u = __builtin_bit_cast(int, v);
+  const auto r = OFF == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                           : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
+}
+template <int OFF>
+__device__ inline double lane_add(double v) {
+  const int2 u = __builtin_bit_cast(int2, v);
+  if constexpr (OFF <= 8) return v + __builtin_bit_cast(double, make_int2(lane_other<OFF>(u.x), lane_other<OFF>(u.y)));
+  const auto lo = OFF == 16 ? __builtin_amdgcn_permlane16_swap(u.x, u.x, false, false)
+                            : __builtin_amdgcn_permlane32_swap(u.x, u.x, false, false);
+  const auto hi = OFF == 16 ? __builtin_amdgcn_permlane16_swap(u.y, u.y, false, false)
+                            : __builtin_amdgcn_permlane32_swap(u.y, u.y, false, false);
+  return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) + __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
+}
+template <int OFF, typename T>
+__device__ inline Blk<T> lane_add(const Blk<T>& v) {
+  return {lane_add<OFF>(v.a), lane_add<OFF>(v.b), lane_add<OFF>(v.c), lane_add<OFF>(v.d)};
+}
+
+// sum over the G lanes of a group (G a power of two, groups aligned to G), in
+// every lane of it
+template <typename T>
+__device__ inline Blk<T> group_sum_rt(Blk<T> v, int G) {
+  if (G > 1) v = lane_add<1>(v);
+  if (G > 2) v = lane_add<2>(v);
+  if (G > 4) v = lane_add<4>(v);
+  if (G > 8) v = lane_add<8>(v);
+  if (G > 16) v = lane_add<16>(v);
+  if (G > 32) v = lane_add<32>(v);
   return v;
+}
+template <typename T, int G>
+__device__ inline Blk<T> group_sum(const Blk<T>& v) {
+  return group_sum_rt(v, G);
 }
 
 // Marker of a solution entry not yet computed: a signalling NaN with a fixed

@@ -817,14 +817,6 @@ __device__ inline Blk<T> fwd_partial(const IR& I, const T* lu_, const T* x_, int
   return acc;
 }
 
-template <typename T, int G, typename IR>
-__device__ inline Blk<T> gather_target(const IR& I, const T* lu, int64_t dest, int64_t tg, int lane) {
-  Blk<T> acc = {T(0), T(0), T(0), T(0)};
-  if (lane == 0) acc = ld_blk<T>(gp(lu), dest);
-  sub_updates<T, G>(acc, lu, I.upd_l, I.upd_u, gp(I.uptr)[tg] + lane, gp(I.uptr)[tg + 1]);
-  return group_sum<T, G>(acc);
-}
-
 // One column j (len blocks from c0) by LANES threads in groups of G: targets
 // t = 0 the diagonal block D, 1 .. len the row of U, len + 1 the forward row
 // of the column's node, len + 2 .. 2 len + 1 the column of L.  The sums of
@@ -843,9 +835,49 @@ __device__ __forceinline__ void factor_column(const IR& I, bool on, int j, int c
   auto dest = [&](int t) -> int64_t {
     return t == 0 ? (int64_t)j : t <= len ? (int64_t)I.ns + I.nnzl + c0 + (t - 1) : (int64_t)I.ns + c0 + (t - len - 2);
   };
+  // the forward row goes through the update lists' code, with y_k's two values
+  // for the first column of a U block (its second column of the sum is not
+  // used): a wave that holds both would otherwise wait for one after the other
   auto sum = [&](int t) -> Blk<T> {
-    if (t == len + 1) return group_sum<T, G>(fwd_partial<T, G>(I, lu, (const T*)I.x, j, lane));
-    return gather_target<T, G>(I, lu, dest(t), t <= len ? tb + t : tb + t - 1, lane);
+    const bool fwd = t == len + 1;
+    const int64_t tg = t <= len ? tb + t : tb + t - 1;
+    const int64_t u0 = gp(I.uptr)[tg], u1 = gp(I.uptr)[tg + 1];
+    const int r0 = gp(I.lrow_ptr)[j], r1 = gp(I.lrow_ptr)[j + 1];
+    const auto gl = gp((const T*)lu), gx = gp((const T*)I.x);
+    Blk<T> acc = {T(0), T(0), T(0), T(0)};
+    if (lane == 0) {
+      const auto p = fwd ? gx + 2 * j : gl + 4 * dest(t);
+      const auto p2 = fwd ? p : p + 2;
+      acc = {p[0], p[1], p2[0], p2[1]};
+      if (fwd) acc.c = acc.b;
+    }
+    const auto il = gp(fwd ? I.lrow_blk : I.upd_l), iu = gp(fwd ? I.lrow_col : I.upd_u);
+    const auto ub = fwd ? gx : gl;
+    const int us = fwd ? 2 : 4, u2 = fwd ? 0 : 2;
+    const int64_t q1 = fwd ? r1 : u1;
+    for (int64_t q = (fwd ? r0 : u0) + lane; q < q1; q += 4 * G) {
+      int a[4], b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t k = q + u * G < q1 ? q + u * G : q;
+        a[u] = il[k];
+        b[u] = iu[k];
+      }
+      Blk<T> L[4], U[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        L[u] = ld_blk<T>(gl, a[u]);
+        const auto p = ub + (int64_t)us * b[u];
+        U[u] = {p[0], p[1], p[u2], p[u2 + 1]};
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (q + u * G < q1) {
+          if (fwd) U[u].c = U[u].b;
+          blk_msub(acc, L[u], U[u]);
+        }
+    }
+    return group_sum<T, G>(acc);
   };
   auto store = [&](int t, const Blk<T>& v, const Blk<T>& di) {
     if (t == len + 1) {
@@ -968,7 +1000,11 @@ __global__ __launch_bounds__(1024) void k_factor_cols_wide(const Inst* const* in
 // since every load after a launch's start comes from the last-level cache.
 // Here the lists come into LDS once, in one round, and the blocks from this
 // CU's caches.  Waves take the level's columns by class, several small
-// columns to a wave.
+// columns to a wave.  A level is then 1.5-2.5 us: 0.2 to find the column, a
+// round of LDS and one of memory for its lists (every index read first, every
+// lane loading, the forward row on the same path: in conditional pieces 0.4
+// more), the group's sum, D^{-1} and the store.  30-bus grid: 18.7 -> 14.4 us a
+// launch with these; 907-bus feeder: 47 -> 37 us.
 
 // Block `id` at a 32-bit offset from a uniform base: such a level is as much
 // bound by one wave's instructions as by its loads, and 64-bit addresses cost
@@ -981,59 +1017,6 @@ template <typename T>
 __device__ __forceinline__ Blk<T> ld_blk32(PF_AS1 T* lu, unsigned id) {
   const PF_AS1 T* q = blk_at(lu, id);
   return {q[0], q[1], q[2], q[3]};
-}
-
-// acc -= the updates of a list of (L, U) pairs in LDS, as sub_updates
-template <typename T>
-__device__ __forceinline__ void tree_updates(Blk<T>& acc, PF_AS1 T* lu, const int* p, int e, int G) {
-  // p: this lane's first pair; e: words of the list from there
-  for (int q = 0; q < e; q += 8 * G) {
-    Blk<T> L[4], U[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (q + 2 * u * G < e) {
-        L[u] = ld_blk32(lu, (unsigned)p[q + 2 * u * G]);
-        U[u] = ld_blk32(lu, (unsigned)p[q + 2 * u * G + 1]);
-      }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (q + 2 * u * G < e) blk_msub(acc, L[u], U[u]);
-  }
-}
-// the forward row's partial sum over a list of (L block, column) pairs, as
-// fwd_partial
-template <typename T>
-__device__ __forceinline__ void tree_forward(Blk<T>& acc, PF_AS1 T* lu, PF_AS1 T* x, const int* p, int e, int G) {
-  for (int q = 0; q < e; q += 8 * G) {
-    Blk<T> L[4];
-    T x0[4], x1[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (q + 2 * u * G < e) {
-        L[u] = ld_blk32(lu, (unsigned)p[q + 2 * u * G]);
-        const unsigned k = (unsigned)p[q + 2 * u * G + 1];
-        const PF_AS1 T* xk = (const PF_AS1 T*)((const PF_AS1 char*)x + k * (unsigned)(2 * sizeof(T)));
-        x0[u] = xk[0];
-        x1[u] = xk[1];
-      }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (q + 2 * u * G < e) {
-        acc.a = sub2(acc.a, L[u].a, x0[u], L[u].b, x1[u]);
-        acc.c = sub2(acc.c, L[u].c, x0[u], L[u].d, x1[u]);
-      }
-  }
-}
-// group_sum for a group size known only when the kernel runs (the same tree)
-template <typename T>
-__device__ inline Blk<T> group_sum_rt(Blk<T> v, int G) {
-  for (int off = G / 2; off > 0; off >>= 1) {
-    v.a += __shfl_xor(v.a, off, 64);
-    v.b += __shfl_xor(v.b, off, 64);
-    v.c += __shfl_xor(v.c, off, 64);
-    v.d += __shfl_xor(v.d, off, 64);
-  }
-  return v;
 }
 
 // A column (its entry at `col` of the program) by `lanes` threads, as
@@ -1050,18 +1033,38 @@ __device__ __forceinline__ void tree_column(const IR& I, const int* prog, int co
   const unsigned u0 = (unsigned)(I.ns + I.nnzl) + (unsigned)c0 - 1, l0 = (unsigned)I.ns + (unsigned)c0 - (unsigned)len - 2;
   auto dest = [&](int t) -> unsigned { return t == 0 ? (unsigned)j : (unsigned)t + (t <= len ? u0 : l0); };
   auto sum = [&](int t) -> Blk<T> {
+    const bool fwd = t == len + 1;
+    const int q1 = tab[t + 1];
+    // bytes of a U block or of a row's two values, and of the way to its second half
+    const PF_AS1 char* ub = fwd ? (const PF_AS1 char*)x : (const PF_AS1 char*)lu;
+    const unsigned us = (fwd ? 2 : 4) * sizeof(T), u2 = fwd ? 0 : 2;
     Blk<T> acc = {T(0), T(0), T(0), T(0)};
-    const int* p = prog + tab[t] + 2 * lane;
-    const int e = tab[t + 1] - tab[t] - 2 * lane;
-    if (t == len + 1) {
-      if (lane == 0) {
-        acc.a = x[2 * j];
-        acc.c = x[2 * j + 1];
+    if (lane == 0) {
+      const PF_AS1 T* p = (const PF_AS1 T*)(ub + (fwd ? (unsigned)j : dest(t)) * us);
+      acc = {p[0], p[1], p[u2], p[u2 + 1]};
+      if (fwd) acc.c = acc.b;
+    }
+    for (int q = tab[t] + 2 * lane; q < q1; q += 8 * G) {
+      int a[4], b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = q + 2 * u * G < q1 ? q + 2 * u * G : q;
+        a[u] = prog[k];
+        b[u] = prog[k + 1];
       }
-      tree_forward<T>(acc, lu, x, p, e, G);
-    } else {
-      if (lane == 0) acc = ld_blk32(lu, dest(t));
-      tree_updates<T>(acc, lu, p, e, G);
+      Blk<T> L[4], U[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        L[u] = ld_blk32(lu, (unsigned)a[u]);
+        const PF_AS1 T* p = (const PF_AS1 T*)(ub + (unsigned)b[u] * us);
+        U[u] = {p[0], p[1], p[u2], p[u2 + 1]};
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (q + 2 * u * G < q1) {
+          if (fwd) U[u].c = U[u].b;
+          blk_msub(acc, L[u], U[u]);
+        }
     }
     return group_sum_rt(acc, G);
   };
