@@ -102,10 +102,29 @@ struct TreePlan {
   std::vector<Stage> stages;
   std::vector<int> bin_off;  // [bins + 1] first word of a bin's program (a multiple of 4)
   std::vector<int> prog;
+  std::vector<int> bin_ptr, bin_cols;  // [bins + 1] the bins' columns
 };
 // max_bins work-groups of 256 threads, or half as many of 512; first_level
 // -1: where the estimated time is least (possibly no level in trees).
 TreePlan plan_trees(const Analysis& an, const std::vector<int>& lanes, int max_bins, int first_level = -1);
+
+// The backward solve of the same subtrees, for a case solved alone: a
+// work-group walks its bin's rows by backward level, the rows' values, the
+// entries of the solution it reads from elsewhere and its own in LDS; the
+// upper stage's bins first (the lower ones read their entries).  A bin's
+// program, in words from its start: records, rows, list entries, entries
+// read from elsewhere; four words per level with rows {first row, rows, log2
+// of the lanes per row, 0}; four per row {row, first list entry, entries, 0};
+// per list entry the place of its column's values (own rows first, then the
+// ones from elsewhere); per list entry its U block; the columns read from
+// elsewhere.
+constexpr int kBwdBytes = 72 * 1024;  // LDS of a bin (two work-groups to a CU)
+constexpr int kBwdRowBytes = 48;      // of a row's inverse and solution, FP64 (a block: 32, an entry read: 16)
+struct BwdTrees {
+  std::vector<int> off, prog;  // [bins + 1]; empty: no bins, every row by levels
+  std::vector<char> in;        // [ns] the row is in a bin
+};
+BwdTrees plan_bwd_trees(const Analysis& an, const TreePlan& tp, const std::vector<int>& lanes);
 
 struct GraphInput {
   int n_nodes = 0;

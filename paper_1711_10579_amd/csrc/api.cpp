@@ -497,6 +497,9 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   const pfh::TreePlan tp = pfh::plan_trees(an, c->fac_g, kTreeBins, small ? -1 : c->nlev);
   c->tree_level = tp.first_level;
   c->tree_stages = tp.stages;
+  pfh::BwdTrees bt = pfh::plan_bwd_trees(an, tp, c->bwd_g);
+  c->bwd_bins = bt.off.empty() ? 0 : (int)bt.off.size() - 1;
+  c->bwd_in = std::move(bt.in);
   std::vector<int4> colinfo(ns);
   for (int k = 0; k < ns; ++k) {
     const int j = an.col_order[k];
@@ -518,7 +521,8 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   total += carve_size<double>(2LL * nu);
   total += carve_size<int>(ns + 1) + carve_size<int>(an.nnzl) + carve_size<int64_t>(c->ntg + 1) +
            2 * carve_size<int>(nupd) + carve_size<int4>(ns) + carve_size<int>((int64_t)tp.bin_off.size()) +
-           carve_size<int>((int64_t)tp.prog.size());
+           carve_size<int>((int64_t)tp.prog.size()) + carve_size<int>((int64_t)bt.off.size()) +
+           carve_size<int>((int64_t)bt.prog.size());
   total += carve_size<int>(c->ntt) + carve_size<int64_t>(c->ntt + 1) + 2 * carve_size<int>(ntail);
   total += carve_size<int>(nu + 1) + 2 * carve_size<int>(an.nnzl);
   total += carve_size<double>(n) + carve_size<int>(2LL * n) + carve_size<double>(6LL * n);
@@ -564,6 +568,8 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   c->colinfo = carve<int4>(p, ns);
   c->tree_off = carve<int>(p, (int64_t)tp.bin_off.size());
   c->tree_prog = carve<int>(p, (int64_t)tp.prog.size());
+  c->bwd_off = carve<int>(p, (int64_t)bt.off.size());
+  c->bwd_prog = carve<int>(p, (int64_t)bt.prog.size());
   c->tail_tgt = carve<int>(p, c->ntt);
   c->tail_uptr = carve<int64_t>(p, c->ntt + 1);
   c->tail_l = carve<int>(p, ntail);
@@ -628,6 +634,8 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   ok &= up(c->colinfo, colinfo.data(), sizeof(int4) * ns);
   ok &= up(c->tree_off, tp.bin_off.data(), sizeof(int) * tp.bin_off.size());
   ok &= up(c->tree_prog, tp.prog.data(), sizeof(int) * tp.prog.size());
+  ok &= up(c->bwd_off, bt.off.data(), sizeof(int) * bt.off.size());
+  ok &= up(c->bwd_prog, bt.prog.data(), sizeof(int) * bt.prog.size());
   ok &= up(c->tail_tgt, an.tail_tgt.data(), sizeof(int) * c->ntt);
   ok &= up(c->tail_uptr, an.tail_uptr.data(), sizeof(int64_t) * (c->ntt + 1));
   ok &= up(c->tail_l, an.tail_l.data(), sizeof(int) * ntail);

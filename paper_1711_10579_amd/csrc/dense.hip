@@ -829,16 +829,16 @@ __device__ __forceinline__ void bwd_rows(const Inst* const* insts, const int2* _
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         if (use[u]) {
-          acc.a -= U[u].a * xv[2 * u] + U[u].b * xv[2 * u + 1];
-          acc.c -= U[u].c * xv[2 * u] + U[u].d * xv[2 * u + 1];
+          acc.a = sub2(acc.a, U[u].a, xv[2 * u], U[u].b, xv[2 * u + 1]);
+          acc.c = sub2(acc.c, U[u].c, xv[2 * u], U[u].d, xv[2 * u + 1]);
         }
     }
   }
   acc = group_sum<T, G>(acc);
   if (__builtin_amdgcn_ballot_w64(!ok) != 0) return;
   if (lane == 0) {
-    const T x0 = D.a * acc.a + D.b * acc.c;
-    const T x1 = D.c * acc.a + D.d * acc.c;
+    const T x0 = fma(D.a, acc.a, D.b * acc.c);
+    const T x1 = fma(D.c, acc.a, D.d * acc.c);
     x[2 * i] = x0;
     x[2 * i + 1] = x1;
     st_dev(xs + 2 * i, x0);
@@ -846,17 +846,157 @@ __device__ __forceinline__ void bwd_rows(const Inst* const* insts, const int2* _
   }
 }
 
-// Work-groups [0, nd): dense blocks (item (slot, w): block nblk - 1 - w, or
-// in single mode (slot, 0): every block of the instance in order); then one
-// work-group per descriptor work[b] = (offset of its first row item,
-// rows | G << 16): rows of one backward level and one lane-group size.
+// One bin of the upper levels' rows of a case solved alone (BwdTrees): its
+// rows by backward level with a barrier after each, sums as in bwd_rows (lane
+// l of a row's group takes entries l, l + G, ...).  By levels, a row waits for
+// its predecessor's value to go through memory, 1.85 us a level; here the
+// rows' blocks, inverses and right-hand sides come into LDS in one round, the
+// entries of rows elsewhere (the dense block, the stage above) are waited for
+// once, and a level is a few LDS round trips and a barrier, 0.6-1 us: the launch
+// takes 41 us for 61 on a 907-bus feeder (33 levels), 65 for 77 on 10,000 buses
+// (12 levels after 26 dense blocks), 10 for 12 on 30 buses (9 levels).
 template <typename T>
+__device__ __forceinline__ void bwd_bin(const PF_AS1 Inst& I, const int* words, int n, char* lds, int* abort_flag,
+                                        unsigned long long t0) {
+  typedef T v2 __attribute__((ext_vector_type(2)));
+  typedef T vb __attribute__((ext_vector_type(4), aligned(16)));
+  const int tid = threadIdx.x;
+  int* prog = (int*)lds;
+  {
+    // whole quads: a program starts and ends on one
+    const auto src = (const PF_AS1 i4v*)words;
+    for (int k = tid; k < n / 4; k += 256) ((i4v*)prog)[k] = src[k];
+  }
+  if (tid == 0) *abort_flag = 0;
+  const bool off = red_of(I)->active == 0;
+  const auto lu = gp((const T*)I.lu), dinv = gp((const T*)I.dinv);
+  const auto x = gp((T*)I.x);
+  T* xs = (T*)I.xs;
+  __syncthreads();
+  if (off) return;
+  const int nrec = __builtin_amdgcn_readfirstlane(prog[0]), nr = __builtin_amdgcn_readfirstlane(prog[1]);
+  const int nent = __builtin_amdgcn_readfirstlane(prog[2]), nout = __builtin_amdgcn_readfirstlane(prog[3]);
+  const i4v* recs = (const i4v*)prog + 1;
+  const i4v* rows = recs + nrec;
+  const int* ref = (const int*)(rows + nr);
+  const int* ids = ref + nent;
+  const int* outs = ids + nent;
+  // solution values by place (a row's right-hand side until it is solved),
+  // the rows' inverted diagonal blocks, as many U blocks as fit
+  vb* dl = (vb*)(prog + n);
+  v2* xl = (v2*)(dl + nr);
+  vb* ul = (vb*)(xl + ((nr + nout + 1) & ~1));
+  const int room = min(nent, (int)((lds + kBwdLds - (char*)ul) / (int)sizeof(vb)));
+  for (int k = tid; k < nr; k += 256) {
+    const int i = rows[k].x;
+    xl[k] = v2{x[2 * i], x[2 * i + 1]};
+    dl[k] = *(const PF_AS1 vb*)(dinv + 4 * (int64_t)i);
+  }
+  for (int f0 = tid; f0 < room; f0 += 4 * 256) {
+    vb u[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) u[k] = *(const PF_AS1 vb*)(lu + 4 * (int64_t)ids[min(f0 + 256 * k, room - 1)]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (f0 + 256 * k < room) ul[f0 + 256 * k] = u[k];
+  }
+  bool ok = true;
+  for (int k = tid; k < nout && ok; k += 256) {
+    const T* p = xs + 2 * (int64_t)outs[k];
+    T a = ld_dev(p), b = ld_dev(p + 1);
+    while (unsolved(a) || unsolved(b)) {
+      if (ld_dev(&I.red->timeout) != 0) {
+        ok = false;
+        break;
+      }
+      if (rt_now() - t0 > kWaitTicks) {
+        st_dev(&I.red->timeout, 1);
+        ok = false;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+      if (unsolved(a)) a = ld_dev(p);
+      if (unsolved(b)) b = ld_dev(p + 1);
+    }
+    xl[nr + k] = v2{a, b};
+  }
+  if (!ok) *abort_flag = 1;
+  __syncthreads();
+  if (*abort_flag != 0) return;  // uniform: read after the barrier
+#pragma unroll 1
+  for (int r = 0; r < nrec; ++r) {
+    const i4v rec = recs[r];
+    const int lg = __builtin_amdgcn_readfirstlane(rec.z), G = 1 << lg, lane = tid & (G - 1);
+    const int first = __builtin_amdgcn_readfirstlane(rec.x), count = __builtin_amdgcn_readfirstlane(rec.y);
+#pragma unroll 1
+    for (int k = tid >> lg; k < count; k += 256 >> lg) {
+      const int at = first + k;
+      const i4v row = rows[at];
+      Blk<T> acc = {T(0), T(0), T(0), T(0)};
+      vb D = vb(T(0));
+      if (lane == 0) {
+        const v2 y = xl[at];
+        acc.a = y[0];
+        acc.c = y[1];
+        D = dl[at];
+      }
+      const int f1 = row.y + row.z;
+      for (int f = row.y + lane; f < f1; f += 4 * G) {
+        vb U[4];
+        v2 xv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int e = f + u * G < f1 ? f + u * G : f;
+          xv[u] = xl[ref[e]];
+          U[u] = ul[min(e, room - 1)];
+          if (e >= room) U[u] = *(const PF_AS1 vb*)(lu + 4 * (int64_t)ids[e]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (f + u * G < f1) {
+            acc.a = sub2(acc.a, U[u][0], xv[u][0], U[u][1], xv[u][1]);
+            acc.c = sub2(acc.c, U[u][2], xv[u][0], U[u][3], xv[u][1]);
+          }
+      }
+      acc = group_sum_rt(acc, G);
+      if (lane == 0) {
+        const T x0 = fma(D[0], acc.a, D[1] * acc.c);
+        const T x1 = fma(D[2], acc.a, D[3] * acc.c);
+        xl[at] = v2{x0, x1};
+        const int i = row.x;
+        x[2 * i] = x0;
+        x[2 * i + 1] = x1;
+        st_dev(xs + 2 * i, x0);
+        st_dev(xs + 2 * i + 1, x1);
+      }
+    }
+    // the next level reads these rows from LDS only: no wait for the stores
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  }
+}
+
+// Work-groups [0, nd): dense blocks (item (slot, w): block nblk - 1 - w, or
+// in single mode (slot, 0): every block of the instance in order); then, TREES,
+// the nbins bins of the only instance; then one work-group per descriptor
+// work[nd + k] = (offset of its first row item, rows | G << 16): rows of one
+// backward level and one lane-group size.
+template <typename T, bool TREES>
 __global__ __launch_bounds__(256, 2) void k_bwd_solve(const Inst* const* insts, const int2* __restrict__ work, int nd,
-                                                   int single) {
-  __shared__ T smem[2 * NB * kBwdLd + 7 * NB];
+                                                   int single, int nbins, const int* __restrict__ bin_off,
+                                                   const int* __restrict__ words) {
+  constexpr int kDense = (2 * NB * kBwdLd + 7 * NB) * sizeof(T);
+  __shared__ __attribute__((aligned(16))) char lds[TREES && kBwdLds > kDense ? kBwdLds : kDense];
+  T* smem = (T*)lds;
   __shared__ int abort_flag;
   const unsigned long long t0 = rt_now();
-  const int2 wk = ld_item(work, blockIdx.x);
+  if (TREES && (int)blockIdx.x >= nd && (int)blockIdx.x < nd + nbins) {
+    const auto o = gp(bin_off) + ((int)blockIdx.x - nd);
+    bwd_bin<T>(inst_at(insts, 0), words + o[0], o[1] - o[0], lds, &abort_flag, t0);
+    return;
+  }
+  const int2 wk = ld_item(work, (int)blockIdx.x - ((int)blockIdx.x < nd ? 0 : nbins));
   if ((int)blockIdx.x < nd) {
     const auto& I = inst_at(insts, wk.x);
     if (red_of(I)->active == 0 || I.M == 0) return;
@@ -904,14 +1044,19 @@ void launch_dense_step(hipStream_t st, const Inst* const* insts, const int2* wor
 }
 
 template <typename T>
-void launch_bwd_solve(hipStream_t st, const Inst* const* insts, const int2* work, int nd, int nrw, int single) {
-  if (nd + nrw <= 0) return;
-  k_bwd_solve<T><<<dim3((unsigned)(nd + nrw)), 256, 0, st>>>(insts, work, nd, single);
+void launch_bwd_solve(hipStream_t st, const Inst* const* insts, const int2* work, int nd, int nrw, int single, int nbins,
+                      const int* bin_off, const int* words) {
+  if (nd + nrw + nbins <= 0) return;
+  const dim3 g((unsigned)(nd + nbins + nrw));
+  if (nbins > 0)
+    k_bwd_solve<T, true><<<g, 256, 0, st>>>(insts, work, nd, single, nbins, bin_off, words);
+  else
+    k_bwd_solve<T, false><<<g, 256, 0, st>>>(insts, work, nd, single, 0, nullptr, nullptr);
 }
 
 #define PF_DINST(T)                                                                        \
   template void launch_dense_step<T>(hipStream_t, const Inst* const*, const int2*, int, int, int, int); \
-  template void launch_bwd_solve<T>(hipStream_t, const Inst* const*, const int2*, int, int, int);
+  template void launch_bwd_solve<T>(hipStream_t, const Inst* const*, const int2*, int, int, int, int, const int*, const int*);
 
 PF_DINST(double)
 PF_DINST(float)

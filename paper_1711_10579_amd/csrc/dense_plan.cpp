@@ -77,7 +77,8 @@ void bwd_plan(const std::vector<BwdInput>& in, bool single, std::vector<int2>* i
       const auto& lp = *in[s].lev_ptr;
       if (l + 1 >= (int)lp.size()) continue;
       auto& v = byG[(*in[s].g)[l]];
-      for (int k = lp[l]; k < lp[l + 1]; ++k) v.push_back(make_int2(s, (*in[s].rows)[k]));
+      for (int k = lp[l]; k < lp[l + 1]; ++k)
+        if (!in[s].skip || !(*in[s].skip)[(*in[s].rows)[k]]) v.push_back(make_int2(s, (*in[s].rows)[k]));
     }
     for (auto& kv : byG) {
       const int G = kv.first, per = 256 / G;

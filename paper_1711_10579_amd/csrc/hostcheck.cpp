@@ -369,6 +369,83 @@ void check_tree_plan(const pfh::Analysis& an, const std::vector<int>& g, int bin
   }
 }
 
+// The backward bins of the plan of check_tree_plan's arguments, with the
+// launch plan of the rows they leave: every row once; a bin's entries name the
+// row's columns, in their order, by places that hold that column: of a row of
+// an earlier record of the bin, or read from elsewhere, from the dense block or
+// a row of an earlier bin; the remaining rows' launch waits only on earlier
+// work-groups or bins.
+void check_bwd_trees(const pfh::Analysis& an, const std::vector<int>& fg, const std::vector<int>& bg, int bins, int first,
+                     int64_t* nchk) {
+  const pfh::TreePlan tp = pfh::plan_trees(an, fg, bins, first);
+  const pfh::BwdTrees bt = pfh::plan_bwd_trees(an, tp, bg);
+  const int ns = an.ns, nb = bt.off.empty() ? 0 : (int)bt.off.size() - 1;
+  std::vector<int> lev(ns), order(an.nu, -1);  // when a row is solved: bins, then the others by level
+  for (int l = 0; l + 1 < (int)an.bwd_lev_ptr.size(); ++l)
+    for (int k = an.bwd_lev_ptr[l]; k < an.bwd_lev_ptr[l + 1]; ++k) lev[an.bwd_rows[k]] = l;
+  req((int)bt.in.size() == ns, "backward bins: flags");
+  for (int b = 0; b < nb; ++b) {
+    const int w0 = bt.off[b], size = bt.off[b + 1] - w0;
+    req(w0 % 4 == 0 && size >= 4 && w0 + size <= (int)bt.prog.size(), "backward bins: program size");
+    const int* P = &bt.prog[w0];
+    const int nrec = P[0], nr = P[1], nent = P[2], nout = P[3];
+    req(nrec >= 0 && nr >= 0 && nent >= 0 && nout >= 0 && 4 + 4LL * nrec + 4LL * nr + 2LL * nent + nout <= size,
+        "backward bins: lists out of range");
+    req(4LL * size + pfh::kBwdRowBytes * (int64_t)nr + 16LL * nout <= pfh::kBwdBytes, "backward bins: LDS");
+    const int* rows = P + 4 + 4 * nrec;
+    const int* ref = rows + 4 * nr;
+    const int* ids = ref + nent;
+    const int* outs = ids + nent;
+    for (int o = 0; o < nout; ++o)
+      req(outs[o] >= 0 && outs[o] < an.nu && (outs[o] >= ns || (order[outs[o]] >= 0 && order[outs[o]] < b)),
+          "backward bins: a bin waits on its own or a later work-group");
+    int next = 0, f = 0;
+    for (int r = 0; r < nrec; ++r) {
+      const int* q = P + 4 + 4 * r;
+      req(q[0] == next && q[1] >= 1 && next + q[1] <= nr && q[2] >= 0 && q[2] <= 6, "backward bins: record");
+      for (int k = next; k < next + q[1]; ++k) {
+        const int i = rows[4 * k], len = rows[4 * k + 2];
+        ++*nchk;
+        req(i >= 0 && i < ns && order[i] < 0 && bt.in[i], "backward bins: row twice or not flagged");
+        req(1 << q[2] == bg[lev[i]], "backward bins: lanes differ from the level's");
+        req(rows[4 * k + 1] == f && len == an.colptr[i + 1] - an.colptr[i] && f + len <= nent, "backward bins: entries");
+        for (int e = 0; e < len; ++e, ++f) {
+          const int c = an.rowidx[an.colptr[i] + e];
+          req(ids[f] == ns + an.nnzl + an.colptr[i] + e, "backward bins: block");
+          req(ref[f] >= 0 && ref[f] < nr + nout, "backward bins: place out of range");
+          req(ref[f] < nr ? ref[f] < next && rows[4 * ref[f]] == c : outs[ref[f] - nr] == c,
+              "backward bins: an entry that is not solved before or another column's");
+        }
+      }
+      next += q[1];
+    }
+    req(next == nr && f == nent, "backward bins: rows outside the records");
+    for (int k = 0; k < nr; ++k) order[rows[4 * k]] = b;
+  }
+  std::vector<BwdInput> in(1);
+  in[0].M = 2 * an.nt;
+  in[0].lev_ptr = &an.bwd_lev_ptr;
+  in[0].rows = &an.bwd_rows;
+  in[0].g = &bg;
+  in[0].skip = &bt.in;
+  std::vector<int2> items;
+  int nd = 0, nrw = 0;
+  bwd_plan(in, false, &items, &nd, &nrw);
+  for (int k = nd; k < nd + nrw; ++k) {
+    const int off = items[k].x, cnt = items[k].y & 0xffff;
+    for (int g = 0; g < cnt; ++g) {
+      const int i = items[off + g].y;
+      req(!bt.in[i] && order[i] < 0, "backward bins: a row in a bin and in the list");
+      for (int q = an.colptr[i]; q < an.colptr[i + 1]; ++q) {
+        const int c = an.rowidx[q];
+        req(c >= ns || (order[c] >= 0 && order[c] < nb + k), "backward bins: a listed row waits on a later work-group");
+      }
+    }
+    for (int g = 0; g < cnt; ++g) order[items[off + g].y] = nb + k;
+  }
+  for (int i = 0; i < ns; ++i) req(order[i] >= 0, "backward bins: row never solved");
+}
+
 }  // namespace
 
 extern "C" pf_status pf_debug_schedule_check(const pf_case_desc* d, const pf_schedule* sched, uint64_t seed,
@@ -622,6 +699,8 @@ extern "C" pf_status pf_debug_schedule_check(const pf_case_desc* d, const pf_sch
       for (const auto* gs : {&g1, &g64, &gmix})
         for (int copies : {1, 3})
           for (bool single : {false, true}) check_bwd_plan(an, M, *gs, copies, single, &nchk);
+      check_bwd_trees(an, pfh::factor_lanes(an, sc.lane_scale), gmix, kTreeBins, -1, &nchk);
+      check_bwd_trees(an, pfh::factor_lanes(an, 4), gmix, 6, 0, &nchk);
     }
     check_tree_plan(an, pfh::factor_lanes(an, sc.lane_scale), kTreeBins, -1, &nchk);
     check_tree_plan(an, pfh::factor_lanes(an, 4), 6, 0, &nchk);

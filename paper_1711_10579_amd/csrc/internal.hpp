@@ -134,6 +134,10 @@ struct Case {
   int tree_level = 0;
   std::vector<pfh::TreePlan::Stage> tree_stages;
   int *tree_off = nullptr, *tree_prog = nullptr;
+  // and of its backward solve
+  int bwd_bins = 0;
+  std::vector<char> bwd_in;
+  int *bwd_off = nullptr, *bwd_prog = nullptr;
   int64_t* uptr = nullptr;
   int *tail_tgt = nullptr, *tail_l = nullptr, *tail_u = nullptr;
   int64_t* tail_uptr = nullptr;
@@ -319,18 +323,21 @@ constexpr int kDenseNB = 64;
 // work-groups the upper levels of a case's sparse refactorisation are dealt
 // to (256 threads, two to a CU; half as many of 512)
 constexpr int kTreeBins = 512;
+static_assert(pfh::kBwdBytes <= pfd::kBwdLds, "a bin's rows fit the kernel's LDS");
 static_assert(pfh::kTreeWords <= pfd::kTreeLds, "a bin's program fits the kernel's LDS");
 void dense_grid(int M, int k, int* kb, int* nrt, int* nct);
 void dense_plan_step(const std::vector<int>& Ms, int k0, std::vector<int2>* items, int* nflag, int* npanel);
 // The backward solve's work list (one launch): nd dense items, then nrw
 // work-group descriptors (offset of the first row item, rows | G << 16),
 // then the row items (slot, row).  Per instance: dense order M, backward
-// level pointers and rows of the sparse part, lanes per row of each level.
+// level pointers and rows of the sparse part, lanes per row of each level.  A
+// case solved alone runs its bins (BwdTrees) between the two.
 struct BwdInput {
   int M = 0;
   const std::vector<int>* lev_ptr = nullptr;
   const std::vector<int>* rows = nullptr;
   const std::vector<int>* g = nullptr;
+  const std::vector<char>* skip = nullptr;  // rows solved by the case's bins
 };
 void bwd_plan(const std::vector<BwdInput>& in, bool single, std::vector<int2>* items, int* nd, int* nrw);
 

@@ -1148,7 +1148,7 @@ __global__ __launch_bounds__(NT) void k_factor_trees(const Inst* const* insts, c
 #pragma unroll 1
   for (int r = 0; r < nrec; ++r) {
     const i4v rec = ((const i4v*)prog)[1 + r];  // first slot, slots, lanes, columns of the whole work-group
-    const int G = rec.z;
+    const int G = __builtin_amdgcn_readfirstlane(rec.z);
 #pragma unroll 1
     for (int s = wave; s < rec.y; s += NT / 64) {
       const int e = prog[rec.x + s];

@@ -62,9 +62,13 @@ void launch_dense_step(hipStream_t, const Inst* const* insts, const int2* work, 
 // backward solve of the whole factorisation in one launch: nd dense items
 // (slot, w) (single: (slot, 0), one work-group per instance), then nrw
 // work-groups of sparse rows, each described by work[nd + k] = (offset of its
-// first row item in work, rows | G << 16), row items (slot, row)
+// first row item in work, rows | G << 16), row items (slot, row); between the
+// two, for the only instance, nbins programs at words[bin_off[b]] of at most
+// kBwdLds bytes with their values
+constexpr int kBwdLds = 72 * 1024;
 template <typename T>
-void launch_bwd_solve(hipStream_t, const Inst* const* insts, const int2* work, int nd, int nrw, int single);
+void launch_bwd_solve(hipStream_t, const Inst* const* insts, const int2* work, int nd, int nrw, int single,
+                      int nbins, const int* bin_off, const int* words);
 
 // Newton-Krylov inner solve (krylov.hip); preconditioner mode 0 = Arnoldi
 // step, 1 = end of a GMRES cycle, 2 and 3 = the halves of a BiCGStab

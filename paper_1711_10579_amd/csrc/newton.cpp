@@ -90,7 +90,7 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
   work.clear();
   seq.clear();
   auto emit = [&](int kind, int cls, int G, int k0, const std::vector<int2>& items, double flops, double bytes) {
-    if (items.empty()) return;
+    if (items.empty() && !(kind == L_BWD && nslots == 1 && cs[0]->bwd_bins > 0)) return;
     Launch l;
     l.kind = kind;
     l.cls = cls;
@@ -278,6 +278,7 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
       in[s].lev_ptr = &c->an.bwd_lev_ptr;
       in[s].rows = &c->an.bwd_rows;
       in[s].g = &c->bwd_g;
+      if (nslots == 1) in[s].skip = &c->bwd_in;
       tfl += (double)c->M * c->M;
       tby += 8.0 * ((double)c->M * c->M / 2 + 2.0 * c->M);
     }
@@ -332,7 +333,8 @@ void lu_solve(Batch* b) {
         break;
       case L_BWD:
         // G: dense items, k0: sparse row work-groups
-        pfd::launch_bwd_solve<T>(s, I, w, l.G, l.k0, b->trsv_single);
+        pfd::launch_bwd_solve<T>(s, I, w, l.G, l.k0, b->trsv_single, b->nslots == 1 ? b->cases[0]->bwd_bins : 0,
+                                 b->cases[0]->bwd_off, b->cases[0]->bwd_prog);
         break;
     }
   };

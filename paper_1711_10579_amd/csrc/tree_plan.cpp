@@ -61,6 +61,7 @@ TreePlan plan_trees(const Analysis& an, const std::vector<int>& g, int max_bins,
   const int ns = an.ns, nl = (int)an.col_lev_ptr.size() - 1;
   tp.first_level = nl;
   tp.bin_off.push_back(0);
+  tp.bin_ptr.push_back(0);
   if (ns == 0) return tp;
   std::vector<int> lev(ns), cls(ns), words(ns), root(ns), comp;
   std::vector<float> cost(ns), work(ns), slots, big;
@@ -274,9 +275,84 @@ TreePlan plan_trees(const Analysis& an, const std::vector<int>& g, int max_bins,
       }
       P.resize((P.size() + 3) / 4 * 4, 0);
       tp.bin_off.push_back((int)P.size());
+      tp.bin_cols.insert(tp.bin_cols.end(), cols.begin() + c0, cols.begin() + c1);
+      tp.bin_ptr.push_back((int)tp.bin_cols.size());
     }
   }
   return tp;
+}
+
+BwdTrees plan_bwd_trees(const Analysis& an, const TreePlan& tp, const std::vector<int>& lanes) {
+  BwdTrees bt;
+  const int ns = an.ns;
+  bt.in.assign(ns, 0);
+  if (tp.stages.empty()) return bt;
+  std::vector<int> lev(ns), place(an.nu, -1), owner(an.nu, -1);
+  for (int l = 0; l + 1 < (int)an.bwd_lev_ptr.size(); ++l)
+    for (int k = an.bwd_lev_ptr[l]; k < an.bwd_lev_ptr[l + 1]; ++k) lev[an.bwd_rows[k]] = l;
+  std::vector<int>& P = bt.prog;
+  bt.off.push_back(0);
+  int serial = 0;
+  for (int s = (int)tp.stages.size() - 1; s >= 0; --s)
+    for (int b = tp.stages[s].bin0; b < tp.stages[s].bin0 + tp.stages[s].nbins; ++b) {
+      std::vector<int> rows(tp.bin_cols.begin() + tp.bin_ptr[b], tp.bin_cols.begin() + tp.bin_ptr[b + 1]);
+      std::stable_sort(rows.begin(), rows.end(), [&](int x, int y) { return lev[x] < lev[y]; });
+      const int nr = (int)rows.size();
+      int nrec = 0, nent = 0;
+      for (int k = 0; k < nr; ++k) {
+        nrec += k == 0 || lev[rows[k]] != lev[rows[k - 1]];
+        nent += an.colptr[rows[k] + 1] - an.colptr[rows[k]];
+        bt.in[rows[k]] = 1;
+        owner[rows[k]] = serial;
+        place[rows[k]] = k;
+      }
+      const size_t base = P.size();
+      const int row0 = 4 + 4 * nrec, ref0 = row0 + 4 * nr;
+      P.resize(base + ref0 + 2 * (size_t)nent, 0);
+      std::vector<int> out;
+      int rec = 0, f = 0;
+      for (int k = 0; k < nr; ++k) {
+        const int i = rows[k], q0 = an.colptr[i], q1 = an.colptr[i + 1];
+        if (k == 0 || lev[i] != lev[rows[k - 1]]) {
+          int lg = 0;
+          while (1 << lg < lanes[lev[i]]) ++lg;
+          int* p = &P[base + 4 + 4 * rec++];
+          p[0] = k;
+          p[2] = lg;
+        }
+        P[base + 4 + 4 * (rec - 1) + 1]++;
+        int* p = &P[base + row0 + 4 * (size_t)k];
+        p[0] = i;
+        p[1] = f;
+        p[2] = q1 - q0;
+        for (int q = q0; q < q1; ++q, ++f) {
+          const int c = an.rowidx[q];
+          if (owner[c] != serial) {  // read from elsewhere
+            owner[c] = serial;
+            place[c] = nr + (int)out.size();
+            out.push_back(c);
+          }
+          P[base + ref0 + f] = place[c];
+          P[base + ref0 + nent + f] = (int)(ns + an.nnzl + q);
+        }
+      }
+      P[base] = nrec;
+      P[base + 1] = nr;
+      P[base + 2] = nent;
+      P[base + 3] = (int)out.size();
+      P.insert(P.end(), out.begin(), out.end());
+      P.resize((P.size() + 3) / 4 * 4, 0);
+      bt.off.push_back((int)P.size());
+      ++serial;
+      if (4 * (int64_t)(P.size() - base) + kBwdRowBytes * (int64_t)nr + 16 * (int64_t)out.size() > kBwdBytes) {
+        // a bin of very many rows: every row by levels
+        bt.off.clear();
+        bt.prog.clear();
+        bt.in.assign(ns, 0);
+        return bt;
+      }
+    }
+  return bt;
 }
 
 }  // namespace pfh
