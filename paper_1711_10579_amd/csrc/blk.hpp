@@ -164,11 +164,12 @@ __device__ inline bool blk_inv(const Blk<T>& m, Blk<T>* out) {
   return true;
 }
 
-// v of this lane plus that of lane ^ OFF, once all lanes of a group of OFF
-// hold the same value (a butterfly taken from the smallest offset up): within
-// rows of 16 lanes a mirror reaches the other group's lanes as well as an xor
-// does, so these are data-parallel moves (a few cycles) and lane swaps, not
-// LDS permutes (some 130 cycles a step)
+// The values a, b of this lane's group of OFF lanes and of the one beside it
+// (lane ^ OFF), in either order, once all lanes of a group hold the same value
+// (a butterfly taken from the smallest offset up): within rows of 16 lanes a
+// mirror reaches the other group's lanes as well as an xor does, so these are
+// data-parallel moves (a few cycles) and lane swaps, not LDS permutes (some
+// 130 cycles a step)
 template <int OFF>
 __device__ inline int lane_other(int x) {
   if constexpr (OFF == 1) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, true);   // quad (1,0,3,2)
@@ -177,38 +178,65 @@ __device__ inline int lane_other(int x) {
   return __builtin_amdgcn_mov_dpp(x, 0x140, 0xf, 0xf, true);                          // row mirrored
 }
 template <int OFF>
-__device__ inline float lane_add(float v) {
-  if constexpr (OFF <= 8) return v + __builtin_bit_cast(float, lane_other<OFF>(__builtin_bit_cast(int, v)));
-  const int u = __builtin_bit_cast(int, v);
-  const auto r = OFF == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
-                           : __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
+__device__ inline void lane_pair(int v, int& a, int& b) {
+  if constexpr (OFF <= 8) {
+    a = v;
+    b = lane_other<OFF>(v);
+  } else {
+    const auto r = OFF == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)
+                             : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+  }
 }
 template <int OFF>
-__device__ inline double lane_add(double v) {
+__device__ inline void lane_pair(float v, float& a, float& b) {
+  int x, y;
+  lane_pair<OFF>(__builtin_bit_cast(int, v), x, y);
+  a = __builtin_bit_cast(float, x);
+  b = __builtin_bit_cast(float, y);
+}
+template <int OFF>
+__device__ inline void lane_pair(double v, double& a, double& b) {
   const int2 u = __builtin_bit_cast(int2, v);
-  if constexpr (OFF <= 8) return v + __builtin_bit_cast(double, make_int2(lane_other<OFF>(u.x), lane_other<OFF>(u.y)));
-  const auto lo = OFF == 16 ? __builtin_amdgcn_permlane16_swap(u.x, u.x, false, false)
-                            : __builtin_amdgcn_permlane32_swap(u.x, u.x, false, false);
-  const auto hi = OFF == 16 ? __builtin_amdgcn_permlane16_swap(u.y, u.y, false, false)
-                            : __builtin_amdgcn_permlane32_swap(u.y, u.y, false, false);
-  return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) + __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
+  int2 x, y;
+  lane_pair<OFF>(u.x, x.x, y.x);
+  lane_pair<OFF>(u.y, x.y, y.y);
+  a = __builtin_bit_cast(double, x);
+  b = __builtin_bit_cast(double, y);
 }
 template <int OFF, typename T>
-__device__ inline Blk<T> lane_add(const Blk<T>& v) {
+__device__ inline T lane_add(T v) {
+  T a, b;
+  lane_pair<OFF>(v, a, b);
+  return a + b;
+}
+// sum over the G lanes of a group (G a power of two, groups aligned to G), in
+// every lane of it
+template <int G, typename T>
+__device__ inline T group_add(T v) {
+  if constexpr (G > 1) v = lane_add<1>(v);
+  if constexpr (G > 2) v = lane_add<2>(v);
+  if constexpr (G > 4) v = lane_add<4>(v);
+  if constexpr (G > 8) v = lane_add<8>(v);
+  if constexpr (G > 16) v = lane_add<16>(v);
+  if constexpr (G > 32) v = lane_add<32>(v);
+  return v;
+}
+template <int OFF, typename T>
+__device__ inline Blk<T> blk_lane_add(const Blk<T>& v) {
   return {lane_add<OFF>(v.a), lane_add<OFF>(v.b), lane_add<OFF>(v.c), lane_add<OFF>(v.d)};
 }
 
-// sum over the G lanes of a group (G a power of two, groups aligned to G), in
-// every lane of it
+// the same of a block, G known only when the kernel runs (uniform)
 template <typename T>
 __device__ inline Blk<T> group_sum_rt(Blk<T> v, int G) {
-  if (G > 1) v = lane_add<1>(v);
-  if (G > 2) v = lane_add<2>(v);
-  if (G > 4) v = lane_add<4>(v);
-  if (G > 8) v = lane_add<8>(v);
-  if (G > 16) v = lane_add<16>(v);
-  if (G > 32) v = lane_add<32>(v);
+  if (G > 1) v = blk_lane_add<1>(v);
+  if (G > 2) v = blk_lane_add<2>(v);
+  if (G > 4) v = blk_lane_add<4>(v);
+  if (G > 8) v = blk_lane_add<8>(v);
+  if (G > 16) v = blk_lane_add<16>(v);
+  if (G > 32) v = blk_lane_add<32>(v);
   return v;
 }
 template <typename T, int G>

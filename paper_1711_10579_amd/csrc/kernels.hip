@@ -31,12 +31,14 @@ __device__ inline void atomic_max_nonneg(unsigned long long* slot, double v) {
   atomicMax(slot, (unsigned long long)__double_as_longlong(v));
 }
 
-__device__ inline double wave_max(double local) {
-  for (int off = 32; off > 0; off >>= 1) {
-    double o = __shfl_xor(local, off, 64);
-    local = (o > local || o != o) ? o : local;
-  }
-  return local;
+template <int OFF>
+__device__ inline double lane_max(double v) {
+  double a, b;
+  lane_pair<OFF>(v, a, b);
+  return (b > a || b != b) ? b : a;
+}
+__device__ inline double wave_max(double v) {
+  return lane_max<32>(lane_max<16>(lane_max<8>(lane_max<4>(lane_max<2>(lane_max<1>(v))))));
 }
 
 template <typename IR>
@@ -397,11 +399,8 @@ __device__ inline void mismatch_heavy_row(const InstRef& I, int h) {
   if (!(I.model == 0 || p >= 0)) return;
   double ir = 0.0, ii = 0.0;
   ydot_part<256>(I, gp(I.row_ptr)[i] + (int)threadIdx.x, gp(I.row_ptr)[i + 1], ir, ii);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    ir += __shfl_xor(ir, off, 64);
-    ii += __shfl_xor(ii, off, 64);
-  }
+  ir = group_add<64>(ir);
+  ii = group_add<64>(ii);
   if ((threadIdx.x & 63) == 0) {
     part[0][threadIdx.x >> 6] = ir;
     part[1][threadIdx.x >> 6] = ii;
@@ -479,11 +478,8 @@ __global__ __launch_bounds__(256) void k_mismatch(const Inst* const* insts, int 
       if (qc + S < q1) ydot_part<S>(I, qc + S, q1, ir, ii);
     }
   }
-#pragma unroll
-  for (int off = S / 2; off > 0; off >>= 1) {
-    ir += __shfl_xor(ir, off, 64);
-    ii += __shfl_xor(ii, off, 64);
-  }
+  ir = group_add<S>(ir);
+  ii = group_add<S>(ii);
   if (!active) return;  // uniform over the work-group
   if (mine && lane == 0) local = mismatch_row(I, i, p, ir, ii, side);
   block_max_store(local, (double*)I.mpart + bx);

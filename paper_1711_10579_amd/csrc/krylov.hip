@@ -77,11 +77,7 @@ __device__ inline void linear_failure(const IR& I) {
   gp(I.ks)->state = KS_DONE;
 }
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
+__device__ inline double wave_sum(double v) { return group_add<64>(v); }
 
 // Sums over the KCH threads of a work-group of the values f(i) for i <
 // count, written to out[i] (thread-uniform count).  Fixed reduction order.
@@ -753,11 +749,8 @@ __global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, co
         a1 += (double)B[u].c * x0[u] + (double)B[u].d * x1[u];
       }
   }
-#pragma unroll
-  for (int off = G / 2; off > 0; off >>= 1) {
-    a0 += __shfl_xor(a0, off, 64);
-    a1 += __shfl_xor(a1, off, 64);
-  }
+  a0 = group_add<G>(a0);
+  a1 = group_add<G>(a1);
   if (!on || lane != 0) return;
   if (Upper) {
     z[2 * r] = (T)a0;
