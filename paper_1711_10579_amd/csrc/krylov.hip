@@ -79,20 +79,20 @@ __device__ inline void linear_failure(const IR& I) {
 
 __device__ inline double wave_sum(double v) { return group_add<64>(v); }
 
-// Sums over the KCH threads of a work-group of the values f(i) for i <
+// Sums over the NT threads of a work-group of the values f(i) for i <
 // count, written to out[i] (thread-uniform count).  Fixed reduction order.
-template <typename F>
-__device__ inline void block_sums(int count, F f, double (*red)[KCH / 64], PF_AS1 double* out) {
+template <int NT = KCH, typename F>
+__device__ inline void block_sums(int count, F f, double (*red)[NT / 64], PF_AS1 double* out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i = 0; i < count; ++i) {
     double s = wave_sum(f(i));
     if (lane == 0) red[i][wave] = s;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < count; i += KCH) {
+  for (int i = threadIdx.x; i < count; i += NT) {
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < KCH / 64; ++w) s += red[i][w];
+    for (int w = 0; w < NT / 64; ++w) s += red[i][w];
     out[i] = s;
   }
 }
@@ -179,6 +179,35 @@ __device__ inline void blk_range_dot(MP M, CP col, int q0, int q1, XP x, double&
 template <bool Sub, typename T, typename IR, typename XP>
 __device__ inline void spmv_row(const IR& I, int r, XP x, double& acc0, double& acc1) {
   blk_range_dot<Sub, T>(gp((const T*)I.jval), gp(I.kcol), gp(I.krow_ptr)[r], gp(I.krow_ptr)[r + 1], x, acc0, acc1);
+}
+
+// The same product of row r by kRowLanes lanes (all of them call; the sum in
+// each): lane l takes blocks l, l + kRowLanes, ... of the row, which lie side
+// by side, two in flight.  With a row to a thread a wave's load touches a line
+// per lane and a chunk of KCH rows keeps one wave per SIMD (9.0 us for the
+// product and its dots in an Arnoldi step on 10,000 buses, 5.5 this way; 8.9
+// and 7.0 us for BiCGStab's two on 48,000, 7.4 and 5.8).
+constexpr int kRowLanes = 4;
+template <typename T, typename IR, typename XP>
+__device__ inline void spmv_row_lanes(const IR& I, int r, int l, XP x, double& acc0, double& acc1) {
+  const auto M = gp((const T*)I.jval);
+  const auto col = gp(I.kcol);
+  const int q0 = gp(I.krow_ptr)[r], q1 = gp(I.krow_ptr)[r + 1];
+  for (int q = q0 + l; q < q1; q += 2 * kRowLanes) {
+    const int q2 = q + kRowLanes < q1 ? q + kRowLanes : q;
+    const int c = col[q], c2 = col[q2];
+    const Blk<T> B = ld_blk(M, q), B2 = ld_blk(M, q2);
+    const double a = (double)x[2 * c], b = (double)x[2 * c + 1];
+    const double a2 = (double)x[2 * c2], b2 = (double)x[2 * c2 + 1];
+    acc0 += (double)B.a * a + (double)B.b * b;
+    acc1 += (double)B.c * a + (double)B.d * b;
+    if (q2 != q) {
+      acc0 += (double)B2.a * a2 + (double)B2.b * b2;
+      acc1 += (double)B2.c * a2 + (double)B2.d * b2;
+    }
+  }
+  acc0 = group_add<kRowLanes>(acc0);
+  acc1 = group_add<kRowLanes>(acc1);
 }
 
 }  // namespace
@@ -1006,32 +1035,51 @@ __global__ __launch_bounds__(64) void k_bj_apply(const Inst* const* insts, const
 
 // w = J z for the rows of one chunk, then the partial dots <w, v_i>, i <= j.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_kspmv_dot(const Inst* const* insts) {
+__global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const* insts) {
   __shared__ double red[KMAX + 1][KCH / 64];
+  __shared__ double ws[2][KCH];
   const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_ITER) || (int)blockIdx.x >= I.kchunks) return;
   const int j = gp(I.ks)->j;
-  const int r = blockIdx.x * KCH + threadIdx.x;
   const int64_t n2 = 2 * (int64_t)I.nu;
-  double w0 = 0.0, w1 = 0.0;
-  if (r < I.nu) {
-    const auto z = gp((const T*)I.kz);
-    spmv_row<false, T>(I, r, z, w0, w1);
-    const auto w = gp((T*)I.kw);
-    w[2 * r] = (T)w0;
-    w[2 * r + 1] = (T)w1;
-    w0 = (double)(T)w0;
-    w1 = (double)(T)w1;
+  {
+    const int k = threadIdx.x / kRowLanes, l = threadIdx.x % kRowLanes, r = blockIdx.x * KCH + k;
+    double w0 = 0.0, w1 = 0.0;
+    if (r < I.nu) {
+      spmv_row_lanes<T>(I, r, l, gp((const T*)I.kz), w0, w1);
+      const auto w = gp((T*)I.kw);
+      if (l == 0) {
+        w[2 * r] = (T)w0;
+        w[2 * r + 1] = (T)w1;
+      }
+    }
+    if (l == 0) {
+      ws[0][k] = (double)(T)w0;
+      ws[1][k] = (double)(T)w1;
+    }
   }
+  __syncthreads();
+  // the dots, dealt out to the kRowLanes quarters of the work-group: a row to
+  // a thread in each
+  const int k = threadIdx.x % KCH, r = blockIdx.x * KCH + k;
+  const double w0 = ws[0][k], w1 = ws[1][k];
   const auto V = gp((const T*)I.kv);
-  block_sums(
-      j + 1,
-      [&](int i) {
-        if (r >= I.nu) return 0.0;
-        const auto vi = V + i * n2;
-        return w0 * (double)vi[2 * r] + w1 * (double)vi[2 * r + 1];
-      },
-      red, kpart(I, 0, blockIdx.x));
+  for (int i = threadIdx.x / KCH; i <= j; i += kRowLanes) {
+    double d = 0.0;
+    if (r < I.nu) {
+      const auto vi = V + i * n2;
+      d = w0 * (double)vi[2 * r] + w1 * (double)vi[2 * r + 1];
+    }
+    d = wave_sum(d);
+    if ((threadIdx.x & 63) == 0) red[i][k >> 6] = d;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i <= j; i += kRowLanes * KCH) {
+    double d = 0.0;
+#pragma unroll
+    for (int w = 0; w < KCH / 64; ++w) d += red[i][w];
+    kpart(I, 0, blockIdx.x)[i] = d;
+  }
 }
 
 // One classical Gram-Schmidt pass: h = sum over chunks of the partial dots
@@ -1468,26 +1516,27 @@ __global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts) {
 
 // p^ = z, v = J p^ for the rows of one chunk, partial <r0, v>.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_bcg_v(const Inst* const* insts) {
-  __shared__ double red[KMAX + 1][KCH / 64];
+__global__ __launch_bounds__(kRowLanes* KCH) void k_bcg_v(const Inst* const* insts) {
+  __shared__ double red[1][kRowLanes * KCH / 64];
   const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+  const int r = blockIdx.x * KCH + (int)threadIdx.x / kRowLanes, l = threadIdx.x % kRowLanes;
   double d = 0.0;
   if (r < I.nu) {
     const auto z = gp((const T*)I.kz);
     const auto Ph = kvec<T>(I, 4);
-    Ph[2 * r] = z[2 * r];
-    Ph[2 * r + 1] = z[2 * r + 1];
+    if (l < 2) Ph[2 * r + l] = z[2 * r + l];
     double v0 = 0.0, v1 = 0.0;
-    spmv_row<false, T>(I, r, z, v0, v1);
-    const auto V = kvec<T>(I, 3);
-    V[2 * r] = (T)v0;
-    V[2 * r + 1] = (T)v1;
-    const auto R0 = kvec<T>(I, 1);
-    d = (double)R0[2 * r] * (double)(T)v0 + (double)R0[2 * r + 1] * (double)(T)v1;
+    spmv_row_lanes<T>(I, r, l, z, v0, v1);
+    if (l == 0) {
+      const auto V = kvec<T>(I, 3);
+      V[2 * r] = (T)v0;
+      V[2 * r + 1] = (T)v1;
+      const auto R0 = kvec<T>(I, 1);
+      d = (double)R0[2 * r] * (double)(T)v0 + (double)R0[2 * r + 1] * (double)(T)v1;
+    }
   }
-  block_sums(
+  block_sums<kRowLanes * KCH>(
       1, [&](int) { return d; }, red, kpart(I, 0, blockIdx.x));
 }
 
@@ -1535,8 +1584,8 @@ __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, int it)
 // <t, t>.  The first work-group counts the iteration and sets the state;
 // the others accept the state it sets as the one they started from.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_bcg_t(const Inst* const* insts, KOpts o) {
-  __shared__ double red[KMAX + 1][KCH / 64];
+__global__ __launch_bounds__(kRowLanes* KCH) void k_bcg_t(const Inst* const* insts, KOpts o) {
+  __shared__ double red[2][kRowLanes * KCH / 64];
   __shared__ int decision;  // 0 second half, 1 first half met, 2 breakdown
   const auto& I = inst_at(insts, blockIdx.y);
   if ((!kstate_is(I, KS_BP) && !kstate_is(I, KS_BS)) || (int)blockIdx.x >= I.kchunks) return;
@@ -1566,25 +1615,26 @@ __global__ __launch_bounds__(KCH) void k_bcg_t(const Inst* const* insts, KOpts o
   }
   __syncthreads();
   if (decision != 0) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+  const int r = blockIdx.x * KCH + (int)threadIdx.x / kRowLanes, l = threadIdx.x % kRowLanes;
   double ts = 0.0, tt = 0.0;
   if (r < I.nu) {
     const auto z = gp((const T*)I.kz);
     const auto Sh = kvec<T>(I, 5);
-    Sh[2 * r] = z[2 * r];
-    Sh[2 * r + 1] = z[2 * r + 1];
+    if (l < 2) Sh[2 * r + l] = z[2 * r + l];
     double t0 = 0.0, t1 = 0.0;
-    spmv_row<false, T>(I, r, z, t0, t1);
-    const auto Tv = kvec<T>(I, 6);
-    Tv[2 * r] = (T)t0;
-    Tv[2 * r + 1] = (T)t1;
-    t0 = (double)(T)t0;
-    t1 = (double)(T)t1;
-    const auto S = kvec<T>(I, 0);
-    ts = t0 * (double)S[2 * r] + t1 * (double)S[2 * r + 1];
-    tt = t0 * t0 + t1 * t1;
+    spmv_row_lanes<T>(I, r, l, z, t0, t1);
+    if (l == 0) {
+      const auto Tv = kvec<T>(I, 6);
+      Tv[2 * r] = (T)t0;
+      Tv[2 * r + 1] = (T)t1;
+      t0 = (double)(T)t0;
+      t1 = (double)(T)t1;
+      const auto S = kvec<T>(I, 0);
+      ts = t0 * (double)S[2 * r] + t1 * (double)S[2 * r + 1];
+      tt = t0 * t0 + t1 * t1;
+    }
   }
-  block_sums(
+  block_sums<kRowLanes * KCH>(
       2, [&](int e) { return e == 0 ? ts : tt; }, red, kpart(I, 2, blockIdx.x));
 }
 
@@ -1811,7 +1861,7 @@ void launch_bj_apply(hipStream_t st, const Inst* const* insts, const int2* work,
 template <typename T>
 void launch_karnoldi(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, KOpts o) {
   const dim3 g = chunk_grid(max_chunks, nslots);
-  k_kspmv_dot<T><<<g, KCH, 0, st>>>(insts);
+  k_kspmv_dot<T><<<g, kRowLanes * KCH, 0, st>>>(insts);
   k_korth<T><<<g, KCH, 0, st>>>(insts, 0);
   k_korth<T><<<g, KCH, 0, st>>>(insts, 1);
   k_karnoldi_end<<<dim3((unsigned)nslots), 64, 0, st>>>(insts, o);
@@ -1850,13 +1900,13 @@ void launch_bcg_dir(hipStream_t st, const Inst* const* insts, int nslots, int ma
 template <typename T>
 void launch_bcg_half(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, int it) {
   const dim3 g = chunk_grid(max_chunks, nslots);
-  k_bcg_v<T><<<g, KCH, 0, st>>>(insts);
+  k_bcg_v<T><<<g, kRowLanes * KCH, 0, st>>>(insts);
   k_bcg_s<T><<<g, KCH, 0, st>>>(insts, it);
 }
 template <typename T>
 void launch_bcg_end(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, KOpts o, int it) {
   const dim3 g = chunk_grid(max_chunks, nslots);
-  k_bcg_t<T><<<g, KCH, 0, st>>>(insts, o);
+  k_bcg_t<T><<<g, kRowLanes * KCH, 0, st>>>(insts, o);
   k_bcg_x<T><<<g, KCH, 0, st>>>(insts);
   k_bcg_next<T><<<g, KCH, 0, st>>>(insts, o, it);
 }
