@@ -7,8 +7,12 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
+#include <future>
+#include <memory>
 #include <string>
+#include <system_error>
 #include <vector>
 
 #include "internal.hpp"
@@ -474,11 +478,37 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
     }
   }
 
+  // the subtrees' plans beside the rest of the analysis, which needs nothing of
+  // them (small cases: a thread costs more)
+  struct Plans {
+    pfh::TreePlan tp;
+    pfh::BwdTrees bt;
+  };
+  // (the trees' kernel addresses blocks by 32-bit byte offsets)
+  const bool small = c->lu_count() * (int64_t)sizeof(double) <= UINT32_MAX;
+  auto make_plans = [c, small] {
+    Plans p;
+    p.tp = pfh::plan_trees(c->an, c->fac_g, kTreeBins, small ? -1 : c->nlev);
+    p.bt = pfh::plan_bwd_trees(c->an, p.tp, c->bwd_g);
+    return p;
+  };
+  std::future<Plans> later;
+  if (an.ns >= 512) {
+    try {
+      later = std::async(std::launch::async, make_plans);
+    } catch (const std::system_error&) {  // no thread: in line, below
+    }
+  }
+  auto plans_done = [&] {
+    if (later.valid()) later.wait();
+  };
+
   // Ybus entry -> LU destination
   std::vector<int> yrow, jmap;
   try {
     pfh::build_jmap(c->an, n, d->row_ptr, d->col_idx, &yrow, &jmap);
   } catch (const std::exception& ex) {
+    plans_done();
     delete c;
     set_error(std::string("pf_create: ") + ex.what());
     return PF_E_INVALID;
@@ -487,17 +517,24 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
     c->ka.reset(new pfh::KAnalysis(pfh::analyze_krylov(an, n, d->row_ptr, d->col_idx, 32)));
     pfh::build_kmap(an, *c->ka, n, d->row_ptr, d->col_idx, &c->kmap_host);
   } catch (const std::exception& ex) {
+    plans_done();
     delete c;
     set_error(std::string("pf_create: Krylov analysis failed: ") + ex.what());
     return PF_E_INVALID;
   }
   const int ns = an.ns;
-  // (the trees' kernel addresses blocks by 32-bit byte offsets)
-  const bool small = c->lu_count() * (int64_t)sizeof(double) <= UINT32_MAX;
-  const pfh::TreePlan tp = pfh::plan_trees(an, c->fac_g, kTreeBins, small ? -1 : c->nlev);
+  Plans plans;
+  try {
+    plans = later.valid() ? later.get() : make_plans();
+  } catch (const std::exception& ex) {
+    delete c;
+    set_error(std::string("pf_create: ") + ex.what());
+    return PF_E_INVALID;
+  }
+  const pfh::TreePlan& tp = plans.tp;
+  pfh::BwdTrees& bt = plans.bt;
   c->tree_level = tp.first_level;
   c->tree_stages = tp.stages;
-  pfh::BwdTrees bt = pfh::plan_bwd_trees(an, tp, c->bwd_g);
   c->bwd_bins = bt.off.empty() ? 0 : (int)bt.off.size() - 1;
   c->bwd_in = std::move(bt.in);
   std::vector<int4> colinfo(ns);
@@ -592,8 +629,15 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
 
   std::vector<double> zeros(n, 0.0);
   hipStream_t s = ctx->stream;
+  // the arrays of all but the large cases go up in one copy (each costs some
+  // 10 us)
+  std::unique_ptr<char, void (*)(void*)> image(total <= (4 << 20) ? (char*)std::calloc(total, 1) : nullptr, std::free);
   auto up = [&](void* dst, const void* src, size_t b) -> bool {
     if (b == 0) return true;
+    if (image) {
+      std::memcpy(image.get() + ((char*)dst - c->base), src, b);
+      return true;
+    }
     return hipMemcpyAsync(dst, src, b, hipMemcpyHostToDevice, s) == hipSuccess;
   };
   bool ok = true;
@@ -644,6 +688,10 @@ pf_status create_case(Ctx* ctx, const pf_case_desc* d, const pf_schedule& sched,
   ok &= up(c->lrow_blk, an.lrow_blk.data(), sizeof(int) * an.nnzl);
   ok &= up(c->lrow_col, an.lrow_col.data(), sizeof(int) * an.nnzl);
   ok &= up(d_heavy, heavy.data(), sizeof(int) * heavy.size());
+  if (image) {
+    const auto all = std::move(image);  // the arrays below go up by themselves
+    ok &= up(c->base, all.get(), total) && hipStreamSynchronize(s) == hipSuccess;
+  }
   ok &= hipMemsetAsync(c->red, 0, sizeof(pfd::Red), s) == hipSuccess;
   {
     pfd::Inst hi;

@@ -190,6 +190,14 @@ TreePlan plan_trees(const Analysis& an, const std::vector<int>& g, int max_bins,
   }
   if (st.empty() || now >= 1e29) return tp;
   tp.first_level = st[0].la;
+  {
+    int64_t total = 0;
+    for (const Binning& b : st) {
+      for (int k = an.col_lev_ptr[b.la]; k < an.col_lev_ptr[b.lb]; ++k) total += words[an.col_order[k]];
+      total += (int64_t)b.nbins * (kTreeHead + kTreeRec * (b.lb - b.la) + 8);
+    }
+    tp.prog.reserve(total);
+  }
   for (const Binning& b : st) {
     tp.stages.push_back({(int)tp.bin_off.size() - 1, b.nbins, b.threads});
     const int k0 = an.col_lev_ptr[b.la];
@@ -231,7 +239,9 @@ TreePlan plan_trees(const Analysis& an, const std::vector<int>& g, int max_bins,
       int slot = kTreeHead + kTreeRec * nrec;
       const int col0 = (slot + nslots + 3) / 4 * 4;
       int tab = col0 + 4 * (c1 - c0);
-      P.resize(base + tab, 0);
+      int size = tab;
+      for (int k = c0; k < c1; ++k) size += words[cols[k]] - 5;
+      P.resize(base + (size + 3) / 4 * 4, 0);
       P[base] = nrec;
       P[base + 1] = nslots;
       for (int r = 0; r < nrec; ++r) {
@@ -252,28 +262,26 @@ TreePlan plan_trees(const Analysis& an, const std::vector<int>& g, int max_bins,
         P[at + 3] = tab;
         // targets: D, the U row, the forward row, the L column
         const int64_t t0 = j + 2LL * an.colptr[j];
-        const int tb = tab;
+        int* const table = &P[base + tab];
         tab += 2 * len + 3;
-        P.resize(base + tab);
+        int* w = &P[base] + tab;
         for (int t = 0; t < 2 * len + 2; ++t) {
-          P[base + tb + t] = tab;
+          table[t] = (int)(w - &P[base]);
           if (t == len + 1) {
             for (int q = an.lrow_ptr[j]; q < an.lrow_ptr[j + 1]; ++q) {
-              P.push_back(an.lrow_blk[q]);
-              P.push_back(an.lrow_col[q]);
+              *w++ = an.lrow_blk[q];
+              *w++ = an.lrow_col[q];
             }
           } else {
             const int64_t tg = t <= len ? t0 + t : t0 + t - 1;
             for (int64_t q = an.uptr[tg]; q < an.uptr[tg + 1]; ++q) {
-              P.push_back(an.upd_l[q]);
-              P.push_back(an.upd_u[q]);
+              *w++ = an.upd_l[q];
+              *w++ = an.upd_u[q];
             }
           }
-          tab = (int)(P.size() - base);
         }
-        P[base + tb + 2 * len + 2] = tab;
+        tab = table[2 * len + 2] = (int)(w - &P[base]);
       }
-      P.resize((P.size() + 3) / 4 * 4, 0);
       tp.bin_off.push_back((int)P.size());
       tp.bin_cols.insert(tp.bin_cols.end(), cols.begin() + c0, cols.begin() + c1);
       tp.bin_ptr.push_back((int)tp.bin_cols.size());
