@@ -261,15 +261,19 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
   // backward solve, one launch: the dense blocks (one work-group per block,
   // each waiting on the solution entries of the blocks after it; or one
   // work-group per instance running its blocks in order, when the batch has
-  // more blocks than half the work-groups the device holds at once), then the
-  // sparse rows by backward level
+  // so many blocks that waiting ones would only keep others out: 512 mixed
+  // grids (2,300 blocks) take 15.95 ms a solve apart and 16.8 in order, 100
+  // grids of 10,000 buses (2,600) 53.4 and 56.4, 1,200 of 1,000 buses (3,600)
+  // 27.8 and 27.3, 1,400 mixed ones (6,300) 42.0 either way), then the sparse
+  // rows by backward level
   {
+    constexpr int kBlocksApart = 3072;
     int total = 0;
     for (Case* c : cs) total += c->M > 0 ? c->nblk() : 0;
     int mode = cs.empty() ? 0 : cs[0]->sched.trsv_mode;
     for (Case* c : cs)
       if (c->sched.trsv_mode != mode) mode = 0;
-    trsv_single = mode == 1 ? 0 : mode == 2 ? 1 : (total > 1024 ? 1 : 0);
+    trsv_single = mode == 1 ? 0 : mode == 2 ? 1 : (total > kBlocksApart ? 1 : 0);
     std::vector<BwdInput> in(nslots);
     double tfl = 0, tby = 0;
     for (int s = 0; s < nslots; ++s) {

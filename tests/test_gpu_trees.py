@@ -38,6 +38,9 @@ SHAPES = [
     ("mesh300", lambda: pfgen.make_polar_grid(300, 90, 30, 6, balanced=True), dict(dense_switch=1.0, min_dense=10000)),
     ("mesh900", lambda: pfgen.make_polar_grid(900, 270, 90, 6, balanced=True), dict(dense_switch=1.0, min_dense=10000)),
     ("mesh700wide", lambda: pfgen.make_polar_grid(700, 210, 70, 8, balanced=True), dict(lane_scale=4)),
+    # the dense block's backward solve in one work-group, and a work-group a block
+    ("mesh900single", lambda: pfgen.make_polar_grid(900, 270, 90, 6, balanced=True), dict(trsv_mode=2)),
+    ("mesh900apart", lambda: pfgen.make_polar_grid(900, 270, 90, 6, balanced=True), dict(trsv_mode=1)),
     ("feeder400", lambda: pfgen.make_feeder(400, 3), {}),
 ]
 
