@@ -1544,27 +1544,24 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_bcg_v(const Inst* const* ins
 // (it: the iteration, counted from 0 in the inner solve).
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, int it) {
-  __shared__ double red[KMAX + 1][KCH / 64];
-  __shared__ double alpha_s;
+  __shared__ double red[1][KCH / 64];
   const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
-  if (threadIdx.x < 64) {
-    const double a = gp(I.ks)->rho[it & 1] / chunk_sum(I, 0, 0);
-    if (threadIdx.x == 0) {
-      alpha_s = a;
-      if (blockIdx.x == 0) gp(I.ks)->alpha = a;
-    }
-  }
-  __syncthreads();
-  const double alpha = alpha_s;
   const int r = blockIdx.x * KCH + threadIdx.x;
+  // every wave forms alpha, its own rows' values on their way meanwhile (3.9 ->
+  // 3.4 us at 48,000 buses; with sixteen waves, as in k_bcg_t, the partials'
+  // loads cost more than the barrier)
+  const auto R = kvec<T>(I, 0);
+  const auto V = kvec<T>(I, 3);
+  const int k = 2 * min(r, I.nu - 1);
+  const T ra = R[k], rb = R[k + 1], va = V[k], vb = V[k + 1];
+  const double alpha = gp(I.ks)->rho[it & 1] / chunk_sum(I, 0, 0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) gp(I.ks)->alpha = alpha;
   double s0 = 0.0, s1 = 0.0;
   if (r < I.nu) {
-    const auto R = kvec<T>(I, 0);
-    const auto V = kvec<T>(I, 3);
     const auto w = gp((T*)I.kw);
-    const T a = (T)((double)R[2 * r] - alpha * (double)V[2 * r]);
-    const T b = (T)((double)R[2 * r + 1] - alpha * (double)V[2 * r + 1]);
+    const T a = (T)((double)ra - alpha * (double)va);
+    const T b = (T)((double)rb - alpha * (double)vb);
     R[2 * r] = a;
     R[2 * r + 1] = b;
     w[2 * r] = a;
@@ -1643,49 +1640,51 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_bcg_t(const Inst* const* ins
 // x += alpha p^.
 template <typename T>
 __global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts) {
-  __shared__ double red[KMAX + 1][KCH / 64];
-  __shared__ double omega_s;
-  __shared__ bool skip_s;
+  __shared__ double red[2][KCH / 64];
   const auto& I = inst_at(insts, blockIdx.y);
   const bool half = kstate_is(I, KS_BH);
   if ((!half && !kstate_is(I, KS_BS)) || (int)blockIdx.x >= I.kchunks) return;
-  const auto& ks = *gp(I.ks);
+  const double alpha = gp(I.ks)->alpha;
   const int r = blockIdx.x * KCH + threadIdx.x;
   const auto x = gp((T*)I.kx);
   const auto Ph = kvec<T>(I, 4);
   if (half) {
     if (r < I.nu) {
 #pragma unroll
-      for (int e = 0; e < 2; ++e) x[2 * r + e] = (T)((double)x[2 * r + e] + ks.alpha * (double)Ph[2 * r + e]);
+      for (int e = 0; e < 2; ++e) x[2 * r + e] = (T)((double)x[2 * r + e] + alpha * (double)Ph[2 * r + e]);
     }
     return;
   }
-  if (threadIdx.x < 64) {
-    double sum[2];
-    chunk_sums<2>(I, {2, 2}, {1, 0}, sum);
-    const double tt = sum[0], ts = sum[1];
-    if (threadIdx.x == 0) {
-      skip_s = !(tt > 0.0);
-      omega_s = skip_s ? 0.0 : ts / tt;
-      if (blockIdx.x == 0) gp(I.ks)->omega = omega_s;
-    }
+  // every wave forms omega, its own rows' values on their way meanwhile (4.75 ->
+  // 4.0 us)
+  const auto R = kvec<T>(I, 0);
+  T xv[2], pv[2], sv[2], tv[2], r0v[2], rv[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int i = 2 * min(r, I.nu - 1) + e;
+    xv[e] = x[i];
+    pv[e] = Ph[i];
+    sv[e] = kvec<T>(I, 5)[i];
+    tv[e] = kvec<T>(I, 6)[i];
+    r0v[e] = kvec<T>(I, 1)[i];
+    rv[e] = R[i];
   }
-  __syncthreads();
-  if (skip_s) return;  // <t, t> = 0: the solve ends as it stands
-  const double omega = omega_s;
+  double sum[2];
+  chunk_sums<2>(I, {2, 2}, {1, 0}, sum);
+  const double tt = sum[0], ts = sum[1];
+  const bool skip = !(tt > 0.0);
+  const double omega = skip ? 0.0 : ts / tt;
+  if (blockIdx.x == 0 && threadIdx.x == 0) gp(I.ks)->omega = omega;
+  if (skip) return;  // <t, t> = 0: the solve ends as it stands
   double d = 0.0, q = 0.0;
   if (r < I.nu) {
-    const auto Sh = kvec<T>(I, 5);
-    const auto Tv = kvec<T>(I, 6);
-    const auto R0 = kvec<T>(I, 1);
-    const auto R = kvec<T>(I, 0);
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const int i = 2 * r + e;
-      x[i] = (T)((double)x[i] + ks.alpha * (double)Ph[i] + omega * (double)Sh[i]);
-      const T rn = (T)((double)R[i] - omega * (double)Tv[i]);
+      x[i] = (T)((double)xv[e] + alpha * (double)pv[e] + omega * (double)sv[e]);
+      const T rn = (T)((double)rv[e] - omega * (double)tv[e]);
       R[i] = rn;
-      d += (double)R0[i] * (double)rn;
+      d += (double)r0v[e] * (double)rn;
       q += (double)rn * (double)rn;
     }
   }
