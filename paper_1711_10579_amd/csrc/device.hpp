@@ -146,6 +146,13 @@ constexpr int kFacClasses = 5;
 struct FacLaunch {
   int end[kFacClasses], first[kFacClasses], count[kFacClasses];
 };
+// A level's columns by lanes per list: group g, G[g] lanes, takes the
+// work-groups from block0[g] on (block0[n]: all of them).
+constexpr int kFacGroups = 7;
+struct FacLevel {
+  int n, G[kFacGroups], block0[kFacGroups + 1];
+  FacLaunch f[kFacGroups];
+};
 // the class of a column of `len` blocks at G lanes per target: the fewest
 // lanes that hold its 2 len + 2 targets in one pass, else a work-group
 inline int fac_class(int len, int G) {

@@ -177,7 +177,7 @@ struct Launch {
   int64_t off;     // first work item
   int count;       // work items
   double flops, bytes;
-  pfd::FacLaunch fac;  // factor columns by class
+  pfd::FacLevel fac;  // factor columns by lanes and class
 };
 enum { L_FACTOR = 0, L_TREES, L_FWD, L_SCHUR, L_PANEL, L_BWD };
 

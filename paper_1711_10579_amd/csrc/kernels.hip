@@ -948,11 +948,10 @@ __device__ inline FacCol fac_col(const int2* work, int idx, bool any) {
   return {w.x, any, w.y};
 }
 template <typename T, int G, int LANES, int NP>
-__device__ __forceinline__ void factor_class(const Inst* const* insts, const int2* work, const FacLaunch& f, int c,
+__device__ __forceinline__ void factor_class(const Inst* const* insts, const int2* work, const FacLaunch& f, int b, int c,
                                              T* sd) {
   constexpr int C = 256 / (LANES < 256 ? LANES : 256);
-  const int b = (int)blockIdx.x - (c ? f.end[c - 1] : 0);
-  const int idx = b * C + (int)threadIdx.x / LANES;
+  const int idx = (b - (c ? f.end[c - 1] : 0)) * C + (int)threadIdx.x / LANES;
   const FacCol w = fac_col(work, f.first[c] + idx, idx < f.count[c]);
   if (!w.any) return;  // whole columns leave together
   const auto& I = inst_at(insts, w.slot);
@@ -961,20 +960,47 @@ __device__ __forceinline__ void factor_class(const Inst* const* insts, const int
   factor_column<T, G, LANES, NP>(I, on, q.x, q.y, q.z, (int)threadIdx.x % LANES, sd);
 }
 template <typename T, int G>
+__device__ __forceinline__ void factor_group(const Inst* const* insts, const int2* work, const FacLaunch& f, int b,
+                                             T* sd) {
+  if (b < f.end[0]) {
+    if constexpr (G <= 8) factor_class<T, G, 8, 1>(insts, work, f, b, 0, sd);
+  } else if (b < f.end[1]) {
+    if constexpr (G <= 16) factor_class<T, G, 16, 1>(insts, work, f, b, 1, sd);
+  } else if (b < f.end[2]) {
+    if constexpr (G <= 32) factor_class<T, G, 32, 1>(insts, work, f, b, 2, sd);
+  } else if (b < f.end[3]) {
+    factor_class<T, G, 64, 1>(insts, work, f, b, 3, sd);
+  } else {
+    factor_class<T, G, 256, 2>(insts, work, f, b, 4, sd);
+  }
+}
+template <typename T, int G>
 __global__ __launch_bounds__(256, 4) void k_factor_cols(const Inst* const* insts, const int2* __restrict__ work,
                                                      FacLaunch f) {
   __shared__ T sd[4];
-  const int b = blockIdx.x;
-  if (b < f.end[0]) {
-    if constexpr (G <= 8) factor_class<T, G, 8, 1>(insts, work, f, 0, sd);
-  } else if (b < f.end[1]) {
-    if constexpr (G <= 16) factor_class<T, G, 16, 1>(insts, work, f, 1, sd);
-  } else if (b < f.end[2]) {
-    if constexpr (G <= 32) factor_class<T, G, 32, 1>(insts, work, f, 2, sd);
-  } else if (b < f.end[3]) {
-    factor_class<T, G, 64, 1>(insts, work, f, 3, sd);
-  } else {
-    factor_class<T, G, 256, 2>(insts, work, f, 4, sd);
+  factor_group<T, G>(insts, work, f, (int)blockIdx.x, sd);
+}
+// Instances of a batch differ in the lanes their levels take: one launch with
+// a group of work-groups per lane count.  A launch for each left the chip
+// mostly idle, one after the other: 512 mixed grids, 64 launches of 7-13 us a
+// factor, then 26 of 17 us, 16.4 -> 15.15 ms a solve.  A level of one lane
+// count keeps the kernel of that count (256 feeder copies 1 % slower here).
+template <typename T>
+__global__ __launch_bounds__(256, 4) void k_factor_level(const Inst* const* insts, const int2* __restrict__ work,
+                                                      FacLevel v) {
+  __shared__ T sd[4];
+  int g = 0;
+  while (g + 1 < v.n && (int)blockIdx.x >= v.block0[g + 1]) ++g;
+  const int b = (int)blockIdx.x - v.block0[g];
+  const FacLaunch& f = v.f[g];
+  switch (v.G[g]) {
+    case 1: factor_group<T, 1>(insts, work, f, b, sd); break;
+    case 2: factor_group<T, 2>(insts, work, f, b, sd); break;
+    case 4: factor_group<T, 4>(insts, work, f, b, sd); break;
+    case 8: factor_group<T, 8>(insts, work, f, b, sd); break;
+    case 16: factor_group<T, 16>(insts, work, f, b, sd); break;
+    case 32: factor_group<T, 32>(insts, work, f, b, sd); break;
+    default: factor_group<T, 64>(insts, work, f, b, sd); break;
   }
 }
 // levels of few columns with many targets: 1024 threads a column
@@ -1338,13 +1364,19 @@ void launch_kfill(hipStream_t st, const Inst* const* insts, int nslots, int max_
   }
 
 template <typename T>
-void launch_factor_cols(hipStream_t st, const Inst* const* insts, const int2* work, const FacLaunch& f, int G,
-                        int wide) {
+void launch_factor_cols(hipStream_t st, const Inst* const* insts, const int2* work, const FacLevel& v, int wide) {
   if (wide) {
+    const FacLaunch& f = v.f[0];
     if (f.count[4] > 0)
-      PF_GSWITCH(G, (k_factor_cols_wide<T, GG><<<dim3((unsigned)f.count[4]), 1024, 0, st>>>(insts, work, f.first[4])));
-  } else if (f.end[4] > 0) {
-    PF_GSWITCH(G, (k_factor_cols<T, GG><<<dim3((unsigned)f.end[4]), 256, 0, st>>>(insts, work, f)));
+      PF_GSWITCH(v.G[0],
+                 (k_factor_cols_wide<T, GG><<<dim3((unsigned)f.count[4]), 1024, 0, st>>>(insts, work, f.first[4])));
+  } else if (v.block0[v.n] > 0) {
+    const dim3 grid((unsigned)v.block0[v.n]);
+    if (v.n > 1) {
+      k_factor_level<T><<<grid, 256, 0, st>>>(insts, work, v);
+    } else {
+      PF_GSWITCH(v.G[0], (k_factor_cols<T, GG><<<grid, 256, 0, st>>>(insts, work, v.f[0])));
+    }
   }
 }
 
@@ -1378,7 +1410,7 @@ void launch_update(hipStream_t st, const Inst* const* insts, int nslots, int max
 
 #define PF_INST(T)                                                                                         \
   template void launch_fill<T>(hipStream_t, const Inst* const*, int, int, const int2*, int, int);          \
-  template void launch_factor_cols<T>(hipStream_t, const Inst* const*, const int2*, const FacLaunch&, int, int); \
+  template void launch_factor_cols<T>(hipStream_t, const Inst* const*, const int2*, const FacLevel&, int); \
   template void launch_tail_schur<T>(hipStream_t, const Inst* const*, const int2*, int, int);              \
   template void launch_factor_trees<T>(hipStream_t, const Inst* const*, const int*, const int*, int, int);   \
   template void launch_fwd_rows<T>(hipStream_t, const Inst* const*, const int2*, int, int);                \

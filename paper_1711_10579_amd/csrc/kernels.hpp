@@ -42,7 +42,7 @@ int zero_chunk_values();
 // null), by class of lanes per column; wide: all in class 4, 1024 threads a
 // column
 template <typename T>
-void launch_factor_cols(hipStream_t, const Inst* const* insts, const int2* work, const FacLaunch& f, int G, int wide);
+void launch_factor_cols(hipStream_t, const Inst* const* insts, const int2* work, const FacLevel& v, int wide);
 // one stage of the upper levels' subtrees: `nbins` programs at
 // words[bin_off[b]], each of at most kTreeLds words, `threads` (256 or 512)
 // threads each

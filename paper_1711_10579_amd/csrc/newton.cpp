@@ -118,7 +118,7 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
     max_blev = std::max(max_blev, c->nbl);
     max_M = std::max(max_M, c->M);
   }
-  // sparse refactorisation, level by level, one launch per lane-group size;
+  // sparse refactorisation, level by level, one launch each;
   // each column's launch also runs the forward row of its node (the rows of
   // a level depend only on earlier levels' L blocks and solution entries).
   // A batch of one names its columns by their positions in the level order;
@@ -147,37 +147,59 @@ void Batch::plan(Ctx* cx, const std::vector<Case*>& cs, std::vector<int2>* out) 
       g.fl += c->fac_flops[l];
       g.by += c->fac_bytes[l];
     }
+    // the level's launch; groups of 1024 threads a column take one each
+    Launch lev;
+    lev.kind = L_FACTOR;
+    lev.cls = PF_K_SPARSE_FACTOR;
+    lev.G = 0;
+    lev.k0 = lev.nflag = 0;
+    lev.off = (int64_t)work.size();
+    lev.count = 0;
+    lev.flops = lev.bytes = 0;
+    lev.fac = {};
+    auto add = [&](Launch& f, int G, Group& g) {
+      const int at = f.fac.n++;
+      f.count += (int)g.count;
+      f.flops += g.fl;
+      f.bytes += g.by;
+      // first column: in the launch's list, or in the only instance's order
+      int first = nslots == 1 ? cs[0]->an.col_lev_ptr[l] : (int)((int64_t)work.size() - f.off), end = 0;
+      pfd::FacLaunch& fl = f.fac.f[at];
+      for (int k = 0; k < pfd::kFacClasses; ++k) {
+        const int n = (int)g.cls[k].size(), per = pfd::kFacClasses - 1 - k;  // 32, 16, 8, 4, 1 columns a work-group
+        const int cols = per == 0 ? 1 : 2 << per;
+        end += (n + cols - 1) / cols;
+        fl.end[k] = end;
+        fl.first[k] = first;
+        fl.count[k] = n;
+        first += n;
+        if (nslots > 1) work.insert(work.end(), g.cls[k].begin(), g.cls[k].end());
+      }
+      f.fac.G[at] = G;
+      f.fac.block0[at + 1] = f.fac.block0[at] + end;
+    };
+    std::vector<std::pair<int, Group*>> apart;
     for (auto& kv : byG) {
       const int G = kv.first;
       Group& g = kv.second;
       // 1024 threads per column when the level has few columns and they need
       // several passes of 256 threads
-      const bool wide = g.count < 128 && (int64_t)g.maxt * G > 256;
-      Launch f;
-      f.kind = L_FACTOR;
-      f.cls = PF_K_SPARSE_FACTOR;
-      f.G = G;
-      f.k0 = wide ? 1 : 0;
-      f.nflag = 0;
+      if (g.count < 128 && (int64_t)g.maxt * G > 256)
+        apart.push_back({G, &g});
+      else
+        add(lev, G, g);
+    }
+    if (lev.fac.n > 0) seq.push_back(lev);
+    for (auto& kv : apart) {
+      Launch f = lev;
+      f.k0 = 1;
       f.off = (int64_t)work.size();
-      f.count = (int)g.count;
-      f.flops = g.fl;
-      f.bytes = g.by;
-      int first = nslots == 1 ? cs[0]->an.col_lev_ptr[l] : 0, end = 0;
-      for (int k = 0; k < pfd::kFacClasses; ++k) {
-        const int n = (int)g.cls[k].size(), per = pfd::kFacClasses - 1 - k;  // 32, 16, 8, 4, 1 columns a work-group
-        const int cols = per == 0 ? 1 : 2 << per;
-        end += (n + cols - 1) / cols;
-        f.fac.end[k] = end;
-        f.fac.first[k] = first;
-        f.fac.count[k] = n;
-        first += n;
-        if (nslots > 1) work.insert(work.end(), g.cls[k].begin(), g.cls[k].end());
-      }
-      if (wide) {
-        f.fac.first[4] = f.fac.first[0];
-        f.fac.count[4] = (int)g.count;
-      }
+      f.count = 0;
+      f.flops = f.bytes = 0;
+      f.fac = {};
+      add(f, kv.first, *kv.second);
+      f.fac.f[0].first[4] = f.fac.f[0].first[0];
+      f.fac.f[0].count[4] = (int)kv.second->count;
       seq.push_back(f);
     }
   }
@@ -321,7 +343,7 @@ void lu_solve(Batch* b) {
     const int2* w = b->d_work + l.off;
     switch (l.kind) {
       case L_FACTOR:
-        pfd::launch_factor_cols<T>(s, I, b->nslots == 1 ? nullptr : w, l.fac, l.G, l.k0);
+        pfd::launch_factor_cols<T>(s, I, b->nslots == 1 ? nullptr : w, l.fac, l.k0);
         break;
       case L_TREES:
         pfd::launch_factor_trees<T>(s, I, b->cases[0]->tree_off + l.k0, b->cases[0]->tree_prog, l.count, l.G);
