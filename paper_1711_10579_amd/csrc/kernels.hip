@@ -688,7 +688,7 @@ __device__ inline void jblock(const IR& I, int e, double* out) {
 template <typename T>
 __global__ void k_jfill(const Inst* const* insts, int nj) {
   const auto& I = inst_at(insts, blockIdx.y);
-  // tested only before the stores: the loads need not wait for it
+  // tested with the thread's first load, so that it adds no round trip
   const bool off = inactive(I);
   if ((int)blockIdx.x >= nj) {
     const int i = ((int)blockIdx.x - nj) * blockDim.x + threadIdx.x;
@@ -703,10 +703,9 @@ __global__ void k_jfill(const Inst* const* insts, int nj) {
   int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= I.nnz) return;
   int code = gp(I.jmap)[e];
-  if (code == -1) return;
+  if (off | (code == -1)) return;
   double blk[4];
   jblock(I, e, blk);
-  if (off) return;
   jstore<T>(I, code, blk[0], blk[1], blk[2], blk[3]);
 }
 
@@ -775,18 +774,18 @@ __device__ inline void sub_updates(Blk<T>& acc, const T* lu_, const int* il_, co
 // - sum_k L(i,k) y_k over the row's L blocks (b_i in x), lane-strided, the
 // loads of four entries issued at once; the fixed-order tree follows.  Every
 // L(i,k) and y_k lies in an earlier level.  (a, c) carry the 2-vector.
+// q0, q1: the row's blocks.
 template <typename T, int G, typename IR>
-__device__ inline Blk<T> fwd_partial(const IR& I, const T* lu_, const T* x_, int i, int lane) {
+__device__ inline Blk<T> fwd_partial(const IR& I, const T* lu_, const T* x_, int i, int q0, int q1, int lane) {
   const auto lu = gp(lu_);
   const auto x = gp(x_);
-  const auto lrow_ptr = gp(I.lrow_ptr), lrow_blk = gp(I.lrow_blk), lrow_col = gp(I.lrow_col);
+  const auto lrow_blk = gp(I.lrow_blk), lrow_col = gp(I.lrow_col);
   Blk<T> acc = {T(0), T(0), T(0), T(0)};
   if (lane == 0) {
     acc.a = x[2 * i];
     acc.c = x[2 * i + 1];
   }
-  const int q1 = lrow_ptr[i + 1];
-  for (int q = lrow_ptr[i] + lane; q < q1; q += 4 * G) {
+  for (int q = q0 + lane; q < q1; q += 4 * G) {
     int bk[4], kk[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -822,7 +821,7 @@ __device__ inline Blk<T> fwd_partial(const IR& I, const T* lu_, const T* x_, int
 // targets take the rest one by one after it.  LANES > 64: a whole work-group
 // (every thread calls this), D^{-1} through sd.
 template <typename T, int G, int LANES, int NP, typename IR>
-__device__ __forceinline__ void factor_column(const IR& I, bool on, int j, int c0, int len, int tid, T* sd) {
+__device__ __forceinline__ void factor_column(const IR& I, int j, int c0, int len, int tid, T* sd) {
   T* lu = (T*)I.lu;
   const int lane = tid % G, grp = tid / G;
   constexpr int NG = LANES / G;
@@ -896,7 +895,7 @@ __device__ __forceinline__ void factor_column(const IR& I, bool on, int j, int c
     T det = blk_det(acc[0]);
     bool bad = !(det != T(0)) || !isfinite((double)det);
     if (bad) {
-      if (on) red_of(I)->singular = 1;
+      red_of(I)->singular = 1;
       det = T(1);
     }
     T r = T(1) / det;
@@ -904,7 +903,7 @@ __device__ __forceinline__ void factor_column(const IR& I, bool on, int j, int c
     di.b = -acc[0].b * r;
     di.c = -acc[0].c * r;
     di.d = acc[0].a * r;
-    if (on) st_blk(gp((T*)I.dinv), j, di);
+    st_blk(gp((T*)I.dinv), j, di);
     if (LANES > 64) {
       sd[0] = di.a;
       sd[1] = di.b;
@@ -922,11 +921,11 @@ __device__ __forceinline__ void factor_column(const IR& I, bool on, int j, int c
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const int t = p * NG + grp;
-    if (t < nt && lane == 0 && on) store(t, acc[p], di);
+    if (t < nt && lane == 0) store(t, acc[p], di);
   }
   for (int t = NP * NG + grp; t < nt; t += NG) {
     const Blk<T> v = sum(t);
-    if (lane == 0 && on) store(t, v, di);
+    if (lane == 0) store(t, v, di);
   }
 }
 
@@ -955,9 +954,16 @@ __device__ __forceinline__ void factor_class(const Inst* const* insts, const int
   const FacCol w = fac_col(work, f.first[c] + idx, idx < f.count[c]);
   if (!w.any) return;  // whole columns leave together
   const auto& I = inst_at(insts, w.slot);
-  const bool on = !inactive(I);
+  // A finished instance leaves here: the flag is tested together with the
+  // column's entry (whose length is never negative), which the next loads wait
+  // for anyway, so an active one pays no round trip for it (tested at the
+  // stores only, 160 feeders of 900 buses with one still iterating took 17.6 us a
+  // launch, 8.7 this way; the dense steps' tiles test late, where leaving
+  // before their loads gained nothing and cost 16 grids of 10,000 buses 1 %).
+  const bool off = inactive(I);
   const i4v q = ((const PF_AS1 i4v*)I.colinfo)[w.pos];
-  factor_column<T, G, LANES, NP>(I, on, q.x, q.y, q.z, (int)threadIdx.x % LANES, sd);
+  if (off | (q.z < 0)) return;
+  factor_column<T, G, LANES, NP>(I, q.x, q.y, q.z, (int)threadIdx.x % LANES, sd);
 }
 template <typename T, int G>
 __device__ __forceinline__ void factor_group(const Inst* const* insts, const int2* work, const FacLaunch& f, int b,
@@ -1010,9 +1016,10 @@ __global__ __launch_bounds__(1024) void k_factor_cols_wide(const Inst* const* in
   __shared__ T sd[4];
   const FacCol w = fac_col(work, first + (int)blockIdx.x, true);
   const auto& I = inst_at(insts, w.slot);
-  const bool on = !inactive(I);
+  const bool off = inactive(I);
   const i4v q = ((const PF_AS1 i4v*)I.colinfo)[w.pos];
-  factor_column<T, G, 1024, 2>(I, on, q.x, q.y, q.z, (int)threadIdx.x, sd);
+  if (off | (q.z < 0)) return;  // as in factor_class
+  factor_column<T, G, 1024, 2>(I, q.x, q.y, q.z, (int)threadIdx.x, sd);
 }
 
 // The upper levels of the refactorisation as subtrees (TreePlan), for a case
@@ -1231,10 +1238,12 @@ __global__ __launch_bounds__(256) void k_fwd_rows(const Inst* const* insts, cons
   if (gid >= nwork) return;  // whole groups leave together
   const int2 w = ld_item(work, gid);
   const auto& I = inst_at(insts, w.x);
-  const bool on = !inactive(I);
+  const bool off = inactive(I);
   const int i = w.y;
-  const Blk<T> v = group_sum<T, G>(fwd_partial<T, G>(I, (const T*)I.lu, (const T*)I.x, i, lane));
-  if (!on || lane != 0) return;
+  const int q0 = gp(I.lrow_ptr)[i], q1 = gp(I.lrow_ptr)[i + 1];
+  if (off | (q1 < q0)) return;  // as in factor_class
+  const Blk<T> v = group_sum<T, G>(fwd_partial<T, G>(I, (const T*)I.lu, (const T*)I.x, i, q0, q1, lane));
+  if (lane != 0) return;
   const auto x = gp((T*)I.x);
   x[2 * i] = v.a;
   x[2 * i + 1] = v.c;
@@ -1254,13 +1263,15 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_update(const Inst* const* insts) {
   const auto& I = inst_at(insts, blockIdx.y);
   if ((int)(blockIdx.x * blockDim.x) >= I.nu) return;
-  // tested after the loads and before the stores (uniform over the work-group)
+  // tested with the thread's first load, so that it adds no round trip
+  // (uniform over the work-group)
   const bool off = inactive(I);
   double local = 0.0;
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  const int i = gp(I.node)[min(p, I.nu - 1)];
+  if (off | (i < 0)) return;
   if (p < I.nu) {
     const auto x = gp((const T*)I.x);
-    const int i = gp(I.node)[p];
     const auto type = gp(I.type);
     const auto va = gp(I.va), vm = gp(I.vm);
     double* v = I.v;  // complex, as pairs
@@ -1269,14 +1280,11 @@ __global__ __launch_bounds__(256) void k_update(const Inst* const* insts) {
     if (I.model == 0) {
       if (ty != 1) d1 = 0.0;
       double a = va[i] + d0, m = vm[i] + d1;
-      if (off) return;
       va[i] = a;
       vm[i] = m;
       double s, c;
       sincos(a, &s, &c);
       st_c(v, i, m * c, m * s);
-    } else if (off) {
-      return;
     } else if (ty == 2) {
       // PV node: rotate by the angle step at the set-point magnitude; the
       // second unknown is the generator Q
@@ -1295,7 +1303,6 @@ __global__ __launch_bounds__(256) void k_update(const Inst* const* insts) {
     if (!(m == m)) m = __longlong_as_double(0x7ff8000000000000ll);
     local = m;
   }
-  if (off) return;
   block_max_store(local, I.upart + blockIdx.x);
 }
 
