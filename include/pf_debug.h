@@ -5,7 +5,7 @@
  * Not a compute path: the solve entry points of pf.h never call these.  The
  * two analysis checks touch no device, so that the fill-reducing ordering and
  * the symbolic block LU of Sec. III-A can be tested on a machine without a
- * GPU; the preconditioner check runs its set-up kernels on the device.
+ * GPU; the two preconditioner checks run its kernels on the device.
  */
 #ifndef PF_DEBUG_H_
 #define PF_DEBUG_H_
@@ -49,8 +49,8 @@ pf_status pf_debug_schedule_check(const pf_case_desc* desc, const pf_schedule* s
 pf_status pf_debug_krylov_check(const pf_case_desc* desc, uint64_t seed, double* ilu_deviation,
                                 double* rel_residual, int64_t* checks);
 
-/* The one call here that uses the device: a check of the Newton-Krylov
- * preconditioner set-up kernels (Sec. III-B).  The case's Jacobian at its
+/* A check of the Newton-Krylov preconditioner set-up kernels on the device
+ * (Sec. III-B).  The case's Jacobian at its
  * flat start is built on the device and the set-up kernels for `precond`
  * run on it exactly as in a Krylov Newton step (FP64); the results are
  * copied back and checked on the host against their definitions:
@@ -65,6 +65,19 @@ pf_status pf_debug_krylov_check(const pf_case_desc* desc, uint64_t seed, double*
  * The case is left at its flat-start voltage.  Host outputs.  PF_E_BUSY while
  * the case is queued or running; PF_E_INVALID for a singular pivot. */
 pf_status pf_debug_precond_check(pf_case* c, int32_t precond, double* deviation, int32_t* max_order);
+
+/* An application of the ILU(0) preconditioner on the device (Sec. III-B): the
+ * factor of the case's Jacobian at its flat start, applied to a random vector
+ * (seeded by `seed`) in the given precision as in a Newton-Krylov step, against
+ * the two triangular solves in FP64 on the host from the same factor.
+ * *deviation receives ||z - z_ref||_2 / ||z_ref||_2, *level_deviation the same
+ * of those solves with every row's result rounded to the inner precision (what
+ * sweeps by levels store), parts[0] and parts[1] the parts of the forward and
+ * backward sweep (0: the case sweeps by levels).  The case is left at its
+ * flat-start voltage.  Host outputs.  PF_E_BUSY while the case is queued or
+ * running; PF_E_INVALID for a singular pivot. */
+pf_status pf_debug_sweep_check(pf_case* c, int32_t precision, uint64_t seed, double* deviation,
+                               double* level_deviation, int32_t* parts);
 
 #ifdef __cplusplus
 }

@@ -155,6 +155,8 @@ _sig = {
     "pf_debug_krylov_check": (C.c_int, [C.POINTER(pf_case_desc), C.c_uint64, C.POINTER(C.c_double),
                                         C.POINTER(C.c_double), C.POINTER(C.c_int64)]),
     "pf_debug_precond_check": (C.c_int, [_P, C.c_int32, C.POINTER(C.c_double), C.POINTER(C.c_int32)]),
+    "pf_debug_sweep_check": (C.c_int, [_P, C.c_int32, C.c_uint64, C.POINTER(C.c_double), C.POINTER(C.c_double),
+                                       C.POINTER(C.c_int32)]),
     "pf_last_error": (C.c_char_p, []),
     "pf_version": (C.c_char_p, []),
 }
@@ -378,6 +380,16 @@ def pf_debug_precond_check(case, precond):
     _check(_lib.pf_debug_precond_check(case.handle, int(precond), C.byref(dev), C.byref(order)),
            "pf_debug_precond_check")
     return dev.value, order.value
+
+
+def pf_debug_sweep_check(case, precision, seed=0):
+    """Device check of an ILU(0) application (include/pf_debug.h).  Returns
+    (deviation, deviation of level sweeps, (forward parts, backward parts))."""
+    dev, lev = C.c_double(), C.c_double()
+    parts = (C.c_int32 * 2)()
+    _check(_lib.pf_debug_sweep_check(case.handle, int(precision), C.c_uint64(seed), C.byref(dev), C.byref(lev),
+                                     parts), "pf_debug_sweep_check")
+    return dev.value, lev.value, tuple(parts)
 
 
 def pf_create_from(ctx, case, schedule=None):

@@ -115,6 +115,11 @@ __device__ inline void st_blk(T* p, int64_t id, const Blk<T>& v) {
   q[3] = v.d;
 }
 
+template <typename T>
+__device__ inline Blk<double> blk_f64(const Blk<T>& v) {
+  return {(double)v.a, (double)v.b, (double)v.c, (double)v.d};
+}
+
 // The block operations name their fused multiply-adds: a column is formed by
 // different kernels alone and in a batch, and left to the compiler each could
 // fuse another product of a sum (results must agree to the bit).

@@ -103,7 +103,7 @@ struct Inst {
   // the ILU(0) sweeps in parts (null: by levels): per position {row, first
   // entry, end, 0}, the forward rows first; per entry its column (~c: the
   // part's input at row c, else row c of an earlier part) and its list of
-  // (factor block, entry) pairs; the entry values, in the block-Jacobi
+  // (factor block, entry) pairs; the entry values, FP64, in the block-Jacobi
   // inverses' storage (a solve uses one preconditioner)
   const int4* sw_rows;
   const int *sw_col, *sw_op_ptr;

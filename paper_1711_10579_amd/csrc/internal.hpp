@@ -306,6 +306,12 @@ uint64_t topology_hash(const pf_case_desc* d);
 pf_status check_opts(const pf_options* opt);
 // The Newton step's linear solve by GMRES and the voltage update.
 pf_status nk_step(Batch* b, const pf_options* opt);
+// The preconditioner (ilu: ILU(0), else block-Jacobi) of every active instance
+// from its Jacobian's blocks, and its application (modes of kernels.hpp).
+template <typename T>
+void precond_setup(Batch* b, bool ilu);
+template <typename T>
+void precond_apply(Batch* b, bool ilu, int mode);
 
 // Launch plan of the dense block's block LU (dense_plan.cpp), one launch per
 // 64-wide block step.  Step k of an instance with dense order M has a

@@ -682,7 +682,9 @@ __device__ inline SweepRow sweep_row(const int2* work, int p0, int nrows) {
 // Entry values of the rows of one step: the rows of a part's first level
 // come from the factor alone, those of its next levels from the entries of
 // rows of earlier steps.  Twice the lanes of an application: an entry is a
-// chain of three loads, so the longest rows set a step's time.
+// chain of three loads, so the longest rows set a step's time.  Formed and
+// held in FP64 whatever the factor's type: the level sweeps sum a row in FP64,
+// and an FP32 value would put its own rounding into every row that uses it.
 constexpr int kValueLanes = 16;
 template <typename T>
 __global__ __launch_bounds__(256) void k_sweep_values(const Inst* const* insts, const int2* __restrict__ work) {
@@ -692,26 +694,26 @@ __global__ __launch_bounds__(256) void k_sweep_values(const Inst* const* insts, 
   const i4v inf = ((const PF_AS1 i4v*)I.sw_rows)[sr.pos];
   const bool upper = sr.pos >= I.nu;
   const auto P = gp((const T*)I.pval);
-  const auto V = gp((T*)I.bjinv);
+  const auto V = gp((double*)I.bjinv);
   const auto optr = gp(I.sw_op_ptr);
-  Blk<T> D = {T(0), T(0), T(0), T(0)};
-  if (upper) D = ld_blk(gp((const T*)I.pdinv), inf.x);
+  Blk<double> D = {0.0, 0.0, 0.0, 0.0};
+  if (upper) D = blk_f64(ld_blk(gp((const T*)I.pdinv), inf.x));
   for (int e = inf.y + (int)threadIdx.x % kValueLanes; e < inf.z; e += kValueLanes) {
     const int o0 = optr[e], o1 = optr[e + 1];
-    Blk<T> acc = {T(0), T(0), T(0), T(0)};
+    Blk<double> acc = {0.0, 0.0, 0.0, 0.0};
     // two terms' loads at once, added in order
     for (int o = o0; o < o1; o += 2) {
       int2 op[2];
-      Blk<T> F[2], S[2];
+      Blk<double> F[2], S[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) op[u] = ld_item(I.sw_ops, o + u < o1 ? o + u : o);
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        F[u] = ld_blk<T>(P, op[u].x);
+        F[u] = blk_f64(ld_blk<T>(P, op[u].x));
         if (op[u].y >= 0)
-          S[u] = ld_blk<T>(V, op[u].y);
+          S[u] = ld_blk<double>(V, op[u].y);
         else
-          S[u] = {T(1), T(0), T(0), T(1)};
+          S[u] = {1.0, 0.0, 0.0, 1.0};
       }
 #pragma unroll
       for (int u = 0; u < 2; ++u)
@@ -744,7 +746,7 @@ __global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, co
   const i4v inf = ((const PF_AS1 i4v*)I.sw_rows)[sr.pos];
   if (off | (inf.z < inf.y)) return;
   const int r = inf.x;
-  const auto V = gp((const T*)I.bjinv);
+  const auto V = gp((const double*)I.bjinv);
   const auto col = gp(I.sw_col);
   const auto yv = gp((T*)I.kv) + (int64_t)I.km * 2 * I.nu;
   const auto z = gp((T*)I.kz);
@@ -760,12 +762,12 @@ __global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, co
   double a0 = 0.0, a1 = 0.0;
   for (int e = inf.y + lane; e < inf.z; e += 4 * G) {
     int c[4];
-    Blk<T> B[4];
+    Blk<double> B[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int q = e + u * G < inf.z ? e + u * G : e;
       c[u] = col[q];
-      B[u] = ld_blk<T>(V, q);
+      B[u] = ld_blk<double>(V, q);
     }
     double x0[4], x1[4];
 #pragma unroll
@@ -779,8 +781,8 @@ __global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, co
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (e + u * G < inf.z) {
-        a0 += (double)B[u].a * x0[u] + (double)B[u].b * x1[u];
-        a1 += (double)B[u].c * x0[u] + (double)B[u].d * x1[u];
+        a0 += B[u].a * x0[u] + B[u].b * x1[u];
+        a1 += B[u].c * x0[u] + B[u].d * x1[u];
       }
   }
   a0 = group_add<G>(a0);

@@ -449,6 +449,49 @@ bool Batch::build_ilu() {
   return ok;
 }
 
+template <typename T>
+void precond_setup(Batch* b, bool ilu) {
+  hipStream_t s = b->stream;
+  const auto* I = b->d_insts;
+  if (ilu) {
+    for (const auto& l : b->f_seg)
+      pfd::launch_ilu_factor<T>(s, I, b->d_fdesc + l.first, l.second, b->d_ftgt, b->d_flev);
+    pfd::launch_ilu_scale<T>(s, I, b->nslots, b->max_kchunks);
+    for (const auto& l : b->s_step) pfd::launch_sweep_values<T>(s, I, b->d_swork + l.first, l.second);
+  } else {
+    pfd::launch_bj_inv<T>(s, I, b->d_kwork + b->k_blocks.first, b->k_blocks_big,
+                          b->k_blocks.second - b->k_blocks_big);
+  }
+}
+
+template <typename T>
+void precond_apply(Batch* b, bool ilu, int mode) {
+  hipStream_t s = b->stream;
+  const auto* I = b->d_insts;
+  const int ns = b->nslots;
+  if (ilu) {
+    auto part = [&](const std::pair<int64_t, int>& l, int upper) {
+      if (ns == 1)
+        pfd::launch_sweep_part<T>(s, I, nullptr, (int)l.first, l.second, upper, mode);
+      else
+        pfd::launch_sweep_part<T>(s, I, b->d_swork + l.first, 0, l.second, upper, mode);
+    };
+    for (const auto& l : b->s_low) part(l, 0);
+    for (const auto& l : b->s_up) part(l, 1);
+    // the instances without a plan, by levels
+    if (b->s_narrow) pfd::launch_ilu_apply_wg<T>(s, I, ns, mode, b->s_min_nu, b->s_max_nu);
+    for (const auto& l : b->s_lev) pfd::launch_ilu_fwd<T>(s, I, b->d_swork + l.first, l.second, mode);
+    for (const auto& l : b->s_ulev) pfd::launch_ilu_bwd<T>(s, I, b->d_swork + l.first, l.second, mode);
+  } else {
+    pfd::launch_bj_apply<T>(s, I, b->d_kwork + b->k_blocks.first, b->k_blocks_big, b->k_blocks.second, mode);
+  }
+}
+
+template void precond_setup<double>(Batch*, bool);
+template void precond_setup<float>(Batch*, bool);
+template void precond_apply<double>(Batch*, bool, int);
+template void precond_apply<float>(Batch*, bool, int);
+
 namespace {
 
 template <typename T>
@@ -469,21 +512,13 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
   ko.max_restarts = opt->gmres_max_restarts;
   const bool ilu = opt->precond == PF_PRECOND_ILU0;
   const int ns = b->nslots, mc = b->max_kchunks;
-  const int2* kw = b->d_kwork;
   {
     Prof p(ctx, PF_K_JFILL, 0.0, 0.0);
     pfd::launch_kfill<T>(s, I, ns, b->max_nnz, ilu ? 1 : 0);
   }
   {
     Prof p(ctx, PF_K_PRECOND_SETUP, 0.0, 0.0);
-    if (ilu) {
-      for (const auto& l : b->f_seg)
-        pfd::launch_ilu_factor<T>(s, I, b->d_fdesc + l.first, l.second, b->d_ftgt, b->d_flev);
-      pfd::launch_ilu_scale<T>(s, I, ns, mc);
-      for (const auto& l : b->s_step) pfd::launch_sweep_values<T>(s, I, b->d_swork + l.first, l.second);
-    } else {
-      pfd::launch_bj_inv<T>(s, I, kw + b->k_blocks.first, b->k_blocks_big, b->k_blocks.second - b->k_blocks_big);
-    }
+    precond_setup<T>(b, ilu);
   }
   const bool bcg = opt->solver == PF_SOLVER_BICGSTAB;
   {
@@ -497,22 +532,7 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
   }
   auto apply = [&](int mode) {
     Prof p(ctx, PF_K_PRECOND_APPLY, 0.0, 0.0);
-    if (ilu) {
-      auto part = [&](const std::pair<int64_t, int>& l, int upper) {
-        if (ns == 1)
-          pfd::launch_sweep_part<T>(s, I, nullptr, (int)l.first, l.second, upper, mode);
-        else
-          pfd::launch_sweep_part<T>(s, I, b->d_swork + l.first, 0, l.second, upper, mode);
-      };
-      for (const auto& l : b->s_low) part(l, 0);
-      for (const auto& l : b->s_up) part(l, 1);
-      // the instances without a plan, by levels
-      if (b->s_narrow) pfd::launch_ilu_apply_wg<T>(s, I, ns, mode, b->s_min_nu, b->s_max_nu);
-      for (const auto& l : b->s_lev) pfd::launch_ilu_fwd<T>(s, I, b->d_swork + l.first, l.second, mode);
-      for (const auto& l : b->s_ulev) pfd::launch_ilu_bwd<T>(s, I, b->d_swork + l.first, l.second, mode);
-    } else {
-      pfd::launch_bj_apply<T>(s, I, kw + b->k_blocks.first, b->k_blocks_big, b->k_blocks.second, mode);
-    }
+    precond_apply<T>(b, ilu, mode);
   };
   // Iterations (BiCGStab) or Arnoldi steps (GMRES) queued per read of the
   // instances' Krylov states: first as many as the inner solve at this

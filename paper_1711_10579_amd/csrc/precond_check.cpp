@@ -5,14 +5,16 @@
 // factor or block-Jacobi group inverses), copies the results back and checks
 // them on the host against their definitions: ILU(0) reproduces A on its
 // pattern, (L U)_ij = A_ij, with U's inverted diagonal blocks the inverses of
-// U's diagonal; a block-Jacobi group's inverse X satisfies A_bb X = I.  A test
-// of the kernels; the solve path never calls it.
+// U's diagonal; a block-Jacobi group's inverse X satisfies A_bb X = I.  And a
+// check of an ILU(0) application against the factor it was set up from.  Tests
+// of the kernels; the solve path never calls them.
 
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <random>
 #include <vector>
 
 #include "../../include/pf_debug.h"
@@ -71,13 +73,7 @@ extern "C" pf_status pf_debug_precond_check(pf_case* c, int32_t precond, double*
   hipStream_t s = b.stream;
   const bool ilu = precond == PF_PRECOND_ILU0;
   pfd::launch_kfill<double>(s, b.d_insts, 1, b.max_nnz, ilu ? 1 : 0);
-  if (ilu) {
-    for (const auto& l : b.f_seg)
-      pfd::launch_ilu_factor<double>(s, b.d_insts, b.d_fdesc + l.first, l.second, b.d_ftgt, b.d_flev);
-    pfd::launch_ilu_scale<double>(s, b.d_insts, 1, b.max_kchunks);
-  } else
-    pfd::launch_bj_inv<double>(s, b.d_insts, b.d_kwork + b.k_blocks.first, b.k_blocks_big,
-                                b.k_blocks.second - b.k_blocks_big);
+  precond_setup<double>(&b, ilu);
   st = launch_status("pf_debug_precond_check");
   if (st != PF_OK) return st;
   const pfh::KAnalysis& ka = *c->ka;
@@ -170,4 +166,124 @@ extern "C" pf_status pf_debug_precond_check(pf_case* c, int32_t precond, double*
   *deviation = dev;
   *max_order = order;
   return PF_OK;
+}
+
+namespace {
+
+// Both triangles row by row in FP64 from the factor P and its inverted diagonal
+// blocks D, every row's result held in S.
+template <typename T, typename S>
+std::vector<double> row_solves(const pfh::KAnalysis& ka, const std::vector<T>& P, const std::vector<T>& D,
+                               const std::vector<T>& w) {
+  std::vector<S> x(w.begin(), w.end());
+  auto sub = [&](int q0, int q1, double* a) {
+    for (int q = q0; q < q1; ++q) {
+      const S* v = &x[2 * (size_t)ka.col[q]];
+      const T* B = &P[4 * (size_t)q];
+      a[0] -= (double)B[0] * (double)v[0] + (double)B[1] * (double)v[1];
+      a[1] -= (double)B[2] * (double)v[0] + (double)B[3] * (double)v[1];
+    }
+  };
+  for (int r = 0; r < ka.nu; ++r) {
+    double a[2] = {(double)x[2 * r], (double)x[2 * r + 1]};
+    sub(ka.row_ptr[r], ka.diag[r], a);
+    x[2 * r] = (S)a[0];
+    x[2 * r + 1] = (S)a[1];
+  }
+  for (int r = ka.nu - 1; r >= 0; --r) {
+    double a[2] = {(double)x[2 * r], (double)x[2 * r + 1]};
+    sub(ka.diag[r] + 1, ka.row_ptr[r + 1], a);
+    const T* B = &D[4 * (size_t)r];
+    x[2 * r] = (S)((double)B[0] * a[0] + (double)B[1] * a[1]);
+    x[2 * r + 1] = (S)((double)B[2] * a[0] + (double)B[3] * a[1]);
+  }
+  return {x.begin(), x.end()};
+}
+
+template <typename T>
+pf_status sweep_check(Case* c, Batch* b, uint64_t seed, double* dev, double* dev_levels) {
+  hipStream_t s = b->stream;
+  pfd::launch_kfill<T>(s, b->d_insts, 1, b->max_nnz, 1);
+  precond_setup<T>(b, true);
+  const pfh::KAnalysis& ka = *c->ka;
+  const int nu = ka.nu;
+  const pfd::Inst& h = c->hinst;
+  // a random input, the instance in the state that takes an application (the
+  // first half of a BiCGStab iteration)
+  std::vector<T> w(2 * (size_t)nu), z(2 * (size_t)nu), P(4 * (size_t)ka.nnz()), D(4 * (size_t)nu);
+  std::mt19937_64 rng(seed);
+  std::normal_distribution<double> normal;
+  for (T& x : w) x = (T)normal(rng);
+  pfd::KState ks;
+  bool ok = hipMemcpyAsync(&ks, h.ks, sizeof ks, hipMemcpyDeviceToHost, s) == hipSuccess;
+  ok &= hipStreamSynchronize(s) == hipSuccess;
+  ks.state = pfd::KS_BP;
+  ok &= hipMemcpyAsync(h.ks, &ks, sizeof ks, hipMemcpyHostToDevice, s) == hipSuccess;
+  ok &= hipMemcpyAsync(h.kw, w.data(), sizeof(T) * w.size(), hipMemcpyHostToDevice, s) == hipSuccess;
+  precond_apply<T>(b, true, 2);
+  ok &= hipMemcpyAsync(z.data(), h.kz, sizeof(T) * z.size(), hipMemcpyDeviceToHost, s) == hipSuccess;
+  ok &= hipMemcpyAsync(P.data(), h.pval, sizeof(T) * P.size(), hipMemcpyDeviceToHost, s) == hipSuccess;
+  ok &= hipMemcpyAsync(D.data(), h.pdinv, sizeof(T) * D.size(), hipMemcpyDeviceToHost, s) == hipSuccess;
+  pfd::Red red;
+  ok &= hipMemcpyAsync(&red, c->red, sizeof red, hipMemcpyDeviceToHost, s) == hipSuccess;
+  ks.state = pfd::KS_DONE;
+  ok &= hipStreamSynchronize(s) == hipSuccess;
+  ok &= hipMemcpyAsync(h.ks, &ks, sizeof ks, hipMemcpyHostToDevice, s) == hipSuccess;
+  ok &= hipStreamSynchronize(s) == hipSuccess;
+  const pf_status st = launch_status("pf_debug_sweep_check");
+  if (st != PF_OK) return st;
+  if (!ok) {
+    set_error("pf_debug_sweep_check: device failure");
+    return PF_E_DEVICE;
+  }
+  if (red.singular || !red.active) {
+    set_error("pf_debug_sweep_check: a singular pivot, or no mismatch at the flat start");
+    return PF_E_INVALID;
+  }
+  const std::vector<double> ref = row_solves<T, double>(ka, P, D, w), lev = row_solves<T, T>(ka, P, D, w);
+  double n2 = 0, e2 = 0, l2 = 0;
+  for (size_t i = 0; i < ref.size(); ++i) {
+    n2 += ref[i] * ref[i];
+    e2 += ((double)z[i] - ref[i]) * ((double)z[i] - ref[i]);
+    l2 += (lev[i] - ref[i]) * (lev[i] - ref[i]);
+  }
+  *dev = std::sqrt(e2 / n2);
+  *dev_levels = std::sqrt(l2 / n2);
+  return PF_OK;
+}
+
+}  // namespace
+
+extern "C" pf_status pf_debug_sweep_check(pf_case* c, int32_t precision, uint64_t seed, double* deviation,
+                                          double* level_deviation, int32_t* parts) {
+  if (!c || !deviation || !level_deviation || !parts ||
+      (precision != PF_PREC_FP64 && precision != PF_PREC_MIXED)) {
+    set_error("pf_debug_sweep_check: bad argument");
+    return PF_E_INVALID;
+  }
+  if (c->busy.load()) {
+    set_error("pf_debug_sweep_check: case is queued or running");
+    return PF_E_BUSY;
+  }
+  std::lock_guard<std::mutex> lk(c->ctx->launch_mu);
+  if (hipSetDevice(c->ctx->device) != hipSuccess) {
+    set_error("pf_debug_sweep_check: hipSetDevice failed");
+    return PF_E_DEVICE;
+  }
+  pf_options o;
+  pf_default_options(&o);
+  o.solver = PF_SOLVER_BICGSTAB;
+  o.precond = PF_PRECOND_ILU0;
+  o.flat_start = 1;
+  Batch b;
+  if (!b.build(c->ctx, {c})) {
+    set_error("pf_debug_sweep_check: batch set-up failed");
+    return PF_E_NOMEM;
+  }
+  const pf_status st = start_batch(&b, &o);
+  if (st != PF_OK) return st;
+  parts[0] = (int32_t)b.s_low.size();
+  parts[1] = (int32_t)b.s_up.size();
+  return precision == PF_PREC_MIXED ? sweep_check<float>(c, &b, seed, deviation, level_deviation)
+                                    : sweep_check<double>(c, &b, seed, deviation, level_deviation);
 }
