@@ -79,6 +79,10 @@ pf_status pf_debug_precond_check(pf_case* c, int32_t precond, double* deviation,
 pf_status pf_debug_sweep_check(pf_case* c, int32_t precision, uint64_t seed, double* deviation,
                                double* level_deviation, int32_t* parts);
 
+/* Give back the pinned memory that pf_get_voltage reads through, as if the
+ * context had got none: its later reads copy through pageable memory. */
+pf_status pf_debug_drop_pinned(pf_ctx* ctx);
+
 #ifdef __cplusplus
 }
 #endif

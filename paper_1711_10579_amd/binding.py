@@ -157,6 +157,7 @@ _sig = {
     "pf_debug_precond_check": (C.c_int, [_P, C.c_int32, C.POINTER(C.c_double), C.POINTER(C.c_int32)]),
     "pf_debug_sweep_check": (C.c_int, [_P, C.c_int32, C.c_uint64, C.POINTER(C.c_double), C.POINTER(C.c_double),
                                        C.POINTER(C.c_int32)]),
+    "pf_debug_drop_pinned": (C.c_int, [_P]),
     "pf_last_error": (C.c_char_p, []),
     "pf_version": (C.c_char_p, []),
 }
@@ -390,6 +391,11 @@ def pf_debug_sweep_check(case, precision, seed=0):
     _check(_lib.pf_debug_sweep_check(case.handle, int(precision), C.c_uint64(seed), C.byref(dev), C.byref(lev),
                                      parts), "pf_debug_sweep_check")
     return dev.value, lev.value, tuple(parts)
+
+
+def pf_debug_drop_pinned(ctx):
+    """Make the context read voltages without pinned memory (include/pf_debug.h)."""
+    _check(_lib.pf_debug_drop_pinned(ctx.handle), "pf_debug_drop_pinned")
 
 
 def pf_create_from(ctx, case, schedule=None):

@@ -15,6 +15,7 @@
 #include <system_error>
 #include <vector>
 
+#include "../../include/pf_debug.h"
 #include "internal.hpp"
 #include "kernels.hpp"
 
@@ -349,6 +350,17 @@ pf_status pf_ctx_create(int32_t device, void* hip_stream, pf_alloc_fn alloc, pf_
       return PF_E_DEVICE;
     }
     c->own_stream = true;
+  }
+  // the pinned halves of pf_get_voltage, here so that reading allocates
+  // nothing; without them it copies through pageable memory
+  void* hp = nullptr;
+  if (hipHostMalloc(&hp, 4 * sizeof(double) * kVoltChunk + 2 * sizeof(unsigned long long) * kVoltBlocks,
+                    hipHostMallocCoherent) == hipSuccess) {
+    c->h_volt = (double*)hp;
+    c->h_vflag = (unsigned long long*)(c->h_volt + 4 * kVoltChunk);
+    std::memset(c->h_vflag, 0, 2 * sizeof(unsigned long long) * kVoltBlocks);
+  } else {
+    (void)hipGetLastError();
   }
   *out = c;
   return PF_OK;
@@ -1012,12 +1024,15 @@ pf_status pf_set_injections(pf_case* c, const double* p_sp, const double* q_sp, 
 // 940 -> 320 us.
 static pf_status read_volt(Ctx* ctx, const double* v, int n, double* re, double* im) {
   hipStream_t s = ctx->stream;
-  if (!ctx->h_volt) {
-    void* hp = nullptr;
-    PF_HIP(hipHostMalloc(&hp, 4 * sizeof(double) * kVoltChunk + 2 * sizeof(unsigned long long) * kVoltBlocks, hipHostMallocCoherent));
-    ctx->h_volt = (double*)hp;
-    ctx->h_vflag = (unsigned long long*)(ctx->h_volt + 4 * kVoltChunk);
-    std::memset(ctx->h_vflag, 0, 2 * sizeof(unsigned long long) * kVoltBlocks);
+  if (!ctx->h_volt) {  // the context got no pinned memory
+    std::vector<double> p(2 * (size_t)n);
+    PF_HIP(hipMemcpyAsync(p.data(), v, sizeof(double) * p.size(), hipMemcpyDeviceToHost, s));
+    PF_HIP(hipStreamSynchronize(s));
+    for (int i = 0; i < n; ++i) {
+      re[i] = p[2 * (size_t)i];
+      im[i] = p[2 * (size_t)i + 1];
+    }
+    return PF_OK;
   }
   const int nc = (n + kVoltChunk - 1) / kVoltChunk;
   const unsigned long long seq = ctx->volt_seq + 1;  // of chunk 0
@@ -1065,6 +1080,18 @@ pf_status pf_get_voltage(const pf_case* c, double* re, double* im) {
   const pf_status st = read_volt(ctx, c->v, c->n, re, im);
   if (dev != ctx->device) (void)hipSetDevice(dev);
   return st;
+}
+
+pf_status pf_debug_drop_pinned(pf_ctx* ctx) {
+  if (!ctx) {
+    set_error("pf_debug_drop_pinned: NULL context");
+    return PF_E_INVALID;
+  }
+  std::lock_guard<std::mutex> lk(ctx->volt_mu);
+  if (ctx->h_volt) PF_HIP(hipHostFree(ctx->h_volt));
+  ctx->h_volt = nullptr;
+  ctx->h_vflag = nullptr;
+  return PF_OK;
 }
 
 pf_status pf_set_voltage(pf_case* c, const double* re, const double* im) {

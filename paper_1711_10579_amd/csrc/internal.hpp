@@ -63,7 +63,8 @@ struct Ctx {
   std::mutex tune_mu;
   std::map<uint64_t, pf_schedule> tuned;  // topology hash -> autotuned schedule
   // pf_get_voltage: two pinned halves of kVoltChunk nodes (real | imaginary
-  // parts), the flags of their blocks, and the last launch's flag value
+  // parts; null when the context got no pinned memory), the flags of their
+  // blocks, and the last launch's flag value
   std::mutex volt_mu;
   double* h_volt = nullptr;
   unsigned long long* h_vflag = nullptr;
