@@ -288,32 +288,43 @@ bool ensure_sweep(Case* c) {
   const size_t total = carve_bytes<int4>(2 * nu) + carve_bytes<int>(ne) + carve_bytes<int>(ne + 1) +
                        carve_bytes<int2>(nops);
   Ctx* ctx = c->ctx;
-  c->swbase = (char*)ctx->dalloc(total);
-  if (!c->swbase) {  // without room for the lists the sweeps go by levels
+  char* base = (char*)ctx->dalloc(total);
+  if (!base) {  // without room for the lists the sweeps go by levels
+    (void)hipGetLastError();  // else the next launch would be held to have failed
     c->sw = pfh::KSweep();
     c->sw_state = Case::SW_NONE;
     return true;
   }
   // the four lists packed on the host as on the device: one copy
   std::vector<char> pack(total);
-  char *p = c->swbase, *q = pack.data();
+  char* p = base;
   auto put = [&](const std::vector<int>& src) {
-    if (!src.empty()) std::memcpy(q + (p - c->swbase), src.data(), sizeof(int) * src.size());
+    if (!src.empty()) std::memcpy(pack.data() + (p - base), src.data(), sizeof(int) * src.size());
     return (const int*)carve<int>(p, (int64_t)src.size());
   };
-  pfd::Inst& h = c->hinst;
+  pfd::Inst h = c->hinst;
   h.sw_rows = (const int4*)put(c->sw.rows);
   h.sw_col = put(c->sw.col);
   h.sw_op_ptr = put(c->sw.op_ptr);
   h.sw_ops = (const int2*)put(c->sw.ops);
   hipStream_t s = ctx->stream;
-  bool ok = hipMemcpyAsync(c->swbase, pack.data(), total, hipMemcpyHostToDevice, s) == hipSuccess;
-  pfd::launch_set_inst(s, c->d_inst, h);
-  ok &= hipStreamSynchronize(s) == hipSuccess;
+  bool ok = hipMemcpyAsync(base, pack.data(), total, hipMemcpyHostToDevice, s) == hipSuccess;
+  if (ok) pfd::launch_set_inst(s, c->d_inst, h);
+  ok &= hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
+  if (!ok) {  // nothing of the plan stays: the kernels index with these lists
+    pfd::launch_set_inst(s, c->d_inst, c->hinst);
+    (void)hipStreamSynchronize(s);
+    (void)hipGetLastError();
+    ctx->dfree(base);
+    c->sw = pfh::KSweep();
+    return false;
+  }
+  c->hinst = h;
+  c->swbase = base;
   // the launch lists need the plan's rows and steps only
   c->sw.col = c->sw.op_ptr = c->sw.ops = std::vector<int>();
   c->sw_state = Case::SW_PLAN;
-  return ok;
+  return true;
 }
 
 namespace {
