@@ -181,7 +181,8 @@ typedef struct {
   int64_t tail_updates; /* 2x2 block updates into the dense trailing block   */
   double flops_factor;  /* algorithmic flops of one refactorisation          */
   size_t device_bytes;  /* device memory the case holds now (resident, plus its
-                           own working and Krylov storage once allocated)    */
+                           own working and Krylov storage once allocated);
+                           its launch plans: pf_case_plan_bytes              */
   double analysis_ms;   /* host analysis time in pf_create                   */
   size_t resident_bytes;/* Ybus, index lists, set-points, state: from
                            pf_create to pf_destroy                           */
@@ -280,6 +281,13 @@ pf_status pf_case_info_get(const pf_case* c, pf_case_info* out);
  * kept; a served request borrows it from the serving pool instead (see
  * pf_serve_config).  Host output; PF_E_INVALID on NULL. */
 pf_status pf_case_footprint(const pf_case* c, size_t* bytes);
+/* Device memory of the case's launch plans, which no size above counts: *bytes
+ * = the work lists of its own solves (from its first pf_solve or pf_submit;
+ * more from its first Newton-Krylov solve) and the index lists of its ILU(0)
+ * sweeps (from its first ILU(0) solve; 2.7 MB at 10,000 buses, 13.7 MB at
+ * 48,000).  Kept to pf_destroy and not taken from the serving pool's budget.
+ * Host output; PF_E_INVALID on NULL. */
+pf_status pf_case_plan_bytes(const pf_case* c, size_t* bytes);
 
 /* Replace the specified injections (same topology): p_sp/q_sp as in
  * pf_case_desc (NULL keeps the old values), zip [6n] for CIM (NULL keeps). */

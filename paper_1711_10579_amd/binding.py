@@ -134,6 +134,7 @@ _sig = {
     "pf_destroy": (C.c_int, [_P]),
     "pf_case_info_get": (C.c_int, [_P, C.POINTER(pf_case_info)]),
     "pf_case_footprint": (C.c_int, [_P, C.POINTER(C.c_size_t)]),
+    "pf_case_plan_bytes": (C.c_int, [_P, C.POINTER(C.c_size_t)]),
     "pf_set_injections": (C.c_int, [_P, C.POINTER(C.c_double), C.POINTER(C.c_double),
                                     C.POINTER(C.c_double)]),
     "pf_solve": (C.c_int, [_P, C.POINTER(pf_options), C.POINTER(pf_result)]),
@@ -430,6 +431,13 @@ def pf_case_info_get(case):
     info = pf_case_info()
     _check(_lib.pf_case_info_get(case.handle, C.byref(info)), "pf_case_info_get")
     return info.as_dict()
+
+
+def pf_case_plan_bytes(case):
+    """Device bytes of the case's launch plans (in none of pf_case_info's sizes)."""
+    b = C.c_size_t()
+    _check(_lib.pf_case_plan_bytes(case.handle if case is not None else None, C.byref(b)), "pf_case_plan_bytes")
+    return b.value
 
 
 def pf_case_footprint(case):

@@ -979,6 +979,15 @@ pf_status pf_case_info_get(const pf_case* c, pf_case_info* o) {
   return PF_OK;
 }
 
+pf_status pf_case_plan_bytes(const pf_case* c, size_t* bytes) {
+  if (!c || !bytes) {
+    set_error("pf_case_plan_bytes: NULL argument");
+    return PF_E_INVALID;
+  }
+  *bytes = c->swbytes + (c->single ? c->single->bytes() : 0);
+  return PF_OK;
+}
+
 pf_status pf_case_footprint(const pf_case* c, size_t* bytes) {
   if (!c || !bytes) {
     set_error("pf_case_footprint: NULL argument");

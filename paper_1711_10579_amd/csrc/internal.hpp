@@ -161,6 +161,7 @@ struct Case {
   enum { SW_NEW = 0, SW_NONE, SW_PLAN } sw_state = SW_NEW;
   pfh::KSweep sw;
   char* swbase = nullptr;
+  size_t swbytes = 0;
 
   int64_t lu_count() const { return 4LL * (an.ns + 2 * an.nnzl); }
   int64_t tail_count() const { return (int64_t)an.ldt * (M + 1); }
@@ -191,6 +192,8 @@ struct Batch {
   std::vector<Case*> cases;
   int nslots = 0;
   char* dmem = nullptr;  // instance pointer table, work items
+  size_t dbytes = 0, kbytes = 0, sbytes = 0;  // of dmem, kmem, smem
+  size_t bytes() const { return dbytes + kbytes + sbytes; }
   // what the kernels take: the table, or for a batch of one its descriptor's
   // address marked by the low bit
   const pfd::Inst* const* d_insts = nullptr;

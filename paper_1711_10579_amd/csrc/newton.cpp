@@ -51,6 +51,7 @@ bool Batch::build(Ctx* cx, const std::vector<Case*>& cs) {
   // device buffer: instance table | work items
   dmem = (char*)ctx->dalloc(plan_bytes(work.size()));
   if (!dmem) return false;
+  dbytes = plan_bytes(work.size());
   {
     void* hp = nullptr;
     const size_t hr = (sizeof(pfd::Red) * std::max(nslots, 1) + 255) & ~(size_t)255;

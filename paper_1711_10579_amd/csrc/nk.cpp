@@ -265,6 +265,7 @@ bool Batch::build_krylov() {
   const size_t bw = (sizeof(int2) * std::max<size_t>(work.size(), 1) + 255) & ~(size_t)255;
   if (kmem) ctx->dfree(kmem);
   kmem = (char*)ctx->dalloc(bw);
+  kbytes = kmem ? bw : 0;
   if (!kmem) return false;
   d_kwork = (int2*)kmem;
   hipStream_t st = stream;
@@ -321,6 +322,7 @@ bool ensure_sweep(Case* c) {
   }
   c->hinst = h;
   c->swbase = base;
+  c->swbytes = total;
   // the launch lists need the plan's rows and steps only
   c->sw.col = c->sw.op_ptr = c->sw.ops = std::vector<int>();
   c->sw_state = Case::SW_PLAN;
@@ -441,6 +443,7 @@ bool Batch::build_ilu() {
                        carve_bytes<int>((int64_t)tgt.size()) + carve_bytes<int>((int64_t)lev.size());
   if (smem) ctx->dfree(smem);
   smem = (char*)ctx->dalloc(std::max<size_t>(total, 256));
+  sbytes = smem ? std::max<size_t>(total, 256) : 0;
   if (!smem) return false;
   std::vector<char> pack(total);
   char* p = smem;

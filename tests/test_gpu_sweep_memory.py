@@ -1,6 +1,8 @@
 """GPU test of the ILU(0) sweep lists' device memory, through a context with
 allocator callbacks: a case whose lists get no memory sweeps by levels, also
-when the refused allocation leaves an error behind in the HIP runtime.
+when the refused allocation leaves an error behind in the HIP runtime; and every
+byte a case has allocated is in pf_case_info's device_bytes or, for its launch
+plans, in pf_case_plan_bytes.
 """
 
 import ctypes
@@ -76,3 +78,30 @@ def test_lists_refused():
         h.close()
         ctx.close()
         assert not live
+
+
+@pytest.mark.parametrize("n", [300, 2399])
+def test_every_byte_is_reported(n):
+    from paper_1711_10579_amd import binding as B
+
+    ctx, live, _ = _context(B, lambda k: False)
+    h = B.pf_create_from(ctx, _mesh(n))
+
+    def held():
+        return B.pf_case_info_get(h)["device_bytes"] + B.pf_case_plan_bytes(h)
+
+    assert B.pf_case_plan_bytes(h) == 0 and held() == sum(live.values())
+    last = 0
+    for opt in (dict(), dict(solver=B.PF_SOLVER_BICGSTAB, precond=B.PF_PRECOND_BJACOBI),
+                dict(solver=B.PF_SOLVER_BICGSTAB, precond=B.PF_PRECOND_ILU0)):
+        print(f"{n} buses, {opt}", flush=True)
+        for _ in range(2):
+            assert B.pf_solve(h, max_iter=40, **opt).status == B.PF_CONVERGED
+            assert held() == sum(live.values())
+        assert B.pf_case_plan_bytes(h) > last
+        last = B.pf_case_plan_bytes(h)
+    info = B.pf_case_info_get(h)
+    assert info["device_bytes"] == info["resident_bytes"] + info["work_bytes"] + info["krylov_bytes"]
+    h.close()
+    assert not live
+    ctx.close()
