@@ -214,13 +214,13 @@ KAnalysis analyze_krylov(const Analysis& an, int n, const int* row_ptr, const in
 void factor_targets(const KAnalysis& ka, std::vector<int>* ptr, std::vector<int>* tgt);
 
 // Merge the sweep levels into parts whose rows have at most `cap` entries
-// each (the rows of a level on its own may have more); false, and the plan
-// unusable, past max_entries.
-bool build_sweep(const KAnalysis& ka, int cap, int64_t max_entries, KSweep* out);
+// each (the rows of a level on its own may have more), the two triangles on
+// up to `threads` threads; false, and the plan unusable, past max_entries.
+bool build_sweep(const KAnalysis& ka, int cap, int64_t max_entries, KSweep* out, int threads = 1);
 // The plan the solver uses, chosen from the case alone; `wide`: without a
 // plan the sweeps take one launch per level.  False when no plan of at most
 // max_entries entries beats the level sweeps.
-bool plan_sweep(const KAnalysis& ka, bool wide, int64_t max_entries, KSweep* out);
+bool plan_sweep(const KAnalysis& ka, bool wide, int64_t max_entries, KSweep* out, int threads = 1);
 
 // Ybus entry -> block position in the Krylov pattern, -1 when the row or the
 // column node has no unknowns.

@@ -156,9 +156,10 @@ struct Case {
   bool kown = false;  // false: lent by the serving loop for one request
   int km = 0;         // restart length the storage holds
   std::vector<int4> k_linfo, k_uinfo;  // per level position {row, first, end, 0}
-  // ILU(0) sweeps in parts: made by the case's first ILU(0) solve; its index
-  // lists are launch-plan memory of the case's own (freed with the case)
-  enum { SW_NEW = 0, SW_NONE, SW_PLAN } sw_state = SW_NEW;
+  // ILU(0) sweeps in parts: made by the case's first ILU(0) solve (SW_HOST:
+  // not on the device yet; SW_NONE: the sweeps go by levels); its index lists
+  // are launch-plan memory of the case's own (freed with the case)
+  enum { SW_NEW = 0, SW_NONE, SW_HOST, SW_PLAN } sw_state = SW_NEW;
   pfh::KSweep sw;
   char* swbase = nullptr;
   size_t swbytes = 0;
@@ -243,6 +244,12 @@ struct Batch {
   // rows padded to whole work-groups of one instance each; rows by forward
   // and by backward level of the instances that take a launch per level
   bool sbuilt = false;
+  // per case, between plan_ilu and build_ilu: the factor's targets by level,
+  // the plan's positions by step
+  struct IluHost {
+    std::vector<int> ptr, tgt, step_ptr, step_pos;
+  };
+  std::vector<IluHost> ilu_host;
   char* smem = nullptr;
   int2* d_swork = nullptr;
   std::vector<std::pair<int64_t, int>> f_seg;
@@ -263,6 +270,9 @@ struct Batch {
   size_t plan_bytes(size_t nwork) const;
   bool place(char* mem, const std::vector<int2>& work);
   bool build_krylov();
+  // the host's share of build_ilu, without a device call: the cases' sweep
+  // plans, factor targets and value steps (false: out of memory)
+  bool plan_ilu();
   bool build_ilu();
 };
 
@@ -287,10 +297,6 @@ void free_krylov(Case* c);
 // detach_krylov), launched on stream s (no synchronisation).
 size_t krylov_bytes(const Case* c, int m);
 bool krylov_wide(const pfh::KAnalysis& ka);
-// The sweep plan of a case's ILU(0) preconditioner: made (host work, one
-// device allocation) on first use; SW_NONE where the sweeps go by levels.
-// False on a device failure.
-bool ensure_sweep(Case* c);
 bool attach_krylov(Case* c, int m, char* base, bool own, hipStream_t s);
 void detach_krylov(Case* c);
 // Working storage of a solve: its size, its set-up in the given memory on

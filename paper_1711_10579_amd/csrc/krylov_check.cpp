@@ -286,7 +286,7 @@ extern "C" pf_status pf_debug_krylov_check(const pf_case_desc* d, uint64_t seed,
     double part_dev = 0;
     for (int cap : {64, 32, 16, 2}) {
       pfh::KSweep sw;
-      req(pfh::build_sweep(ka, cap, INT64_MAX, &sw), "sweep plan refused");
+      req(pfh::build_sweep(ka, cap, INT64_MAX, &sw, 2), "sweep plan refused");
       const int np = sw.nlp + sw.nup;
       const int64_t ne = sw.ne();
       req((int)sw.part_ptr.size() == np + 1 && sw.part_ptr[0] == 0 && sw.part_ptr[np] == 2 * nu &&

@@ -14,6 +14,7 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "parallel.hpp"
 
 namespace pfi {
 
@@ -277,55 +278,111 @@ bool Batch::build_krylov() {
   return ok;
 }
 
-bool ensure_sweep(Case* c) {
-  if (c->sw_state != Case::SW_NEW) return true;
-  const pfh::KAnalysis& ka = *c->ka;
-  // the entry values take the place of the block-Jacobi inverses
-  if (!pfh::plan_sweep(ka, krylov_wide(ka), ka.bj_off.back() / 4, &c->sw)) {
-    c->sw_state = Case::SW_NONE;
-    return true;
-  }
-  const int64_t nu = ka.nu, ne = c->sw.ne(), nops = c->sw.nops();
-  const size_t total = carve_bytes<int4>(2 * nu) + carve_bytes<int>(ne) + carve_bytes<int>(ne + 1) +
-                       carve_bytes<int2>(nops);
-  Ctx* ctx = c->ctx;
-  char* base = (char*)ctx->dalloc(total);
-  if (!base) {  // without room for the lists the sweeps go by levels
-    (void)hipGetLastError();  // else the next launch would be held to have failed
-    c->sw = pfh::KSweep();
-    c->sw_state = Case::SW_NONE;
-    return true;
-  }
-  // the four lists packed on the host as on the device: one copy
-  std::vector<char> pack(total);
-  char* p = base;
-  auto put = [&](const std::vector<int>& src) {
-    if (!src.empty()) std::memcpy(pack.data() + (p - base), src.data(), sizeof(int) * src.size());
-    return (const int*)carve<int>(p, (int64_t)src.size());
+namespace {
+
+// The index lists of the cases' sweep plans on the device, with one
+// synchronisation for all; a case that gets no memory sweeps by levels.
+// False on a device failure: nothing of these plans stays, since the kernels
+// index with the lists.
+bool upload_sweeps(const std::vector<Case*>& cases, hipStream_t s) {
+  struct Up {
+    Case* c;
+    char* base;
+    size_t bytes;
+    pfd::Inst h;
   };
-  pfd::Inst h = c->hinst;
-  h.sw_rows = (const int4*)put(c->sw.rows);
-  h.sw_col = put(c->sw.col);
-  h.sw_op_ptr = put(c->sw.op_ptr);
-  h.sw_ops = (const int2*)put(c->sw.ops);
-  hipStream_t s = ctx->stream;
-  bool ok = hipMemcpyAsync(base, pack.data(), total, hipMemcpyHostToDevice, s) == hipSuccess;
-  if (ok) pfd::launch_set_inst(s, c->d_inst, h);
+  std::vector<Up> ups;
+  bool ok = true;
+  for (Case* c : cases) {
+    if (c->sw_state != Case::SW_HOST) continue;
+    const int64_t nu = c->ka->nu, ne = c->sw.ne(), nops = c->sw.nops();
+    Up u;
+    u.c = c;
+    u.bytes = carve_bytes<int4>(2 * nu) + carve_bytes<int>(ne) + carve_bytes<int>(ne + 1) + carve_bytes<int2>(nops);
+    u.base = (char*)c->ctx->dalloc(u.bytes);
+    if (!u.base) {
+      (void)hipGetLastError();  // else the next launch would be held to have failed
+      c->sw = pfh::KSweep();
+      c->sw_state = Case::SW_NONE;
+      continue;
+    }
+    u.h = c->hinst;
+    char* p = u.base;
+    auto put = [&](const std::vector<int>& src) {
+      int* d = carve<int>(p, (int64_t)src.size());
+      if (!src.empty())
+        ok &= hipMemcpyAsync(d, src.data(), sizeof(int) * src.size(), hipMemcpyHostToDevice, s) == hipSuccess;
+      return (const int*)d;
+    };
+    u.h.sw_rows = (const int4*)put(c->sw.rows);
+    u.h.sw_col = put(c->sw.col);
+    u.h.sw_op_ptr = put(c->sw.op_ptr);
+    u.h.sw_ops = (const int2*)put(c->sw.ops);
+    if (ok) pfd::launch_set_inst(s, c->d_inst, u.h);
+    ups.push_back(u);
+  }
+  if (ups.empty()) return true;
   ok &= hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
-  if (!ok) {  // nothing of the plan stays: the kernels index with these lists
-    pfd::launch_set_inst(s, c->d_inst, c->hinst);
-    (void)hipStreamSynchronize(s);
-    (void)hipGetLastError();
-    ctx->dfree(base);
-    c->sw = pfh::KSweep();
+  if (!ok)
+    for (const Up& u : ups) pfd::launch_set_inst(s, u.c->d_inst, u.c->hinst);
+  if (!ok) (void)hipStreamSynchronize(s);
+  if (!ok) (void)hipGetLastError();
+  for (const Up& u : ups) {
+    Case* c = u.c;
+    if (!ok) {
+      c->ctx->dfree(u.base);
+      continue;
+    }
+    c->hinst = u.h;
+    c->swbase = u.base;
+    c->swbytes = u.bytes;
+    // the launch lists need the plan's rows and steps only
+    c->sw.col = c->sw.op_ptr = c->sw.ops = std::vector<int>();
+    c->sw_state = Case::SW_PLAN;
+  }
+  return ok;
+}
+
+}  // namespace
+
+bool Batch::plan_ilu() {
+  int64_t rows = 0;
+  for (Case* c : cases) {
+    if (!c->ka) return false;
+    rows += c->ka->nu;
+  }
+  ilu_host.assign(nslots, IluHost());
+  // a thread pays for itself from some thousands of rows (10,000 buses: 1.7 ms
+  // for the plan of a case, 0.3 ms for its targets)
+  const int threads = (int)std::min<int64_t>(8, 1 + rows / 2048);
+  try {
+    pfh::parallel_for(2 * nslots, threads, [&](int i) {
+      Case* c = cases[i / 2];
+      const pfh::KAnalysis& ka = *c->ka;
+      IluHost& h = ilu_host[i / 2];
+      if (i % 2) {
+        pfh::factor_targets(ka, &h.ptr, &h.tgt);
+        return;
+      }
+      // the entry values take the place of the block-Jacobi inverses
+      if (c->sw_state == Case::SW_NEW)
+        c->sw_state = pfh::plan_sweep(ka, krylov_wide(ka), ka.bj_off.back() / 4, &c->sw, nslots == 1 ? 2 : 1)
+                          ? Case::SW_HOST
+                          : Case::SW_NONE;
+      if (c->sw_state == Case::SW_NONE) return;
+      // the positions by their step
+      const auto& step = c->sw.step;
+      h.step_ptr.assign(c->sw.nsteps + 1, 0);
+      for (int t : step) h.step_ptr[t + 1]++;
+      for (int t = 0; t < c->sw.nsteps; ++t) h.step_ptr[t + 1] += h.step_ptr[t];
+      std::vector<int> fill(h.step_ptr.begin(), h.step_ptr.end() - 1);
+      h.step_pos.resize(step.size());
+      for (int k = 0; k < (int)step.size(); ++k) h.step_pos[fill[step[k]]++] = k;
+    });
+  } catch (const std::exception&) {
+    ilu_host.clear();
     return false;
   }
-  c->hinst = h;
-  c->swbase = base;
-  c->swbytes = total;
-  // the launch lists need the plan's rows and steps only
-  c->sw.col = c->sw.op_ptr = c->sw.ops = std::vector<int>();
-  c->sw_state = Case::SW_PLAN;
   return true;
 }
 
@@ -338,12 +395,16 @@ constexpr int kNarrowTargets = 1536;
 }  // namespace
 
 bool Batch::build_ilu() {
+  if (ilu_host.empty() && !plan_ilu()) return false;
+  const std::vector<IluHost> host = std::move(ilu_host);
+  ilu_host.clear();
+  if (!upload_sweeps(cases, stream)) return false;
   std::vector<int2> work;
   for (auto* v : {&f_seg, &s_low, &s_up, &s_step, &s_lev, &s_ulev}) v->clear();
   s_narrow = false;
   s_min_nu = s_max_nu = 0;
   // factor targets and levels of every instance, its launches' descriptors
-  std::vector<int> tgt, lev, ptr, one;
+  std::vector<int> tgt, lev;
   std::vector<std::vector<int4>> seg;
   int nlp = 0, nup = 0, nst = 0;
   size_t max_l = 0, max_u = 0;
@@ -351,9 +412,8 @@ bool Batch::build_ilu() {
   std::vector<char> by_level(nslots, 0);
   for (int s = 0; s < nslots; ++s) {
     Case* c = cases[s];
-    if (!c->ka || !ensure_sweep(c)) return false;
     const pfh::KAnalysis& ka = *c->ka;
-    pfh::factor_targets(ka, &ptr, &one);
+    const std::vector<int>&ptr = host[s].ptr, &one = host[s].tgt;
     const int t0 = (int)tgt.size(), l0 = (int)lev.size(), nl = (int)ptr.size() - 1;
     tgt.insert(tgt.end(), one.begin(), one.end());
     for (int p : ptr) lev.push_back(t0 + p);
@@ -414,8 +474,9 @@ bool Batch::build_ilu() {
   parts(nup, true, &s_up);
   for (int t = 0; t < nst; ++t)
     list(&s_step, [&](int s, const pfh::KSweep& sw) {
-      for (int k = 0; k < (int)sw.step.size(); ++k)
-        if (sw.step[k] == t) work.push_back(make_int2(s, k));
+      if (t >= sw.nsteps) return;
+      for (int k = host[s].step_ptr[t]; k < host[s].step_ptr[t + 1]; ++k)
+        work.push_back(make_int2(s, host[s].step_pos[k]));
     });
   auto levels = [&](bool upper, size_t nl, std::vector<std::pair<int64_t, int>>* out) {
     for (size_t l = 0; l < nl; ++l) {
