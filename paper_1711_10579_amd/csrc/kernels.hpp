@@ -120,10 +120,12 @@ template <typename T>
 void launch_bcg_begin(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, KOpts o);
 template <typename T>
 void launch_bcg_dir(hipStream_t, const Inst* const* insts, int nslots, int max_chunks);
+// (rows: of all instances)
 template <typename T>
-void launch_bcg_half(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, int it);
+void launch_bcg_half(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, int64_t rows, int it);
 template <typename T>
-void launch_bcg_end(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, KOpts o, int it);
+void launch_bcg_end(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, int64_t rows, KOpts o,
+                    int it);
 void launch_kgather(hipStream_t, const Inst* const* insts, int nslots, int* out);
 int krylov_max_restart();
 

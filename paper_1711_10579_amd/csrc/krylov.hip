@@ -79,20 +79,20 @@ __device__ inline void linear_failure(const IR& I) {
 
 __device__ inline double wave_sum(double v) { return group_add<64>(v); }
 
-// Sums over the NT threads of a work-group of the values f(i) for i <
+// Sums over the KCH threads of a work-group of the values f(i) for i <
 // count, written to out[i] (thread-uniform count).  Fixed reduction order.
-template <int NT = KCH, typename F>
-__device__ inline void block_sums(int count, F f, double (*red)[NT / 64], PF_AS1 double* out) {
+template <typename F>
+__device__ inline void block_sums(int count, F f, double (*red)[KCH / 64], PF_AS1 double* out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i = 0; i < count; ++i) {
     double s = wave_sum(f(i));
     if (lane == 0) red[i][wave] = s;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < count; i += NT) {
+  for (int i = threadIdx.x; i < count; i += KCH) {
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) s += red[i][w];
+    for (int w = 0; w < KCH / 64; ++w) s += red[i][w];
     out[i] = s;
   }
 }
@@ -181,33 +181,100 @@ __device__ inline void spmv_row(const IR& I, int r, XP x, double& acc0, double& 
   blk_range_dot<Sub, T>(gp((const T*)I.jval), gp(I.kcol), gp(I.krow_ptr)[r], gp(I.krow_ptr)[r + 1], x, acc0, acc1);
 }
 
-// The same product of row r by kRowLanes lanes (all of them call; the sum in
-// each): lane l takes blocks l, l + kRowLanes, ... of the row, which lie side
-// by side, two in flight.  With a row to a thread a wave's load touches a line
-// per lane and a chunk of KCH rows keeps one wave per SIMD (9.0 us for the
-// product and its dots in an Arnoldi step on 10,000 buses, 5.5 this way; 8.9
-// and 7.0 us for BiCGStab's two on 48,000, 7.4 and 5.8).
+// The row's product by L lanes (all of them call; the sum in each), as the sum
+// of kRowLanes partial sums, the blocks of the row dealt to them in turn.
+// L = kRowLanes: a partial sum a lane, the lanes' blocks side by side, two in
+// flight.  L = 1: all of them in one thread, four blocks in flight; the bits are
+// the same (the fused multiply-adds are named for that).
+// A thread a row touches a line per lane and keeps one wave per SIMD for a chunk
+// of KCH rows (9.0 us for the product and its dots in an Arnoldi step on 10,000
+// buses, 5.5 with four lanes; 8.9 and 7.0 us for BiCGStab's two on 48,000, 7.4
+// and 5.8), but is a quarter of the waves: row_lanes.
 constexpr int kRowLanes = 4;
-template <typename T, typename IR, typename XP>
+// a + x y + z w
+__device__ inline double add2(double a, double x, double y, double z, double w) {
+  return a + fma(x, y, z * w);
+}
+template <typename T, int L, typename IR, typename XP>
 __device__ inline void spmv_row_lanes(const IR& I, int r, int l, XP x, double& acc0, double& acc1) {
   const auto M = gp((const T*)I.jval);
   const auto col = gp(I.kcol);
   const int q0 = gp(I.krow_ptr)[r], q1 = gp(I.krow_ptr)[r + 1];
-  for (int q = q0 + l; q < q1; q += 2 * kRowLanes) {
-    const int q2 = q + kRowLanes < q1 ? q + kRowLanes : q;
-    const int c = col[q], c2 = col[q2];
-    const Blk<T> B = ld_blk(M, q), B2 = ld_blk(M, q2);
-    const double a = (double)x[2 * c], b = (double)x[2 * c + 1];
-    const double a2 = (double)x[2 * c2], b2 = (double)x[2 * c2 + 1];
-    acc0 += (double)B.a * a + (double)B.b * b;
-    acc1 += (double)B.c * a + (double)B.d * b;
-    if (q2 != q) {
-      acc0 += (double)B2.a * a2 + (double)B2.b * b2;
-      acc1 += (double)B2.c * a2 + (double)B2.d * b2;
+  if constexpr (L == kRowLanes) {
+    for (int q = q0 + l; q < q1; q += 2 * L) {
+      const int q2 = q + L < q1 ? q + L : q;
+      const int c = col[q], c2 = col[q2];
+      const Blk<T> B = ld_blk(M, q), B2 = ld_blk(M, q2);
+      const double a = (double)x[2 * c], b = (double)x[2 * c + 1];
+      const double a2 = (double)x[2 * c2], b2 = (double)x[2 * c2 + 1];
+      acc0 = add2(acc0, (double)B.a, a, (double)B.b, b);
+      acc1 = add2(acc1, (double)B.c, a, (double)B.d, b);
+      if (q2 != q) {
+        acc0 = add2(acc0, (double)B2.a, a2, (double)B2.b, b2);
+        acc1 = add2(acc1, (double)B2.c, a2, (double)B2.d, b2);
+      }
     }
+    acc0 = group_add<L>(acc0);
+    acc1 = group_add<L>(acc1);
+  } else {
+    constexpr int W = kRowLanes;
+    double s0[W], s1[W];
+#pragma unroll
+    for (int u = 0; u < W; ++u) s0[u] = s1[u] = 0.0;
+    for (int q = q0; q < q1; q += W) {
+      int c[W];
+      Blk<T> B[W];
+#pragma unroll
+      for (int u = 0; u < W; ++u) {
+        const int qq = u == 0 || q + u < q1 ? q + u : q;
+        c[u] = col[qq];
+        B[u] = ld_blk(M, qq);
+      }
+      double a[W], b[W];
+#pragma unroll
+      for (int u = 0; u < W; ++u) {
+        a[u] = (double)x[2 * c[u]];
+        b[u] = (double)x[2 * c[u] + 1];
+      }
+#pragma unroll
+      for (int u = 0; u < W; ++u)
+        if (u == 0 || q + u < q1) {
+          s0[u] = add2(s0[u], (double)B[u].a, a[u], (double)B[u].b, b[u]);
+          s1[u] = add2(s1[u], (double)B[u].c, a[u], (double)B[u].d, b[u]);
+        }
+    }
+    acc0 = (s0[0] + s0[1]) + (s0[2] + s0[3]);
+    acc1 = (s1[0] + s1[1]) + (s1[2] + s1[3]);
   }
-  acc0 = group_add<kRowLanes>(acc0);
-  acc1 = group_add<kRowLanes>(acc1);
+}
+// the two values of row r, by the row's lanes
+template <int L, typename D, typename S>
+__device__ inline void row_copy(D dst, S src, int r, int l) {
+  if constexpr (L == 1) {
+    dst[2 * r] = src[2 * r];
+    dst[2 * r + 1] = src[2 * r + 1];
+  } else if (l < 2) {
+    dst[2 * r + l] = src[2 * r + l];
+  }
+}
+// Sums over a chunk's KCH rows of `count` values, of L lanes each (lane l = 0 of
+// a row holds its value, the others 0), written to out: rows by sixteen, then
+// these in turn, whatever L.
+template <int L, typename F>
+__device__ inline void row_sums(int count, F f, double (*red)[KCH / 16], PF_AS1 double* out) {
+  static_assert(L == 1 || L == 4, "sixteen rows to a wave, or to sixteen lanes of one");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = 0; i < count; ++i) {
+    const double s = L == 1 ? group_add<16>(f(i)) : wave_sum(f(i));
+    if (L == 1 ? lane % 16 == 0 : lane == 0) red[i][L == 1 ? 4 * wave + lane / 16 : wave] = s;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < count; i += L * KCH) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < KCH / 16; ++w) s += red[i][w];
+    out[i] = s;
+  }
 }
 
 }  // namespace
@@ -1053,7 +1120,7 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const*
     const int k = threadIdx.x / kRowLanes, l = threadIdx.x % kRowLanes, r = blockIdx.x * KCH + k;
     double w0 = 0.0, w1 = 0.0;
     if (r < I.nu) {
-      spmv_row_lanes<T>(I, r, l, gp((const T*)I.kz), w0, w1);
+      spmv_row_lanes<T, kRowLanes>(I, r, l, gp((const T*)I.kz), w0, w1);
       const auto w = gp((T*)I.kw);
       if (l == 0) {
         w[2 * r] = (T)w0;
@@ -1522,28 +1589,28 @@ __global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts) {
 }
 
 // p^ = z, v = J p^ for the rows of one chunk, partial <r0, v>.
-template <typename T>
-__global__ __launch_bounds__(kRowLanes* KCH) void k_bcg_v(const Inst* const* insts) {
-  __shared__ double red[1][kRowLanes * KCH / 64];
+template <typename T, int L>
+__global__ __launch_bounds__(L* KCH) void k_bcg_v(const Inst* const* insts) {
+  __shared__ double red[1][KCH / 16];
   const auto& I = inst_at(insts, blockIdx.y);
   if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + (int)threadIdx.x / kRowLanes, l = threadIdx.x % kRowLanes;
+  const int r = blockIdx.x * KCH + (int)threadIdx.x / L, l = threadIdx.x % L;
   double d = 0.0;
   if (r < I.nu) {
     const auto z = gp((const T*)I.kz);
     const auto Ph = kvec<T>(I, 4);
-    if (l < 2) Ph[2 * r + l] = z[2 * r + l];
+    row_copy<L>(Ph, z, r, l);
     double v0 = 0.0, v1 = 0.0;
-    spmv_row_lanes<T>(I, r, l, z, v0, v1);
+    spmv_row_lanes<T, L>(I, r, l, z, v0, v1);
     if (l == 0) {
       const auto V = kvec<T>(I, 3);
       V[2 * r] = (T)v0;
       V[2 * r + 1] = (T)v1;
       const auto R0 = kvec<T>(I, 1);
-      d = (double)R0[2 * r] * (double)(T)v0 + (double)R0[2 * r + 1] * (double)(T)v1;
+      d = fma((double)R0[2 * r], (double)(T)v0, (double)R0[2 * r + 1] * (double)(T)v1);
     }
   }
-  block_sums<kRowLanes * KCH>(
+  row_sums<L>(
       1, [&](int) { return d; }, red, kpart(I, 0, blockIdx.x));
 }
 
@@ -1587,9 +1654,9 @@ __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, int it)
 // (KS_BS) s^ = z, t = J s^ for the rows of one chunk, partial <t, s>,
 // <t, t>.  The first work-group counts the iteration and sets the state;
 // the others accept the state it sets as the one they started from.
-template <typename T>
-__global__ __launch_bounds__(kRowLanes* KCH) void k_bcg_t(const Inst* const* insts, KOpts o) {
-  __shared__ double red[2][kRowLanes * KCH / 64];
+template <typename T, int L>
+__global__ __launch_bounds__(L* KCH) void k_bcg_t(const Inst* const* insts, KOpts o) {
+  __shared__ double red[2][KCH / 16];
   __shared__ int decision;  // 0 second half, 1 first half met, 2 breakdown
   const auto& I = inst_at(insts, blockIdx.y);
   if ((!kstate_is(I, KS_BP) && !kstate_is(I, KS_BS)) || (int)blockIdx.x >= I.kchunks) return;
@@ -1619,14 +1686,14 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_bcg_t(const Inst* const* ins
   }
   __syncthreads();
   if (decision != 0) return;
-  const int r = blockIdx.x * KCH + (int)threadIdx.x / kRowLanes, l = threadIdx.x % kRowLanes;
+  const int r = blockIdx.x * KCH + (int)threadIdx.x / L, l = threadIdx.x % L;
   double ts = 0.0, tt = 0.0;
   if (r < I.nu) {
     const auto z = gp((const T*)I.kz);
     const auto Sh = kvec<T>(I, 5);
-    if (l < 2) Sh[2 * r + l] = z[2 * r + l];
+    row_copy<L>(Sh, z, r, l);
     double t0 = 0.0, t1 = 0.0;
-    spmv_row_lanes<T>(I, r, l, z, t0, t1);
+    spmv_row_lanes<T, L>(I, r, l, z, t0, t1);
     if (l == 0) {
       const auto Tv = kvec<T>(I, 6);
       Tv[2 * r] = (T)t0;
@@ -1634,11 +1701,11 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_bcg_t(const Inst* const* ins
       t0 = (double)(T)t0;
       t1 = (double)(T)t1;
       const auto S = kvec<T>(I, 0);
-      ts = t0 * (double)S[2 * r] + t1 * (double)S[2 * r + 1];
-      tt = t0 * t0 + t1 * t1;
+      ts = fma(t0, (double)S[2 * r], t1 * (double)S[2 * r + 1]);
+      tt = fma(t0, t0, t1 * t1);
     }
   }
-  block_sums<kRowLanes * KCH>(
+  row_sums<L>(
       2, [&](int e) { return e == 0 ? ts : tt; }, red, kpart(I, 2, blockIdx.x));
 }
 
@@ -1803,6 +1870,18 @@ __global__ void k_kgather(const Inst* const* insts, int nslots, int* out) {
 static inline dim3 chunk_grid(int max_chunks, int nslots) {
   return dim3((unsigned)(max_chunks > 0 ? max_chunks : 1), (unsigned)nslots);
 }
+// Lanes a row of BiCGStab's matrix products: four, but one where the launch has
+// room for so many rows past its instances' own (max_chunks chunks a slot,
+// whatever its size) that starting those waves, four times as many, costs more
+// than the lanes save.  512 grids of 100-5,000 buses (room for 2,015,000 more
+// rows): 45.1 ms with four lanes, 42.0 with one; 256 of 150-3,000 (543,000) 17.2
+// and 16.5; 1,200 of 300 (256,000) 15.0 and 14.7; 64 of 1,000-5,000 (175,000)
+// 13.4 and 13.8; 48 of 10,000 (11,000) 40.2 and 41.5.  (GMRES, whose launch also
+// forms the dots: 71.5 ms either way for the 512.)
+constexpr int64_t kIdleRows = 204800;
+static inline int row_lanes(const dim3& g, int64_t rows) {
+  return (int64_t)g.x * g.y * KCH - rows > kIdleRows ? 1 : kRowLanes;
+}
 static inline dim3 slot_grid(int nslots) { return dim3((unsigned)((nslots + 63) / 64)); }
 static inline dim3 item_grid(int nwork) { return dim3((unsigned)((nwork + 255) / 256)); }
 
@@ -1904,15 +1983,21 @@ void launch_bcg_dir(hipStream_t st, const Inst* const* insts, int nslots, int ma
   k_bcg_dir<T><<<chunk_grid(max_chunks, nslots), KCH, 0, st>>>(insts);
 }
 template <typename T>
-void launch_bcg_half(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, int it) {
+void launch_bcg_half(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, int64_t rows, int it) {
   const dim3 g = chunk_grid(max_chunks, nslots);
-  k_bcg_v<T><<<g, kRowLanes * KCH, 0, st>>>(insts);
+  if (row_lanes(g, rows) == 1)
+    k_bcg_v<T, 1><<<g, KCH, 0, st>>>(insts);
+  else
+    k_bcg_v<T, kRowLanes><<<g, kRowLanes * KCH, 0, st>>>(insts);
   k_bcg_s<T><<<g, KCH, 0, st>>>(insts, it);
 }
 template <typename T>
-void launch_bcg_end(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, KOpts o, int it) {
+void launch_bcg_end(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, int64_t rows, KOpts o, int it) {
   const dim3 g = chunk_grid(max_chunks, nslots);
-  k_bcg_t<T><<<g, kRowLanes * KCH, 0, st>>>(insts, o);
+  if (row_lanes(g, rows) == 1)
+    k_bcg_t<T, 1><<<g, KCH, 0, st>>>(insts, o);
+  else
+    k_bcg_t<T, kRowLanes><<<g, kRowLanes * KCH, 0, st>>>(insts, o);
   k_bcg_x<T><<<g, KCH, 0, st>>>(insts);
   k_bcg_next<T><<<g, KCH, 0, st>>>(insts, o, it);
 }
@@ -1938,8 +2023,8 @@ int krylov_max_restart() { return KMAX; }
   template void launch_kfinish<T>(hipStream_t, const Inst* const*, int, int);                  \
   template void launch_bcg_begin<T>(hipStream_t, const Inst* const*, int, int, KOpts);        \
   template void launch_bcg_dir<T>(hipStream_t, const Inst* const*, int, int);                 \
-  template void launch_bcg_half<T>(hipStream_t, const Inst* const*, int, int, int);           \
-  template void launch_bcg_end<T>(hipStream_t, const Inst* const*, int, int, KOpts, int);
+  template void launch_bcg_half<T>(hipStream_t, const Inst* const*, int, int, int64_t, int);           \
+  template void launch_bcg_end<T>(hipStream_t, const Inst* const*, int, int, int64_t, KOpts, int);
 
 PF_KINST(double)
 PF_KINST(float)

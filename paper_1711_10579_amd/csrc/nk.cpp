@@ -240,10 +240,12 @@ bool ensure_krylov(Case* c, int m) {
 bool Batch::build_krylov() {
   std::vector<int2> work;
   max_kchunks = 0;
+  krows = 0;
   k_blocks_big = 0;
   for (Case* c : cases) {
     if (!c->ka) return false;
     max_kchunks = std::max(max_kchunks, (c->ka->nu + pfd::KCH - 1) / pfd::KCH);
+    krows += c->ka->nu;
   }
   {
     // the groups above the small size first (a work-group each), then the
@@ -663,11 +665,11 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
         apply(2);
         {
           Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
-          pfd::launch_bcg_half<T>(s, I, ns, mc, it);
+          pfd::launch_bcg_half<T>(s, I, ns, mc, b->krows, it);
         }
         apply(3);
         Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
-        pfd::launch_bcg_end<T>(s, I, ns, mc, ko, it);
+        pfd::launch_bcg_end<T>(s, I, ns, mc, b->krows, ko, it);
       }
       Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
       pfd::launch_kfinish<T>(s, I, ns, mc);
