@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstring>
 
 #include "internal.hpp"
@@ -393,6 +394,11 @@ namespace {
 // Levels of up to this many targets run behind barriers of one work-group (a
 // pass of 512 targets takes about 1.2 us, a launch of its own 4.5 us).
 constexpr int kNarrowTargets = 1536;
+// A batch of many instances has the chip full in any case, and a launch of its
+// own for the wide levels of some holds up the others (512 grids of 100-5,000
+// buses: 219 and 130 us, with every level behind barriers 204; 64 of 1,000-5,000
+// 17.5 -> 16.8 ms a GMRES solve; 32 of 150-3,000 the same either way).
+constexpr int kManyInstances = 64;
 
 }  // namespace
 
@@ -412,6 +418,7 @@ bool Batch::build_ilu() {
   size_t max_l = 0, max_u = 0;
   // each instance takes its own path, whatever the batch holds
   std::vector<char> by_level(nslots, 0);
+  const int narrow = nslots < kManyInstances ? kNarrowTargets : INT_MAX;
   for (int s = 0; s < nslots; ++s) {
     Case* c = cases[s];
     const pfh::KAnalysis& ka = *c->ka;
@@ -423,7 +430,7 @@ bool Batch::build_ilu() {
     for (int l = 0; l < nl; ++k) {
       if (seg.size() <= k) seg.emplace_back();
       int e = l;
-      while (e < nl && ptr[e + 1] - ptr[e] <= kNarrowTargets) ++e;
+      while (e < nl && ptr[e + 1] - ptr[e] <= narrow) ++e;
       if (e > l) {
         seg[k].push_back(make_int4(s, l0 + l, l0 + e, 1));
         l = e;
