@@ -91,8 +91,10 @@ template <typename T>
 void launch_ilu_fwd(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int mode);
 template <typename T>
 void launch_ilu_bwd(hipStream_t, const Inst* const* insts, const int2* work, int nwork, int mode);
+// (work, nrows: rows of a forward part that run beside them, a list; 0: none)
 template <typename T>
-void launch_ilu_apply_wg(hipStream_t, const Inst* const* insts, int nslots, int mode, int min_nu, int max_nu);
+void launch_ilu_apply_wg(hipStream_t, const Inst* const* insts, int nslots, int mode, int min_nu, int max_nu,
+                         const int2* work, int nrows);
 template <typename T>
 void launch_bj_apply(hipStream_t, const Inst* const* insts, const int2* work, int nbig, int nwork, int mode);
 // ILU(0) sweeps in parts: rows of one launch are positions p0.. of the only

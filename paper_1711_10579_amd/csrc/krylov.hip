@@ -797,10 +797,8 @@ __global__ __launch_bounds__(256) void k_sweep_values(const Inst* const* insts, 
 // 31), since a backward part reads y at rows whose z it writes.  In an Arnoldi
 // step (mode 0) the scaled input is also stored as basis vector v_j.
 template <typename T, bool Upper>
-__global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, const int2* __restrict__ work, int p0,
-                                                    int nrows, int mode) {
+__device__ __forceinline__ void sweep_part(const Inst* const* insts, const SweepRow sr, int mode) {
   constexpr int G = kSweepLanes;
-  const SweepRow sr = sweep_row<G>(work, p0, nrows);
   if (sr.pos < 0) return;  // whole lane groups leave together
   const auto& I = inst_at(insts, sr.slot);
   // The state is tested together with the row's entry (whose range is never
@@ -868,6 +866,11 @@ __global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, co
     }
   }
 }
+template <typename T, bool Upper>
+__global__ __launch_bounds__(256) void k_sweep_part(const Inst* const* insts, const int2* __restrict__ work, int p0,
+                                                    int nrows, int mode) {
+  sweep_part<T, Upper>(insts, sweep_row<kSweepLanes>(work, p0, nrows), mode);
+}
 
 namespace {
 
@@ -921,10 +924,9 @@ __device__ inline void sweep_data(const i4v& inf, const PF_AS1 T* P, const PF_AS
 // out at the end; ZV = 0: z lives in device memory.  Instances of the other
 // sizes are skipped.
 template <typename T, int ZV>
-__global__ __launch_bounds__(1024) void k_ilu_apply_wg(const Inst* const* insts, int mode, int zmin) {
-  __shared__ T zl[ZV > 0 ? ZV : 1];
-  __shared__ int lpf[LPM + 1], lpb[LPM + 1];
-  const auto& I = inst_at(insts, blockIdx.x);
+__device__ __forceinline__ void ilu_apply_wg(const Inst* const* insts, int slot, int mode, int zmin, T* zl, int* lpf,
+                                             int* lpb) {
+  const auto& I = inst_at(insts, slot);
   const auto ks = gp(I.ks);
   if (!red_of(I)->active || I.kwide || I.sw_rows || ks->state != (apply_state(mode))) return;
   const int nu = I.nu;
@@ -1041,6 +1043,25 @@ __global__ __launch_bounds__(1024) void k_ilu_apply_wg(const Inst* const* insts,
     const auto zg = gp((T*)I.kz);
     for (int i = tid; i < 2 * nu; i += 1024) zg[i] = zl[i];
   }
+}
+// Slots [0, nslots), then the rows of a batch's first forward part (list `work`,
+// as k_sweep_part's), 128 a work-group: neither the instances that sweep by
+// levels nor that part fill the chip, and nothing orders them (512 grids of
+// 100-5,000 buses: 61 and 19 us a launch, 69 together).
+template <typename T, int ZV>
+__global__ __launch_bounds__(1024) void k_ilu_apply_wg(const Inst* const* insts, int nslots, int mode, int zmin,
+                                                       const int2* __restrict__ work, int nrows) {
+  __shared__ T zl[ZV > 0 ? ZV : 1];
+  __shared__ int lpf[LPM + 1], lpb[LPM + 1];
+  if ((int)blockIdx.x < nslots) {
+    ilu_apply_wg<T, ZV>(insts, blockIdx.x, mode, zmin, zl, lpf, lpb);
+    return;
+  }
+  constexpr int G = kSweepLanes;
+  const int idx = ((int)blockIdx.x - nslots) * (1024 / G) + (int)threadIdx.x / G;
+  // (a wave's rows are of one instance: the list is padded to whole groups of 32)
+  const auto wp = (const PF_AS1 int*)work + 2 * min(idx, nrows - 1);
+  sweep_part<T, false>(insts, {__builtin_amdgcn_readfirstlane(wp[0]), idx < nrows ? wp[1] : -1}, mode);
 }
 
 // Block-Jacobi application z_b = A_bb^{-1} (s w_b) (mode 0 also stores s w_b
@@ -1913,14 +1934,23 @@ void launch_ilu_bwd(hipStream_t st, const Inst* const* insts, const int2* work, 
 // z in LDS up to 160,000 bytes of values per work-group, in two sizes so that
 // small instances keep several work-groups per CU
 template <typename T>
-void launch_ilu_apply_wg(hipStream_t st, const Inst* const* insts, int nslots, int mode, int min_nu, int max_nu) {
+void launch_ilu_apply_wg(hipStream_t st, const Inst* const* insts, int nslots, int mode, int min_nu, int max_nu,
+                         const int2* work, int nrows) {
   constexpr int small = 8192 / sizeof(T) * 4;   // 32 KiB
   constexpr int big = 160000 / sizeof(T);
   const dim3 g((unsigned)nslots);
-  // only the size classes some instance of the batch falls in
-  if (2 * min_nu <= small) k_ilu_apply_wg<T, small><<<g, 1024, 0, st>>>(insts, mode, 0);
-  if (2 * max_nu > small && 2 * min_nu <= big) k_ilu_apply_wg<T, big><<<g, 1024, 0, st>>>(insts, mode, small);
-  if (2 * max_nu > big) k_ilu_apply_wg<T, 0><<<g, 1024, 0, st>>>(insts, mode, big);
+  // only the size classes some instance of the batch falls in; the part's rows
+  // with the smallest, whose LDS leaves room for two work-groups to a CU
+  if (2 * min_nu <= small) {
+    constexpr int R = 1024 / kSweepLanes;
+    const dim3 gp((unsigned)(nslots + (nrows + R - 1) / R));
+    k_ilu_apply_wg<T, small><<<gp, 1024, 0, st>>>(insts, nslots, mode, 0, work, nrows);
+  } else if (nrows > 0) {
+    launch_sweep_part<T>(st, insts, work, 0, nrows, 0, mode);
+  }
+  if (2 * max_nu > small && 2 * min_nu <= big)
+    k_ilu_apply_wg<T, big><<<g, 1024, 0, st>>>(insts, nslots, mode, small, nullptr, 0);
+  if (2 * max_nu > big) k_ilu_apply_wg<T, 0><<<g, 1024, 0, st>>>(insts, nslots, mode, big, nullptr, 0);
 }
 int sweep_rows_per_group() { return 256 / kSweepLanes; }
 template <typename T>
@@ -2015,7 +2045,7 @@ int krylov_max_restart() { return KMAX; }
   template void launch_bj_apply<T>(hipStream_t, const Inst* const*, const int2*, int, int, int);\
   template void launch_sweep_values<T>(hipStream_t, const Inst* const*, const int2*, int);  \
   template void launch_sweep_part<T>(hipStream_t, const Inst* const*, const int2*, int, int, int, int); \
-  template void launch_ilu_apply_wg<T>(hipStream_t, const Inst* const*, int, int, int, int);\
+  template void launch_ilu_apply_wg<T>(hipStream_t, const Inst* const*, int, int, int, int, const int2*, int);\
   template void launch_karnoldi<T>(hipStream_t, const Inst* const*, int, int, KOpts);       \
   template void launch_kbegin<T>(hipStream_t, const Inst* const*, int, int, KOpts);         \
   template void launch_kycomb<T>(hipStream_t, const Inst* const*, int, int);                \

@@ -560,10 +560,17 @@ void precond_apply(Batch* b, bool ilu, int mode) {
       else
         pfd::launch_sweep_part<T>(s, I, b->d_swork + l.first, 0, l.second, upper, mode);
     };
-    for (const auto& l : b->s_low) part(l, 0);
+    // the instances without a plan, by levels, the narrow ones beside the others'
+    // first part
+    size_t first = 0;
+    if (b->s_narrow) {
+      const bool beside = ns > 1 && !b->s_low.empty();
+      pfd::launch_ilu_apply_wg<T>(s, I, ns, mode, b->s_min_nu, b->s_max_nu,
+                                  beside ? b->d_swork + b->s_low[0].first : nullptr, beside ? b->s_low[0].second : 0);
+      first = beside;
+    }
+    for (size_t k = first; k < b->s_low.size(); ++k) part(b->s_low[k], 0);
     for (const auto& l : b->s_up) part(l, 1);
-    // the instances without a plan, by levels
-    if (b->s_narrow) pfd::launch_ilu_apply_wg<T>(s, I, ns, mode, b->s_min_nu, b->s_max_nu);
     for (const auto& l : b->s_lev) pfd::launch_ilu_fwd<T>(s, I, b->d_swork + l.first, l.second, mode);
     for (const auto& l : b->s_ulev) pfd::launch_ilu_bwd<T>(s, I, b->d_swork + l.first, l.second, mode);
   } else {

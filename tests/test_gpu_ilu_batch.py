@@ -39,3 +39,23 @@ def test_batch_equals_alone(solver, mixed):
             assert np.array_equal(B.pf_get_voltage(h), V), k
         h.close()
     ctx.close()
+
+
+def test_parts_beside_large_level_sweeps():
+    """A grid with a plan beside a feeder that sweeps by levels with its vector in
+    more than 32 KB of LDS, the part then in a launch of its own."""
+    from paper_1711_10579_amd import binding as B
+
+    ctx = B.pf_ctx_create(0)
+    opt = dict(solver=B.PF_SOLVER_BICGSTAB, max_iter=40)
+    hs = [B.pf_create_from(ctx, g) for g in (_mesh(2300), pfgen.make_feeder(1200, 5))]
+    parts = [B.pf_debug_sweep_check(h, B.PF_PREC_FP64)[2] for h in hs]
+    assert min(parts[0]) >= 2 and parts[1] == (0, 0) and B.pf_case_info_get(hs[1])["n_unknown"] > 2048
+    res = B.pf_solve_batch(ctx, hs, **opt)
+    for h, b in zip(hs, res):
+        V = B.pf_get_voltage(h)
+        r = B.pf_solve(h, **opt)
+        assert (r.status, r.iters, r.linear_iters) == (b.status, b.iters, b.linear_iters)
+        assert b.status == B.PF_CONVERGED and np.array_equal(B.pf_get_voltage(h), V)
+        h.close()
+    ctx.close()
