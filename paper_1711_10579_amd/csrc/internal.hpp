@@ -236,8 +236,7 @@ struct Batch {
   int2* d_kwork = nullptr;
   std::pair<int64_t, int> k_blocks{0, 0};
   int k_blocks_big = 0;  // the first k_blocks_big groups of k_blocks are above the small size
-  int max_kchunks = 0;
-  int64_t krows = 0;  // Krylov rows of all instances
+  pfd::KChunks kchunks = {};
   // ILU(0) lists (built on the first ILU(0) step of the batch).  Factor: per
   // launch a range of work-group descriptors (an instance's k-th launch is
   // its k-th run of narrow levels or wide level).  Sweeps: row ranges of the

@@ -70,6 +70,14 @@ template <typename T>
 void launch_bwd_solve(hipStream_t, const Inst* const* insts, const int2* work, int nd, int nrw, int single,
                       int nbins, const int* bin_off, const int* words);
 
+// The chunks of a batch's Krylov vectors: a list of all `count` {slot, chunk}, or
+// (null) the `most` of an instance for every one of nslots; their rows.
+struct KChunks {
+  const int2* list;
+  int count, most, nslots;
+  int64_t rows;
+};
+
 // Newton-Krylov inner solve (krylov.hip); preconditioner mode 0 = Arnoldi
 // step, 1 = end of a GMRES cycle, 2 and 3 = the halves of a BiCGStab
 // iteration
@@ -83,7 +91,7 @@ template <typename T>
 void launch_ilu_factor(hipStream_t, const Inst* const* insts, const int4* desc, int ngroups, const int* tgt,
                        const int* lev);
 template <typename T>
-void launch_ilu_scale(hipStream_t, const Inst* const* insts, int nslots, int max_chunks);
+void launch_ilu_scale(hipStream_t, const Inst* const* insts, const KChunks& c);
 template <typename T>
 void launch_bj_inv(hipStream_t, const Inst* const* insts, const int2* work, int nbig, int nsmall);
 int bj_small_nodes();  // groups of at most this many nodes are inverted one per wave
@@ -106,27 +114,26 @@ void launch_sweep_values(hipStream_t, const Inst* const* insts, const int2* work
 template <typename T>
 void launch_sweep_part(hipStream_t, const Inst* const* insts, const int2* work, int p0, int nrows, int upper, int mode);
 template <typename T>
-void launch_karnoldi(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, KOpts o);
+void launch_karnoldi(hipStream_t, const Inst* const* insts, const KChunks& c, KOpts o);
 template <typename T>
-void launch_kbegin(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, KOpts o);
+void launch_kbegin(hipStream_t, const Inst* const* insts, const KChunks& c, KOpts o);
 template <typename T>
-void launch_kycomb(hipStream_t, const Inst* const* insts, int nslots, int max_chunks);
+void launch_kycomb(hipStream_t, const Inst* const* insts, const KChunks& c);
 template <typename T>
-void launch_kcycle_end(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, KOpts o);
+void launch_kcycle_end(hipStream_t, const Inst* const* insts, const KChunks& c, KOpts o);
 template <typename T>
-void launch_kfinish(hipStream_t, const Inst* const* insts, int nslots, int max_chunks);
+void launch_kfinish(hipStream_t, const Inst* const* insts, const KChunks& c);
 // BiCGStab: start and the first direction, then per iteration it [apply
 // mode 2], v = J p^ and s, [apply mode 3], the first half's test with
 // t = J s^, the update of x and r, and the test with the next direction
 template <typename T>
-void launch_bcg_begin(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, KOpts o);
+void launch_bcg_begin(hipStream_t, const Inst* const* insts, const KChunks& c, KOpts o);
 template <typename T>
-void launch_bcg_dir(hipStream_t, const Inst* const* insts, int nslots, int max_chunks);
-// (rows: of all instances)
+void launch_bcg_dir(hipStream_t, const Inst* const* insts, const KChunks& c);
 template <typename T>
-void launch_bcg_half(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, int64_t rows, int it);
+void launch_bcg_half(hipStream_t, const Inst* const* insts, const KChunks& c, int it);
 template <typename T>
-void launch_bcg_end(hipStream_t, const Inst* const* insts, int nslots, int max_chunks, int64_t rows, KOpts o,
+void launch_bcg_end(hipStream_t, const Inst* const* insts, const KChunks& c, KOpts o,
                     int it);
 void launch_kgather(hipStream_t, const Inst* const* insts, int nslots, int* out);
 int krylov_max_restart();

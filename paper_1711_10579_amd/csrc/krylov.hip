@@ -79,6 +79,12 @@ __device__ inline void linear_failure(const IR& I) {
 
 __device__ inline double wave_sum(double v) { return group_add<64>(v); }
 
+// {slot, chunk} of a work-group: from the list of a batch's chunks, or (null) a
+// grid of the largest instance's chunks by the slots
+__device__ inline int2 chunk_at(const int2* chunks) {
+  return chunks ? ld_item(chunks, blockIdx.x) : make_int2((int)blockIdx.y, (int)blockIdx.x);
+}
+
 // Sums over the KCH threads of a work-group of the values f(i) for i <
 // count, written to out[i] (thread-uniform count).  Fixed reduction order.
 template <typename F>
@@ -399,9 +405,10 @@ __global__ __launch_bounds__(kFacThreads) void k_ilu_factor(const Inst* const* i
 // The last pass: L(r, k) = P(r, k) D_k^{-1} for the blocks left of the
 // diagonal, one thread per row.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_ilu_scale(const Inst* const* insts) {
-  const auto& I = inst_at(insts, blockIdx.y);
-  const int r = blockIdx.x * KCH + threadIdx.x;
+__global__ __launch_bounds__(KCH) void k_ilu_scale(const Inst* const* insts, const int2* __restrict__ chunks) {
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  const int r = at.y * KCH + threadIdx.x;
   if (!red_of(I)->active || r >= I.nu) return;
   const auto P = gp((T*)I.pval);
   const auto D = gp((const T*)I.pdinv);
@@ -1130,15 +1137,16 @@ __global__ __launch_bounds__(64) void k_bj_apply(const Inst* const* insts, const
 
 // w = J z for the rows of one chunk, then the partial dots <w, v_i>, i <= j.
 template <typename T>
-__global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const* insts) {
+__global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[KMAX + 1][KCH / 64];
   __shared__ double ws[2][KCH];
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_ITER) || (int)blockIdx.x >= I.kchunks) return;
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_ITER) || at.y >= I.kchunks) return;
   const int j = gp(I.ks)->j;
   const int64_t n2 = 2 * (int64_t)I.nu;
   {
-    const int k = threadIdx.x / kRowLanes, l = threadIdx.x % kRowLanes, r = blockIdx.x * KCH + k;
+    const int k = threadIdx.x / kRowLanes, l = threadIdx.x % kRowLanes, r = at.y * KCH + k;
     double w0 = 0.0, w1 = 0.0;
     if (r < I.nu) {
       spmv_row_lanes<T, kRowLanes>(I, r, l, gp((const T*)I.kz), w0, w1);
@@ -1156,7 +1164,7 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const*
   __syncthreads();
   // the dots, dealt out to the kRowLanes quarters of the work-group: a row to
   // a thread in each
-  const int k = threadIdx.x % KCH, r = blockIdx.x * KCH + k;
+  const int k = threadIdx.x % KCH, r = at.y * KCH + k;
   const double w0 = ws[0][k], w1 = ws[1][k];
   const auto V = gp((const T*)I.kv);
   for (int i = threadIdx.x / KCH; i <= j; i += kRowLanes) {
@@ -1173,7 +1181,7 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const*
     double d = 0.0;
 #pragma unroll
     for (int w = 0; w < KCH / 64; ++w) d += red[i][w];
-    kpart(I, 0, blockIdx.x)[i] = d;
+    kpart(I, 0, at.y)[i] = d;
   }
 }
 
@@ -1182,12 +1190,13 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const*
 // Pass 0 leaves the partial dots of the re-orthogonalisation, pass 1 the
 // partial squared norm of w.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_korth(const Inst* const* insts, int pass) {
+__global__ __launch_bounds__(KCH) void k_korth(const Inst* const* insts, const int2* __restrict__ chunks, int pass) {
   __shared__ double red[KMAX + 1][KCH / 64];
   __shared__ double h[KMAX + 1];
   __shared__ double hg[8][KMAX + 1];
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_ITER) || (int)blockIdx.x >= I.kchunks) return;
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_ITER) || at.y >= I.kchunks) return;
   const int j = gp(I.ks)->j;
   // h_i = sum over chunks of the pass's partial dots: 8 interleaved groups
   // of chunks (group g adds chunks g, g + 8, ... in turn, the loads of eight
@@ -1215,13 +1224,13 @@ __global__ __launch_bounds__(KCH) void k_korth(const Inst* const* insts, int pas
 #pragma unroll
     for (int grp = 0; grp < 8; ++grp) s += hg[grp][i];
     h[i] = s;
-    if (blockIdx.x == 0) {
+    if (at.y == 0) {
       double* H = kh_H(I) + (int64_t)i * I.km + j;
       *H = pass == 0 ? s : *H + s;
     }
   }
   __syncthreads();
-  const int r = blockIdx.x * KCH + threadIdx.x;
+  const int r = at.y * KCH + threadIdx.x;
   const int64_t n2 = 2 * (int64_t)I.nu;
   const auto V = gp((const T*)I.kv);
   double w0 = 0.0, w1 = 0.0;
@@ -1247,10 +1256,10 @@ __global__ __launch_bounds__(KCH) void k_korth(const Inst* const* insts, int pas
           const auto vi = V + i * n2;
           return w0 * (double)vi[2 * r] + w1 * (double)vi[2 * r + 1];
         },
-        red, kpart(I, 1, blockIdx.x));
+        red, kpart(I, 1, at.y));
   } else {
     block_sums(
-        1, [&](int) { return w0 * w0 + w1 * w1; }, red, kpart(I, 2, blockIdx.x));
+        1, [&](int) { return w0 * w0 + w1 * w1; }, red, kpart(I, 2, at.y));
   }
 }
 
@@ -1335,11 +1344,12 @@ __global__ __launch_bounds__(64) void k_karnoldi_end(const Inst* const* insts, K
 
 // Start of the inner solve: w = F in Krylov order, x = 0, partial ||F||^2.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_kbegin(const Inst* const* insts) {
+__global__ __launch_bounds__(KCH) void k_kbegin(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[KMAX + 1][KCH / 64];
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!red_of(I)->active || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!red_of(I)->active || at.y >= I.kchunks) return;
+  const int r = at.y * KCH + threadIdx.x;
   double f0 = 0.0, f1 = 0.0;
   if (r < I.nu) {
     const int p = gp(I.kp_of_r)[r];
@@ -1353,7 +1363,7 @@ __global__ __launch_bounds__(KCH) void k_kbegin(const Inst* const* insts) {
     x[2 * r + 1] = T(0);
   }
   block_sums(
-      1, [&](int) { return f0 * f0 + f1 * f1; }, red, kpart(I, 2, blockIdx.x));
+      1, [&](int) { return f0 * f0 + f1 * f1; }, red, kpart(I, 2, at.y));
 }
 
 // Per instance: ||F||_2, the forcing term eta = max(min(eta_max,
@@ -1393,10 +1403,11 @@ __global__ __launch_bounds__(64) void k_kbegin_fin(const Inst* const* insts, KOp
 
 // u = V y over the basis of the finished cycle (into w).
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_kycomb(const Inst* const* insts) {
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_CYCLE) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+__global__ __launch_bounds__(KCH) void k_kycomb(const Inst* const* insts, const int2* __restrict__ chunks) {
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_CYCLE) || at.y >= I.kchunks) return;
+  const int r = at.y * KCH + threadIdx.x;
   if (r >= I.nu) return;
   const int k = gp(I.ks)->j;
   const double* y = kh_y(I);
@@ -1414,10 +1425,11 @@ __global__ __launch_bounds__(KCH) void k_kycomb(const Inst* const* insts) {
 
 // x += z (the preconditioned correction of the cycle).
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_kxadd(const Inst* const* insts) {
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_CYCLE) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+__global__ __launch_bounds__(KCH) void k_kxadd(const Inst* const* insts, const int2* __restrict__ chunks) {
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_CYCLE) || at.y >= I.kchunks) return;
+  const int r = at.y * KCH + threadIdx.x;
   if (r >= I.nu) return;
   const auto x = gp((T*)I.kx);
   const auto z = gp((const T*)I.kz);
@@ -1450,11 +1462,12 @@ __global__ void k_kcycle_fin(const Inst* const* insts, int nslots, KOpts o) {
 
 // Restart: w = F - J x for the rows of one chunk, partial ||w||^2.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_kresid(const Inst* const* insts) {
+__global__ __launch_bounds__(KCH) void k_kresid(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[KMAX + 1][KCH / 64];
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_RESTART) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_RESTART) || at.y >= I.kchunks) return;
+  const int r = at.y * KCH + threadIdx.x;
   double w0 = 0.0, w1 = 0.0;
   if (r < I.nu) {
     const int p = gp(I.kp_of_r)[r];
@@ -1469,7 +1482,7 @@ __global__ __launch_bounds__(KCH) void k_kresid(const Inst* const* insts) {
     w1 = (double)(T)w1;
   }
   block_sums(
-      1, [&](int) { return w0 * w0 + w1 * w1; }, red, kpart(I, 2, blockIdx.x));
+      1, [&](int) { return w0 * w0 + w1 * w1; }, red, kpart(I, 2, at.y));
 }
 
 // Per instance: the true residual starts the next cycle, or ends the solve
@@ -1494,10 +1507,11 @@ __global__ __launch_bounds__(64) void k_krestart_fin(const Inst* const* insts) {
 
 // The Newton step in the factor layout that the voltage update reads.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_kfinish(const Inst* const* insts) {
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_FINISH) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+__global__ __launch_bounds__(KCH) void k_kfinish(const Inst* const* insts, const int2* __restrict__ chunks) {
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_FINISH) || at.y >= I.kchunks) return;
+  const int r = at.y * KCH + threadIdx.x;
   if (r >= I.nu) return;
   const int p = gp(I.kp_of_r)[r];
   const auto x = gp((const T*)I.kx);
@@ -1583,10 +1597,11 @@ __global__ __launch_bounds__(64) void k_bcg_begin_fin(const Inst* const* insts, 
 
 // p = r + beta (p - omega v), or r = r0 = p = F in the first iteration; w = p.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts) {
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+__global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts, const int2* __restrict__ chunks) {
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_BP) || at.y >= I.kchunks) return;
+  const int r = at.y * KCH + threadIdx.x;
   if (r >= I.nu) return;
   const auto& ks = *gp(I.ks);
   const auto w = gp((T*)I.kw);
@@ -1611,11 +1626,12 @@ __global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts) {
 
 // p^ = z, v = J p^ for the rows of one chunk, partial <r0, v>.
 template <typename T, int L>
-__global__ __launch_bounds__(L* KCH) void k_bcg_v(const Inst* const* insts) {
+__global__ __launch_bounds__(L* KCH) void k_bcg_v(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[1][KCH / 16];
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + (int)threadIdx.x / L, l = threadIdx.x % L;
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_BP) || at.y >= I.kchunks) return;
+  const int r = at.y * KCH + (int)threadIdx.x / L, l = threadIdx.x % L;
   double d = 0.0;
   if (r < I.nu) {
     const auto z = gp((const T*)I.kz);
@@ -1632,17 +1648,18 @@ __global__ __launch_bounds__(L* KCH) void k_bcg_v(const Inst* const* insts) {
     }
   }
   row_sums<L>(
-      1, [&](int) { return d; }, red, kpart(I, 0, blockIdx.x));
+      1, [&](int) { return d; }, red, kpart(I, 0, at.y));
 }
 
 // alpha = <r0, r> / <r0, v>; s = r - alpha v into r and w; partial ||s||^2
 // (it: the iteration, counted from 0 in the inner solve).
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, int it) {
+__global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, const int2* __restrict__ chunks, int it) {
   __shared__ double red[1][KCH / 64];
-  const auto& I = inst_at(insts, blockIdx.y);
-  if (!kstate_is(I, KS_BP) || (int)blockIdx.x >= I.kchunks) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if (!kstate_is(I, KS_BP) || at.y >= I.kchunks) return;
+  const int r = at.y * KCH + threadIdx.x;
   // every wave forms alpha, its own rows' values on their way meanwhile (3.9 ->
   // 3.4 us at 48,000 buses; with sixteen waves, as in k_bcg_t, the partials'
   // loads cost more than the barrier)
@@ -1651,7 +1668,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, int it)
   const int k = 2 * min(r, I.nu - 1);
   const T ra = R[k], rb = R[k + 1], va = V[k], vb = V[k + 1];
   const double alpha = gp(I.ks)->rho[it & 1] / chunk_sum(I, 0, 0);
-  if (blockIdx.x == 0 && threadIdx.x == 0) gp(I.ks)->alpha = alpha;
+  if (at.y == 0 && threadIdx.x == 0) gp(I.ks)->alpha = alpha;
   double s0 = 0.0, s1 = 0.0;
   if (r < I.nu) {
     const auto w = gp((T*)I.kw);
@@ -1665,7 +1682,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, int it)
     s1 = (double)b;
   }
   block_sums(
-      1, [&](int) { return s0 * s0 + s1 * s1; }, red, kpart(I, 1, blockIdx.x));
+      1, [&](int) { return s0 * s0 + s1 * s1; }, red, kpart(I, 1, at.y));
 }
 
 // The first half of the iteration, decided in every work-group from the
@@ -1676,11 +1693,12 @@ __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, int it)
 // <t, t>.  The first work-group counts the iteration and sets the state;
 // the others accept the state it sets as the one they started from.
 template <typename T, int L>
-__global__ __launch_bounds__(L* KCH) void k_bcg_t(const Inst* const* insts, KOpts o) {
+__global__ __launch_bounds__(L* KCH) void k_bcg_t(const Inst* const* insts, const int2* __restrict__ chunks, KOpts o) {
   __shared__ double red[2][KCH / 16];
   __shared__ int decision;  // 0 second half, 1 first half met, 2 breakdown
-  const auto& I = inst_at(insts, blockIdx.y);
-  if ((!kstate_is(I, KS_BP) && !kstate_is(I, KS_BS)) || (int)blockIdx.x >= I.kchunks) return;
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
+  if ((!kstate_is(I, KS_BP) && !kstate_is(I, KS_BS)) || at.y >= I.kchunks) return;
   auto& ks = *gp(I.ks);
   if (threadIdx.x < 64) {
     double sum[2];
@@ -1690,7 +1708,7 @@ __global__ __launch_bounds__(L* KCH) void k_bcg_t(const Inst* const* insts, KOpt
       const double srel = sqrt(ss) / ks.bnorm;
       const int dec = (!(sv > 0.0) || !isfinite(ks.alpha)) ? 2 : srel <= ks.eta ? 1 : 0;
       decision = dec;
-      if (blockIdx.x == 0) {
+      if (at.y == 0) {
         ks.total += 1;
         red_of(I)->linear_iters += 1;
         if (dec == 2) {
@@ -1707,7 +1725,7 @@ __global__ __launch_bounds__(L* KCH) void k_bcg_t(const Inst* const* insts, KOpt
   }
   __syncthreads();
   if (decision != 0) return;
-  const int r = blockIdx.x * KCH + (int)threadIdx.x / L, l = threadIdx.x % L;
+  const int r = at.y * KCH + (int)threadIdx.x / L, l = threadIdx.x % L;
   double ts = 0.0, tt = 0.0;
   if (r < I.nu) {
     const auto z = gp((const T*)I.kz);
@@ -1727,20 +1745,21 @@ __global__ __launch_bounds__(L* KCH) void k_bcg_t(const Inst* const* insts, KOpt
     }
   }
   row_sums<L>(
-      2, [&](int e) { return e == 0 ? ts : tt; }, red, kpart(I, 2, blockIdx.x));
+      2, [&](int e) { return e == 0 ? ts : tt; }, red, kpart(I, 2, at.y));
 }
 
 // KS_BS: omega = <t, s> / <t, t>, x += alpha p^ + omega s^, r = s - omega t,
 // partial <r0, r> and ||r||^2 (nothing when <t, t> = 0).  KS_BH:
 // x += alpha p^.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts) {
+__global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[2][KCH / 64];
-  const auto& I = inst_at(insts, blockIdx.y);
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
   const bool half = kstate_is(I, KS_BH);
-  if ((!half && !kstate_is(I, KS_BS)) || (int)blockIdx.x >= I.kchunks) return;
+  if ((!half && !kstate_is(I, KS_BS)) || at.y >= I.kchunks) return;
   const double alpha = gp(I.ks)->alpha;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+  const int r = at.y * KCH + threadIdx.x;
   const auto x = gp((T*)I.kx);
   const auto Ph = kvec<T>(I, 4);
   if (half) {
@@ -1769,7 +1788,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts) {
   const double tt = sum[0], ts = sum[1];
   const bool skip = !(tt > 0.0);
   const double omega = skip ? 0.0 : ts / tt;
-  if (blockIdx.x == 0 && threadIdx.x == 0) gp(I.ks)->omega = omega;
+  if (at.y == 0 && threadIdx.x == 0) gp(I.ks)->omega = omega;
   if (skip) return;  // <t, t> = 0: the solve ends as it stands
   double d = 0.0, q = 0.0;
   if (r < I.nu) {
@@ -1784,7 +1803,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts) {
     }
   }
   block_sums(
-      2, [&](int e) { return e == 0 ? d : q; }, red, kpart(I, 1, blockIdx.x));
+      2, [&](int e) { return e == 0 ? d : q; }, red, kpart(I, 1, at.y));
 }
 
 // The end of iteration it, decided in every work-group from the chunk
@@ -1797,12 +1816,13 @@ __global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts) {
 // state (<r0, r> goes to the other parity, so no work-group reads a value
 // this launch writes); the others accept the state it sets.
 template <typename T>
-__global__ __launch_bounds__(KCH) void k_bcg_next(const Inst* const* insts, KOpts o, int it) {
+__global__ __launch_bounds__(KCH) void k_bcg_next(const Inst* const* insts, const int2* __restrict__ chunks, KOpts o, int it) {
   __shared__ double beta_s;
   __shared__ int go;
-  const auto& I = inst_at(insts, blockIdx.y);
+  const int2 at = chunk_at(chunks);
+  const auto& I = inst_at(insts, at.x);
   const bool half = kstate_is(I, KS_BH);
-  if ((!half && !kstate_is(I, KS_BS) && !kstate_is(I, KS_BP)) || (int)blockIdx.x >= I.kchunks) return;
+  if ((!half && !kstate_is(I, KS_BS) && !kstate_is(I, KS_BP)) || at.y >= I.kchunks) return;
   auto& ks = *gp(I.ks);
   if (threadIdx.x < 64) {
     double sum[3];
@@ -1832,7 +1852,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_next(const Inst* const* insts, KOpt
       const double beta = (rho / ks.rho[it & 1]) * (ks.alpha / ks.omega);
       go = dec == 2;
       beta_s = beta;
-      if (blockIdx.x == 0) {
+      if (at.y == 0) {
         if (set_rel) ks.rel = rel;
         if (set_rel && dec != 0) ks.j = it + 1;
         if (dec == 0) {
@@ -1850,7 +1870,7 @@ __global__ __launch_bounds__(KCH) void k_bcg_next(const Inst* const* insts, KOpt
   }
   __syncthreads();
   if (!go) return;
-  const int r = blockIdx.x * KCH + threadIdx.x;
+  const int r = at.y * KCH + threadIdx.x;
   if (r >= I.nu) return;
   const double beta = beta_s, omega = ks.omega;
   const auto w = gp((T*)I.kw);
@@ -1888,21 +1908,16 @@ __global__ void k_kgather(const Inst* const* insts, int nslots, int* out) {
 // ---------------------------------------------------------------------------
 // host launchers
 
-static inline dim3 chunk_grid(int max_chunks, int nslots) {
-  return dim3((unsigned)(max_chunks > 0 ? max_chunks : 1), (unsigned)nslots);
+static inline dim3 chunk_grid(const KChunks& c) {
+  if (c.list) return dim3((unsigned)(c.count > 0 ? c.count : 1));
+  return dim3((unsigned)(c.most > 0 ? c.most : 1), (unsigned)c.nslots);
 }
-// Lanes a row of BiCGStab's matrix products: four, but one where the launch has
-// room for so many rows past its instances' own (max_chunks chunks a slot,
-// whatever its size) that starting those waves, four times as many, costs more
-// than the lanes save.  512 grids of 100-5,000 buses (room for 2,015,000 more
-// rows): 45.1 ms with four lanes, 42.0 with one; 256 of 150-3,000 (543,000) 17.2
-// and 16.5; 1,200 of 300 (256,000) 15.0 and 14.7; 64 of 1,000-5,000 (175,000)
-// 13.4 and 13.8; 48 of 10,000 (11,000) 40.2 and 41.5.  (GMRES, whose launch also
-// forms the dots: 71.5 ms either way for the 512.)
+// Lanes a row of BiCGStab's matrix products: four, but one where the chunks have
+// room for so many rows more than there are that four lanes' waves for them cost
+// more than the lanes save: 1,200 grids of 300 buses (256,000 rows more) 14.8 ms
+// with four lanes, 14.4 with one; 48 of 10,000 (11,000 more) 40.2 and 41.5.
 constexpr int64_t kIdleRows = 204800;
-static inline int row_lanes(const dim3& g, int64_t rows) {
-  return (int64_t)g.x * g.y * KCH - rows > kIdleRows ? 1 : kRowLanes;
-}
+static inline int row_lanes(const KChunks& c) { return (int64_t)c.count * KCH - c.rows > kIdleRows ? 1 : kRowLanes; }
 static inline dim3 slot_grid(int nslots) { return dim3((unsigned)((nslots + 63) / 64)); }
 static inline dim3 item_grid(int nwork) { return dim3((unsigned)((nwork + 255) / 256)); }
 
@@ -1913,8 +1928,8 @@ void launch_ilu_factor(hipStream_t st, const Inst* const* insts, const int4* des
   if (ngroups > 0) k_ilu_factor<T><<<dim3((unsigned)ngroups), kFacThreads, 0, st>>>(insts, desc, tgt, lev);
 }
 template <typename T>
-void launch_ilu_scale(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks) {
-  k_ilu_scale<T><<<chunk_grid(max_chunks, nslots), KCH, 0, st>>>(insts);
+void launch_ilu_scale(hipStream_t st, const Inst* const* insts, const KChunks& c) {
+  k_ilu_scale<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
 }
 template <typename T>
 void launch_bj_inv(hipStream_t st, const Inst* const* insts, const int2* work, int nbig, int nsmall) {
@@ -1974,62 +1989,62 @@ void launch_bj_apply(hipStream_t st, const Inst* const* insts, const int2* work,
   if (nwork > 0) k_bj_apply<T><<<dim3((unsigned)(nbig + (nwork - nbig) / 4)), 64, 0, st>>>(insts, work, nbig, mode);
 }
 template <typename T>
-void launch_karnoldi(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, KOpts o) {
-  const dim3 g = chunk_grid(max_chunks, nslots);
-  k_kspmv_dot<T><<<g, kRowLanes * KCH, 0, st>>>(insts);
-  k_korth<T><<<g, KCH, 0, st>>>(insts, 0);
-  k_korth<T><<<g, KCH, 0, st>>>(insts, 1);
-  k_karnoldi_end<<<dim3((unsigned)nslots), 64, 0, st>>>(insts, o);
+void launch_karnoldi(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o) {
+  const dim3 g = chunk_grid(c);
+  k_kspmv_dot<T><<<g, kRowLanes * KCH, 0, st>>>(insts, c.list);
+  k_korth<T><<<g, KCH, 0, st>>>(insts, c.list, 0);
+  k_korth<T><<<g, KCH, 0, st>>>(insts, c.list, 1);
+  k_karnoldi_end<<<dim3((unsigned)c.nslots), 64, 0, st>>>(insts, o);
 }
 template <typename T>
-void launch_kbegin(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, KOpts o) {
-  k_kbegin<T><<<chunk_grid(max_chunks, nslots), KCH, 0, st>>>(insts);
-  k_kbegin_fin<<<dim3((unsigned)nslots), 64, 0, st>>>(insts, o);
+void launch_kbegin(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o) {
+  k_kbegin<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  k_kbegin_fin<<<dim3((unsigned)c.nslots), 64, 0, st>>>(insts, o);
 }
 template <typename T>
-void launch_kycomb(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks) {
-  k_kycomb<T><<<chunk_grid(max_chunks, nslots), KCH, 0, st>>>(insts);
+void launch_kycomb(hipStream_t st, const Inst* const* insts, const KChunks& c) {
+  k_kycomb<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
 }
 template <typename T>
-void launch_kcycle_end(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, KOpts o) {
-  const dim3 g = chunk_grid(max_chunks, nslots);
-  k_kxadd<T><<<g, KCH, 0, st>>>(insts);
-  k_kcycle_fin<<<slot_grid(nslots), 64, 0, st>>>(insts, nslots, o);
-  k_kresid<T><<<g, KCH, 0, st>>>(insts);
-  k_krestart_fin<<<dim3((unsigned)nslots), 64, 0, st>>>(insts);
+void launch_kcycle_end(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o) {
+  const dim3 g = chunk_grid(c);
+  k_kxadd<T><<<g, KCH, 0, st>>>(insts, c.list);
+  k_kcycle_fin<<<slot_grid(c.nslots), 64, 0, st>>>(insts, c.nslots, o);
+  k_kresid<T><<<g, KCH, 0, st>>>(insts, c.list);
+  k_krestart_fin<<<dim3((unsigned)c.nslots), 64, 0, st>>>(insts);
 }
 template <typename T>
-void launch_kfinish(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks) {
-  k_kfinish<T><<<chunk_grid(max_chunks, nslots), KCH, 0, st>>>(insts);
-  k_kretire<<<slot_grid(nslots), 64, 0, st>>>(insts, nslots);
+void launch_kfinish(hipStream_t st, const Inst* const* insts, const KChunks& c) {
+  k_kfinish<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  k_kretire<<<slot_grid(c.nslots), 64, 0, st>>>(insts, c.nslots);
 }
 template <typename T>
-void launch_bcg_begin(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, KOpts o) {
-  k_kbegin<T><<<chunk_grid(max_chunks, nslots), KCH, 0, st>>>(insts);
-  k_bcg_begin_fin<<<dim3((unsigned)nslots), 64, 0, st>>>(insts, o);
+void launch_bcg_begin(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o) {
+  k_kbegin<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  k_bcg_begin_fin<<<dim3((unsigned)c.nslots), 64, 0, st>>>(insts, o);
 }
 template <typename T>
-void launch_bcg_dir(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks) {
-  k_bcg_dir<T><<<chunk_grid(max_chunks, nslots), KCH, 0, st>>>(insts);
+void launch_bcg_dir(hipStream_t st, const Inst* const* insts, const KChunks& c) {
+  k_bcg_dir<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
 }
 template <typename T>
-void launch_bcg_half(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, int64_t rows, int it) {
-  const dim3 g = chunk_grid(max_chunks, nslots);
-  if (row_lanes(g, rows) == 1)
-    k_bcg_v<T, 1><<<g, KCH, 0, st>>>(insts);
+void launch_bcg_half(hipStream_t st, const Inst* const* insts, const KChunks& c, int it) {
+  const dim3 g = chunk_grid(c);
+  if (row_lanes(c) == 1)
+    k_bcg_v<T, 1><<<g, KCH, 0, st>>>(insts, c.list);
   else
-    k_bcg_v<T, kRowLanes><<<g, kRowLanes * KCH, 0, st>>>(insts);
-  k_bcg_s<T><<<g, KCH, 0, st>>>(insts, it);
+    k_bcg_v<T, kRowLanes><<<g, kRowLanes * KCH, 0, st>>>(insts, c.list);
+  k_bcg_s<T><<<g, KCH, 0, st>>>(insts, c.list, it);
 }
 template <typename T>
-void launch_bcg_end(hipStream_t st, const Inst* const* insts, int nslots, int max_chunks, int64_t rows, KOpts o, int it) {
-  const dim3 g = chunk_grid(max_chunks, nslots);
-  if (row_lanes(g, rows) == 1)
-    k_bcg_t<T, 1><<<g, KCH, 0, st>>>(insts, o);
+void launch_bcg_end(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o, int it) {
+  const dim3 g = chunk_grid(c);
+  if (row_lanes(c) == 1)
+    k_bcg_t<T, 1><<<g, KCH, 0, st>>>(insts, c.list, o);
   else
-    k_bcg_t<T, kRowLanes><<<g, kRowLanes * KCH, 0, st>>>(insts, o);
-  k_bcg_x<T><<<g, KCH, 0, st>>>(insts);
-  k_bcg_next<T><<<g, KCH, 0, st>>>(insts, o, it);
+    k_bcg_t<T, kRowLanes><<<g, kRowLanes * KCH, 0, st>>>(insts, c.list, o);
+  k_bcg_x<T><<<g, KCH, 0, st>>>(insts, c.list);
+  k_bcg_next<T><<<g, KCH, 0, st>>>(insts, c.list, o, it);
 }
 void launch_kgather(hipStream_t st, const Inst* const* insts, int nslots, int* out) {
   k_kgather<<<slot_grid(nslots), 64, 0, st>>>(insts, nslots, out);
@@ -2038,7 +2053,7 @@ int krylov_max_restart() { return KMAX; }
 
 #define PF_KINST(T)                                                                    \
   template void launch_ilu_factor<T>(hipStream_t, const Inst* const*, const int4*, int, const int*, const int*); \
-  template void launch_ilu_scale<T>(hipStream_t, const Inst* const*, int, int);             \
+  template void launch_ilu_scale<T>(hipStream_t, const Inst* const*, const KChunks&);             \
   template void launch_bj_inv<T>(hipStream_t, const Inst* const*, const int2*, int, int);   \
   template void launch_ilu_fwd<T>(hipStream_t, const Inst* const*, const int2*, int, int);  \
   template void launch_ilu_bwd<T>(hipStream_t, const Inst* const*, const int2*, int, int);  \
@@ -2046,15 +2061,15 @@ int krylov_max_restart() { return KMAX; }
   template void launch_sweep_values<T>(hipStream_t, const Inst* const*, const int2*, int);  \
   template void launch_sweep_part<T>(hipStream_t, const Inst* const*, const int2*, int, int, int, int); \
   template void launch_ilu_apply_wg<T>(hipStream_t, const Inst* const*, int, int, int, int, const int2*, int);\
-  template void launch_karnoldi<T>(hipStream_t, const Inst* const*, int, int, KOpts);       \
-  template void launch_kbegin<T>(hipStream_t, const Inst* const*, int, int, KOpts);         \
-  template void launch_kycomb<T>(hipStream_t, const Inst* const*, int, int);                \
-  template void launch_kcycle_end<T>(hipStream_t, const Inst* const*, int, int, KOpts);     \
-  template void launch_kfinish<T>(hipStream_t, const Inst* const*, int, int);                  \
-  template void launch_bcg_begin<T>(hipStream_t, const Inst* const*, int, int, KOpts);        \
-  template void launch_bcg_dir<T>(hipStream_t, const Inst* const*, int, int);                 \
-  template void launch_bcg_half<T>(hipStream_t, const Inst* const*, int, int, int64_t, int);           \
-  template void launch_bcg_end<T>(hipStream_t, const Inst* const*, int, int, int64_t, KOpts, int);
+  template void launch_karnoldi<T>(hipStream_t, const Inst* const*, const KChunks&, KOpts);       \
+  template void launch_kbegin<T>(hipStream_t, const Inst* const*, const KChunks&, KOpts);         \
+  template void launch_kycomb<T>(hipStream_t, const Inst* const*, const KChunks&);                \
+  template void launch_kcycle_end<T>(hipStream_t, const Inst* const*, const KChunks&, KOpts);     \
+  template void launch_kfinish<T>(hipStream_t, const Inst* const*, const KChunks&);                  \
+  template void launch_bcg_begin<T>(hipStream_t, const Inst* const*, const KChunks&, KOpts);        \
+  template void launch_bcg_dir<T>(hipStream_t, const Inst* const*, const KChunks&);                 \
+  template void launch_bcg_half<T>(hipStream_t, const Inst* const*, const KChunks&, int);           \
+  template void launch_bcg_end<T>(hipStream_t, const Inst* const*, const KChunks&, KOpts, int);
 
 PF_KINST(double)
 PF_KINST(float)

@@ -238,15 +238,29 @@ bool ensure_krylov(Case* c, int m) {
   return true;
 }
 
+namespace {
+
+// Work-groups without a chunk past which a batch's chunks go by a list (one more
+// load at the start of a work-group).  With four lanes a row such a work-group
+// is 16 waves to start: 512 grids of 100-5,000 buses (7,626 of 10,240 without)
+// with block-Jacobi GMRES 71.5 -> 65.5 ms and BiCGStab 45.1 -> 40.1, with ILU(0)
+// 31.5 -> 29.6 and 29.5 -> 28.8; 16 of 500-10,000 (400 of 608) 14.7 -> 14.4 and
+// 6.5 -> 6.3; 32 of 150-3,000 (208 of 352, by the grid) the same either way.
+constexpr int64_t kEmptyChunks = 256;
+
+}  // namespace
+
 bool Batch::build_krylov() {
   std::vector<int2> work;
-  max_kchunks = 0;
-  krows = 0;
+  kchunks = {};
+  kchunks.nslots = nslots;
   k_blocks_big = 0;
   for (Case* c : cases) {
     if (!c->ka) return false;
-    max_kchunks = std::max(max_kchunks, (c->ka->nu + pfd::KCH - 1) / pfd::KCH);
-    krows += c->ka->nu;
+    const int nc = (c->ka->nu + pfd::KCH - 1) / pfd::KCH;
+    kchunks.most = std::max(kchunks.most, nc);
+    kchunks.count += nc;
+    kchunks.rows += c->ka->nu;
   }
   {
     // the groups above the small size first (a work-group each), then the
@@ -266,12 +280,19 @@ bool Batch::build_krylov() {
     }
     k_blocks = {off, (int)((int64_t)work.size() - off)};
   }
+  // the chunks by a list where a grid of the most chunks for every instance would
+  // hold many work-groups without one
+  const int64_t chunks_off = (int64_t)work.size();
+  const bool list = (int64_t)kchunks.most * nslots - kchunks.count > kEmptyChunks;
+  for (int s = 0; list && s < nslots; ++s)
+    for (int k = 0; k * pfd::KCH < cases[s]->ka->nu; ++k) work.push_back(make_int2(s, k));
   const size_t bw = (sizeof(int2) * std::max<size_t>(work.size(), 1) + 255) & ~(size_t)255;
   if (kmem) ctx->dfree(kmem);
   kmem = (char*)ctx->dalloc(bw);
   kbytes = kmem ? bw : 0;
   if (!kmem) return false;
   d_kwork = (int2*)kmem;
+  if (list) kchunks.list = d_kwork + chunks_off;
   hipStream_t st = stream;
   bool ok = true;
   if (!work.empty())
@@ -540,7 +561,7 @@ void precond_setup(Batch* b, bool ilu) {
   if (ilu) {
     for (const auto& l : b->f_seg)
       pfd::launch_ilu_factor<T>(s, I, b->d_fdesc + l.first, l.second, b->d_ftgt, b->d_flev);
-    pfd::launch_ilu_scale<T>(s, I, b->nslots, b->max_kchunks);
+    pfd::launch_ilu_scale<T>(s, I, b->kchunks);
     for (const auto& l : b->s_step) pfd::launch_sweep_values<T>(s, I, b->d_swork + l.first, l.second);
   } else {
     pfd::launch_bj_inv<T>(s, I, b->d_kwork + b->k_blocks.first, b->k_blocks_big,
@@ -602,7 +623,8 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
   ko.m = opt->gmres_m;
   ko.max_restarts = opt->gmres_max_restarts;
   const bool ilu = opt->precond == PF_PRECOND_ILU0;
-  const int ns = b->nslots, mc = b->max_kchunks;
+  const int ns = b->nslots;
+  const pfd::KChunks& kc = b->kchunks;
   {
     Prof p(ctx, PF_K_JFILL, 0.0, 0.0);
     pfd::launch_kfill<T>(s, I, ns, b->max_nnz, ilu ? 1 : 0);
@@ -615,11 +637,11 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
   {
     Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
     if (bcg) {
-      pfd::launch_bcg_begin<T>(s, I, ns, mc, ko);
-      pfd::launch_bcg_dir<T>(s, I, ns, mc);  // p = r = r0 = F
+      pfd::launch_bcg_begin<T>(s, I, kc, ko);
+      pfd::launch_bcg_dir<T>(s, I, kc);  // p = r = r0 = F
     } else
-      pfd::launch_kbegin<T>(s, I, ns, mc, ko);
-    pfd::launch_kfinish<T>(s, I, ns, mc);
+      pfd::launch_kbegin<T>(s, I, kc, ko);
+    pfd::launch_kfinish<T>(s, I, kc);
   }
   auto apply = [&](int mode) {
     Prof p(ctx, PF_K_PRECOND_APPLY, 0.0, 0.0);
@@ -679,14 +701,14 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
         apply(2);
         {
           Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
-          pfd::launch_bcg_half<T>(s, I, ns, mc, b->krows, it);
+          pfd::launch_bcg_half<T>(s, I, kc, it);
         }
         apply(3);
         Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
-        pfd::launch_bcg_end<T>(s, I, ns, mc, b->krows, ko, it);
+        pfd::launch_bcg_end<T>(s, I, kc, ko, it);
       }
       Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
-      pfd::launch_kfinish<T>(s, I, ns, mc);
+      pfd::launch_kfinish<T>(s, I, kc);
       continue;
     }
     bool iter = false, cyc = false;
@@ -709,16 +731,16 @@ pf_status nk_step_t(Batch* b, const pf_options* opt) {
     for (int i = 0; i < run; ++i) {
       apply(0);
       Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
-      pfd::launch_karnoldi<T>(s, I, ns, mc, ko);
+      pfd::launch_karnoldi<T>(s, I, kc, ko);
     }
     {
       Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
-      pfd::launch_kycomb<T>(s, I, ns, mc);
+      pfd::launch_kycomb<T>(s, I, kc);
     }
     apply(1);
     Prof p(ctx, PF_K_KRYLOV, 0.0, 0.0);
-    pfd::launch_kcycle_end<T>(s, I, ns, mc, ko);
-    pfd::launch_kfinish<T>(s, I, ns, mc);
+    pfd::launch_kcycle_end<T>(s, I, kc, ko);
+    pfd::launch_kfinish<T>(s, I, kc);
   }
   {
     Prof p(ctx, PF_K_UPDATE, 0.0, 0.0);
