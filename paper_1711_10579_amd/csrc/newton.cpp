@@ -8,8 +8,10 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <future>
 #include <map>
 #include <string>
+#include <system_error>
 
 #include "internal.hpp"
 #include "kernels.hpp"
@@ -430,6 +432,19 @@ static pfd::DevOpts dev_opts(const pf_options* opt) {
 pf_status start_batch(Batch* b, const pf_options* opt) {
   pf_status st = check_opts(opt);
   if (st != PF_OK) return st;
+  // the first ILU(0) solve's plans beside the storage's set-up, which needs
+  // nothing of them (a few rows: a thread costs more)
+  std::future<bool> plan;
+  if (opt->solver != PF_SOLVER_LU && opt->precond == PF_PRECOND_ILU0 && !b->sbuilt && b->ilu_host.empty()) {
+    int64_t rows = 0;
+    for (Case* c : b->cases) rows += c->an.nu;
+    if (rows > 2048) {
+      try {
+        plan = std::async(std::launch::async, [b] { return b->plan_ilu(); });
+      } catch (const std::system_error&) {  // no thread: by build_ilu
+      }
+    }
+  }
   for (Case* c : b->cases)
     if (!ensure_work(c)) return PF_E_NOMEM;
   if (opt->solver != PF_SOLVER_LU) {
@@ -439,6 +454,7 @@ pf_status start_batch(Batch* b, const pf_options* opt) {
       set_error("pf_solve: Krylov batch set-up failed");
       return PF_E_NOMEM;
     }
+    if (plan.valid()) (void)plan.get();  // where it failed, build_ilu tries and reports
     if (opt->precond == PF_PRECOND_ILU0 && !b->sbuilt && !b->build_ilu()) {
       set_error("pf_solve: set-up of the ILU(0) lists failed");
       return PF_E_NOMEM;

@@ -434,6 +434,19 @@ bool Batch::build_ilu() {
   s_min_nu = s_max_nu = 0;
   // factor targets and levels of every instance, its launches' descriptors
   std::vector<int> tgt, lev;
+  {
+    size_t nt = 0, nl = 0, nw = 0;
+    for (int s = 0; s < nslots; ++s) {
+      nt += host[s].tgt.size();
+      nl += host[s].ptr.size();
+      // rows of the steps and parts, each padded for an instance
+      if (cases[s]->sw_state == Case::SW_PLAN)
+        nw += 2 * cases[s]->sw.step.size() + 32 * (cases[s]->sw.part_ptr.size() + cases[s]->sw.nsteps);
+    }
+    tgt.reserve(nt);
+    lev.reserve(nl);
+    work.reserve(nw);
+  }
   std::vector<std::vector<int4>> seg;
   int nlp = 0, nup = 0, nst = 0;
   size_t max_l = 0, max_u = 0;
