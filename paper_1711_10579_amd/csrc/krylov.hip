@@ -79,10 +79,14 @@ __device__ inline void linear_failure(const IR& I) {
 
 __device__ inline double wave_sum(double v) { return group_add<64>(v); }
 
-// {slot, chunk} of a work-group: from the list of a batch's chunks, or (null) a
-// grid of the largest instance's chunks by the slots
+// {slot, chunk} of a work-group: from the list of a batch's chunks, or from a grid
+// of the largest instance's chunks by the slots (a kernel of its own: the test
+// for a list cost a single solve's kernels 0.5 %)
+template <bool List>
 __device__ inline int2 chunk_at(const int2* chunks) {
-  return chunks ? ld_item(chunks, blockIdx.x) : make_int2((int)blockIdx.y, (int)blockIdx.x);
+  if (!List) return make_int2((int)blockIdx.y, (int)blockIdx.x);
+  const int2 c = ld_item(chunks, blockIdx.x);
+  return make_int2(__builtin_amdgcn_readfirstlane(c.x), __builtin_amdgcn_readfirstlane(c.y));
 }
 
 // Sums over the KCH threads of a work-group of the values f(i) for i <
@@ -404,9 +408,9 @@ __global__ __launch_bounds__(kFacThreads) void k_ilu_factor(const Inst* const* i
 
 // The last pass: L(r, k) = P(r, k) D_k^{-1} for the blocks left of the
 // diagonal, one thread per row.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_ilu_scale(const Inst* const* insts, const int2* __restrict__ chunks) {
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   const int r = at.y * KCH + threadIdx.x;
   if (!red_of(I)->active || r >= I.nu) return;
@@ -1136,11 +1140,11 @@ __global__ __launch_bounds__(64) void k_bj_apply(const Inst* const* insts, const
 // Arnoldi step
 
 // w = J z for the rows of one chunk, then the partial dots <w, v_i>, i <= j.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[KMAX + 1][KCH / 64];
   __shared__ double ws[2][KCH];
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_ITER) || at.y >= I.kchunks) return;
   const int j = gp(I.ks)->j;
@@ -1189,12 +1193,12 @@ __global__ __launch_bounds__(kRowLanes* KCH) void k_kspmv_dot(const Inst* const*
 // of pass p; w -= V h; column j of H gets h (p = 0) or h added (p = 1).
 // Pass 0 leaves the partial dots of the re-orthogonalisation, pass 1 the
 // partial squared norm of w.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_korth(const Inst* const* insts, const int2* __restrict__ chunks, int pass) {
   __shared__ double red[KMAX + 1][KCH / 64];
   __shared__ double h[KMAX + 1];
   __shared__ double hg[8][KMAX + 1];
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_ITER) || at.y >= I.kchunks) return;
   const int j = gp(I.ks)->j;
@@ -1343,10 +1347,10 @@ __global__ __launch_bounds__(64) void k_karnoldi_end(const Inst* const* insts, K
 // start, end of cycle, restart, result
 
 // Start of the inner solve: w = F in Krylov order, x = 0, partial ||F||^2.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_kbegin(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[KMAX + 1][KCH / 64];
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!red_of(I)->active || at.y >= I.kchunks) return;
   const int r = at.y * KCH + threadIdx.x;
@@ -1402,9 +1406,9 @@ __global__ __launch_bounds__(64) void k_kbegin_fin(const Inst* const* insts, KOp
 }
 
 // u = V y over the basis of the finished cycle (into w).
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_kycomb(const Inst* const* insts, const int2* __restrict__ chunks) {
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_CYCLE) || at.y >= I.kchunks) return;
   const int r = at.y * KCH + threadIdx.x;
@@ -1424,9 +1428,9 @@ __global__ __launch_bounds__(KCH) void k_kycomb(const Inst* const* insts, const 
 }
 
 // x += z (the preconditioned correction of the cycle).
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_kxadd(const Inst* const* insts, const int2* __restrict__ chunks) {
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_CYCLE) || at.y >= I.kchunks) return;
   const int r = at.y * KCH + threadIdx.x;
@@ -1461,10 +1465,10 @@ __global__ void k_kcycle_fin(const Inst* const* insts, int nslots, KOpts o) {
 }
 
 // Restart: w = F - J x for the rows of one chunk, partial ||w||^2.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_kresid(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[KMAX + 1][KCH / 64];
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_RESTART) || at.y >= I.kchunks) return;
   const int r = at.y * KCH + threadIdx.x;
@@ -1506,9 +1510,9 @@ __global__ __launch_bounds__(64) void k_krestart_fin(const Inst* const* insts) {
 }
 
 // The Newton step in the factor layout that the voltage update reads.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_kfinish(const Inst* const* insts, const int2* __restrict__ chunks) {
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_FINISH) || at.y >= I.kchunks) return;
   const int r = at.y * KCH + threadIdx.x;
@@ -1596,9 +1600,9 @@ __global__ __launch_bounds__(64) void k_bcg_begin_fin(const Inst* const* insts, 
 }
 
 // p = r + beta (p - omega v), or r = r0 = p = F in the first iteration; w = p.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts, const int2* __restrict__ chunks) {
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_BP) || at.y >= I.kchunks) return;
   const int r = at.y * KCH + threadIdx.x;
@@ -1625,10 +1629,10 @@ __global__ __launch_bounds__(KCH) void k_bcg_dir(const Inst* const* insts, const
 }
 
 // p^ = z, v = J p^ for the rows of one chunk, partial <r0, v>.
-template <typename T, int L>
+template <typename T, int L, bool List>
 __global__ __launch_bounds__(L* KCH) void k_bcg_v(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[1][KCH / 16];
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_BP) || at.y >= I.kchunks) return;
   const int r = at.y * KCH + (int)threadIdx.x / L, l = threadIdx.x % L;
@@ -1653,10 +1657,10 @@ __global__ __launch_bounds__(L* KCH) void k_bcg_v(const Inst* const* insts, cons
 
 // alpha = <r0, r> / <r0, v>; s = r - alpha v into r and w; partial ||s||^2
 // (it: the iteration, counted from 0 in the inner solve).
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, const int2* __restrict__ chunks, int it) {
   __shared__ double red[1][KCH / 64];
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if (!kstate_is(I, KS_BP) || at.y >= I.kchunks) return;
   const int r = at.y * KCH + threadIdx.x;
@@ -1692,11 +1696,11 @@ __global__ __launch_bounds__(KCH) void k_bcg_s(const Inst* const* insts, const i
 // (KS_BS) s^ = z, t = J s^ for the rows of one chunk, partial <t, s>,
 // <t, t>.  The first work-group counts the iteration and sets the state;
 // the others accept the state it sets as the one they started from.
-template <typename T, int L>
+template <typename T, int L, bool List>
 __global__ __launch_bounds__(L* KCH) void k_bcg_t(const Inst* const* insts, const int2* __restrict__ chunks, KOpts o) {
   __shared__ double red[2][KCH / 16];
   __shared__ int decision;  // 0 second half, 1 first half met, 2 breakdown
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   if ((!kstate_is(I, KS_BP) && !kstate_is(I, KS_BS)) || at.y >= I.kchunks) return;
   auto& ks = *gp(I.ks);
@@ -1751,10 +1755,10 @@ __global__ __launch_bounds__(L* KCH) void k_bcg_t(const Inst* const* insts, cons
 // KS_BS: omega = <t, s> / <t, t>, x += alpha p^ + omega s^, r = s - omega t,
 // partial <r0, r> and ||r||^2 (nothing when <t, t> = 0).  KS_BH:
 // x += alpha p^.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts, const int2* __restrict__ chunks) {
   __shared__ double red[2][KCH / 64];
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   const bool half = kstate_is(I, KS_BH);
   if ((!half && !kstate_is(I, KS_BS)) || at.y >= I.kchunks) return;
@@ -1815,11 +1819,11 @@ __global__ __launch_bounds__(KCH) void k_bcg_x(const Inst* const* insts, const i
 // rows of one chunk.  The first work-group sets the instance's scalars and
 // state (<r0, r> goes to the other parity, so no work-group reads a value
 // this launch writes); the others accept the state it sets.
-template <typename T>
+template <typename T, bool List>
 __global__ __launch_bounds__(KCH) void k_bcg_next(const Inst* const* insts, const int2* __restrict__ chunks, KOpts o, int it) {
   __shared__ double beta_s;
   __shared__ int go;
-  const int2 at = chunk_at(chunks);
+  const int2 at = chunk_at<List>(chunks);
   const auto& I = inst_at(insts, at.x);
   const bool half = kstate_is(I, KS_BH);
   if ((!half && !kstate_is(I, KS_BS) && !kstate_is(I, KS_BP)) || at.y >= I.kchunks) return;
@@ -1918,6 +1922,15 @@ static inline dim3 chunk_grid(const KChunks& c) {
 // with four lanes, 14.4 with one; 48 of 10,000 (11,000 more) 40.2 and 41.5.
 constexpr int64_t kIdleRows = 204800;
 static inline int row_lanes(const KChunks& c) { return (int64_t)c.count * KCH - c.rows > kIdleRows ? 1 : kRowLanes; }
+// kernel K<T.., List> on the grid of the chunks c
+#define PF_ARGS(...) __VA_ARGS__
+#define PF_CHUNKS(K, TS, G, NT, ...)                                                            \
+  do {                                                                                          \
+    if (c.list)                                                                                 \
+      K<PF_ARGS TS, true><<<G, NT, 0, st>>>(insts, c.list __VA_OPT__(, ) __VA_ARGS__);          \
+    else                                                                                        \
+      K<PF_ARGS TS, false><<<G, NT, 0, st>>>(insts, nullptr __VA_OPT__(, ) __VA_ARGS__);        \
+  } while (0)
 static inline dim3 slot_grid(int nslots) { return dim3((unsigned)((nslots + 63) / 64)); }
 static inline dim3 item_grid(int nwork) { return dim3((unsigned)((nwork + 255) / 256)); }
 
@@ -1929,7 +1942,7 @@ void launch_ilu_factor(hipStream_t st, const Inst* const* insts, const int4* des
 }
 template <typename T>
 void launch_ilu_scale(hipStream_t st, const Inst* const* insts, const KChunks& c) {
-  k_ilu_scale<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  PF_CHUNKS(k_ilu_scale, (T), chunk_grid(c), KCH);
 }
 template <typename T>
 void launch_bj_inv(hipStream_t st, const Inst* const* insts, const int2* work, int nbig, int nsmall) {
@@ -1991,60 +2004,60 @@ void launch_bj_apply(hipStream_t st, const Inst* const* insts, const int2* work,
 template <typename T>
 void launch_karnoldi(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o) {
   const dim3 g = chunk_grid(c);
-  k_kspmv_dot<T><<<g, kRowLanes * KCH, 0, st>>>(insts, c.list);
-  k_korth<T><<<g, KCH, 0, st>>>(insts, c.list, 0);
-  k_korth<T><<<g, KCH, 0, st>>>(insts, c.list, 1);
+  PF_CHUNKS(k_kspmv_dot, (T), g, kRowLanes * KCH);
+  PF_CHUNKS(k_korth, (T), g, KCH, 0);
+  PF_CHUNKS(k_korth, (T), g, KCH, 1);
   k_karnoldi_end<<<dim3((unsigned)c.nslots), 64, 0, st>>>(insts, o);
 }
 template <typename T>
 void launch_kbegin(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o) {
-  k_kbegin<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  PF_CHUNKS(k_kbegin, (T), chunk_grid(c), KCH);
   k_kbegin_fin<<<dim3((unsigned)c.nslots), 64, 0, st>>>(insts, o);
 }
 template <typename T>
 void launch_kycomb(hipStream_t st, const Inst* const* insts, const KChunks& c) {
-  k_kycomb<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  PF_CHUNKS(k_kycomb, (T), chunk_grid(c), KCH);
 }
 template <typename T>
 void launch_kcycle_end(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o) {
   const dim3 g = chunk_grid(c);
-  k_kxadd<T><<<g, KCH, 0, st>>>(insts, c.list);
+  PF_CHUNKS(k_kxadd, (T), g, KCH);
   k_kcycle_fin<<<slot_grid(c.nslots), 64, 0, st>>>(insts, c.nslots, o);
-  k_kresid<T><<<g, KCH, 0, st>>>(insts, c.list);
+  PF_CHUNKS(k_kresid, (T), g, KCH);
   k_krestart_fin<<<dim3((unsigned)c.nslots), 64, 0, st>>>(insts);
 }
 template <typename T>
 void launch_kfinish(hipStream_t st, const Inst* const* insts, const KChunks& c) {
-  k_kfinish<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  PF_CHUNKS(k_kfinish, (T), chunk_grid(c), KCH);
   k_kretire<<<slot_grid(c.nslots), 64, 0, st>>>(insts, c.nslots);
 }
 template <typename T>
 void launch_bcg_begin(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o) {
-  k_kbegin<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  PF_CHUNKS(k_kbegin, (T), chunk_grid(c), KCH);
   k_bcg_begin_fin<<<dim3((unsigned)c.nslots), 64, 0, st>>>(insts, o);
 }
 template <typename T>
 void launch_bcg_dir(hipStream_t st, const Inst* const* insts, const KChunks& c) {
-  k_bcg_dir<T><<<chunk_grid(c), KCH, 0, st>>>(insts, c.list);
+  PF_CHUNKS(k_bcg_dir, (T), chunk_grid(c), KCH);
 }
 template <typename T>
 void launch_bcg_half(hipStream_t st, const Inst* const* insts, const KChunks& c, int it) {
   const dim3 g = chunk_grid(c);
   if (row_lanes(c) == 1)
-    k_bcg_v<T, 1><<<g, KCH, 0, st>>>(insts, c.list);
+    PF_CHUNKS(k_bcg_v, (T, 1), g, KCH);
   else
-    k_bcg_v<T, kRowLanes><<<g, kRowLanes * KCH, 0, st>>>(insts, c.list);
-  k_bcg_s<T><<<g, KCH, 0, st>>>(insts, c.list, it);
+    PF_CHUNKS(k_bcg_v, (T, kRowLanes), g, kRowLanes * KCH);
+  PF_CHUNKS(k_bcg_s, (T), g, KCH, it);
 }
 template <typename T>
 void launch_bcg_end(hipStream_t st, const Inst* const* insts, const KChunks& c, KOpts o, int it) {
   const dim3 g = chunk_grid(c);
   if (row_lanes(c) == 1)
-    k_bcg_t<T, 1><<<g, KCH, 0, st>>>(insts, c.list, o);
+    PF_CHUNKS(k_bcg_t, (T, 1), g, KCH, o);
   else
-    k_bcg_t<T, kRowLanes><<<g, kRowLanes * KCH, 0, st>>>(insts, c.list, o);
-  k_bcg_x<T><<<g, KCH, 0, st>>>(insts, c.list);
-  k_bcg_next<T><<<g, KCH, 0, st>>>(insts, c.list, o, it);
+    PF_CHUNKS(k_bcg_t, (T, kRowLanes), g, kRowLanes * KCH, o);
+  PF_CHUNKS(k_bcg_x, (T), g, KCH);
+  PF_CHUNKS(k_bcg_next, (T), g, KCH, o, it);
 }
 void launch_kgather(hipStream_t st, const Inst* const* insts, int nslots, int* out) {
   k_kgather<<<slot_grid(nslots), 64, 0, st>>>(insts, nslots, out);
