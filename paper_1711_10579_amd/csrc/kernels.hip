@@ -737,11 +737,12 @@ __global__ void k_kfill(const Inst* const* insts, int ilu) {
 }
 
 // ---------------------------------------------------------------------------
-// sparse block refactorisation, one launch per level and lane count: each
-// target block (D_j, U(j, .), L(., j)) of a column is reduced by a group of G
-// lanes that split its update list (lane-strided partial sums, fixed-order
-// tree); a column's node runs its forward row beside them, so the forward
-// substitution of the sparse part needs no launches of its own.
+// sparse block refactorisation, one launch per level (and one for each lane
+// count whose columns take 1024 threads; the upper levels of a case alone as
+// subtrees, below): each target block (D_j, U(j, .), L(., j)) of a column is
+// reduced by a group of G lanes that split its update list (lane-strided partial
+// sums, fixed-order tree); a column's node runs its forward row beside them, so
+// the forward substitution of the sparse part needs no launches of its own.
 
 // acc -= sum over updates q = q0, q0 + G, ... < q1 of L(q) U(q) (block ids
 // from il / iu), in that order, the loads of four updates issued at once

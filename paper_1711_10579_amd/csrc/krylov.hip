@@ -149,12 +149,12 @@ __device__ inline double chunk_sum(const IR& I, int pass, int e) {
   return o[0];
 }
 
-// acc -= (Sub) or += (not Sub) sum over entries q in [q0, q1) of block
-// M(q) times entries col(q) of vector x, in order of q; the loads of four
-// entries (their blocks, columns and the gathered x values) are issued
-// together, so a row costs two round trips rather than two per entry (past
-// the range's end a load repeats its first entry and adds nothing).
-template <bool Sub, typename T, typename MP, typename CP, typename XP>
+// acc -= sum over entries q in [q0, q1) of block M(q) times entries col(q) of
+// vector x, in order of q; the loads of four entries (their blocks, columns and
+// the gathered x values) are issued together, so a row costs two round trips
+// rather than two per entry (past the range's end a load repeats its first entry
+// and adds nothing).
+template <typename T, typename MP, typename CP, typename XP>
 __device__ inline void blk_range_dot(MP M, CP col, int q0, int q1, XP x, double& acc0, double& acc1) {
   for (int q = q0; q < q1; q += 4) {
     int c[4];
@@ -174,21 +174,16 @@ __device__ inline void blk_range_dot(MP M, CP col, int q0, int q1, XP x, double&
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (q + u < q1) {
-        if (Sub) {
-          acc0 -= (double)B[u].a * a[u] + (double)B[u].b * b[u];
-          acc1 -= (double)B[u].c * a[u] + (double)B[u].d * b[u];
-        } else {
-          acc0 += (double)B[u].a * a[u] + (double)B[u].b * b[u];
-          acc1 += (double)B[u].c * a[u] + (double)B[u].d * b[u];
-        }
+        acc0 -= (double)B[u].a * a[u] + (double)B[u].b * b[u];
+        acc1 -= (double)B[u].c * a[u] + (double)B[u].d * b[u];
       }
   }
 }
 
-// acc -= (Sub) or += (not Sub) row r of the block Jacobian times x
-template <bool Sub, typename T, typename IR, typename XP>
-__device__ inline void spmv_row(const IR& I, int r, XP x, double& acc0, double& acc1) {
-  blk_range_dot<Sub, T>(gp((const T*)I.jval), gp(I.kcol), gp(I.krow_ptr)[r], gp(I.krow_ptr)[r + 1], x, acc0, acc1);
+// acc -= row r of the block Jacobian times x
+template <typename T, typename IR, typename XP>
+__device__ inline void spmv_row_sub(const IR& I, int r, XP x, double& acc0, double& acc1) {
+  blk_range_dot<T>(gp((const T*)I.jval), gp(I.kcol), gp(I.krow_ptr)[r], gp(I.krow_ptr)[r + 1], x, acc0, acc1);
 }
 
 // The row's product by L lanes (all of them call; the sum in each), as the sum
@@ -704,7 +699,7 @@ __global__ __launch_bounds__(256) void k_ilu_fwd(const Inst* const* insts, const
     vj[2 * r + 1] = v1;
   }
   double y0 = (double)v0, y1 = (double)v1;
-  blk_range_dot<true, T>(P, gp(I.kcol), gp(I.krow_ptr)[r], gp(I.kdiag)[r], z, y0, y1);
+  blk_range_dot<T>(P, gp(I.kcol), gp(I.krow_ptr)[r], gp(I.kdiag)[r], z, y0, y1);
   z[2 * r] = (T)y0;
   z[2 * r + 1] = (T)y1;
 }
@@ -723,7 +718,7 @@ __global__ __launch_bounds__(256) void k_ilu_bwd(const Inst* const* insts, const
   const auto z = gp((T*)I.kz);
   const auto P = gp((const T*)I.pval);
   double s0 = (double)z[2 * r], s1 = (double)z[2 * r + 1];
-  blk_range_dot<true, T>(P, gp(I.kcol), gp(I.kdiag)[r] + 1, gp(I.krow_ptr)[r + 1], z, s0, s1);
+  blk_range_dot<T>(P, gp(I.kcol), gp(I.kdiag)[r] + 1, gp(I.krow_ptr)[r + 1], z, s0, s1);
   const Blk<T> D = ld_blk((const T*)I.pdinv, r);
   z[2 * r] = (T)((double)D.a * s0 + (double)D.b * s1);
   z[2 * r + 1] = (T)((double)D.c * s0 + (double)D.d * s1);
@@ -1478,7 +1473,7 @@ __global__ __launch_bounds__(KCH) void k_kresid(const Inst* const* insts, const 
     w0 = I.F[2 * p];
     w1 = I.F[2 * p + 1];
     const auto x = gp((const T*)I.kx);
-    spmv_row<true, T>(I, r, x, w0, w1);
+    spmv_row_sub<T>(I, r, x, w0, w1);
     const auto w = gp((T*)I.kw);
     w[2 * r] = (T)w0;
     w[2 * r + 1] = (T)w1;
