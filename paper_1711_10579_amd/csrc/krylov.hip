@@ -1913,9 +1913,11 @@ static inline dim3 chunk_grid(const KChunks& c) {
 }
 // Lanes a row of BiCGStab's matrix products: four, but one where the chunks have
 // room for so many rows more than there are that four lanes' waves for them cost
-// more than the lanes save: 1,200 grids of 300 buses (256,000 rows more) 14.8 ms
-// with four lanes, 14.4 with one; 48 of 10,000 (11,000 more) 40.2 and 41.5.
-constexpr int64_t kIdleRows = 204800;
+// more than the lanes save.  With four and with one, block-Jacobi: 800 grids of
+// 100 buses (room for 126,000 rows more) 3.89 and 3.70 ms, 800 of 300 (170,000)
+// 9.73 and 9.48, 400 of 600 (67,600) 14.8 and 14.5; 200 of 300 (42,600) 3.56 and
+// 3.64, 100 of 600 (16,900) 5.72 and 5.95, 48 of 10,000 (11,000) 40.2 and 41.5.
+constexpr int64_t kIdleRows = 65536;
 static inline int row_lanes(const KChunks& c) { return (int64_t)c.count * KCH - c.rows > kIdleRows ? 1 : kRowLanes; }
 // kernel K<T.., List> on the grid of the chunks c
 #define PF_ARGS(...) __VA_ARGS__

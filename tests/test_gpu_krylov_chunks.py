@@ -1,6 +1,6 @@
 """GPU test of the Krylov kernels' forms for batches of unequal and of small
 grids: chunks by a list (more than 256 work-groups of the grid without one), and
-BiCGStab's matrix products with a lane a row (room for more than 204,800 rows
+BiCGStab's matrix products with a lane a row (room for more than 65,536 rows
 past the instances' own): a large grid beside small ones, and very many small
 ones, with rows of one to forty blocks (a star's middle) and instances of one
 row to a whole chunk of 256 and one more.  The grids alone take neither form;
@@ -67,6 +67,6 @@ def test_chunks_by_a_list(solver, precond, mixed):
 def test_lane_a_row(mixed):
     print(f"mixed {mixed}", flush=True)
     base = _mesh(40)
-    rows = _check(lambda small: small + [pfgen.perturb_loads(base, i) for i in range(960)], solver=2, precond=1,
+    rows = _check(lambda small: small + [pfgen.perturb_loads(base, i) for i in range(320)], solver=2, precond=1,
                   precision=mixed)
-    assert sum(-(-r // 256) * 256 - r for r in rows) > 204800
+    assert sum(-(-r // 256) * 256 - r for r in rows) > 65536
