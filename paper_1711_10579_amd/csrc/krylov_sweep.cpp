@@ -235,15 +235,18 @@ bool plan_sweep(const KAnalysis& ka, bool wide, int64_t max_entries, KSweep* out
   // each Newton step outweighs the few applications such a solve takes
   // (300-bus feeder: 1.89 ms by levels, 2.02 ms in parts).
   if (ka.nu <= 2048 || 2 * ka.nup() > ka.nnz()) return false;
-  // Where every update falls on a diagonal block the pattern is a forest and the
-  // factor exact: an inner solve takes one iteration, so its few applications
-  // carry neither long plans nor, where the level sweeps run in one work-group,
-  // any.  Radial grids of 2,100, 3,000 and 6,000 buses: 1.56, 0.92 and 4.1 ms a
-  // GMRES solve by levels, 1.80, 0.95 and 4.0 in parts, their first solve 2.0, 1.3
-  // and 4.5 for 2.8, 2.2 and 6.0; of 20,000 (a launch per level otherwise) 1.68 and
-  // 1.61 ms with rows of 8 and of 16 entries, the first 3.9 and 9.3, by levels 3.0
-  // and 4.8.
-  const bool exact = 2 * ka.nup() <= ka.nnz() - ka.nu;
+  // Where no update falls outside the pattern the factor is exact (a radial
+  // grid; a mesh without triangles drops fill instead): an inner solve takes
+  // one iteration, so its few applications carry neither long plans nor, where
+  // the level sweeps run in one work-group, any.  Radial grids of 2,100, 3,000 and
+  // 6,000 buses: 1.56, 0.92 and 4.1 ms a GMRES solve by levels, 1.80, 0.95 and 4.0
+  // in parts, their first solve 2.0, 1.3 and 4.5 for 2.8, 2.2 and 6.0; of 20,000 (a
+  // launch per level otherwise) 1.68 and 1.61 ms with rows of 8 and of 16 entries,
+  // the first 3.9 and 9.3, by levels 3.0 and 4.8.
+  int64_t updates = 0;  // of the entries in and outside the pattern
+  for (int r = 0; r < ka.nu; ++r)
+    for (int q = ka.row_ptr[r]; q < ka.diag[r]; ++q) updates += ka.row_ptr[ka.col[q] + 1] - ka.diag[ka.col[q]] - 1;
+  const bool exact = ka.nup() == updates;
   if (exact && !wide) return false;
   const int levels = (int)(ka.lev_ptr.size() + ka.ulev_ptr.size()) - 2;
   for (int cap : {64, 32, 16, 8}) {

@@ -42,3 +42,22 @@ def test_radial(n, planned):
         assert np.max(np.abs(B.pf_get_voltage(h) - ref)) <= 1e-7
     h.close()
     ctx.close()
+
+
+def test_mesh_without_triangles():
+    """Updates of diagonal blocks only, as in a radial grid, but fill that the
+    factor drops: such a mesh keeps its plan."""
+    from paper_1711_10579_amd import binding as B
+
+    import pfgen
+
+    g = pfgen.make_polar_grid(2399, 719, 239, 11, balanced=True)
+    nb = [set(map(int, g.col[g.row_ptr[i] : g.row_ptr[i + 1]])) - {i} for i in range(g.n)]
+    assert not any(nb[i] & nb[j] for i in range(g.n) for j in nb[i]) and sum(map(len, nb)) > 2 * g.n
+    ctx = B.pf_ctx_create(0)
+    h = B.pf_create_from(ctx, g)
+    dev, _, parts = B.pf_debug_sweep_check(h, B.PF_PREC_FP64, seed=3)
+    print(f"parts {parts}, deviation {dev:.2g}", flush=True)
+    assert min(parts) > 0 and dev <= 1e-11
+    h.close()
+    ctx.close()
